@@ -1,0 +1,276 @@
+"""Timed cases of the per-chunk Hierarchical Sparse Attention path.
+
+A case is one call (or one fixed sequence of calls) that a program using this library makes on
+tensors resident on the GPU, through the public binding ``paper_2602_04789_amd.lf``:
+
+  step     lf_select_mask, lf_sparse_attn: one denoising step of one layer
+  rollout  lf_select_mask_cached (the current chunk's keys refreshed), lf_sparse_attn_split, then
+           lf_kcache_update of the chunk's frames: the last denoising step of a chunk in a program
+           that keeps the pooled-key cache, which commits the chunk's keys
+  select   lf_select_mask alone
+  train    lf_select_mask, lf_sparse_attn_fwd, lf_sparse_attn_bwd: one finetuning step of one layer
+  produce  lf_qk_norm_rope twice: Q, and K into the current chunk's rows of the cache
+
+Inputs are drawn on the GPU from the seed with the statistics of ``synth.make_inputs``: unit normal
+activations, a bias per (head, frame) on the keys that shrinks with the frame's age, the first
+cached frame doubled, a bias per frame on the queries and, per query block, a part of one history
+frame's key bias.  Budgets come from lf_chunk_budget.  Index buffers, outputs, workspaces and the
+pooled-key cache are kept by the caller, as bench.py keeps them.
+"""
+import math
+
+import torch
+
+from paper_2602_04789_amd import lf, synth
+
+BLOCK = 64
+
+
+def _case(name, op, heads, head_dim, frame_len, per_chunk, chunk, **sched):
+    base = dict(mode=synth.SCHED_FIXED, n_chunks=7, n_sink=1, n_win=2, k_frames=3,
+                ratio_of=synth.OF_HISTORY, current_mandatory=1, first_chunk_dense=0,
+                keep_fixed=1.0, keep_first=0.80, keep_last=0.25, s_base=0.98, s_target=0.88)
+    base.update(sched)
+    c = dict(op=op, heads=heads, head_dim=head_dim, frame_len=frame_len, per_chunk=per_chunk,
+             chunk=chunk, **base)
+    if name:
+        c["name"] = name
+    return c
+
+
+_PAPER_5S = dict(mode=synth.SCHED_CAG, ratio_of=synth.OF_ALL, current_mandatory=0, first_chunk_dense=1)
+_PAPER_15S = dict(mode=synth.SCHED_CAG, n_chunks=21, n_win=1, k_frames=1, ratio_of=synth.OF_ALL,
+                  current_mandatory=0, first_chunk_dense=1, s_base=0.95, s_target=0.85)
+
+
+def listed():
+    return [
+        # smallest calls: a handful of query blocks, where launches, latency and the host side count
+        _case("step_tiny", "step", 2, 64, 256, 1, 5, n_chunks=5, n_sink=0, n_win=0, k_frames=2,
+              ratio_of=synth.OF_CANDIDATES, keep_fixed=0.5),
+        _case("step_ragged_small", "step", 3, 128, 200, 2, 4, n_chunks=8, n_win=1, k_frames=2,
+              keep_fixed=0.4),
+        # first chunk of a 12-head rollout: no history, the chunk's own blocks compete
+        _case("step_first_chunk", "step", 12, 128, 1560, 3, 1, ratio_of=synth.OF_CANDIDATES,
+              current_mandatory=0, keep_fixed=0.6),
+        # middle of a rollout, with the pooled-key cache and the two-phase attention
+        _case("rollout_mid", "rollout", 12, 128, 1560, 3, 4, keep_fixed=0.40),
+        # last chunk, full cache: the benchmark's default workload
+        _case("step_last_chunk", "step", 12, 128, 1560, 3, 7, keep_fixed=0.25),
+        # the paper's 5 s operating point at its last chunk (whole blocks, current chunk competing)
+        _case("step_paper_5s_last", "step", 12, 128, 1536, 3, 7, **_PAPER_5S),
+        # mask selection alone over the longest cache: the 15 s setting at chunk 20
+        _case("select_paper_15s_late", "select", 12, 128, 1536, 3, 20, **_PAPER_15S),
+        # the larger layer: one call of the 40-head rollout near its end
+        _case("rollout_40_heads", "rollout", 40, 128, 1560, 3, 6, mode=synth.SCHED_LINEAR),
+        # finetuning: small and ragged at head_dim 64, a first chunk, and the last chunk
+        _case("train_ragged_small", "train", 4, 64, 400, 2, 3, n_chunks=8, n_win=1, k_frames=2,
+              keep_fixed=0.5),
+        _case("train_first_chunk", "train", 12, 128, 1560, 3, 1, ratio_of=synth.OF_CANDIDATES,
+              current_mandatory=0, keep_fixed=0.6),
+        _case("train_last_chunk", "train", 12, 128, 1560, 3, 7, keep_fixed=0.25),
+        # the producer of Q and K for one chunk
+        _case("produce_chunk", "produce", 12, 128, 1560, 3, 7),
+    ]
+
+
+_MOST = {}
+
+
+def _most():
+    """Work and memory of the largest listed case, which no drawn one exceeds."""
+    if not _MOST:
+        ws = [work(c) for c in listed()]
+        _MOST.update(flops=max(w["flops"] for w in ws), bytes=max(w["bytes"] for w in ws))
+    return _MOST
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    while True:
+        op = rng.choice(["step", "step", "rollout", "rollout", "select", "train", "train", "produce"])
+        head_dim = rng.choice([128, 128, 128, 64])
+        heads = _log(rng, 2, 40)
+        frame_len = rng.choice([_log(rng, 128, 1600), 1560, 1536, 64 * _log(rng, 2, 25)])
+        per_chunk = rng.choice([1, 2, 3, 3, 3])
+        chunk = rng.randint(1, 7)
+        # the paper's settings (Chunk-Aware Growth, current chunk competing) and the mandatory form
+        sched = rng.choice(["fixed", "linear", "paper"])
+        if sched == "paper":
+            long = rng.random() < 0.3
+            if long:
+                chunk = rng.randint(2, 20)
+            s = dict(_PAPER_15S if long else _PAPER_5S)
+        else:
+            s = dict(n_sink=rng.randint(0, 1), n_win=rng.randint(0, 2), k_frames=rng.randint(1, 4),
+                     mode=synth.SCHED_FIXED if sched == "fixed" else synth.SCHED_LINEAR,
+                     keep_fixed=round(rng.uniform(0.15, 0.8), 3),
+                     current_mandatory=rng.choice([1, 1, 0]))
+            s["ratio_of"] = rng.choice([synth.OF_HISTORY, synth.OF_CANDIDATES])
+        c = _case(None, op, heads, head_dim, frame_len, per_chunk, chunk, **s)
+        w = work(c)
+        if w["flops"] <= _most()["flops"] and w["bytes"] <= _most()["bytes"]:
+            return c
+
+
+def _schedule(c):
+    return synth.Schedule(frames_per_chunk=c["per_chunk"], frame_len=c["frame_len"], block=BLOCK,
+                          **{k: c[k] for k in ("mode", "n_chunks", "n_sink", "n_win", "k_frames",
+                                               "ratio_of", "current_mandatory", "first_chunk_dense",
+                                               "keep_fixed", "keep_first", "keep_last", "s_base",
+                                               "s_target")})
+
+
+def _sizes(c):
+    n, f = c["frame_len"], c["per_chunk"]
+    nb = -(-n // BLOCK)
+    hist = (c["chunk"] - 1) * f
+    return n, f, nb, hist, hist + f
+
+
+def work(case):
+    """Bytes: every input read once, every output written once.  Operations: the products over the
+    kept (query token, KV token) pairs, 4 d each forward and 10 d backward, a block counted with
+    its frame's mean number of tokens; mask selection adds the sums of its pooling."""
+    c = case
+    n, f, nb, hist, F = _sizes(c)
+    H, d = c["heads"], c["head_dim"]
+    q, kv = 2.0 * H * f * n * d, 2.0 * H * F * n * d
+    if c["op"] == "produce":
+        # activations read and written for Q and for K, the angle tables once, a few operations each
+        return {"bytes": 4 * q + 4.0 * f * n * d + 8.0 * H * d, "flops": 2 * 10.0 * H * f * n * d}
+    b = lf.lf_chunk_budget(c["chunk"], _schedule(c))
+    lists = 4.0 * H * f * nb * b.list_len
+    pairs = float(H) * f * n * (b.list_len * n / nb)
+    pool = (q + kv) / 2
+    if c["op"] == "select":
+        return {"bytes": q + kv + lists, "flops": pool}
+    if c["op"] == "step":
+        return {"bytes": 2 * q + 2 * kv + lists, "flops": pool + 4 * d * pairs}
+    if c["op"] == "rollout":
+        # history keys need no second pass for the selection: their means are cached
+        return {"bytes": 2 * q + 2 * kv + lists + 4.0 * H * F * (nb + 1) * d, "flops": q + 4 * d * pairs}
+    return {"bytes": 4 * q + 4 * kv + lists + 4.0 * H * f * n, "flops": pool + 14 * d * pairs}
+
+
+def _heads_first(c, g, frames, bias):
+    """[H, frames * n, d]: unit normal, plus `bias` [H, frames, d] on every token of a frame."""
+    H, d, n = c["heads"], c["head_dim"], c["frame_len"]
+    x = torch.randn((H, frames, n, d), generator=g, device="cuda", dtype=torch.float32)
+    x += bias[:, :, None, :]
+    return x
+
+
+def _qkv(c, g):
+    n, f, nb, hist, F = _sizes(c)
+    H, d = c["heads"], c["head_dim"]
+    bias = 0.5 * torch.randn((H, F, d), generator=g, device="cuda", dtype=torch.float32)
+    age = torch.clamp(hist - 1 - torch.arange(F, device="cuda"), min=0).float()
+    bias = bias * (0.9 ** age)[None, :, None]
+    K = torch.empty((H, F, n, d), dtype=torch.bfloat16, device="cuda")
+    V = torch.empty_like(K)
+    for t in range(F):
+        k = _heads_first(c, g, 1, bias[:, t:t + 1])[:, 0]
+        if t == 0 and hist > 0:
+            k = 2.0 * k
+        K[:, t] = k.to(torch.bfloat16)
+        V[:, t] = torch.randn((H, n, d), generator=g, device="cuda", dtype=torch.float32).to(torch.bfloat16)
+    q = _heads_first(c, g, f, 0.5 * torch.randn((H, f, d), generator=g, device="cuda"))
+    if hist > 0:
+        pick = torch.randint(0, hist, (H, f, nb), generator=g, device="cuda")
+        follow = torch.gather(bias, 1, pick.reshape(H, f * nb, 1).expand(-1, -1, d)).reshape(H, f, nb, 1, d)
+        q += 0.25 * follow.expand(-1, -1, -1, BLOCK, -1).reshape(H, f, nb * BLOCK, d)[:, :, :n]
+    Q = q.to(torch.bfloat16)
+    for t in (Q, K):   # the selection's arithmetic is exact for zero or |x| >= 2^-30
+        t[t.abs() < 2.0 ** -30] = 0
+    return Q.reshape(H, f * n, d), K.reshape(H, F * n, d), V.reshape(H, F * n, d)
+
+
+def prepare(case, seed):
+    c = case
+    n, f, nb, hist, F = _sizes(c)
+    H, d = c["heads"], c["head_dim"]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    dev = dict(device="cuda")
+    if c["op"] == "produce":
+        L = f * n
+        gain = torch.exp(0.5 * torch.randn((2, 1, H * d), generator=g, **dev))
+        X = (torch.randn((2, L, H * d), generator=g, **dev) * gain).to(torch.bfloat16)
+        norm = 1.0 + 0.1 * torch.randn((2, H * d), generator=g, **dev)
+        # a rotary table over (frame, row, column) of a patch grid about twice as wide as high
+        half = d // 2
+        gw = max(1, int(round(math.sqrt(n * 52 / 30))))
+        tok = torch.arange(L, **dev)
+        pos = [tok // n + hist, (tok % n) // gw, (tok % n) % gw]
+        sizes = [half - 2 * (half // 3), half // 3, half // 3]
+        theta = torch.cat([p[:, None].double() * (10000.0 ** (-torch.arange(s, **dev).double() / max(s, 1)))
+                           for p, s in zip(pos, sizes)], dim=1)
+        return dict(c=c, X=X, norm=norm, cos=torch.cos(theta).float().contiguous(),
+                    sin=torch.sin(theta).float().contiguous(),
+                    Q=torch.empty((H, L, d), dtype=torch.bfloat16, **dev),
+                    K=torch.zeros((H, F * n, d), dtype=torch.bfloat16, **dev))
+    Q, K, V = _qkv(c, g)
+    budget = lf.lf_chunk_budget(c["chunk"], lf.make_schedule(_schedule(c)))
+    sh = lf.make_shape(Q, K, frame_len=n, block=BLOCK)
+    s = dict(c=c, Q=Q, K=K, V=V, budget=budget,
+             idx=torch.empty((H, f * nb, budget.list_len), dtype=torch.int32, **dev),
+             ws=torch.empty(max(256, lf.lf_workspace_bytes(sh, budget)), dtype=torch.uint8, **dev),
+             O=torch.empty_like(Q))
+    if c["op"] == "rollout":
+        s["max_frames"] = max(F, c["n_chunks"] * f)
+        s["kcache"] = torch.zeros(lf.lf_kcache_bytes(sh, s["max_frames"]), dtype=torch.uint8, **dev)
+        s["aws"] = torch.empty(max(256, lf.lf_attn_workspace_bytes(sh)), dtype=torch.uint8, **dev)
+        if hist:
+            lf.lf_kcache_update(K, n, BLOCK, 0, hist, s["max_frames"], s["kcache"])
+    if c["op"] == "train":
+        s["dO"] = torch.randn(Q.shape, generator=g, **dev).to(torch.bfloat16)
+        s["lse2"] = torch.empty((H, f * n), dtype=torch.float32, **dev)
+        s["grads"] = tuple(torch.empty_like(t) for t in (Q, K, V))
+        s["bws"] = torch.empty(max(256, lf.lf_attn_bwd_workspace_bytes(sh)), dtype=torch.uint8, **dev)
+    return s
+
+
+def run(state):
+    s, c = state, state["c"]
+    n, op = c["frame_len"], c["op"]
+    if op == "produce":
+        L = s["Q"].shape[1]
+        kcur = s["K"][:, s["K"].shape[1] - L:]
+        lf.lf_qk_norm_rope(s["X"][0], s["norm"][0], s["cos"], s["sin"], c["heads"], s["Q"], across_heads=True)
+        lf.lf_qk_norm_rope(s["X"][1], s["norm"][1], s["cos"], s["sin"], c["heads"], kcur, across_heads=True)
+        return s["Q"], kcur
+    b = s["budget"]
+    if op == "rollout":
+        lf.lf_select_mask_cached(s["Q"], s["kcache"], s["max_frames"], s["K"].shape[1], n, BLOCK, b,
+                                 Kcache=s["K"], indices=s["idx"], workspace=s["ws"])
+        lf.lf_sparse_attn_split(s["Q"], s["K"], s["V"], s["idx"], n, BLOCK, b, O=s["O"], workspace=s["aws"])
+        F = s["K"].shape[1] // n
+        lf.lf_kcache_update(s["K"], n, BLOCK, F - c["per_chunk"], F, s["max_frames"], s["kcache"])
+        return s["idx"], s["O"], s["kcache"].view(torch.float32)
+    lf.lf_select_mask(s["Q"], s["K"], n, BLOCK, b, indices=s["idx"], workspace=s["ws"])
+    if op == "select":
+        return s["idx"]
+    if op == "step":
+        lf.lf_sparse_attn(s["Q"], s["K"], s["V"], s["idx"], n, BLOCK, O=s["O"])
+        return s["idx"], s["O"]
+    lf.lf_sparse_attn_fwd(s["Q"], s["K"], s["V"], s["idx"], n, BLOCK, O=s["O"], lse2=s["lse2"])
+    lf.lf_sparse_attn_bwd(s["Q"], s["K"], s["V"], s["O"], s["dO"], s["lse2"], s["idx"], n, BLOCK,
+                          workspace=s["bws"], grads=s["grads"])
+    return (s["idx"], s["O"], s["lse2"]) + s["grads"]
+
+
+def tolerance(case):
+    """Index lists are whole numbers and stay the same.  Measured against the path in 64 bits on the
+    same lists (2-norms): O 2.0e-3 .. 2.3e-3, dQ, dK, dV 2.4e-3 .. 3.1e-3 with single elements up to
+    0.16 of the root mean square (sums of bfloat16-rounded probabilities), the producer 1.7e-3."""
+    if case["op"] == "select":
+        return "exact"
+    if case["op"] == "train":
+        return {"rel": 1e-2, "max": 0.5}
+    if case["op"] == "produce":
+        return {"rel": 6e-3, "max": 2e-2}
+    return {"rel": 8e-3, "max": 0.1}
