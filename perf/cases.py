@@ -263,6 +263,97 @@ def run(state):
     return (s["idx"], s["O"], s["lse2"]) + s["grads"]
 
 
+def _exact_select(c, b, Q, K):
+    """Index lists in 64 bits by the selection's stated arithmetic (block means and frame means
+    rounded to float32, each score a 64-bit sum rounded to float32 once, ties to the lower index)."""
+    n, f, nb, hist, F = _sizes(c)
+    H, d = c["heads"], c["head_dim"]
+
+    def pooled(x, frames):
+        x = x.reshape(H, frames, n, d).double()
+        pad = torch.zeros((H, frames, nb * BLOCK - n, d), dtype=torch.float64, device=x.device)
+        cnt = torch.full((nb, 1), BLOCK, dtype=torch.float64, device=x.device)
+        cnt[-1] = n - (nb - 1) * BLOCK
+        return (torch.cat([x, pad], 2).reshape(H, frames, nb, BLOCK, d).sum(3) / cnt).float()
+
+    q = pooled(Q, f).reshape(H, f * nb, d).double()
+    kb = pooled(K, F)
+    kf = (kb.double().sum(2) / nb).float().double()
+    on = torch.ones((H, f * nb, hist), dtype=torch.bool, device=Q.device)
+    m0, m1 = b.n_sink, hist - b.n_win
+    if b.k_frames < m1 - m0:
+        score = torch.matmul(q, kf[:, m0:m1].transpose(1, 2).contiguous()).float()
+        rank = torch.sort(score, dim=-1, descending=True, stable=True).indices[..., :b.k_frames]
+        on[..., m0:m1] = False
+        on[..., m0:m1].scatter_(-1, rank, True)
+    cand = on[..., None].expand(-1, -1, -1, nb).reshape(H, f * nb, hist * nb)
+    current = torch.full((H, f * nb, f * nb), not b.current_mandatory, dtype=torch.bool, device=Q.device)
+    cand = torch.cat([cand, current], -1)
+    score = torch.matmul(q, kb.reshape(H, F * nb, d).double().transpose(1, 2).contiguous()).float()
+    score = score.masked_fill(~cand, -math.inf)
+    ids = torch.sort(score, dim=-1, descending=True, stable=True).indices[..., :b.k_blocks]
+    if b.current_mandatory:
+        ids = torch.cat([ids, torch.arange(hist * nb, F * nb, device=Q.device).expand(H, f * nb, -1)], -1)
+    return ids.sort(-1).values, kb, kf
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits; the whole-number index lists have no such value."""
+    c, s = case, prepare(case, seed)
+    n, f, nb, hist, F = _sizes(c)
+    H, d = c["heads"], c["head_dim"]
+    if c["op"] == "select":
+        return None
+    if c["op"] == "produce":
+        out = []
+        for i in range(2):
+            x = s["X"][i].double()
+            x = x / torch.sqrt((x * x).mean(-1, keepdim=True) + 1e-6) * s["norm"][i].double()
+            x = x.reshape(-1, H, d // 2, 2)
+            co, si = s["cos"].double()[:, None], s["sin"].double()[:, None]
+            y = torch.stack([x[..., 0] * co - x[..., 1] * si, x[..., 0] * si + x[..., 1] * co], -1)
+            out.append(y.reshape(-1, H, d).transpose(0, 1))
+        return tuple(out)
+    Q, K, V, train = s["Q"], s["K"], s["V"], c["op"] == "train"
+    ids, kb, kf = _exact_select(c, s["budget"], Q, K)
+    scale = d ** -0.5
+    O = torch.zeros(Q.shape, dtype=torch.float64, device=Q.device)
+    lse2 = torch.zeros(Q.shape[:2], dtype=torch.float64, device=Q.device)
+    dQ, dK, dV = (torch.zeros(t.shape if train else (0,), dtype=torch.float64, device=Q.device) for t in (Q, K, V))
+    tok = torch.arange(BLOCK, device=Q.device)
+    for h in range(H):
+        k, v = K[h].double(), V[h].double()
+        for r in range(f * nb):
+            q0, j = (r // nb) * n + (r % nb) * BLOCK, ids[h, r]
+            rows = slice(q0, q0 + min(BLOCK, n - (r % nb) * BLOCK))
+            within = (j % nb)[:, None] * BLOCK + tok
+            cols = ((j // nb)[:, None] * n + within)[within < n]
+            q, kc, vc = Q[h, rows].double(), k[cols], v[cols]
+            z = torch.matmul(q, kc.T.contiguous()) * scale
+            p = torch.softmax(z, -1)
+            O[h, rows] = torch.matmul(p, vc)
+            lse2[h, rows] = torch.logsumexp(z, -1) / math.log(2.0)
+            if train:
+                g = s["dO"][h, rows].double()
+                ds = p * (torch.matmul(g, vc.T.contiguous()) - (g * O[h, rows]).sum(-1, keepdim=True))
+                dQ[h, rows] = scale * torch.matmul(ds, kc)
+                dK[h].index_add_(0, cols, scale * torch.matmul(ds.T.contiguous(), q))
+                dV[h].index_add_(0, cols, torch.matmul(p.T.contiguous(), g))
+    if train:
+        return None, O, lse2, dQ, dK, dV
+    if c["op"] == "step":
+        return None, O
+    # the pooled-key cache: block means, then frame means, both channel-quad major
+    cache = torch.zeros(s["kcache"].numel() // 4, dtype=torch.float64, device=Q.device)
+    M, at = s["max_frames"], 0
+    for rows, x in ((M * nb, kb.reshape(H, F * nb, d)), (M, kf)):
+        part = torch.zeros((H, d // 4, rows, 4), dtype=torch.float64, device=Q.device)
+        part[:, :, :x.shape[1]] = x.double().reshape(H, -1, d // 4, 4).transpose(1, 2)
+        cache[at:at + part.numel()] = part.flatten()
+        at += part.numel()
+    return None, O, cache
+
+
 def tolerance(case):
     """Index lists are whole numbers and stay the same.  Measured against the path in 64 bits on the
     same lists (2-norms): O 2.0e-3 .. 2.3e-3, dQ, dK, dV 2.4e-3 .. 3.1e-3 with single elements up to
