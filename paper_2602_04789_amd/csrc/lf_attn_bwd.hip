@@ -680,20 +680,32 @@ __global__ __launch_bounds__(256) void lf_transpose_lists_kernel(const int32_t* 
 
 // Launch order of the key-major pass: its workgroups differ in work by the length of their
 // transposed list (a sink or current-chunk block is kept by every query block, a block of the
-// middle history by few), and workgroups are started in index order, so the long ones go first.
-// The workgroup indices are dealt to the eight XCDs in contiguous ranges (see the kernel); one
-// block per range sorts it by descending count with a counting sort.  The place of equal counts
+// middle history by few).  Workgroup indices go round-robin to the eight XCDs, so every XCD works
+// through a fixed set of blocks: `per_xcd` places of the sequence "head after head, and inside a
+// head the KV blocks in steps of `step` blocks".  All heads carry the same number of tiles; where
+// an XCD's share ends inside a head, the step (about 0.618 n_k, prime to n_k) spreads the share
+// evenly over the head's blocks, heavy and light.  With the blocks in plain order the XCD that
+// got the head's second half, current chunk included, had 27 % more tiles than the one with the
+// first half, and a quarter of the launch's time was spent waiting for it (12 heads, 525 KV
+// blocks: the forward and backward calls together 1780 us, now 1672 us).
+// Inside an XCD workgroups are started in index order, so the long ones go first: one
+// block per XCD sorts its share by descending count with a counting sort.  The place of equal counts
 // among each other is left to the order the atomics happen to take: any permutation is valid,
 // and the gradients do not depend on which workgroup computes a block.
 constexpr int kOrderBins = 1024;
 __global__ __launch_bounds__(1024) void lf_order_kernel(const int32_t* __restrict__ tcnt,
                                                         int32_t* __restrict__ order, int total,
-                                                        int per_xcd) {
+                                                        int per_xcd, int n_k, uint32_t step) {
   __shared__ int bins[kOrderBins];
+  // block at place i of the sequence
+  auto at = [&](int i) -> int {
+    const int h = i / n_k;
+    return h * n_k + (int)((uint64_t)(uint32_t)(i - h * n_k) * step % (uint32_t)n_k);
+  };
   const int w0 = blockIdx.x * per_xcd, w1 = min(total, w0 + per_xcd);
   for (int i = threadIdx.x; i < kOrderBins; i += 1024) bins[i] = 0;
   __syncthreads();
-  for (int w = w0 + threadIdx.x; w < w1; w += 1024) atomicAdd(&bins[min(tcnt[w], kOrderBins - 1)], 1);
+  for (int i = w0 + threadIdx.x; i < w1; i += 1024) atomicAdd(&bins[min(tcnt[at(i)], kOrderBins - 1)], 1);
   __syncthreads();
   // bins[b] <- number of workgroups in bins above b (where bin b starts in the descending order):
   // an inclusive scan over the reversed bins by doubling, minus the bin's own count
@@ -711,8 +723,21 @@ __global__ __launch_bounds__(1024) void lf_order_kernel(const int32_t* __restric
     bins[b] = run - own;
   }
   __syncthreads();
-  for (int w = w0 + threadIdx.x; w < w1; w += 1024)
+  for (int i = w0 + threadIdx.x; i < w1; i += 1024) {
+    const int w = at(i);
     order[w0 + atomicAdd(&bins[min(tcnt[w], kOrderBins - 1)], 1)] = w;
+  }
+}
+
+// The step of the launch order: the number nearest below 0.618 n that is prime to n (1 for n < 3).
+uint32_t spread_step(uint32_t n) {
+  uint32_t s = (uint32_t)(0.6180339887 * n);
+  for (; s > 1; --s) {
+    uint32_t a = n, b = s;
+    while (b) { const uint32_t t = a % b; a = b; b = t; }
+    if (a == 1) break;
+  }
+  return s > 1 ? s : 1;
 }
 
 }  // namespace
@@ -774,7 +799,7 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.total_wg = dm->H * dm->n_k;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
   if (lf_launch(lf_order_kernel, dim3(8), dim3(1024), 0, st, (const int32_t*)tcnt, order, a.total_wg,
-                a.wg_per_xcd) != hipSuccess)
+                a.wg_per_xcd, dm->n_k, spread_step((uint32_t)dm->n_k)) != hipSuccess)
     return LF_ERR_HIP;
   a.order = order;
   const dim3 grid2((unsigned)(a.wg_per_xcd * 8));
