@@ -45,7 +45,8 @@ struct BwdArgs {
   const uint16_t* A2;    // streamed operand of dP (V for dQ, dO for dK and dV)
   uint16_t* out1;        // dQ or dK: scale * sum of A1^T dS'
   uint16_t* out2;        // dV: sum of A2^T P'
-  const float2* stats;   // (lse2, delta) per query row, [H][q_len]
+  const float* lse2;     // log-sum-exp per query row (exp2 domain), [H][q_len]
+  const float* ndelta;   // -delta per query row, [H][q_len]
   const int32_t* idx;    // lists: [H][owners][list_stride]
   const int32_t* cnt;    // key-major: entries per transposed list
   const int32_t* order;  // key-major: owner handled by workgroup slot w
@@ -130,8 +131,11 @@ __global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
   }
   // dQ: the query row of this lane; its log-sum-exp and delta (a row outside the block gets
   // +inf, which makes all its probabilities zero)
-  float2 mine = make_float2(INFINITY, 0.0f);
-  if (o_ok) mine = a.stats[(int64_t)h * a.q_len + otok0 + orow];
+  float my_lse = INFINITY, my_nd = 0.0f;
+  if (o_ok) {
+    my_lse = a.lse2[(int64_t)h * a.q_len + otok0 + orow];
+    my_nd = a.ndelta[(int64_t)h * a.q_len + otok0 + orow];
+  }
 
   const char* A1h = reinterpret_cast<const char*>(a.A1 + (int64_t)h * a.a1_head);
   const char* A2h = reinterpret_cast<const char*>(a.A2 + (int64_t)h * a.a2_head);
@@ -259,8 +263,8 @@ __global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float p = __builtin_amdgcn_exp2f(fmaf(sacc[i], a.c, -mine.x));
-      dsf[i >> 3][i & 7] = (__bf16)(p * (pacc[i] - mine.y));
+      const float p = __builtin_amdgcn_exp2f(fmaf(sacc[i], a.c, -my_lse));
+      dsf[i >> 3][i & 7] = (__bf16)(p * (pacc[i] + my_nd));
     }
   };
   // acc += K^T dS'.  The transposed fragments of the first 16
@@ -355,7 +359,8 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
   static_assert(LPW == 1 || LPW == 2, "a half tile splits over four wavefronts");
 
   __shared__ uint4 buf[3][2 * T32];         // [half tile mod 3][Q | dO]
-  __shared__ float2 st[3][4][32];           // (lse2, delta) of the 32 streamed rows, one copy per wavefront
+  __shared__ float4 st[3][4][16];           // lse2 (role 0) or -delta (role 1) of the 32 streamed rows, one copy per
+                                            // wavefront; its upper half takes the zeros of the lanes past the 32 rows
   __shared__ uint4 ph[2][2][2][64];         // P' handoff: [step parity][rh][k-step][lane]
   __shared__ int2 ent[kPass];
 
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
 
   const char* A1h = reinterpret_cast<const char*>(a.A1 + (int64_t)h * a.a1_head);
   const char* A2h = reinterpret_cast<const char*>(a.A2 + (int64_t)h * a.a2_head);
-  const char* STh = reinterpret_cast<const char*>(a.stats + (int64_t)h * a.q_len);
+  const char* STh = reinterpret_cast<const char*>((is_ds ? a.ndelta : a.lse2) + (int64_t)h * a.q_len);
   const uint32_t a1_row_bytes = (uint32_t)(a.a1_tok * 2), a2_row_bytes = (uint32_t)(a.a2_tok * 2);
 
   // tile loads: wavefront `wave` fills rows [8 wave, +8) of a half tile with LPW instructions
@@ -429,12 +434,12 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     const int2 u = make_int2(__builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y));
     return (t & 1) ? make_int2(u.x + 32, max(u.y - 32, 0)) : make_int2(u.x, min(u.y, 32));
   };
-  // half tile t -> stage t mod 3: the Q and dO rows and the (lse2, delta) pairs (every wavefront its own copy)
+  // half tile t -> stage t mod 3: the Q and dO rows and the row statistic of this wavefront's role
   auto request = [&](int t, int stage) __attribute__((always_inline)) {
     const int2 e = half(t);
     fetch(rsrc(A1h, a1_row_bytes, e.x, e.y), buf[stage], off1);
     fetch(rsrc(A2h, a2_row_bytes, e.x, e.y), buf[stage] + T32, off2);
-    const int32x4 rs = rsrc(STh, 8u, e.x, e.y);
+    const int32x4 rs = rsrc(STh, 4u, e.x, e.y);
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)LDS_PTR(void, st[stage][wave]));
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "buffer_load_dword %1, %2, 0 offen lds"
@@ -472,11 +477,10 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
 #pragma unroll
   for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
 
-  // the score-like product of this wavefront's role: rows of `tile` times the owner operand
-  auto product = [&](const uint4* tile) __attribute__((always_inline)) {
+  // the score-like product of this wavefront's role: `c` + rows of `tile` times the owner operand
+  auto product = [&](const uint4* tile, f32x16 c) __attribute__((always_inline)) {
     constexpr int HB = KS / 2;
     Frag f[HB];
-    f32x16 c = zero16;
 #pragma unroll
     for (int s = 0; s < HB; ++s) f[s].u = tile[raddr[s]];
     __builtin_amdgcn_sched_barrier(0);
@@ -504,13 +508,17 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     for (int mb = 0; mb < MB; ++mb)
       acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[mb], b[1], acc[mb], 0, 0, 0);
   };
-  // accumulator i of a score tile is streamed row 8 (i/4) + 4 kg + i%4; the (lse2, delta)
-  // pairs of rows 8 g + 4 kg .. + 3 are two 16-byte reads
-  auto stats4 = [&](const float2* strow, int g, float (&lse)[4], float (&dl)[4]) __attribute__((always_inline)) {
-    const float4 sa = *reinterpret_cast<const float4*>(strow + 8 * g + 4 * kg);
-    const float4 sb = *reinterpret_cast<const float4*>(strow + 8 * g + 4 * kg + 2);
-    lse[0] = sa.x; lse[1] = sa.z; lse[2] = sb.x; lse[3] = sb.z;
-    dl[0] = sa.y; dl[1] = sa.w; dl[2] = sb.y; dl[3] = sb.w;
+  // accumulator i of a score tile is streamed row 8 (i/4) + 4 kg + i%4: the row statistics in
+  // that order are four 16-byte reads.  Role 1 starts its product from them (dP' - delta needs no
+  // subtraction then); a role reads only its own statistic (pairs of both took twice the LDS reads).
+  auto stats16 = [&](int stage) __attribute__((always_inline)) {
+    f32x16 v;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 x = st[stage][wave][2 * g + kg];
+      v[4 * g] = x.x; v[4 * g + 1] = x.y; v[4 * g + 2] = x.z; v[4 * g + 3] = x.w;
+    }
+    return v;
   };
 
   for (int l0 = 0; l0 < n_ent; l0 += kPass) {
@@ -536,7 +544,7 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     // role 0 on half tile t (stage cur): S', P' (handed over), dV^T += dO^T P'
     auto p_step = [&](int t) __attribute__((always_inline)) {
       const int cnt = half(t).y;
-      f32x16 sacc = product(buf[cur]);
+      f32x16 sacc = product(buf[cur], zero16);
       // stream rows past a short half tile's count were loaded as zeros (scores and statistics
       // alike): their scores become -inf (P' = 0); a full half tile, the common case, skips this
       if (cnt < 32) {
@@ -544,43 +552,29 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
         for (int i = 0; i < 16; ++i)
           if (8 * (i >> 2) + 4 * kg + (i & 3) >= cnt) sacc[i] = -INFINITY;
       }
+      const f32x16 lse = stats16(cur);
       bf16x8 pf[2];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float lse[4], dl[4];
-        stats4(st[cur][wave], g, lse, dl);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = 4 * g + e;
-          pf[i >> 3][i & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[i], a.c, -lse[e]));
-        }
-      }
+      for (int i = 0; i < 16; ++i)
+        pf[i >> 3][i & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[i], a.c, -lse[i]));
       ph[t & 1][pair][0][lane] = __builtin_bit_cast(uint4, pf[0]);
       ph[t & 1][pair][1][lane] = __builtin_bit_cast(uint4, pf[1]);
       accumulate(buf[cur] + T32, pf);
     };
-    // role 1 finishing half tile t (stage prv): dS' = P' (dP' - delta), dK^T += Q^T dS'
+    // role 1 finishing half tile t (stage prv): dS' = P' (dP' - delta), dK^T += Q^T dS'; dp_prev holds dP' - delta
     auto ds_finish = [&](int t) __attribute__((always_inline)) {
       bf16x8 pf[2], dsf[2];
       pf[0] = __builtin_bit_cast(bf16x8, ph[t & 1][pair][0][lane]);
       pf[1] = __builtin_bit_cast(bf16x8, ph[t & 1][pair][1][lane]);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float lse[4], dl[4];
-        stats4(st[prv][wave], g, lse, dl);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = 4 * g + e;
-          dsf[i >> 3][i & 7] = (__bf16)((float)pf[i >> 3][i & 7] * (dp_prev[i] - dl[e]));
-        }
-      }
+      for (int i = 0; i < 16; ++i) dsf[i >> 3][i & 7] = (__bf16)((float)pf[i >> 3][i & 7] * dp_prev[i]);
       accumulate(buf[prv], dsf);
     };
     request(0, 0);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     lds_barrier();
     request(1, nxt);                       // steps >= 2: a list entry is two half tiles
-    if (!is_ds) p_step(0); else dp_prev = product(buf[cur] + T32);
+    if (!is_ds) p_step(0); else dp_prev = product(buf[cur] + T32, stats16(cur));
     rotate();
     for (int t = 1; t < steps; ++t) {
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -589,7 +583,7 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
       if (!is_ds) {
         p_step(t);
       } else {
-        const f32x16 dp_cur = product(buf[cur] + T32);   // dP' of half tile t
+        const f32x16 dp_cur = product(buf[cur] + T32, stats16(cur));   // dP' - delta of half tile t
         ds_finish(t - 1);
         dp_prev = dp_cur;
       }
@@ -618,13 +612,11 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
   }
 }
 
-// delta_x = dO_x . O_x (float32), one group of d/8 lanes per row; written next to the row's
-// log-sum-exp, so that the attention kernels fetch both with one load.
+// -delta_x, delta_x = dO_x . O_x (float32), one group of d/8 lanes per row.
 template <int D>
 __global__ __launch_bounds__(256) void lf_attn_delta_kernel(const uint16_t* __restrict__ O,
                                                             const uint16_t* __restrict__ dO,
-                                                            const float* __restrict__ lse2,
-                                                            float2* __restrict__ stats, int64_t o_tok,
+                                                            float* __restrict__ ndelta, int64_t o_tok,
                                                             int64_t o_head, int q_len, int rows) {
   constexpr int LPR = D / 8;                  // lanes per row
   const int gid = blockIdx.x * 256 + threadIdx.x;
@@ -643,7 +635,7 @@ __global__ __launch_bounds__(256) void lf_attn_delta_kernel(const uint16_t* __re
   }
 #pragma unroll
   for (int o = 1; o < LPR; o <<= 1) s += __shfl_xor(s, o);
-  if (row < rows && ch == 0) stats[row] = make_float2(lse2[row], s);
+  if (row < rows && ch == 0) ndelta[row] = -s;
 }
 
 // Transposed lists: for every (head, KV block c) the query blocks whose list holds c, ascending.
@@ -744,7 +736,7 @@ uint32_t spread_step(uint32_t n) {
 
 int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,
                        const float* lse2, const lf_shape* s, const lf_dims* dm, const int32_t* indices,
-                       int32_t list_len, float scale, void* dQ, void* dK, void* dV, float* stats,
+                       int32_t list_len, float scale, void* dQ, void* dK, void* dV, float* ndelta,
                        int32_t* tlist, int32_t* tcnt, int32_t* order, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int q_len = dm->f * dm->n;
@@ -754,9 +746,9 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
     const unsigned grid = (unsigned)((lanes + 255) / 256);
     const hipError_t rc = dm->d == 128
         ? lf_launch(lf_attn_delta_kernel<128>, dim3(grid), dim3(256), 0, st, (const uint16_t*)O,
-                    (const uint16_t*)dO, lse2, (float2*)stats, (int64_t)s->o_stride_tok, (int64_t)s->o_stride_head, q_len, rows)
+                    (const uint16_t*)dO, ndelta, (int64_t)s->o_stride_tok, (int64_t)s->o_stride_head, q_len, rows)
         : lf_launch(lf_attn_delta_kernel<64>, dim3(grid), dim3(256), 0, st, (const uint16_t*)O,
-                    (const uint16_t*)dO, lse2, (float2*)stats, (int64_t)s->o_stride_tok, (int64_t)s->o_stride_head, q_len, rows);
+                    (const uint16_t*)dO, ndelta, (int64_t)s->o_stride_tok, (int64_t)s->o_stride_head, q_len, rows);
     if (rc != hipSuccess) return LF_ERR_HIP;
   }
   {
@@ -766,7 +758,8 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
       return LF_ERR_HIP;
   }
   BwdArgs a = {};
-  a.stats = (const float2*)stats;
+  a.lse2 = lse2;
+  a.ndelta = ndelta;
   a.n = dm->n;
   a.nb = dm->nb;
   a.q_len = q_len;

@@ -374,7 +374,7 @@ extern "C" int lf_sparse_attn_fwd(const void* Q, const void* K, const void* V, c
                         stream);
 }
 
-// Scratch of lf_sparse_attn_bwd: (lse2, delta) float32 [H][q_len][2], the transposed lists int32
+// Scratch of lf_sparse_attn_bwd: -delta float32 [H][q_len] (room for two values per row), the transposed lists int32
 // [H][n_k][n_q], their lengths int32 [H][n_k] and the launch order int32 [H][n_k].
 static size_t attn_bwd_bytes(const lf_dims& dm, size_t* off_tlist, size_t* off_tcnt, size_t* off_order) {
   const size_t rows = (size_t)dm.H * dm.f * dm.n;
