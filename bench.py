@@ -202,21 +202,21 @@ def run_select_phases(torch, lf, synth, workload):
     if rc != 0:
         sys.exit(f"bench.py: lf_probe_select_stamps failed ({rc})")
     n_wg = min(4096, w.heads * w.frames_per_chunk * w.blocks_per_frame)
-    st = out.reshape(4096, 8)[:n_wg, :7].astype(np.int64)
+    st = out.reshape(4096, 8)[:n_wg, :6].astype(np.int64)
     names = ["load q_tilde", "frame scores (+ scores of the known candidates)", "frame ranking and list",
-             "block scores of the retrieved frames", "block ranking", "compaction and store"]
+             "block scores of the retrieved frames", "block ranking and store"]
     phases = []
     for i, name in enumerate(names):
         d = (st[:, i + 1] - st[:, i]) * 10.0
         phases.append({"phase": name, "mean_ns": float(d.mean()), "median_ns": float(np.median(d)),
                        "p90_ns": float(np.percentile(d, 90)), "max_ns": float(d.max())})
-    tot = (st[:, 6] - st[:, 0]) * 10.0
+    tot = (st[:, 5] - st[:, 0]) * 10.0
     t0 = st[:, 0].min()
     print(json.dumps({"select_phases": phases, "workload": w.name, "workgroups": int(n_wg),
                       "workgroup_ns": {"mean": float(tot.mean()), "max": float(tot.max())},
                       "start_spread_ns": {"median": float(np.median(st[:, 0] - t0) * 10.0),
                                           "max": float((st[:, 0] - t0).max() * 10.0)},
-                      "first_start_to_last_end_ns": float((st[:, 6].max() - t0) * 10.0),
+                      "first_start_to_last_end_ns": float((st[:, 5].max() - t0) * 10.0),
                       "lists_equal_product": bool(torch.equal(idx, ref)),
                       "what": "probe build (LF_PROBE_STAMPS): wall clock of 10 ns ticks read by thread 0 of every "
                               "workgroup at the phase boundaries; last of 5 launches"}))

@@ -5,10 +5,8 @@
 //   lf_frame_mean_kernel  frame means of the candidate frames (Eq. 7, framewise); the block
 //                         means of Q ride along in the same launch.
 //   lf_select_kernel      per (head, query block): frame scores (Eq. 8), frame top-k
-//                         (Eq. 9), block scores (Eq. 10), block top-k (Eq. 11: by counting
-//                         the keys that rank before each candidate when there are at most
-//                         256 of them, by a bitonic sort over lane shuffles and LDS beyond
-//                         that), ascending index list (Eq. 12).
+//                         (Eq. 9), block scores (Eq. 10), block top-k (Eq. 11: one wavefront
+//                         searches the k-th largest key bit by bit), ascending index list (Eq. 12).
 //
 // Arithmetic contract (see lf.h): block sums in binary64 (exact for in-range bf16 inputs,
 // so the reduction tree is free), means rounded to float32; scores are binary64 sums over
@@ -173,10 +171,10 @@ struct SelectArgs {
 // Dynamic LDS of lf_select_kernel<D, E>; must mirror the carving at the top of the kernel.
 inline size_t select_lds_bytes(const SelectArgs& a, int e) {
   size_t b = (size_t)a.d * sizeof(double);
-  b += (size_t)kThreads * e * (sizeof(float) + sizeof(int));   // exchange arrays of the sort
+  b += (size_t)kThreads * e * sizeof(uint32_t);                // score keys
   b += (size_t)a.m * sizeof(float);
   b += (size_t)(a.n_tf + a.f) * sizeof(int);
-  b += (size_t)((a.F_h + 3) & ~3) + (size_t)((a.n_cand + 3) & ~3);
+  b += (size_t)((a.F_h + 3) & ~3);
   return b;
 }
 
@@ -247,63 +245,84 @@ __device__ __forceinline__ void wave_compact(const unsigned char* flag, int coun
   }
 }
 
-// Bitonic sort of 256*E (score, position) pairs held E per thread, element e of thread t
-// being index e*256 + t, into ranks_before order along the index.  Partners at distance
-// < 64 are reached with lane shuffles, at distance 64 and 128 through the LDS arrays xs/xp
-// (one barrier pair per such step), at distance >= 256 inside the thread.
-template <int E>
-__device__ __forceinline__ void bitonic_sort(float (&s)[E], int (&p)[E], float* xs, int* xp) {
-  const int tid = threadIdx.x;
-#pragma unroll 1
-  for (int k = 2; k <= kThreads * E; k <<= 1) {
-#pragma unroll 1
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j >= kThreads) {
-        const int de = j / kThreads;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if ((e & de) == 0 && (e | de) < E) {
-            const int e2 = e | de, i = e * kThreads + tid;
-            const bool up = (i & k) == 0;
-            const bool first_is_lo = ranks_before(s[e], p[e], s[e2], p[e2]);
-            if (first_is_lo != up) {
-              const float ts = s[e]; s[e] = s[e2]; s[e2] = ts;
-              const int tp = p[e]; p[e] = p[e2]; p[e2] = tp;
-            }
-          }
-        }
-      } else {
-        float os[E];
-        int op[E];
-        if (j >= 64) {
-          __syncthreads();
-#pragma unroll
-          for (int e = 0; e < E; ++e) { xs[e * kThreads + tid] = s[e]; xp[e * kThreads + tid] = p[e]; }
-          __syncthreads();
-#pragma unroll
-          for (int e = 0; e < E; ++e) { os[e] = xs[e * kThreads + (tid ^ j)]; op[e] = xp[e * kThreads + (tid ^ j)]; }
-        } else {
-#pragma unroll
-          for (int e = 0; e < E; ++e) { os[e] = __shfl_xor(s[e], j); op[e] = __shfl_xor(p[e], j); }
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const int i = e * kThreads + tid;
-          const bool want_first = ((i & j) == 0) == ((i & k) == 0);
-          const bool mine_first = ranks_before(s[e], p[e], os[e], op[e]);
-          const bool other_first = ranks_before(os[e], op[e], s[e], p[e]);
-          if (want_first ? other_first : mine_first) { s[e] = os[e]; p[e] = op[e]; }
-        }
-      }
-    }
-  }
-}
-
 // 32-bit key whose unsigned order is the score order: float32 bits made monotonic, -0.0
 // folded onto +0.0 so that the two tie (ties go to the lower position, see ranks_before).
 __device__ __forceinline__ uint32_t rank_key32(float score) {
   const uint32_t u = __float_as_uint(score + 0.0f);
   return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
+
+// Eq. 11 and the ordered store of Eq. 12 by one wavefront: the k keys that rank first among the 256 E
+// keys in LDS (position order; pads hold 0 and come last), k < number of candidates, are passed to
+// emit(place, position) in ascending position.  Lane l holds keys 256 e + 4 l .. + 3.
+// The k-th largest key is found bit by bit from the top: a bit stays set if at least k keys are not
+// below the value so far; when exactly k are, these are the selection and the search ends (after
+// 10 - 20 bits on scores that differ).  Keys equal to the k-th go by lower position.  A step is a
+// compare per key a lane holds and scalar counting, so this is a short serial chain of one wavefront in place of
+// every wavefront comparing every pair of keys (kernel at 12 heads, 900 query blocks: 216 candidates 17.2 -> 12.7 us, 150 candidates 14.0 -> 11.6 us;
+// 40 heads, 3 000 query blocks: 44.6 -> 33.0 us).
+template <int E, typename Emit>
+__device__ __forceinline__ void wave_top_k(const uint32_t* keys, int k, Emit emit) {
+  const int lane = threadIdx.x & 63;
+  uint32_t key[E][4];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint4 v = *reinterpret_cast<const uint4*>(keys + 256 * e + 4 * lane);
+    key[e][0] = v.x; key[e][1] = v.y; key[e][2] = v.z; key[e][3] = v.w;
+  }
+  // the search, all of it wavefront-uniform
+  uint32_t t = 0;
+  int at_least = 256 * E;               // keys >= t
+  for (int bit = 31; bit >= 0 && at_least != k; --bit) {
+    const uint32_t with = t | (1u << bit);
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c += __popcll(__ballot(key[e][j] >= with));
+    if (c >= k) { t = with; at_least = c; }
+  }
+  // Keys above t are in; of the keys equal to t, the first `ties` (all of them if at_least == k).
+  int ties = at_least;
+  if (at_least != k) {
+    int above = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) above += __popcll(__ballot(key[e][j] > t));
+    ties = k - above;
+  }
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int seen_eq = 0, placed = 0;          // among positions below 256 e
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    unsigned long long eq[4], in[4];
+    int eq_before = seen_eq, eq_all = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      eq[j] = __ballot(key[e][j] == t);
+      eq_before += __popcll(eq[j] & below);
+      eq_all += __popcll(eq[j]);
+    }
+    bool on[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool is_eq = key[e][j] == t;
+      on[j] = key[e][j] > t || (is_eq && eq_before < ties);
+      eq_before += is_eq ? 1 : 0;
+    }
+    int pos = placed;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      in[j] = __ballot(on[j]);
+      pos += __popcll(in[j] & below);
+      placed += __popcll(in[j]);
+    }
+    seen_eq += eq_all;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (on[j]) emit(pos++, 256 * e + 4 * lane + j);
+  }
 }
 
 // Probe build only (liblf_hsa_probe_stamps.so, for `bench.py --select-phases`): thread 0 of the
@@ -324,12 +343,10 @@ __global__ __launch_bounds__(kThreads, (E <= 2 ? 4 : 2)) void lf_select_kernel(S
   // LDS carved from one dynamic allocation sized for this call (see select_lds_bytes()).
   extern __shared__ double lds_raw[];
   double* qd = lds_raw;                                         // [D]
-  float* xs = reinterpret_cast<float*>(qd + D);                 // [256*E]
-  int* xp = reinterpret_cast<int*>(xs + kThreads * E);          // [256*E]
-  float* fscore = reinterpret_cast<float*>(xp + kThreads * E);  // [m]
+  uint32_t* keys = reinterpret_cast<uint32_t*>(qd + D);         // [256*E], 16-byte aligned
+  float* fscore = reinterpret_cast<float*>(keys + kThreads * E);   // [m]
   int* flist = reinterpret_cast<int*>(fscore + a.m);            // [n_tf + f]
   unsigned char* fflag = reinterpret_cast<unsigned char*>(flist + a.n_tf + a.f);  // [F_h]
-  unsigned char* sel = fflag + ((a.F_h + 3) & ~3);              // [n_cand]
 
   const int tid = threadIdx.x;
   const int h = blockIdx.x / a.n_q, r = blockIdx.x % a.n_q;
@@ -354,9 +371,7 @@ __global__ __launch_bounds__(kThreads, (E <= 2 ? 4 : 2)) void lf_select_kernel(S
   float s1 = -INFINITY;   // E == 1: this thread's score and its candidate's position
   int p1 = -1;
   if (E == 1) {
-    uint32_t* keys = reinterpret_cast<uint32_t*>(xs);
-    keys[tid] = 0u;       // pads must hold 0 (see the ranking below)
-    if (tid < a.n_cand) sel[tid] = 0;
+    keys[tid] = 0u;       // pads must hold 0 (see wave_top_k)
     const int slot = kThreads - 1 - tid, sink_b = a.n_sink * a.nb;
     if (need_scores && slot < a.n_cand - ret_b) {
       p1 = slot < sink_b ? slot : slot + ret_b;
@@ -394,94 +409,43 @@ __global__ __launch_bounds__(kThreads, (E <= 2 ? 4 : 2)) void lf_select_kernel(S
   LF_STAMP(3);   // frame ranking and frame list
 
   // Eq. 10: block-level scores over B_r, candidates in ascending block id; candidate
-  // e*256 + tid is element e of this thread (E > 1; for E == 1 see above).
-  float s[E];
-  int p[E];
+  // e*256 + tid is element e of this thread (E > 1; for E == 1 see above).  The keys go to LDS in
+  // position order.
   if (E == 1) {
     if (need_scores && tid < ret_b) {
       p1 = a.n_sink * a.nb + tid;
       s1 = dot_quad_major<D>(qd, kth, (uint32_t)(flist[p1 / a.nb] * a.nb + p1 % a.nb), a.kt_rows);
     }
-    s[0] = s1;
-    p[0] = p1;
-  } else {
+    if (p1 >= 0) keys[p1] = rank_key32(s1);
+  } else if (need_scores) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int i = e * kThreads + tid;
-      s[e] = -INFINITY;
-      p[e] = 0x7fffffff;
+      uint32_t key = 0u;
       if (i < a.n_cand) {
         const int c = flist[i / a.nb] * a.nb + i % a.nb;
-        s[e] = dot_quad_major<D>(qd, kth, (uint32_t)c, a.kt_rows);
-        p[e] = i;
-        sel[i] = 0;
+        key = rank_key32(dot_quad_major<D>(qd, kth, (uint32_t)c, a.kt_rows));
       }
+      keys[i] = key;
     }
-  }
-
-  LF_STAMP_SYNC();
-  LF_STAMP(4);   // block scores
-  // Eq. 11: top-k blocks, J_r = the candidates of rank < k_blocks.  With at most one
-  // candidate per thread the rank is counted directly (how many keys are larger, keys read
-  // as LDS broadcasts); larger candidate sets are sorted, after which index = rank.
-  if (a.k_blocks < a.n_cand && E == 1) {
-    // 32-bit keys in position order.  A candidate's rank = earlier positions with a key >= its
-    // own + later positions with a key > its own; for a wavefront the positions before its
-    // first lane are all earlier and those after its last lane all later, so only the 64
-    // positions of its own lanes need the position compared.  Pads hold 0, which no key is below.
-    uint32_t* keys = reinterpret_cast<uint32_t*>(xs);   // [256], 16-byte aligned, zeroed above
-    if (p[0] >= 0) keys[p[0]] = rank_key32(s[0]);
-    __syncthreads();
-    const uint32_t mine = keys[tid];
-    const int w0 = __builtin_amdgcn_readfirstlane(tid & ~63);
-    if (w0 < a.n_cand) {
-      // four counters, so that a compare and the add that takes its carry need not be neighbours
-      int r0 = 0, r1 = 0, r2 = 0, r3 = 0;
-#pragma unroll 4
-      for (int j = 0; j < w0; j += 4) {
-        const uint4 kk = *reinterpret_cast<const uint4*>(keys + j);
-        r0 += kk.x >= mine ? 1 : 0; r1 += kk.y >= mine ? 1 : 0;
-        r2 += kk.z >= mine ? 1 : 0; r3 += kk.w >= mine ? 1 : 0;
-      }
-      const int lane = tid & 63;
-#pragma unroll 4
-      for (int j = 0; j < 64; j += 4) {
-        const uint4 kk = *reinterpret_cast<const uint4*>(keys + w0 + j);
-        r0 += (kk.x > mine || (kk.x == mine && j + 0 < lane)) ? 1 : 0;
-        r1 += (kk.y > mine || (kk.y == mine && j + 1 < lane)) ? 1 : 0;
-        r2 += (kk.z > mine || (kk.z == mine && j + 2 < lane)) ? 1 : 0;
-        r3 += (kk.w > mine || (kk.w == mine && j + 3 < lane)) ? 1 : 0;
-      }
-#pragma unroll 4
-      for (int j = w0 + 64; j < a.n_cand; j += 4) {
-        const uint4 kk = *reinterpret_cast<const uint4*>(keys + j);
-        r0 += kk.x > mine ? 1 : 0; r1 += kk.y > mine ? 1 : 0;
-        r2 += kk.z > mine ? 1 : 0; r3 += kk.w > mine ? 1 : 0;
-      }
-      const int rank = (r0 + r1) + (r2 + r3);
-      if (tid < a.n_cand && rank < a.k_blocks) sel[tid] = 1;
-    }
-  } else if (a.k_blocks < a.n_cand) {
-    bitonic_sort<E>(s, p, xs, xp);
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (e * kThreads + tid < a.k_blocks) sel[p[e]] = 1;
-  } else {
-    __syncthreads();
-    for (int i = tid; i < a.n_cand; i += kThreads) sel[i] = 1;
   }
   __syncthreads();
-  LF_STAMP(5);   // block ranking
+  LF_STAMP(4);   // block scores
 
-  // Eq. 12 as a sorted list: kept candidates in ascending id, then the mandatory current blocks.
+  // Eq. 11 and 12: the kept candidates in ascending id, then the mandatory current blocks.  The
+  // first wavefront ranks and stores the former, the others store the latter.
   int32_t* out = a.indices + ((int64_t)h * a.n_q + r) * a.list_len;
-  if (tid < 64)
-    wave_compact(sel, a.n_cand, [&](int pos, int i) { out[pos] = flist[i / a.nb] * a.nb + i % a.nb; });
-  if (a.current_mandatory)
-    for (int i = tid; i < a.f * a.nb; i += kThreads) out[a.k_blocks + i] = a.F_h * a.nb + i;
+  if (!need_scores) {
+    for (int i = tid; i < a.n_cand; i += kThreads) out[i] = flist[i / a.nb] * a.nb + i % a.nb;
+  } else if (tid < 64) {
+    wave_top_k<E>(keys, a.k_blocks, [&](int pos, int i) { out[pos] = flist[i / a.nb] * a.nb + i % a.nb; });
+  }
+  if (a.current_mandatory && (tid >= 64 || !need_scores)) {
+    const int t0 = need_scores ? 64 : 0;
+    for (int i = tid - t0; i < a.f * a.nb; i += kThreads - t0) out[a.k_blocks + i] = a.F_h * a.nb + i;
+  }
   LF_STAMP_SYNC();
-  LF_STAMP(6);   // compaction and store
+  LF_STAMP(5);   // block ranking and store
 }
 
 }  // namespace
@@ -563,7 +527,7 @@ static hipError_t launch_select(const lf_budget* b, const lf_dims* dm, const flo
   sa.kt_rows = kt_rows;
   sa.kh_rows = kh_rows;
   sa.kh_row0 = kh_row0;
-  // E = candidate pairs per thread in the sort: 256*E >= n_cand, E a power of two
+  // E = candidates per thread: 256*E >= n_cand, E a power of two
   int e = 1;
   while (kThreads * e < dm->n_cand) e <<= 1;
   const unsigned sel_grid = (unsigned)(dm->H * dm->n_q);
@@ -645,7 +609,7 @@ void* g_scratch_ptr[kMaxDevices];   // zero-initialised; written once per device
 }
 
 #ifdef LF_PROBE_STAMPS
-// Copies the stamps of the last selection launch to host memory: [4096][8] uint64, entries 0..6 of
+// Copies the stamps of the last selection launch to host memory: [4096][8] uint64, entries 0..5 of
 // a workgroup as noted above.  Returns 0 or a hipError_t.
 extern "C" int lf_probe_select_stamps(void* host_out) {
   return (int)hipMemcpyFromSymbol(host_out, HIP_SYMBOL(g_stamps), sizeof(unsigned long long) * 4096 * 8);
