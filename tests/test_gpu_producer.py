@@ -76,6 +76,16 @@ def test_chunk_sized_call_on_sampled_tokens(gpu, heads):
     print(f"producer {heads} heads: worst relative error {worst:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("across", [0, 1])
+@pytest.mark.parametrize("heads,d", [(16, 128), (17, 128), (48, 128), (49, 128), (96, 64), (97, 64)])
+def test_token_lengths_around_the_register_forms(gpu, heads, d, across):
+    """Tokens of 256, 272, 768 and 784 chunks (of 8 channels): the last and first ones of the forms
+    that hold 4 x 64 and 12 x 64 chunks in registers and of the one that reads a token twice."""
+    torch, lf = gpu
+    print(f"producer case heads={heads} d={d} across={across}", flush=True)
+    _check(torch, lf, 9, heads, d, seed=heads, across=across, pairing=across, x_pad=8, into_cache=True)
+
+
 def test_binding_rejects_bad_arguments(gpu):
     torch, lf = gpu
     x = synth.make_producer_inputs(8, 2, 64, 0)
