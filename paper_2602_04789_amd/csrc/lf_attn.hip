@@ -42,8 +42,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int int32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kMaxEnt = 512;  // half tiles decoded per pass (power of two)
-
 struct AttnArgs {
   const uint16_t* Q;
   const uint16_t* K;
@@ -109,12 +107,20 @@ __device__ __forceinline__ void lds_barrier() {
 
 // WAVES wavefronts of 32 query rows each per workgroup.  DENSE: the workgroup walks the KV
 // token range [kv0, kv1) and stores its state, all wavefronts sharing one tile stage.  Otherwise
-// it holds WAVES / 2 query blocks of two wavefronts each, every query block with a tile stage of
-// its own and walking its own list (two query blocks per workgroup measured 2 % faster than
-// one); the barriers are common, the lists being equally long.
-template <int D, int WAVES, bool DENSE>
+// it holds WAVES / 2 pairs of wavefronts, every pair with a tile stage of its own; the barriers are
+// common.  SPLIT = 1: each pair has a query block of its own and walks its list (two query blocks per
+// workgroup measured 2 % faster than one; the lists are equally long).  SPLIT > 1 (= WAVES / 2): the
+// pairs share one query block, each walks a SPLIT-th of its list, and their online-softmax states
+// are merged through LDS at the end.  A call with few query blocks leaves compute units idle while
+// every wavefront goes through its list step by step (one wavefront per SIMD: 0.55 - 0.8 us a step,
+// mostly latency); dividing the list shortens that chain.
+template <int D, int WAVES, bool DENSE, int SPLIT = 1>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs a) {
-  constexpr int QPW = DENSE ? 1 : WAVES / 2;    // query blocks per workgroup
+  constexpr int QPW = DENSE ? 1 : WAVES / 2;    // tile stages per workgroup
+  constexpr int QB = QPW / SPLIT;               // query blocks per workgroup
+  // half tiles decoded per pass (power of two); half of them where the lists are divided, so that two
+  // such workgroups of d = 64 fit the LDS of a compute unit
+  constexpr int kMaxEnt = SPLIT > 1 ? 256 : 512;
   constexpr int WPQ = WAVES / QPW;              // wavefronts that share one tile stage
   constexpr int kThreads = 64 * WPQ;            // ... and their threads
   constexpr int CH = D / 8;                 // 16-byte chunks per token row
@@ -124,6 +130,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   constexpr int LPW = 32 / (RPI * WPQ);     // load instructions per wavefront, per tile, per tensor
   constexpr int TILE = 32 * CH;             // uint4 per half tile (32 KV rows)
   static_assert(LPW >= 1 && LPW * RPI * WPQ == 32, "a half tile must split evenly over the wavefronts");
+  static_assert(SPLIT == 1 || (!DENSE && SPLIT == QPW && MB * 4 % SPLIT == 0), "a split block has the workgroup to itself");
 
   __shared__ uint4 buf0_all[QPW][2 * TILE];          // K | V of even tiles
   __shared__ uint4 buf1_all[QPW][2 * TILE];          // K | V of odd tiles
@@ -133,11 +140,11 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of
   // (head, query block) pairs so that neighbours sharing KV blocks share an L2.
   const int wg = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
-  const int qb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / WPQ;   // query block inside the workgroup
-  int w = wg * QPW + qb;
+  const int qb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / WPQ;   // tile stage: query block (or slice of one)
+  int w = SPLIT > 1 ? wg : wg * QPW + qb;
   // A workgroup past the end leaves as a whole.  Inside the last one a query block past the end
   // repeats the last valid one (it has to keep step at the barriers) and stores nothing.
-  if (wg * QPW >= a.total_wg) return;
+  if (wg * QB >= a.total_wg) return;
   const bool w_valid = w < a.total_wg;
   w = min(w, a.total_wg - 1);
   const int per_head = DENSE ? a.wg_per_head : a.n_q;
@@ -160,14 +167,17 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
 
   // The list entries of the first pass are requested first, so that they travel together with
   // the Q fragments instead of after them.
-  const int32_t* list = DENSE ? nullptr : a.idx + ((int64_t)h * a.n_q + r) * a.list_stride;
+  // A slice is entries [qb slice_len, (qb + 1) slice_len) of the list, the last ones shorter or empty.
+  const int slice_len = SPLIT > 1 ? (a.list_len + SPLIT - 1) / SPLIT : a.list_len;
+  const int my_len = SPLIT > 1 ? min(max(a.list_len - qb * slice_len, 0), slice_len) : a.list_len;
+  const int32_t* list = DENSE ? nullptr : a.idx + ((int64_t)h * a.n_q + r) * a.list_stride + (SPLIT > 1 ? qb * slice_len : 0);
   constexpr int EPT = DENSE ? 1 : kMaxEnt / 2 / kThreads;   // list entries per thread and pass (up to two half tiles each)
   int pre[EPT];
   if constexpr (!DENSE) {
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
       const int i = EPT * tid + j;
-      pre[j] = i < a.list_len ? list[i] : -1;
+      pre[j] = i < my_len ? list[i] : -1;
     }
   }
   // A wavefront whose 32 query rows all lie past the end of a short query block loads its share
@@ -303,7 +313,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   // Accumulator i of oacc[mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of query row qrow; the
   // stored state uses the same order within a row, so a lane moves float4s.
   float* state_row = nullptr;
-  if (a.state_o != nullptr && qrow < q_cnt) {
+  if (a.state_o != nullptr && qrow < q_cnt && (SPLIT == 1 || qb == 0)) {   // one slice carries a state on
     const int64_t row = (int64_t)h * a.q_len + qtok0 + qrow;
     state_row = a.state_o + row * D;
     if constexpr (!DENSE) {
@@ -333,7 +343,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     const int tok = a.kv0 + 32 * t;
     return make_int2(min(tok, a.kv1), min(max(a.kv1 - tok, 0), 32));
   };
-  const int n_entries = DENSE ? (a.kv1 - a.kv0 + 63) / 64 : a.list_len;
+  const int n_entries = DENSE ? (a.kv1 - a.kv0 + 63) / 64 : slice_len;
   const int pass_len = DENSE ? n_entries : kMaxEnt / 2;
   for (int l0 = 0; l0 < n_entries; l0 += pass_len) {
     const int l1 = min(n_entries, l0 + pass_len);
@@ -343,7 +353,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
         const int i = l0 + EPT * tid + e;
-        const int c = i < l1 ? (l0 == 0 ? pre[e] : list[i]) : -1;
+        const int c = i < min(l1, my_len) ? (l0 == 0 ? pre[e] : list[i]) : -1;
         const bool ok = (unsigned)c < (unsigned)a.n_k;
         const int tau = ok ? c / a.nb : 0, j = ok ? c % a.nb : 0;
         htok[e] = tau * a.n + j * 64;
@@ -595,6 +605,57 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     }
     return;
   }
+  if constexpr (SPLIT > 1) {
+    // Merge of the slices: every pair leaves (m, l) and O of its rows where its tiles were, then the
+    // SPLIT wavefronts of a row half each take a SPLIT-th of the channels of all slices' O.  A slice
+    // without a valid id has m = -1e30, l = 0 and O = 0.
+    constexpr int NGRP = MB * 4, PER = NGRP / SPLIT;   // float4 groups of a row, and per wavefront
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));          // the last requests (empty tiles) write zeros
+    __syncthreads();
+    float4* const mine = reinterpret_cast<float4*>(rh == 0 ? buf0 : buf1);
+    static_assert(NGRP * 64 == 2 * TILE, "a row half of O fills one tile buffer");
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        mine[(mb * 4 + g) * 64 + lane] =
+            make_float4(oacc[mb][4 * g + 0], oacc[mb][4 * g + 1], oacc[mb][4 * g + 2], oacc[mb][4 * g + 3]);
+    if (kg == 0) ent[32 * rh + ln] = make_int2(__float_as_int(m_run), __float_as_int(l_run));
+    __syncthreads();
+    float m = -1.0e30f, l = 0.0f, f[SPLIT];
+    int2 ml[SPLIT];
+#pragma unroll
+    for (int q2 = 0; q2 < SPLIT; ++q2) {
+      ml[q2] = ent_all[q2][32 * rh + ln];
+      m = fmaxf(m, __int_as_float(ml[q2].x));
+    }
+#pragma unroll
+    for (int q2 = 0; q2 < SPLIT; ++q2) {
+      f[q2] = __builtin_amdgcn_exp2f(__int_as_float(ml[q2].x) - m);
+      l = fmaf(__int_as_float(ml[q2].y), f[q2], l);
+    }
+    if (qrow >= q_cnt) return;
+    if (a.lse2 != nullptr && kg == 0 && qb == 0)
+      a.lse2[(int64_t)h * a.q_len + qtok0 + qrow] = l > 0.0f ? m + __builtin_log2f(l) : INFINITY;
+    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+    uint16_t* op = a.O + (int64_t)h * a.o_stride_head + (int64_t)(qtok0 + qrow) * a.o_stride_tok;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int grp = qb * PER + p;
+      float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int q2 = 0; q2 < SPLIT; ++q2) {
+        const float4 v = reinterpret_cast<const float4*>(rh == 0 ? buf0_all[q2] : buf1_all[q2])[grp * 64 + lane];
+        o[0] = fmaf(v.x, f[q2], o[0]); o[1] = fmaf(v.y, f[q2], o[1]);
+        o[2] = fmaf(v.z, f[q2], o[2]); o[3] = fmaf(v.w, f[q2], o[3]);
+      }
+      bf16x4 o4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(o[e] * inv);
+      *reinterpret_cast<bf16x4*>(op + 32 * (grp >> 2) + 8 * (grp & 3) + 4 * kg) = o4;
+    }
+    return;
+  }
   // normalise and store
   const float inv = l_run > 0.0f ? 1.0f / l_run : 0.0f;   // a list without a valid id gives zero rows
   if (qrow < q_cnt && w_valid) {
@@ -654,11 +715,19 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.state_o = const_cast<float*>(state_o);
   a.state_ml = reinterpret_cast<float2*>(const_cast<float*>(state_ml));
   a.total_wg = dm->H * dm->n_q;
+  hipStream_t st = (hipStream_t)stream;
+  if (lf_split_lists(a.total_wg, list_len)) {
+    a.wg_per_xcd = (a.total_wg + 7) / 8;
+    const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
+    const hipError_t rc = dm->d == 128
+        ? lf_launch(lf_attn_kernel<128, 8, false, 4>, dim3(grid), dim3(512), 0, st, a)
+        : lf_launch(lf_attn_kernel<64, 8, false, 4>, dim3(grid), dim3(512), 0, st, a);
+    return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
+  }
   constexpr int kListWaves = 4;                  // two query blocks per workgroup
   const int n_wg = (a.total_wg + kListWaves / 2 - 1) / (kListWaves / 2);
   a.wg_per_xcd = (n_wg + 7) / 8;
   const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
-  hipStream_t st = (hipStream_t)stream;
   const hipError_t rc = dm->d == 128
       ? lf_launch(lf_attn_kernel<128, kListWaves, false>, dim3(grid), dim3(64 * kListWaves), 0, st, a)
       : lf_launch(lf_attn_kernel<64, kListWaves, false>, dim3(grid), dim3(64 * kListWaves), 0, st, a);

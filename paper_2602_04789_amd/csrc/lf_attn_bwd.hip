@@ -88,9 +88,12 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // dQ: a workgroup of two wavefronts owns a query block (wavefront rh its rows [32 rh, +32)) and
-// walks the block's list of KV blocks in half tiles of 32 KV rows.
-template <int D>
-__global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
+// walks the block's list of KV blocks in half tiles of 32 KV rows.  SPLIT > 1: the workgroup has
+// SPLIT such pairs with a tile stage each, every pair walks a SPLIT-th of the list (the barriers are
+// common, the slices equally long but for empty entries at the end), and their sums are added
+// through LDS in a fixed order: for calls with too few query blocks to fill the chip.
+template <int D, int SPLIT>
+__global__ __launch_bounds__(kThreads * SPLIT, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;
   constexpr int MB = D / 32;
@@ -99,13 +102,16 @@ __global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
   constexpr int TILE = 32 * CH;             // uint4 per 32-row tile
   constexpr int NBUF = 2;
 
-  __shared__ uint4 buf[NBUF][2 * TILE];     // [step mod NBUF][A1 tile | A2 tile]
-  __shared__ int2 ent[kPass];               // (first token, token count) per list entry of a pass
+  __shared__ uint4 buf_all[SPLIT][NBUF][2 * TILE];     // [slice][step mod NBUF][A1 tile | A2 tile]
+  __shared__ int2 ent_all[SPLIT][kPass];               // (first token, token count) per list entry of a pass
 
   const int w = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
   if (w >= a.total_wg) return;
   const int h = w / a.owners, r = w % a.owners;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
+  uint4 (*const buf)[2 * TILE] = buf_all[slice];
+  int2* const ent = ent_all[slice];
+  const int tid = threadIdx.x % kThreads, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, kg = lane >> 5;
 
@@ -115,8 +121,10 @@ __global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
   const int orow = 32 * wave + ln;
   const bool o_ok = orow < o_cnt;
 
-  const int32_t* list = a.idx + ((int64_t)h * a.owners + r) * a.list_stride;
-  const int n_ent = a.list_len;
+  // this pair's slice: entries [slice n_ent, +n_ent) of the list, of which my_ent exist
+  const int n_ent = (a.list_len + SPLIT - 1) / SPLIT;
+  const int my_ent = SPLIT > 1 ? min(max(a.list_len - slice * n_ent, 0), n_ent) : n_ent;
+  const int32_t* list = a.idx + ((int64_t)h * a.owners + r) * a.list_stride + (SPLIT > 1 ? slice * n_ent : 0);
 
   // B operands: lane (column ln, k-group kg) holds 8 consecutive channels of its owner row
   Frag xf[KS], yf[KS];
@@ -294,7 +302,7 @@ __global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
     for (int i = tid; i < n_local; i += kThreads) {
-      const int cidx = list[l0 + i];
+      const int cidx = l0 + i < my_ent ? list[l0 + i] : -1;
       const bool ok = (unsigned)cidx < (unsigned)a.streams;
       const int tau = ok ? cidx / a.nb : 0, j = ok ? cidx % a.nb : 0;
       ent[i] = make_int2(tau * a.n + j * 64, ok ? min(64, a.n - j * 64) : 0);
@@ -323,6 +331,38 @@ __global__ __launch_bounds__(kThreads, 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
   }
 
   // accumulator i of acc[mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of the owner row
+  if constexpr (SPLIT > 1) {
+    // every pair leaves its sums where its tiles were; wavefront (slice, row half) adds and stores a
+    // SPLIT-th of the row half's channels
+    constexpr int NGRP = MB * 4, PER = NGRP / SPLIT;
+    static_assert(NGRP * 64 == 2 * TILE && NGRP % SPLIT == 0, "a row half fills one tile buffer");
+    __syncthreads();                          // no request is in flight: the last step makes none
+    float4* const mine = reinterpret_cast<float4*>(buf[wave]);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        mine[(mb * 4 + g) * 64 + lane] =
+            make_float4(acc[mb][4 * g + 0], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]);
+    __syncthreads();
+    if (!o_ok) return;
+    uint16_t* op = a.out1 + (int64_t)h * a.o1_head + (int64_t)(otok0 + orow) * a.o1_tok;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int grp = slice * PER + p;
+      float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int q2 = 0; q2 < SPLIT; ++q2) {
+        const float4 v = reinterpret_cast<const float4*>(buf_all[q2][wave])[grp * 64 + lane];
+        o[0] += v.x; o[1] += v.y; o[2] += v.z; o[3] += v.w;
+      }
+      bf16x4 o4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(o[e] * a.scale);
+      *reinterpret_cast<bf16x4*>(op + 32 * (grp >> 2) + 8 * (grp & 3) + 4 * kg) = o4;
+    }
+    return;
+  }
   if (o_ok) {
     uint16_t* op = a.out1 + (int64_t)h * a.o1_head + (int64_t)(otok0 + orow) * a.o1_tok;
     const float factor = a.scale;
@@ -776,9 +816,11 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_q; a.streams = dm->n_k;
   a.total_wg = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
+  const bool split = lf_split_lists(a.total_wg, list_len);
+  const dim3 grid1((unsigned)(a.wg_per_xcd * 8)), block1((unsigned)(split ? 4 * kThreads : kThreads));
   hipError_t rc = dm->d == 128
-      ? lf_launch(lf_attn_bwd_q_kernel<128>, dim3((unsigned)(a.wg_per_xcd * 8)), dim3(kThreads), 0, st, a)
-      : lf_launch(lf_attn_bwd_q_kernel<64>, dim3((unsigned)(a.wg_per_xcd * 8)), dim3(kThreads), 0, st, a);
+      ? lf_launch(split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>, grid1, block1, 0, st, a)
+      : lf_launch(split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>, grid1, block1, 0, st, a);
   if (rc != hipSuccess) return LF_ERR_HIP;
   // dK and dV
   a.X = (const uint16_t*)K;   a.x_tok = s->k_stride_tok;  a.x_head = s->k_stride_head;

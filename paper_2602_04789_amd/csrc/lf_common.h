@@ -28,6 +28,21 @@ struct lf_dims {
 // Validates shape (and budget when non-NULL); returns LF_OK or an lf_status.
 int lf_derive(const lf_shape* s, const lf_budget* b, lf_dims* out);
 
+// Whether the query-major attention kernels divide each list among the four pairs of wavefronts of
+// a workgroup instead of giving every (head, query block) one pair.  A divided block takes a
+// compute unit (256 of them) to itself at d = 128.  Measured, d = 128, forward call / backward call
+// (dQ divided, the rest as it was), us before -> after:
+//   <= 256 blocks: 192 blocks, lists of 8: 18.0 -> 14.3 / 53.5 -> 48.9; of 40: 51.1 -> 27.9 / 130 -> 97;
+//     lists of 4 are one step a slice: 13.5 -> 13.3 / 41.1 -> 41.6, not divided;
+//   two rounds: 320 blocks, lists of 16: 27.8 -> 31.2 / 90.3 -> 89.1; of 40: 54.8 -> 52.1 / 158 -> 149;
+//     480 blocks, lists of 40: 63.1 -> 56.2 / 199 -> 188;
+//   three: 560 blocks, lists of 40: 74.4 -> 80.4 / 217 -> 242.
+// At d = 64 two divided blocks share a compute unit and the gain is larger (480 blocks, lists of 40:
+// 47.3 -> 37.8 / 165 -> 153; of 8: 16.0 -> 18.3 / 57.4 -> 58.5); the same line serves.
+inline bool lf_split_lists(int blocks, int list_len) {
+  return (blocks <= 256 && list_len >= 6) || (blocks <= 512 && list_len >= 32);
+}
+
 // Kernel launchers (defined in the .hip files); return LF_OK or LF_ERR_HIP.
 int lf_launch_select(const void* Q, const void* K, const lf_shape* s, const lf_budget* b,
                      const lf_dims* dm, int32_t* indices, void* workspace, void* stream);

@@ -320,3 +320,25 @@ def test_training_step_replays_from_a_captured_graph(gpu):
         torch.cuda.synchronize()
         for a, e in zip(got, want):
             assert torch.equal(a.view(torch.int16), e.view(torch.int16))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,list_len", [(2, 5), (2, 6), (2, 9), (16, 31), (16, 32), (17, 32), (1, 47)])
+def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len, head_dim):
+    """dQ with and without each list divided among four pairs of wavefronts (both sides of the edges
+    of that rule, 512 and 544 query blocks among them), one head of each against the oracle."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=1000, chunk_idx=2, heads=heads, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    x["dO"] = synth.make_upstream_grad(w)
+    n_q, n_k = w.frames_per_chunk * w.blocks_per_frame, w.frames * w.blocks_per_frame
+    rng = np.random.default_rng(list_len)
+    lists = np.stack([np.stack([np.sort(rng.choice(n_k, list_len, replace=False)) for _ in range(n_q)])
+                      for _ in range(heads)]).astype(np.int32)
+    print(f"divided lists, backward: heads={heads} d={head_dim} list length {list_len}", flush=True)
+    (dQ, dK, dV), _ = _run(torch, lf, w, x, lists)
+    h = heads - 1
+    Qf, Kf, Vf, dOf = (_f32(x[k])[h:h + 1] for k in ("Q", "K", "V", "dO"))
+    ref = O.sparse_attention_backward(Qf, Kf, Vf, dOf, lists[h:h + 1], w.frame_len, w.block)
+    for name, got, want in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
+        _close(name, got[h:h + 1], want)

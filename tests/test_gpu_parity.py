@@ -521,3 +521,59 @@ def test_rollout_calls_40_heads(gpu, chunk, step):
     print(f"rollout chunk {chunk} step {step}: max-abs {worst:.2e} mean-abs {mean:.2e}", flush=True)
     _, worst, mean = _check_attn(torch, lf, w, x, dev, idx, lists, pairs=pairs, split=True)
     print(f"rollout chunk {chunk} step {step} split: max-abs {worst:.2e} mean-abs {mean:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,list_len", [(2, 5), (2, 6), (2, 7), (8, 31), (16, 31), (16, 32), (16, 33), (17, 32),
+                                            (2, 129), (2, 517)])
+def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len, head_dim):
+    """The attention kernels divide lists among four pairs of wavefronts when a call has few query
+    blocks: both sides of each edge of that rule (list lengths 5/6 and 31/32, 512 and 544 query
+    blocks), slices of unequal length, slices without any valid id, several decode passes, ragged
+    query blocks, a continued state (the two-phase call) and the log-sum-exp, on lists with
+    out-of-range and repeated ids."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=1000, chunk_idx=2, heads=heads, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    n_q, n_k = w.frames_per_chunk * w.blocks_per_frame, w.frames * w.blocks_per_frame
+    rng = np.random.default_rng(list_len)
+    lists = rng.integers(-2, n_k + 2, (heads, n_q, list_len)).astype(np.int32)
+    lists[0, 0, 1:] = -1                                  # one valid id: three empty slices
+    lists[0, 0, 0] = 3
+    lists[heads - 1, n_q - 1, :list_len // 2] = n_k       # the first slices empty, and a ragged query block
+    lists[heads - 1, n_q - 1, list_len - 1] = 0
+    lists[heads - 1, 0] = -1                              # none: zero rows
+    print(f"divided lists: heads={heads} d={head_dim} list length {list_len}", flush=True)
+    idx = torch.from_numpy(lists).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, w.frame_len, w.block)
+    assert torch.equal(out, lf.lf_sparse_attn(Q, K, V, idx, w.frame_len, w.block))
+    torch.cuda.synchronize()
+    got, lse2 = out.float().cpu().numpy().astype(np.float64), lse2.cpu().numpy()
+    pairs = {(0, 0), (heads - 1, n_q - 1), (heads - 1, 0), (0, w.blocks_per_frame - 1)}
+    while len(pairs) < 24:
+        pairs.add((int(rng.integers(heads)), int(rng.integers(n_q))))
+    for h, r in sorted(pairs):
+        kept = [int(c) for c in lists[h, r] if 0 <= c < n_k]
+        lo, hi = O.block_token_range(r, w.frame_len, w.block)
+        if not kept:
+            assert np.all(got[h, lo:hi] == 0.0) and np.isposinf(lse2[h, lo:hi]).all()
+            continue
+        ref = O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, kept, w.frame_len, w.block)
+        err = np.abs(got[h, lo:hi] - ref)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max())
+        cols = np.concatenate([np.arange(*O.block_token_range(c, w.frame_len, w.block)) for c in kept])
+        s = Qf[h, lo:hi].astype(np.float64) @ Kf[h, cols].astype(np.float64).T / np.sqrt(head_dim) / np.log(2.0)
+        top = s.max(axis=1)
+        ref2 = top + np.log2(np.exp2(s - top[:, None]).sum(axis=1))
+        # the row sum is of probabilities rounded to bfloat16: at most 2^-8 of it, 2^-8 / ln 2 in log2
+        assert np.abs(lse2[h, lo:hi] - ref2).max() <= 2.0 ** -8 / np.log(2.0) + 1e-4
+    # the two-phase call continues a state in one of the slices
+    b = lf.lf_chunk_budget(w.chunk_idx, w.schedule)
+    idx = lf.lf_select_mask(Q, K, w.frame_len, w.block, b)
+    one = lf.lf_sparse_attn(Q, K, V, idx, w.frame_len, w.block)
+    two = lf.lf_sparse_attn_split(Q, K, V, idx, w.frame_len, w.block, b)
+    torch.cuda.synchronize()
+    diff = (one.float() - two.float()).abs()
+    assert float(diff.max()) <= 2 * MAX_ABS and float(diff.mean()) <= 2 * MEAN_ABS
