@@ -155,17 +155,13 @@ def lf_chunk_budget(chunk_idx: int, schedule) -> lf_budget:
 
 def make_shape(Q, K, V=None, O=None, frame_len: int = 0, block: int = 64) -> lf_shape:
     """Geometry of [H, L, d] tensors (any object with .shape and .stride() in elements)."""
-    sh = lf_shape()
-    sh.heads, sh.q_len, sh.head_dim = int(Q.shape[0]), int(Q.shape[1]), int(Q.shape[2])
-    sh.kv_len = int(K.shape[1])
-    sh.frame_len, sh.block, sh.dtype = int(frame_len), int(block), LF_BF16
-    sh.q_stride_head, sh.q_stride_tok = int(Q.stride(0)), int(Q.stride(1))
-    sh.k_stride_head, sh.k_stride_tok = int(K.stride(0)), int(K.stride(1))
     Vt = K if V is None else V
     Ot = Q if O is None else O
-    sh.v_stride_head, sh.v_stride_tok = int(Vt.stride(0)), int(Vt.stride(1))
-    sh.o_stride_head, sh.o_stride_tok = int(Ot.stride(0)), int(Ot.stride(1))
-    return sh
+    qs, ks, vs, os_, i = Q.shape, K.stride, Vt.stride, Ot.stride, int
+    # one positional construction costs a third of sixteen attribute assignments
+    return lf_shape(i(qs[0]), i(qs[2]), i(frame_len), i(block), i(qs[1]), i(K.shape[1]), LF_BF16, 0,
+                    i(Q.stride(1)), i(Q.stride(0)), i(ks(1)), i(ks(0)), i(vs(1)), i(vs(0)),
+                    i(os_(1)), i(os_(0)))
 
 
 def lf_workspace_bytes(shape: lf_shape, budget: lf_budget) -> int:
@@ -180,38 +176,49 @@ def lf_workspace_layout(shape: lf_shape, budget: lf_budget) -> Tuple[int, int, i
     return int(off[0]), int(off[1]), int(off[2])
 
 
+_torch = None   # the torch module, once a tensor has been seen (the budget functions do without it)
+
+
+def _get_torch():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _check_tensor(t, name: str):
-    import torch
     if not t.is_cuda:
         raise ValueError(f"{name} must live in GPU memory")
-    if t.dtype != torch.bfloat16:
+    if t.dtype != (_torch or _get_torch()).bfloat16:
         raise ValueError(f"{name} must be bfloat16")
     if t.dim() != 3 or t.stride(2) != 1:
         raise ValueError(f"{name} must be [H, L, d] with d contiguous")
 
 
 def _stream_ptr(stream) -> int:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    torch = _torch or _get_torch()
+    # the current device's current stream, without building a Stream object around it (2 us)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def lf_select_mask(Q, Kcache, frame_len: int, block: int, budget: lf_budget, indices=None,
                    workspace=None, stream=None):
     """Enqueue mask selection; returns the int32 [H, n_q, list_len] index tensor (device)."""
-    import torch
+    torch = _torch or _get_torch()
     _check_tensor(Q, "Q")
     _check_tensor(Kcache, "Kcache")
     sh = make_shape(Q, Kcache, frame_len=frame_len, block=block)
     lib = load()
-    need = lf_workspace_bytes(sh, budget)
     nb = -(-frame_len // block)
     n_q = (sh.q_len // frame_len) * nb if frame_len > 0 else 0
     if indices is None:
         indices = torch.empty((sh.heads, n_q, max(int(budget.list_len), 0)), dtype=torch.int32,
                               device=Q.device)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=Q.device)
+        workspace = torch.empty(max(lf_workspace_bytes(sh, budget), 256), dtype=torch.uint8, device=Q.device)
     rc = lib.lf_select_mask(Q.data_ptr(), Kcache.data_ptr(), C.byref(sh), C.byref(budget),
                             indices.data_ptr(), workspace.data_ptr(),
                             workspace.numel() * workspace.element_size(), _stream_ptr(stream))
@@ -266,7 +273,7 @@ def lf_select_mask_cached(Q, kcache, max_frames: int, kv_len: int, frame_len: in
                           budget: lf_budget, Kcache=None, indices=None, workspace=None, stream=None):
     """Mask selection with the pooled keys taken from ``kcache``; returns the index tensor.
     With ``Kcache`` the current chunk's block means are refreshed from it in the same call."""
-    import torch
+    torch = _torch or _get_torch()
     _check_tensor(Q, "Q")
     if Kcache is not None:
         _check_tensor(Kcache, "Kcache")
@@ -295,7 +302,7 @@ def lf_select_mask_cached(Q, kcache, max_frames: int, kv_len: int, frame_len: in
 def lf_sparse_attn(Q, Kcache, Vcache, indices, frame_len: int, block: int,
                    softmax_scale: float = 0.0, O=None, stream=None):
     """Enqueue blockwise sparse attention; returns O (bfloat16 [H, q_len, d], device)."""
-    import torch
+    torch = _torch or _get_torch()
     _check_tensor(Q, "Q")
     _check_tensor(Kcache, "Kcache")
     _check_tensor(Vcache, "Vcache")
@@ -324,7 +331,7 @@ def lf_sparse_attn_split(Q, Kcache, Vcache, indices, frame_len: int, block: int,
                          softmax_scale: float = 0.0, O=None, workspace=None, stream=None):
     """Blockwise sparse attention in two phases (dense over the current chunk, list-driven over
     the retrieved blocks); returns O.  ``indices`` as written by lf_select_mask for ``budget``."""
-    import torch
+    torch = _torch or _get_torch()
     _check_tensor(Q, "Q")
     _check_tensor(Kcache, "Kcache")
     _check_tensor(Vcache, "Vcache")
@@ -349,7 +356,7 @@ def lf_sparse_attn_split(Q, Kcache, Vcache, indices, frame_len: int, block: int,
 
 
 def _check_lists(indices, sh, frame_len):
-    import torch
+    torch = _torch or _get_torch()
     if not indices.is_cuda or indices.dtype != torch.int32 or not indices.is_contiguous():
         raise ValueError("indices must be a contiguous int32 GPU tensor [H, n_q, list_len]")
     n_q = (sh.q_len // frame_len) * (-(-frame_len // sh.block)) if frame_len > 0 else -1
@@ -361,7 +368,7 @@ def lf_sparse_attn_fwd(Q, Kcache, Vcache, indices, frame_len: int, block: int,
                        softmax_scale: float = 0.0, O=None, lse2=None, stream=None):
     """Blockwise sparse attention that also leaves the rows' log-sum-exp (exp2 domain) for
     lf_sparse_attn_bwd; returns (O, lse2)."""
-    import torch
+    torch = _torch or _get_torch()
     _check_tensor(Q, "Q")
     _check_tensor(Kcache, "Kcache")
     _check_tensor(Vcache, "Vcache")
@@ -392,7 +399,7 @@ def lf_sparse_attn_bwd(Q, Kcache, Vcache, O, dO, lse2, indices, frame_len: int, 
     """Gradients of the blockwise sparse attention; returns (dQ, dK, dV), bfloat16 with the
     strides of Q, Kcache and Vcache (``grads``: three such tensors to write into instead of new
     ones).  ``indices`` ascending and duplicate-free per list."""
-    import torch
+    torch = _torch or _get_torch()
     for t, name in ((Q, "Q"), (Kcache, "Kcache"), (Vcache, "Vcache"), (O, "O"), (dO, "dO")):
         _check_tensor(t, name)
     if tuple(dO.shape) != tuple(O.shape) or dO.stride() != O.stride():
@@ -429,7 +436,7 @@ def lf_qk_norm_rope(X, g, cos_table, sin_table, heads: int, Y, eps: float = 1e-6
                     across_heads: bool = False, pairing: int = 0, stream=None):
     """RMSNorm + rotary embedding of the token-major activation X [L, >= H*d] (bfloat16) into the
     head-major tensor Y [H, L, d] (bfloat16; may be a view into Q or into the K cache)."""
-    import torch
+    torch = _torch or _get_torch()
     if X.dtype != torch.bfloat16 or Y.dtype != torch.bfloat16 or X.dim() != 2 or Y.dim() != 3:
         raise ValueError("X must be bfloat16 [L, H*d] and Y bfloat16 [H, L, d]")
     if X.stride(1) != 1 or Y.stride(2) != 1 or not (X.is_cuda and Y.is_cuda):
@@ -437,12 +444,11 @@ def lf_qk_norm_rope(X, g, cos_table, sin_table, heads: int, Y, eps: float = 1e-6
     for t in (g, cos_table, sin_table):
         if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous():
             raise ValueError("g, cos_table, sin_table must be contiguous float32 GPU tensors")
-    p = lf_producer_shape()
-    p.heads, p.head_dim, p.tokens = int(heads), int(Y.shape[2]), int(X.shape[0])
-    p.across_heads, p.pairing, p.eps = int(bool(across_heads)), int(pairing), float(eps)
-    p.x_stride_tok, p.y_stride_tok, p.y_stride_head = int(X.stride(0)), int(Y.stride(1)), int(Y.stride(0))
-    if tuple(Y.shape[:2]) != (p.heads, p.tokens) or g.numel() != p.heads * p.head_dim \
-            or tuple(cos_table.shape) != (p.tokens, p.head_dim // 2) or cos_table.shape != sin_table.shape:
+    heads, tokens, d, Ysh = int(heads), int(X.shape[0]), int(Y.shape[2]), Y.shape
+    p = lf_producer_shape(heads, d, tokens, int(bool(across_heads)), int(pairing), float(eps),
+                          int(X.stride(0)), int(Y.stride(1)), int(Y.stride(0)))
+    if Ysh[0] != heads or Ysh[1] != tokens or g.numel() != heads * d \
+            or tuple(cos_table.shape) != (tokens, d // 2) or cos_table.shape != sin_table.shape:
         raise ValueError("shapes of Y, g or the angle tables do not fit X")
     rc = load().lf_qk_norm_rope(X.data_ptr(), g.data_ptr(), cos_table.data_ptr(), sin_table.data_ptr(),
                                 C.byref(p), Y.data_ptr(), _stream_ptr(stream))
