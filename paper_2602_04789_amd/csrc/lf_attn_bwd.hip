@@ -468,15 +468,13 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
                    "buffer_load_dwordx4 %1, %2, 0 offen lds"
                    :: "s"(lds0), "v"(off[0]), "s"(rs) : "memory", "m0");
   };
-  // half tile t of the pass: list entry t/2, rows [32 (t&1), +32) of its block
-  auto half = [&](int t) {
-    const int2 e = ent[t >> 1];
+  // half tile t of the pass: list entry t/2 (given as read from `ent`), rows [32 (t&1), +32) of its block
+  auto half = [&](int2 e, int t) {
     const int2 u = make_int2(__builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y));
     return (t & 1) ? make_int2(u.x + 32, max(u.y - 32, 0)) : make_int2(u.x, min(u.y, 32));
   };
-  // half tile t -> stage t mod 3: the Q and dO rows and the row statistic of this wavefront's role
-  auto request = [&](int t, int stage) __attribute__((always_inline)) {
-    const int2 e = half(t);
+  // half tile e -> its stage: the Q and dO rows and the row statistic of this wavefront's role
+  auto request = [&](int2 e, int stage) __attribute__((always_inline)) {
     fetch(rsrc(A1h, a1_row_bytes, e.x, e.y), buf[stage], off1);
     fetch(rsrc(A2h, a2_row_bytes, e.x, e.y), buf[stage] + T32, off2);
     const int32x4 rs = rsrc(STh, 4u, e.x, e.y);
@@ -517,36 +515,34 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
 #pragma unroll
   for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
 
-  // the score-like product of this wavefront's role: `c` + rows of `tile` times the owner operand
-  auto product = [&](const uint4* tile, f32x16 c) __attribute__((always_inline)) {
-    constexpr int HB = KS / 2;
-    Frag f[HB];
+  // The parts of a step.  All LDS reads of a part are requested before the first matrix instruction that
+  // needs one of them (the scheduling barriers pin that order; left alone the compiler keeps two to
+  // four in flight and every matrix instruction waits for its operand).
+  // Fragments of a tile's rows, and the score-like product: `c` + rows of the tile times the owner operand.
+  auto rows_of = [&](const uint4* tile, Frag (&f)[KS]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < HB; ++s) f[s].u = tile[raddr[s]];
-    __builtin_amdgcn_sched_barrier(0);
+    for (int s = 0; s < KS; ++s) f[s].u = tile[raddr[s]];
+  };
+  auto product = [&](const Frag (&f)[KS], f32x16 c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < HB; ++s) {
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s].v, of[s].v, c, 0, 0, 0);
-      f[s].u = tile[raddr[HB + s]];
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int s = 0; s < HB; ++s) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s].v, of[HB + s].v, c, 0, 0, 0);
+    for (int s = 0; s < KS; ++s) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s].v, of[s].v, c, 0, 0, 0);
     return c;
   };
-  // acc += tile^T (transposing reads) times b[0], b[1]
-  auto accumulate = [&](const uint4* tile, const bf16x8 (&b)[2]) __attribute__((always_inline)) {
-    bf16x8 tf[MB];
+  // acc += tile^T (transposing reads) times b[0], b[1]; tf holds the fragments of the first 16 rows
+  auto first_half = [&](const uint4* tile, bf16x8 (&tf)[MB]) __attribute__((always_inline)) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) tf[mb] = tfrag(tile, 0, mb);
+  };
+  auto accumulate = [&](const uint4* tile, bf16x8 (&tf)[MB], const bf16x8 (&b)[2]) __attribute__((always_inline)) {
+    bf16x8 t2[MB];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[mb], b[0], acc[mb], 0, 0, 0);
-      tf[mb] = tfrag(tile, 1, mb);
-    }
+    for (int mb = 0; mb < MB; ++mb) t2[mb] = tfrag(tile, 1, mb);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
-      acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[mb], b[1], acc[mb], 0, 0, 0);
+      acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf[mb], b[0], acc[mb], 0, 0, 0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+      acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t2[mb], b[1], acc[mb], 0, 0, 0);
   };
   // accumulator i of a score tile is streamed row 8 (i/4) + 4 kg + i%4: the row statistics in
   // that order are four 16-byte reads.  Role 1 starts its product from them (dP' - delta needs no
@@ -581,10 +577,16 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     f32x16 dp_prev = zero16;
     int cur = 0, nxt = 1, prv = 2;
     auto rotate = [&]() { const int was = prv; prv = cur; cur = nxt; nxt = was; };
-    // role 0 on half tile t (stage cur): S', P' (handed over), dV^T += dO^T P'
-    auto p_step = [&](int t) __attribute__((always_inline)) {
-      const int cnt = half(t).y;
-      f32x16 sacc = product(buf[cur], zero16);
+    // role 0 on half tile t (stage cur, cnt rows): S', P' (handed over), dV^T += dO^T P'
+    auto p_step = [&](int t, int cnt) __attribute__((always_inline)) {
+      Frag f[KS];
+      rows_of(buf[cur], f);
+      const f32x16 lse = stats16(cur);
+      __builtin_amdgcn_sched_barrier(0);
+      f32x16 sacc = product(f, zero16);
+      bf16x8 tf[MB];
+      first_half(buf[cur] + T32, tf);
+      __builtin_amdgcn_sched_barrier(0);
       // stream rows past a short half tile's count were loaded as zeros (scores and statistics
       // alike): their scores become -inf (P' = 0); a full half tile, the common case, skips this
       if (cnt < 32) {
@@ -592,46 +594,78 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
         for (int i = 0; i < 16; ++i)
           if (8 * (i >> 2) + 4 * kg + (i & 3) >= cnt) sacc[i] = -INFINITY;
       }
-      const f32x16 lse = stats16(cur);
       bf16x8 pf[2];
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         pf[i >> 3][i & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[i], a.c, -lse[i]));
       ph[t & 1][pair][0][lane] = __builtin_bit_cast(uint4, pf[0]);
       ph[t & 1][pair][1][lane] = __builtin_bit_cast(uint4, pf[1]);
-      accumulate(buf[cur] + T32, pf);
+      accumulate(buf[cur] + T32, tf, pf);
     };
-    // role 1 finishing half tile t (stage prv): dS' = P' (dP' - delta), dK^T += Q^T dS'; dp_prev holds dP' - delta
-    auto ds_finish = [&](int t) __attribute__((always_inline)) {
-      bf16x8 pf[2], dsf[2];
-      pf[0] = __builtin_bit_cast(bf16x8, ph[t & 1][pair][0][lane]);
-      pf[1] = __builtin_bit_cast(bf16x8, ph[t & 1][pair][1][lane]);
+    // role 1 finishing half tile t (stage prv): dS' = P' (dP' - delta), dK^T += Q^T dS'; dp_prev holds
+    // dP' - delta, pu the P' its partner left, tf the first transposed fragments of Q
+    auto ds_finish = [&](const uint4 (&pu)[2], bf16x8 (&tf)[MB]) __attribute__((always_inline)) {
+      bf16x8 dsf[2];
+      const bf16x8 pf[2] = {__builtin_bit_cast(bf16x8, pu[0]), __builtin_bit_cast(bf16x8, pu[1])};
 #pragma unroll
       for (int i = 0; i < 16; ++i) dsf[i >> 3][i & 7] = (__bf16)((float)pf[i >> 3][i & 7] * dp_prev[i]);
-      accumulate(buf[prv], dsf);
+      accumulate(buf[prv], tf, dsf);
     };
-    request(0, 0);
+    auto take_p = [&](int t, uint4 (&pu)[2]) __attribute__((always_inline)) {
+      pu[0] = ph[t & 1][pair][0][lane];
+      pu[1] = ph[t & 1][pair][1][lane];
+    };
+    // e_cur, e_nxt: half tiles t and t + 1; that of t + 2 is looked up a step ahead
+    int2 e_cur = half(ent[0], 0), e_nxt = half(ent[0], 1);
+    request(e_cur, cur);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     lds_barrier();
-    request(1, nxt);                       // steps >= 2: a list entry is two half tiles
-    if (!is_ds) p_step(0); else dp_prev = product(buf[cur] + T32, stats16(cur));
+    request(e_nxt, nxt);                   // steps >= 2: a list entry is two half tiles
+    if (!is_ds) {
+      p_step(0, e_cur.y);
+    } else {
+      Frag f[KS];
+      dp_prev = stats16(cur);
+      rows_of(buf[cur] + T32, f);
+      dp_prev = product(f, dp_prev);
+    }
     rotate();
     for (int t = 1; t < steps; ++t) {
+      e_cur = e_nxt;
+      const int2 e_raw = ent[min(t + 1, steps - 1) >> 1];
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-      lds_barrier();
-      if (t + 1 < steps) request(t + 1, nxt);
+      lds_barrier();                       // (waits for e_raw too)
+      if (t + 1 < steps) {
+        e_nxt = half(e_raw, t + 1);
+        request(e_nxt, nxt);
+      }
       if (!is_ds) {
-        p_step(t);
+        p_step(t, e_cur.y);
       } else {
-        const f32x16 dp_cur = product(buf[cur] + T32, stats16(cur));   // dP' - delta of half tile t
-        ds_finish(t - 1);
+        Frag f[KS];
+        uint4 pu[2];
+        f32x16 dp_cur = stats16(cur);
+        rows_of(buf[cur] + T32, f);
+        take_p(t - 1, pu);
+        __builtin_amdgcn_sched_barrier(0);
+        dp_cur = product(f, dp_cur);       // dP' - delta of half tile t
+        bf16x8 tf[MB];
+        first_half(buf[prv], tf);
+        __builtin_amdgcn_sched_barrier(0);
+        ds_finish(pu, tf);
         dp_prev = dp_cur;
       }
       rotate();
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     lds_barrier();
-    if (is_ds) ds_finish(steps - 1);
+    if (is_ds) {
+      uint4 pu[2];
+      bf16x8 tf[MB];
+      take_p(steps - 1, pu);
+      first_half(buf[prv], tf);
+      ds_finish(pu, tf);
+    }
   }
 
   // accumulator i of acc[mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of the owner row
