@@ -49,7 +49,10 @@ struct BwdArgs {
   const float* ndelta;   // -delta per query row, [H][q_len]
   const int32_t* idx;    // lists: [H][owners][list_stride]
   const int32_t* cnt;    // key-major: entries per transposed list
-  const int32_t* order;  // key-major: owner handled by workgroup slot w
+  int32_t* order;        // owner handled by workgroup slot w of the key-major launch (made beside the dQ launch)
+  const int32_t* order_cnt;                      // dQ launch: entries per transposed list, for the order
+  int order_total, order_per_xcd, order_n_k;
+  uint32_t order_step;
   int64_t x_tok, x_head, y_tok, y_head, a1_tok, a1_head, a2_tok, a2_head;
   int64_t o1_tok, o1_head, o2_tok, o2_head;
   int n, nb, owners, streams, list_len, list_stride, q_len;
@@ -87,6 +90,64 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// Launch order of the key-major pass: its workgroups differ in work by the length of their
+// transposed list (a sink or current-chunk block is kept by every query block, a block of the
+// middle history by few).  Workgroup indices go round-robin to the eight XCDs, so every XCD works
+// through a fixed set of blocks: `per_xcd` places of the sequence "head after head, and inside a
+// head the KV blocks in steps of `step` blocks".  All heads carry the same number of tiles; where
+// an XCD's share ends inside a head, the step (about 0.618 n_k, prime to n_k) spreads the share
+// evenly over the head's blocks, heavy and light.  With the blocks in plain order the XCD that
+// got the head's second half, current chunk included, had 27 % more tiles than the one with the
+// first half, and a quarter of the launch's time was spent waiting for it (12 heads, 525 KV
+// blocks: the forward and backward calls together 1780 us, now 1672 us).
+// Inside an XCD workgroups are started in index order, so the long ones go first: one workgroup per
+// XCD sorts its share by descending count with a counting sort.  These eight ride at the front of
+// the dQ launch, which does not need the order (a launch of their own took 5 us).  The place of equal counts
+// among each other is left to the order the atomics happen to take: any permutation is valid,
+// and the gradients do not depend on which workgroup computes a block.
+constexpr int kOrderBins = 1024;
+__device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins /* [kOrderBins] in LDS */) {
+  const int threads = blockDim.x, tid = threadIdx.x;
+  const int w0 = xcd * a.order_per_xcd, w1 = min(a.order_total, w0 + a.order_per_xcd);
+  // block at place i of the sequence
+  auto at = [&](int i) -> int {
+    const int h = i / a.order_n_k;
+    return h * a.order_n_k + (int)((uint64_t)(uint32_t)(i - h * a.order_n_k) * a.order_step % (uint32_t)a.order_n_k);
+  };
+  for (int i = tid; i < kOrderBins; i += threads) bins[i] = 0;
+  __syncthreads();
+  for (int i = w0 + tid; i < w1; i += threads) atomicAdd(&bins[min(a.order_cnt[at(i)], kOrderBins - 1)], 1);
+  __syncthreads();
+  // bins[b] <- number of places in bins above b (where bin b starts in the descending order); lane l
+  // of the first wavefront takes the l-th sixteen bins from the top
+  if (tid < 64) {
+    constexpr int PER = kOrderBins / 64;
+    int cnt[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      cnt[j] = bins[kOrderBins - 1 - (PER * tid + j)];
+      sum += cnt[j];
+    }
+    int run = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(run, d);
+      if (tid >= d) run += up;
+    }
+    run -= sum;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      bins[kOrderBins - 1 - (PER * tid + j)] = run;
+      run += cnt[j];
+    }
+  }
+  __syncthreads();
+  for (int i = w0 + tid; i < w1; i += threads) {
+    const int w = at(i);
+    a.order[w0 + atomicAdd(&bins[min(a.order_cnt[w], kOrderBins - 1)], 1)] = w;
+  }
+}
+
 // dQ: a workgroup of two wavefronts owns a query block (wavefront rh its rows [32 rh, +32)) and
 // walks the block's list of KV blocks in half tiles of 32 KV rows.  SPLIT > 1: the workgroup has
 // SPLIT such pairs with a tile stage each, every pair walks a SPLIT-th of the list (the barriers are
@@ -105,7 +166,12 @@ __global__ __launch_bounds__(kThreads * SPLIT, 2) void lf_attn_bwd_q_kernel(BwdA
   __shared__ uint4 buf_all[SPLIT][NBUF][2 * TILE];     // [slice][step mod NBUF][A1 tile | A2 tile]
   __shared__ int2 ent_all[SPLIT][kPass];               // (first token, token count) per list entry of a pass
 
-  const int w = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
+  if (blockIdx.x < 8) {
+    static_assert(sizeof(buf_all) >= kOrderBins * sizeof(int), "the order's bins use the tile stage");
+    order_share(a, blockIdx.x, reinterpret_cast<int*>(buf_all));
+    return;
+  }
+  const int w = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3) - 1;
   if (w >= a.total_wg) return;
   const int h = w / a.owners, r = w % a.owners;
   const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
@@ -686,20 +752,64 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
   }
 }
 
-// -delta_x, delta_x = dO_x . O_x (float32), one group of d/8 lanes per row.
+// What the two gradient launches need beforehand, in one launch: the first workgroups make the transposed
+// lists, the others delta.  The former wait for dependent loads, the latter stream O and dO, so they
+// fit beside each other (apart: 10 and 7 us on the last-chunk call).  With the launch order beside the dQ launch a backward call
+// is three launches instead of five: small ragged training step 79.7 -> 74.0 us.
+struct PrepArgs {
+  const int32_t* idx;
+  int32_t* tlist;
+  int32_t* tcnt;
+  const uint16_t* O;
+  const uint16_t* dO;
+  float* ndelta;
+  int64_t o_tok, o_head;
+  int heads, n_q, n_k, list_len, q_len, rows, tr_blocks;
+};
+
+// Transposed lists: for every (head, KV block c) the query blocks whose list holds c, ascending.
+// One wavefront per (head, c): lane i looks c up in the list of query block r0 + i by bisection
+// (lists are ascending), and the hits of the 64 lanes are compacted in order through a ballot.
+__device__ __forceinline__ void transpose_lists(const PrepArgs& a, int gid) {
+  if (gid >= a.heads * a.n_k) return;
+  const int lane = threadIdx.x & 63;
+  const int h = gid / a.n_k, c = gid % a.n_k;
+  int32_t* out = a.tlist + (int64_t)gid * a.n_q;
+  int cnt = 0;
+  for (int r0 = 0; r0 < a.n_q; r0 += 64) {
+    const int r = r0 + lane;
+    bool hit = false;
+    if (r < a.n_q) {
+      const int32_t* l = a.idx + ((int64_t)h * a.n_q + r) * a.list_len;
+      int lo = 0, hi = a.list_len;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (l[mid] < c) lo = mid + 1; else hi = mid;
+      }
+      hit = lo < a.list_len && l[lo] == c;
+    }
+    const uint64_t m = __ballot(hit);
+    if (hit) out[cnt + __popcll(m & ((1ull << lane) - 1))] = r;
+    cnt += __popcll(m);
+  }
+  if (lane == 0) a.tcnt[gid] = cnt;
+}
+
 template <int D>
-__global__ __launch_bounds__(256) void lf_attn_delta_kernel(const uint16_t* __restrict__ O,
-                                                            const uint16_t* __restrict__ dO,
-                                                            float* __restrict__ ndelta, int64_t o_tok,
-                                                            int64_t o_head, int q_len, int rows) {
+__global__ __launch_bounds__(256) void lf_attn_bwd_prep_kernel(PrepArgs a) {
+  if ((int)blockIdx.x < a.tr_blocks) {
+    transpose_lists(a, blockIdx.x * 4 + (threadIdx.x >> 6));
+    return;
+  }
+  // -delta_x, delta_x = dO_x . O_x (float32), one group of d/8 lanes per row
   constexpr int LPR = D / 8;                  // lanes per row
-  const int gid = blockIdx.x * 256 + threadIdx.x;
+  const int gid = (blockIdx.x - a.tr_blocks) * 256 + threadIdx.x;
   const int row = gid / LPR, ch = gid % LPR;
   float s = 0.0f;
-  if (row < rows) {
-    const int h = row / q_len, x = row % q_len;
-    const int64_t off = (int64_t)h * o_head + (int64_t)x * o_tok + ch * 8;
-    const uint4 u = *reinterpret_cast<const uint4*>(O + off), v = *reinterpret_cast<const uint4*>(dO + off);
+  if (row < a.rows) {
+    const int h = row / a.q_len, x = row % a.q_len;
+    const int64_t off = (int64_t)h * a.o_head + (int64_t)x * a.o_tok + ch * 8;
+    const uint4 u = *reinterpret_cast<const uint4*>(a.O + off), v = *reinterpret_cast<const uint4*>(a.dO + off);
     const uint32_t uu[4] = {u.x, u.y, u.z, u.w}, vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -709,90 +819,7 @@ __global__ __launch_bounds__(256) void lf_attn_delta_kernel(const uint16_t* __re
   }
 #pragma unroll
   for (int o = 1; o < LPR; o <<= 1) s += __shfl_xor(s, o);
-  if (row < rows && ch == 0) ndelta[row] = -s;
-}
-
-// Transposed lists: for every (head, KV block c) the query blocks whose list holds c, ascending.
-// One wavefront per (head, c): lane i looks c up in the list of query block r0 + i by bisection
-// (lists are ascending), and the hits of the 64 lanes are compacted in order through a ballot.
-__global__ __launch_bounds__(256) void lf_transpose_lists_kernel(const int32_t* __restrict__ idx,
-                                                                 int32_t* __restrict__ tlist,
-                                                                 int32_t* __restrict__ tcnt, int heads,
-                                                                 int n_q, int n_k, int list_len) {
-  const int gid = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (gid >= heads * n_k) return;
-  const int lane = threadIdx.x & 63;
-  const int h = gid / n_k, c = gid % n_k;
-  int32_t* out = tlist + (int64_t)gid * n_q;
-  int cnt = 0;
-  for (int r0 = 0; r0 < n_q; r0 += 64) {
-    const int r = r0 + lane;
-    bool hit = false;
-    if (r < n_q) {
-      const int32_t* l = idx + ((int64_t)h * n_q + r) * list_len;
-      int lo = 0, hi = list_len;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (l[mid] < c) lo = mid + 1; else hi = mid;
-      }
-      hit = lo < list_len && l[lo] == c;
-    }
-    const uint64_t m = __ballot(hit);
-    if (hit) out[cnt + __popcll(m & ((1ull << lane) - 1))] = r;
-    cnt += __popcll(m);
-  }
-  if (lane == 0) tcnt[gid] = cnt;
-}
-
-// Launch order of the key-major pass: its workgroups differ in work by the length of their
-// transposed list (a sink or current-chunk block is kept by every query block, a block of the
-// middle history by few).  Workgroup indices go round-robin to the eight XCDs, so every XCD works
-// through a fixed set of blocks: `per_xcd` places of the sequence "head after head, and inside a
-// head the KV blocks in steps of `step` blocks".  All heads carry the same number of tiles; where
-// an XCD's share ends inside a head, the step (about 0.618 n_k, prime to n_k) spreads the share
-// evenly over the head's blocks, heavy and light.  With the blocks in plain order the XCD that
-// got the head's second half, current chunk included, had 27 % more tiles than the one with the
-// first half, and a quarter of the launch's time was spent waiting for it (12 heads, 525 KV
-// blocks: the forward and backward calls together 1780 us, now 1672 us).
-// Inside an XCD workgroups are started in index order, so the long ones go first: one
-// block per XCD sorts its share by descending count with a counting sort.  The place of equal counts
-// among each other is left to the order the atomics happen to take: any permutation is valid,
-// and the gradients do not depend on which workgroup computes a block.
-constexpr int kOrderBins = 1024;
-__global__ __launch_bounds__(1024) void lf_order_kernel(const int32_t* __restrict__ tcnt,
-                                                        int32_t* __restrict__ order, int total,
-                                                        int per_xcd, int n_k, uint32_t step) {
-  __shared__ int bins[kOrderBins];
-  // block at place i of the sequence
-  auto at = [&](int i) -> int {
-    const int h = i / n_k;
-    return h * n_k + (int)((uint64_t)(uint32_t)(i - h * n_k) * step % (uint32_t)n_k);
-  };
-  const int w0 = blockIdx.x * per_xcd, w1 = min(total, w0 + per_xcd);
-  for (int i = threadIdx.x; i < kOrderBins; i += 1024) bins[i] = 0;
-  __syncthreads();
-  for (int i = w0 + threadIdx.x; i < w1; i += 1024) atomicAdd(&bins[min(tcnt[at(i)], kOrderBins - 1)], 1);
-  __syncthreads();
-  // bins[b] <- number of workgroups in bins above b (where bin b starts in the descending order):
-  // an inclusive scan over the reversed bins by doubling, minus the bin's own count
-  {
-    const int b = kOrderBins - 1 - threadIdx.x;   // thread i scans position i of the reversed bins
-    const int own = bins[b];
-    int run = own;
-    for (int d = 1; d < kOrderBins; d <<= 1) {
-      const int other = (int)threadIdx.x >= d ? bins[b + d] : 0;
-      __syncthreads();
-      run += other;
-      bins[b] = run;
-      __syncthreads();
-    }
-    bins[b] = run - own;
-  }
-  __syncthreads();
-  for (int i = w0 + threadIdx.x; i < w1; i += 1024) {
-    const int w = at(i);
-    order[w0 + atomicAdd(&bins[min(tcnt[w], kOrderBins - 1)], 1)] = w;
-  }
+  if (row < a.rows && ch == 0) a.ndelta[row] = -s;
 }
 
 // The step of the launch order: the number nearest below 0.618 n that is prime to n (1 for n < 3).
@@ -814,22 +841,27 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
                        int32_t* tlist, int32_t* tcnt, int32_t* order, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int q_len = dm->f * dm->n;
-  const int rows = dm->H * q_len;
   {
-    const int lanes = rows * (dm->d / 8);
-    const unsigned grid = (unsigned)((lanes + 255) / 256);
-    const hipError_t rc = dm->d == 128
-        ? lf_launch(lf_attn_delta_kernel<128>, dim3(grid), dim3(256), 0, st, (const uint16_t*)O,
-                    (const uint16_t*)dO, ndelta, (int64_t)s->o_stride_tok, (int64_t)s->o_stride_head, q_len, rows)
-        : lf_launch(lf_attn_delta_kernel<64>, dim3(grid), dim3(256), 0, st, (const uint16_t*)O,
-                    (const uint16_t*)dO, ndelta, (int64_t)s->o_stride_tok, (int64_t)s->o_stride_head, q_len, rows);
+    PrepArgs p;
+    p.idx = indices;
+    p.tlist = tlist;
+    p.tcnt = tcnt;
+    p.O = (const uint16_t*)O;
+    p.dO = (const uint16_t*)dO;
+    p.ndelta = ndelta;
+    p.o_tok = s->o_stride_tok;
+    p.o_head = s->o_stride_head;
+    p.heads = dm->H;
+    p.n_q = dm->n_q;
+    p.n_k = dm->n_k;
+    p.list_len = list_len;
+    p.q_len = q_len;
+    p.rows = dm->H * q_len;
+    p.tr_blocks = (dm->H * dm->n_k + 3) / 4;
+    const unsigned grid = (unsigned)(p.tr_blocks + (p.rows * (dm->d / 8) + 255) / 256);
+    const hipError_t rc = dm->d == 128 ? lf_launch(lf_attn_bwd_prep_kernel<128>, dim3(grid), dim3(256), 0, st, p)
+                                       : lf_launch(lf_attn_bwd_prep_kernel<64>, dim3(grid), dim3(256), 0, st, p);
     if (rc != hipSuccess) return LF_ERR_HIP;
-  }
-  {
-    const unsigned grid = (unsigned)((dm->H * dm->n_k + 3) / 4);
-    if (lf_launch(lf_transpose_lists_kernel, dim3(grid), dim3(256), 0, st, indices, tlist, tcnt, dm->H,
-                  dm->n_q, dm->n_k, (int)list_len) != hipSuccess)
-      return LF_ERR_HIP;
   }
   BwdArgs a = {};
   a.lse2 = lse2;
@@ -851,7 +883,14 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.total_wg = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
   const bool split = lf_split_lists(a.total_wg, list_len);
-  const dim3 grid1((unsigned)(a.wg_per_xcd * 8)), block1((unsigned)(split ? 4 * kThreads : kThreads));
+  a.order = order;
+  a.order_cnt = tcnt;
+  a.order_n_k = dm->n_k;
+  a.order_total = dm->H * dm->n_k;
+  a.order_per_xcd = (a.order_total + 7) / 8;
+  a.order_step = spread_step((uint32_t)dm->n_k);
+  // eight workgroups in front for the order of the next launch
+  const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(split ? 4 * kThreads : kThreads));
   hipError_t rc = dm->d == 128
       ? lf_launch(split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>, grid1, block1, 0, st, a)
       : lf_launch(split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>, grid1, block1, 0, st, a);
@@ -867,10 +906,6 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_k; a.streams = dm->n_q;
   a.total_wg = dm->H * dm->n_k;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
-  if (lf_launch(lf_order_kernel, dim3(8), dim3(1024), 0, st, (const int32_t*)tcnt, order, a.total_wg,
-                a.wg_per_xcd, dm->n_k, spread_step((uint32_t)dm->n_k)) != hipSuccess)
-    return LF_ERR_HIP;
-  a.order = order;
   const dim3 grid2((unsigned)(a.wg_per_xcd * 8));
   rc = dm->d == 128 ? lf_launch(lf_attn_bwd_kv_kernel<128>, grid2, dim3(kKvThreads), 0, st, a)
                     : lf_launch(lf_attn_bwd_kv_kernel<64>, grid2, dim3(kKvThreads), 0, st, a);
