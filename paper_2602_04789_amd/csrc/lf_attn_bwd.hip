@@ -641,10 +641,8 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     // so they are peeled off and the loop body has no condition but the role.
     const int steps = 2 * n_local;
     f32x16 dp_prev = zero16;
-    int cur = 0, nxt = 1, prv = 2;
-    auto rotate = [&]() { const int was = prv; prv = cur; cur = nxt; nxt = was; };
     // role 0 on half tile t (stage cur, cnt rows): S', P' (handed over), dV^T += dO^T P'
-    auto p_step = [&](int t, int cnt) __attribute__((always_inline)) {
+    auto p_step = [&](int t, int cur, int cnt) __attribute__((always_inline)) {
       Frag f[KS];
       rows_of(buf[cur], f);
       const f32x16 lse = stats16(cur);
@@ -670,7 +668,7 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     };
     // role 1 finishing half tile t (stage prv): dS' = P' (dP' - delta), dK^T += Q^T dS'; dp_prev holds
     // dP' - delta, pu the P' its partner left, tf the first transposed fragments of Q
-    auto ds_finish = [&](const uint4 (&pu)[2], bf16x8 (&tf)[MB]) __attribute__((always_inline)) {
+    auto ds_finish = [&](int prv, const uint4 (&pu)[2], bf16x8 (&tf)[MB]) __attribute__((always_inline)) {
       bf16x8 dsf[2];
       const bf16x8 pf[2] = {__builtin_bit_cast(bf16x8, pu[0]), __builtin_bit_cast(bf16x8, pu[1])};
 #pragma unroll
@@ -683,20 +681,20 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
     };
     // e_cur, e_nxt: half tiles t and t + 1; that of t + 2 is looked up a step ahead
     int2 e_cur = half(ent[0], 0), e_nxt = half(ent[0], 1);
-    request(e_cur, cur);
+    request(e_cur, 0);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     lds_barrier();
-    request(e_nxt, nxt);                   // steps >= 2: a list entry is two half tiles
+    request(e_nxt, 1);                     // steps >= 2: a list entry is two half tiles
     if (!is_ds) {
-      p_step(0, e_cur.y);
+      p_step(0, 0, e_cur.y);
     } else {
       Frag f[KS];
-      dp_prev = stats16(cur);
-      rows_of(buf[cur] + T32, f);
+      dp_prev = stats16(0);
+      rows_of(buf[0] + T32, f);
       dp_prev = product(f, dp_prev);
     }
-    rotate();
-    for (int t = 1; t < steps; ++t) {
+    // stages of step t: cur = t mod 3, nxt = t + 1 mod 3, prv = t + 2 mod 3, constants in a loop of three steps
+    auto step = [&](int t, int cur, int nxt, int prv) __attribute__((always_inline)) {
       e_cur = e_nxt;
       const int2 e_raw = ent[min(t + 1, steps - 1) >> 1];
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -706,7 +704,7 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
         request(e_nxt, nxt);
       }
       if (!is_ds) {
-        p_step(t, e_cur.y);
+        p_step(t, cur, e_cur.y);
       } else {
         Frag f[KS];
         uint4 pu[2];
@@ -718,19 +716,27 @@ __global__ __launch_bounds__(kKvThreads, 2) void lf_attn_bwd_kv_kernel(BwdArgs a
         bf16x8 tf[MB];
         first_half(buf[prv], tf);
         __builtin_amdgcn_sched_barrier(0);
-        ds_finish(pu, tf);
+        ds_finish(prv, pu, tf);
         dp_prev = dp_cur;
       }
-      rotate();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int t = 1; t < steps; t += 3) {
+      step(t, 1, 2, 0);
+      if (t + 1 >= steps) break;
+      step(t + 1, 2, 0, 1);
+      if (t + 2 >= steps) break;
+      step(t + 2, 0, 1, 2);
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     lds_barrier();
     if (is_ds) {
       uint4 pu[2];
       bf16x8 tf[MB];
+      const int prv = (steps - 1) % 3;
       take_p(steps - 1, pu);
       first_half(buf[prv], tf);
-      ds_finish(pu, tf);
+      ds_finish(prv, pu, tf);
     }
   }
 
