@@ -468,8 +468,15 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
 // keeps one owner operand and one accumulator set, which fits two wavefronts per SIMD (two
 // workgroups per CU, not in step with each other).
 constexpr int kKvThreads = 256;
-template <int D>
-__global__ __launch_bounds__(kKvThreads, D == 64 ? 3 : 2) void lf_attn_bwd_kv_kernel(BwdArgs a) {
+// Calls with at most kKvSplitBlocks (head, KV block) pairs give a block two groups of wavefronts: such a
+// workgroup has a compute unit (of 256) to itself at d = 128.  Backward call in us, d = 128, mean transposed list of
+// 12: 64 blocks 49.9 -> 47.8, 256 blocks 52.9 -> 50.4; of 24: 256 blocks 76.6 -> 70.0; two rounds, of 12:
+// 384 blocks 59.5 -> 66.8.  d = 64, of 12: 256 blocks 49.1 -> 46.9, 384 blocks 55.8 -> 58.8.
+constexpr int kKvSplitBlocks = 256;
+// SPLIT = 2: a workgroup holds two such groups of four wavefronts, each with a stage of its own and half of
+// the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.
+template <int D, int SPLIT>
+__global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) void lf_attn_bwd_kv_kernel(BwdArgs a) {
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;
   constexpr int MB = D / 32;
@@ -478,17 +485,22 @@ __global__ __launch_bounds__(kKvThreads, D == 64 ? 3 : 2) void lf_attn_bwd_kv_ke
   constexpr int T32 = 32 * CH;              // uint4 per half tile (32 rows)
   static_assert(LPW == 1 || LPW == 2, "a half tile splits over four wavefronts");
 
-  __shared__ uint4 buf[3][2 * T32];         // [half tile mod 3][Q | dO]
-  __shared__ float4 st[3][4][16];           // lse2 (role 0) or -delta (role 1) of the 32 streamed rows, one copy per
+  __shared__ uint4 buf_all[SPLIT][3][2 * T32];   // [half tile mod 3][Q | dO]
+  __shared__ float4 st_all[SPLIT][3][4][16];     // lse2 (role 0) or -delta (role 1) of the 32 streamed rows, one copy per
                                             // wavefront; its upper half takes the zeros of the lanes past the 32 rows
-  __shared__ uint4 ph[2][2][2][64];         // P' handoff: [step parity][rh][k-step][lane]
-  __shared__ int2 ent[kPass];
+  __shared__ uint4 ph_all[SPLIT][2][2][2][64];   // P' handoff: [step parity][rh][k-step][lane]
+  __shared__ int2 ent_all[SPLIT][kPass];
 
   const int slot = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
   if (slot >= a.total_wg) return;
   const int w = a.order[slot];
   const int h = w / a.owners, r = w % a.owners;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kKvThreads) : 0;
+  uint4 (*const buf)[2 * T32] = buf_all[slice];
+  float4 (*const st)[4][16] = st_all[slice];
+  uint4 (*const ph)[2][2][64] = ph_all[slice];
+  int2* const ent = ent_all[slice];
+  const int tid = threadIdx.x % kKvThreads, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rh = wave & 1, pair = rh;
   const bool is_ds = wave >= 2;             // role 1: dP', dS', dK
@@ -498,8 +510,11 @@ __global__ __launch_bounds__(kKvThreads, D == 64 ? 3 : 2) void lf_attn_bwd_kv_ke
   const int o_cnt = min(64, a.n - (r % a.nb) * 64);
   const int orow = 32 * rh + ln;
   const bool o_ok = orow < o_cnt;
-  const int32_t* list = a.idx + ((int64_t)h * a.owners + r) * a.list_stride;
-  const int n_ent = a.cnt[(int64_t)h * a.owners + r];
+  // this group's slice of the list: entries [slice n_ent, +n_ent), of which my_ent exist
+  const int n_all = a.cnt[(int64_t)h * a.owners + r];
+  const int n_ent = (n_all + SPLIT - 1) / SPLIT;
+  const int my_ent = SPLIT > 1 ? min(n_all - slice * n_ent, n_ent) : n_ent;
+  const int32_t* list = a.idx + ((int64_t)h * a.owners + r) * a.list_stride + (SPLIT > 1 ? slice * n_ent : 0);
 
   // owner operand: K rows for role 0 (scores), V rows for role 1 (dP')
   Frag of[KS];
@@ -642,7 +657,7 @@ __global__ __launch_bounds__(kKvThreads, D == 64 ? 3 : 2) void lf_attn_bwd_kv_ke
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
     for (int i = tid; i < n_local; i += kKvThreads) {
-      const int cidx = list[l0 + i];
+      const int cidx = l0 + i < my_ent ? list[l0 + i] : -1;
       const bool ok = (unsigned)cidx < (unsigned)a.streams;
       const int tau = ok ? cidx / a.nb : 0, j = ok ? cidx % a.nb : 0;
       ent[i] = make_int2(tau * a.n + j * 64, ok ? min(64, a.n - j * 64) : 0);
@@ -756,6 +771,31 @@ __global__ __launch_bounds__(kKvThreads, D == 64 ? 3 : 2) void lf_attn_bwd_kv_ke
 
   // accumulator i of acc[mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of the owner row
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  if constexpr (SPLIT > 1) {
+    // the second group leaves its sums where both groups' tiles were, the first adds them to its own
+    constexpr int NGRP = MB * 4;
+    static_assert(SPLIT == 2 && 4 * NGRP * 64 <= 2 * 3 * 2 * T32, "the sums of four wavefronts fit the stages");
+    float4* const sums = reinterpret_cast<float4*>(buf_all) + wave * NGRP * 64;
+    __syncthreads();
+    if (slice == 1) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          sums[(mb * 4 + g) * 64 + lane] =
+              make_float4(acc[mb][4 * g + 0], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]);
+    }
+    __syncthreads();
+    if (slice == 1) return;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = sums[(mb * 4 + g) * 64 + lane];
+        acc[mb][4 * g + 0] += v.x; acc[mb][4 * g + 1] += v.y;
+        acc[mb][4 * g + 2] += v.z; acc[mb][4 * g + 3] += v.w;
+      }
+  }
   if (o_ok) {
     uint16_t* op = is_ds ? a.out1 + (int64_t)h * a.o1_head + (int64_t)(otok0 + orow) * a.o1_tok
                          : a.out2 + (int64_t)h * a.o2_head + (int64_t)(otok0 + orow) * a.o2_tok;
@@ -927,7 +967,10 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.total_wg = dm->H * dm->n_k;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
   const dim3 grid2((unsigned)(a.wg_per_xcd * 8));
-  rc = dm->d == 128 ? lf_launch(lf_attn_bwd_kv_kernel<128>, grid2, dim3(kKvThreads), 0, st, a)
-                    : lf_launch(lf_attn_bwd_kv_kernel<64>, grid2, dim3(kKvThreads), 0, st, a);
+  const bool halves = a.total_wg <= kKvSplitBlocks;
+  const dim3 block2((unsigned)(halves ? 2 * kKvThreads : kKvThreads));
+  rc = dm->d == 128
+      ? lf_launch(halves ? lf_attn_bwd_kv_kernel<128, 2> : lf_attn_bwd_kv_kernel<128, 1>, grid2, block2, 0, st, a)
+      : lf_launch(halves ? lf_attn_bwd_kv_kernel<64, 2> : lf_attn_bwd_kv_kernel<64, 1>, grid2, block2, 0, st, a);
   return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
 }

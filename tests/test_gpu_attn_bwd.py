@@ -342,3 +342,25 @@ def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len,
     ref = O.sparse_attention_backward(Qf, Kf, Vf, dOf, lists[h:h + 1], w.frame_len, w.block)
     for name, got, want in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
         _close(name, got[h:h + 1], want)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,list_len", [(4, 9), (4, 1), (5, 9)])
+def test_few_kv_blocks_take_two_groups_of_wavefronts(gpu, heads, list_len, head_dim):
+    """dK and dV with each KV block's query blocks divided between two groups of wavefronts (256 KV
+    blocks, transposed lists of 0, odd and even lengths) and, at 320 KV blocks, not."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=1000, chunk_idx=2, heads=heads, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    x["dO"] = synth.make_upstream_grad(w)
+    n_q, n_k = w.frames_per_chunk * w.blocks_per_frame, w.frames * w.blocks_per_frame
+    rng = np.random.default_rng(heads + list_len)
+    lists = np.stack([np.stack([np.sort(rng.choice(n_k, list_len, replace=False)) for _ in range(n_q)])
+                      for _ in range(heads)]).astype(np.int32)
+    print(f"two groups: heads={heads} d={head_dim} list length {list_len}", flush=True)
+    got, _ = _run(torch, lf, w, x, lists)
+    for h in (0, heads - 1):
+        Qf, Kf, Vf, dOf = (_f32(x[k])[h:h + 1] for k in ("Q", "K", "V", "dO"))
+        ref = O.sparse_attention_backward(Qf, Kf, Vf, dOf, lists[h:h + 1], w.frame_len, w.block)
+        for name, g, want in zip(("dQ", "dK", "dV"), got, ref):
+            _close(name, g[h:h + 1], want)
