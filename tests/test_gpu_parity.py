@@ -577,3 +577,25 @@ def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len,
     torch.cuda.synchronize()
     diff = (one.float() - two.float()).abs()
     assert float(diff.max()) <= 2 * MAX_ABS and float(diff.mean()) <= 2 * MEAN_ABS
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,frame_len,chunk", [(2, 512, 4), (2, 513, 4), (1, 449, 5), (3, 257, 4), (2, 64, 6), (2, 1, 6),
+                                                   (16, 65, 16), (16, 65, 17)])
+def test_short_frames_pooled_in_one_launch(gpu, heads, frame_len, chunk, head_dim):
+    """Block and frame means of short frames come from one launch: frames of 1, 2, 5 and 8 blocks (one
+    and two rounds, the last ones short) and of 9, which take two launches; 512 and 544 frames in
+    all; the same through the pooled-key cache."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=chunk, heads=heads, head_dim=head_dim, n_win=1)
+    x = synth.make_inputs(w)
+    print(f"short frames: heads={heads} d={head_dim} n={frame_len} frames={w.frames}", flush=True)
+    dev, idx, lists = _run_select(torch, lf, w, x)[:3]
+    Q, K = dev[0], dev[1]
+    b = lf.lf_chunk_budget(w.chunk_idx, w.schedule)
+    sh = lf.make_shape(Q, K, frame_len=w.frame_len, block=w.block)
+    cache = torch.zeros(lf.lf_kcache_bytes(sh, w.frames), dtype=torch.uint8, device="cuda")
+    lf.lf_kcache_update(K, w.frame_len, w.block, 0, w.frames, w.frames, cache)
+    again = lf.lf_select_mask_cached(Q, cache, w.frames, w.kv_len, w.frame_len, w.block, b)
+    torch.cuda.synchronize()
+    assert np.array_equal(again.cpu().numpy(), idx.cpu().numpy())
