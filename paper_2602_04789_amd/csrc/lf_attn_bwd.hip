@@ -813,9 +813,9 @@ __global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) 
 }
 
 // What the two gradient launches need beforehand, in one launch: the first workgroups make the transposed
-// lists, the others delta.  The former wait for dependent loads, the latter stream O and dO, so they
-// fit beside each other (apart: 10 and 7 us on the last-chunk call).  With the launch order beside the dQ launch a backward call
-// is three launches instead of five: small ragged training step 79.7 -> 74.0 us.
+// lists, the others delta.  The former wait for dependent loads, the latter stream O and dO (on the
+// last-chunk call 10 and 7 us and a gap apart, 15 us together).  With the launch order beside the dQ
+// launch a backward call is three launches instead of five: small ragged training step 79.7 -> 74.0 us.
 struct PrepArgs {
   const int32_t* idx;
   int32_t* tlist;
