@@ -161,17 +161,16 @@ __global__ __launch_bounds__(kThreads) void lf_frame_mean_kernel(FrameMeanArgs f
 }
 
 // Short frames: block means and frame means in one launch.  A workgroup of four groups of 256 threads owns
-// a frame: every group pools every fourth block, the means also stay in LDS, and the frame's sum is
+// a frame: every group pools a block, the means also stay in LDS, and the frame's sum is
 // taken from there in the same ascending order.  Query blocks follow, four to a workgroup.  `pa` names
 // the KV blocks of frames [frame0, frame0 + n_frames); frame means are written for frames
-// [f.tau0, f.tau0 + f.count).  It replaces a launch of about 3 us that waits for the one before; with long
-// frames the serial rounds of a frame's blocks cost more than that (see pools_whole_frames).
-constexpr int kFrameGroups = 4, kFrameBlocks = 8;
+// [f.tau0, f.tau0 + f.count).  It replaces a launch of about 3 us that waits for the one before.
+constexpr int kFrameGroups = 4;
 template <int D>
 __global__ __launch_bounds__(kThreads * kFrameGroups) void lf_pool_frames_kernel(PoolArgs pa, FrameMeanArgs f,
                                                                                  int frame0, int n_frames) {
   __shared__ double red[kFrameGroups][pool_lds_doubles<D>()];
-  __shared__ float means[kFrameBlocks][D];
+  __shared__ float means[kFrameGroups][D];
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
   const int n_units = f.H * n_frames;
   if ((int)blockIdx.x >= n_units) {
@@ -181,14 +180,11 @@ __global__ __launch_bounds__(kThreads * kFrameGroups) void lf_pool_frames_kernel
     return;
   }
   const int h = blockIdx.x / n_frames, tau = frame0 + blockIdx.x % n_frames;
-  for (int j0 = 0; j0 < f.nb; j0 += kFrameGroups) {
-    const int j = j0 + grp;
-    const bool on = j < f.nb;
-    const int jj = on ? j : 0;
-    // unit n_q + i of `pa` is KV block k_block0 + i
-    pool_block<D>(pa, h, pa.n_q + tau * f.nb + jj - pa.k_block0, red[grp], tid, on, means[jj]);
-    __syncthreads();
-  }
+  const bool on = grp < f.nb;
+  const int j = on ? grp : 0;
+  // unit n_q + i of `pa` is KV block k_block0 + i
+  pool_block<D>(pa, h, pa.n_q + tau * f.nb + j - pa.k_block0, red[grp], tid, on, means[grp]);
+  __syncthreads();
   const int t = threadIdx.x;
   if (t < D && tau >= f.tau0 && tau < f.tau0 + f.count) {
     double sum = 0.0;
@@ -197,11 +193,13 @@ __global__ __launch_bounds__(kThreads * kFrameGroups) void lf_pool_frames_kernel
   }
 }
 
-// One launch for block and frame means: frames of at most eight blocks (two rounds of four), and no more
-// frames than the chip holds of these workgroups at once (two per compute unit).  Step of 2 heads x 64,
-// frames of 256: 21.3 -> 18.3 us; 3 heads x 128, frames of 200: 30.9 -> 29.4 us.
+// One launch for block and frame means: frames of at most four blocks, and no more frames than the chip
+// holds of these workgroups at once (two per compute unit; half of that for frames of one block, where three
+// groups idle).  The whole selection in us, two launches -> one: d 128, frames of 200 / 256, 24 .. 480
+// frames over all heads: 1.0 - 1.6 us less; frames of 400 / 512, a second round: 14.0 -> 14.7 (24 frames), 13.5 -> 14.1;
+// frames of 64: 192 frames 11.3 -> 9.8 (d 64), 480 frames 13.8 -> 14.2, 960 frames 13.7 -> 14.7.
 inline bool pools_whole_frames(const lf_dims* dm, int n_frames) {
-  return dm->nb <= kFrameBlocks && (int64_t)dm->H * n_frames <= 512;
+  return dm->nb <= kFrameGroups && (int64_t)dm->H * n_frames <= (dm->nb > 1 ? 512 : 256);
 }
 
 struct SelectArgs {

@@ -580,12 +580,12 @@ def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len,
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("heads,frame_len,chunk", [(2, 512, 4), (2, 513, 4), (1, 449, 5), (3, 257, 4), (2, 64, 6), (2, 1, 6),
-                                                   (16, 65, 16), (16, 65, 17)])
+@pytest.mark.parametrize("heads,frame_len,chunk", [(2, 256, 4), (2, 257, 4), (1, 512, 5), (3, 193, 4), (2, 64, 6), (2, 1, 6),
+                                                   (16, 65, 16), (16, 65, 17), (8, 64, 16), (8, 64, 17)])
 def test_short_frames_pooled_in_one_launch(gpu, heads, frame_len, chunk, head_dim):
-    """Block and frame means of short frames come from one launch: frames of 1, 2, 5 and 8 blocks (one
-    and two rounds, the last ones short) and of 9, which take two launches; 512 and 544 frames in
-    all; the same through the pooled-key cache."""
+    """Block and frame means of short frames come from one launch: frames of 1, 2 and 4 blocks (full
+    and short last ones) and of 5 and 8, which take two launches; 512 and 544 frames in all (of one
+    block: 256 and 272); the same through the pooled-key cache."""
     torch, lf = gpu
     w = synth.small_ragged(frame_len=frame_len, chunk_idx=chunk, heads=heads, head_dim=head_dim, n_win=1)
     x = synth.make_inputs(w)
