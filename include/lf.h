@@ -201,6 +201,11 @@ int lf_select_mask(const void* Q, const void* Kcache, const lf_shape* shape,
  *                      query block whose list holds no valid id are written as zeros.
  *   softmax_scale      0 selects 1/sqrt(d).
  *   O                  device, bfloat16 [H][q_len][d] with the o_ strides, written.
+ * Reproducibility: the same call gives the same bits.  Calls with few (head, query block) pairs
+ *   add up a list in several parts (likewise the transposed lists of lf_sparse_attn_bwd, by the
+ *   number of (head, KV block) pairs), so a head may differ between calls with few and with many heads by the
+ *   order of float32 sums: the probabilities are rounded to the same bfloat16 values, and O then
+ *   differs in about one element in ten thousand, by one bfloat16 step.
  * Errors: LF_ERR_NULL, LF_ERR_SHAPE, LF_ERR_DTYPE, LF_ERR_ALIGN, LF_ERR_BUDGET
  *   (list_len < 1), LF_ERR_HIP.
  */

@@ -111,7 +111,9 @@ __device__ __forceinline__ void lds_barrier() {
 // common.  SPLIT = 1: each pair has a query block of its own and walks its list (two query blocks per
 // workgroup measured 2 % faster than one; the lists are equally long).  SPLIT > 1 (= WAVES / 2): the
 // pairs share one query block, each walks a SPLIT-th of its list, and their online-softmax states
-// are merged through LDS at the end.  A call with few query blocks leaves compute units idle while
+// are merged through LDS at the end.  All pairs start from the reference that one pair walking the whole
+// list would take (the row maxima of the list's first half tile, or that of the state carried on), so that the probabilities are rounded to the same bfloat16 values in either form and only the
+// order of float32 sums differs.  A call with few query blocks leaves compute units idle while
 // every wavefront goes through its list step by step (one wavefront per SIMD: 0.55 - 0.8 us a step,
 // mostly latency); dividing the list shortens that chain.
 template <int D, int WAVES, bool DENSE, int SPLIT = 1>
@@ -313,23 +315,39 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   // Accumulator i of oacc[mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of query row qrow; the
   // stored state uses the same order within a row, so a lane moves float4s.
   float* state_row = nullptr;
-  if (a.state_o != nullptr && qrow < q_cnt && (SPLIT == 1 || qb == 0)) {   // one slice carries a state on
+  if (a.state_o != nullptr && qrow < q_cnt) {
     const int64_t row = (int64_t)h * a.q_len + qtok0 + qrow;
     state_row = a.state_o + row * D;
     if constexpr (!DENSE) {
       const float2 ml = a.state_ml[row];
       m_run = ml.x;
-      l_run = kg == 0 ? ml.y : 0.0f;   // the two lanes of a row each carry part of the sum
+      if (SPLIT == 1 || qb == 0) {         // one slice carries the state on, all start from its reference
+        l_run = kg == 0 ? ml.y : 0.0f;     // the two lanes of a row each carry part of the sum
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 v = *reinterpret_cast<const float4*>(state_row + 32 * mb + 8 * g + 4 * kg);
-          oacc[mb][4 * g + 0] = v.x; oacc[mb][4 * g + 1] = v.y;
-          oacc[mb][4 * g + 2] = v.z; oacc[mb][4 * g + 3] = v.w;
-        }
+          for (int g = 0; g < 4; ++g) {
+            const float4 v = *reinterpret_cast<const float4*>(state_row + 32 * mb + 8 * g + 4 * kg);
+            oacc[mb][4 * g + 0] = v.x; oacc[mb][4 * g + 1] = v.y;
+            oacc[mb][4 * g + 2] = v.z; oacc[mb][4 * g + 3] = v.w;
+          }
+      }
     }
   }
+  // Divided list: the reference is taken from the list's first half tile, by the wavefronts that would
+  // move theirs there if they walked it alone: those without a state, and those with rows past a short
+  // block's end (such a row has no state, and when one row moves all of the wavefront do).
+  bool need_ref = SPLIT > 1 && (a.state_o == nullptr || q_cnt % 32 != 0);
+
+  // Row maxima (both lanes of a row) of a half tile's scores.
+  auto row_max = [](const f32x16& sc) __attribute__((always_inline)) {
+    float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+#pragma unroll
+    for (int i = 4; i < 16; i += 2) mx = fmaxf(mx, fmaxf(sc[i], sc[i + 1]));
+    // lanes l and l+32 hold the same query column: exchange through the lane-swap unit
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  };
 
   // Lists are decoded kMaxEnt / 2 entries at a time into LDS: block id -> its half tiles of 32
   // KV rows (first token, count), one for a block of at most 32 tokens, two otherwise, none
@@ -348,6 +366,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   for (int l0 = 0; l0 < n_entries; l0 += pass_len) {
     const int l1 = min(n_entries, l0 + pass_len);
     int nsteps = 2 * (l1 - l0);   // half-tile steps of this pass
+    int ref_slice = 0;            // divided list: the first slice with a half tile in this pass
     if constexpr (!DENSE) {
       int htok[EPT], hcnt[EPT], halves = 0;
 #pragma unroll
@@ -382,11 +401,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       nh_q = __builtin_amdgcn_readfirstlane(nh_q);
       int longest = 0;
 #pragma unroll
-      for (int q2 = 0; q2 < QPW; ++q2) {
+      for (int q2 = QPW - 1; q2 >= 0; --q2) {
         int n = 0;
 #pragma unroll
         for (int w2 = 0; w2 < WPQ; ++w2) n += nh_all[q2][w2];
         longest = max(longest, n);
+        if (n > 0) ref_slice = q2;
       }
       nsteps = __builtin_amdgcn_readfirstlane((longest + 1) & ~1);
 #pragma unroll
@@ -410,6 +430,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     fetch_k(k_rsrc(e0), buf0);
     fetch_v(v_rsrc(e0), buf0);
     fetch_k(k_rsrc(e1), buf1);
+    int2 e_ref = make_int2(0, 0);
+    if constexpr (SPLIT > 1) {
+      if (need_ref) {                      // K of the list's first half tile, where V of half tile 1 comes later
+        e_ref = ent_all[__builtin_amdgcn_readfirstlane(ref_slice)][0];
+        fetch_k(k_rsrc(e_ref), buf1 + TILE);
+      }
+    }
 
     // S^T[kv, q] of this wavefront's 32 KV rows x 32 query rows, from the K tile in `kt`.
     auto s_half = [&](const uint4* kt, f32x16 acc, int s0) __attribute__((always_inline)) {
@@ -427,6 +454,32 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     f32x16 zero16;
 #pragma unroll
     for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
+    // accumulator i of a lane: KV row 8 (i/4) + 4 kg + i%4 of the half tile, query column ln
+    auto mask_past = [&](f32x16& sc, int cnt) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (8 * (i >> 2) + 4 * kg + (i & 3) >= cnt) sc[i] = -INFINITY;
+    };
+    if constexpr (SPLIT > 1) {
+      if (need_ref) {
+        const int cnt = __builtin_amdgcn_readfirstlane(e_ref.y);
+        f32x16 sref = s_half(buf1 + TILE, s_half(buf1 + TILE, zero16, 0), KS / 2);
+        if (cnt < 32) mask_past(sref, cnt);
+        if (a.state_o == nullptr || 32 * rh + 32 > q_cnt) {
+          const float m_new = fmaxf(m_run, row_max(sref) * a.c);
+          if (a.state_o != nullptr) {      // without one there is nothing to rescale yet
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
+          }
+          m_run = m_new;
+        }
+        need_ref = false;
+      }
+    }
     f32x16 sacc = s_half(buf0, s_half(buf0, zero16, 0), KS / 2);
 
     // Past the pass's last half tile the pipeline runs on empty ones: their loads touch no memory
@@ -439,14 +492,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       const int2 e_raw = DENSE ? make_int2(0, 0) : ent[(t + 3) & (kMaxEnt - 1)];
       const int32x4 krs = k_rsrc(e2), vrs = v_rsrc(e1);
       fetch_v(vrs, other);
-      // accumulator i of a lane: KV row 8 (i/4) + 4 kg + i%4 of the half tile, query column ln
-      if (cnt < 32) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int kv = 8 * (i >> 2) + 4 * kg + (i & 3);
-          if (kv >= cnt) sacc[i] = -INFINITY;
-        }
-      }
+      if (cnt < 32) mask_past(sacc, cnt);
       f32x16 snext = s_half(other, zero16, 0);
       fetch_k(krs, cur);
       // P^T = exp2(s c - m_run), packed to bfloat16 in the
@@ -493,13 +539,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       // Rare: the row sum says the reference is far too low (or was never set).  Then the
       // maxima are taken, the reference moves up to them and P^T is made again.
       if (__ballot(l_new > kSumMax) != 0ull) {
-        float mx = fmaxf(fmaxf(sacc[0], sacc[1]), fmaxf(sacc[2], sacc[3]));
-#pragma unroll
-        for (int i = 4; i < 16; i += 2) mx = fmaxf(mx, fmaxf(sacc[i], sacc[i + 1]));
-        // lanes l and l+32 hold the same query column: exchange through the lane-swap unit
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        const float m_new = fmaxf(m_run, mx * a.c);
+        const float m_new = fmaxf(m_run, row_max(sacc) * a.c);
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
         l_run *= alpha;

@@ -599,3 +599,53 @@ def test_short_frames_pooled_in_one_launch(gpu, heads, frame_len, chunk, head_di
     again = lf.lf_select_mask_cached(Q, cache, w.frames, w.kv_len, w.frame_len, w.block, b)
     torch.cuda.synchronize()
     assert np.array_equal(again.cpu().numpy(), idx.cpu().numpy())
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("frame_len,keep", [(200, 40), (129, 11)])
+def test_a_head_gives_the_same_whether_its_lists_are_divided_or_not(gpu, frame_len, keep, head_dim):
+    """The first heads of a call with many query blocks (undivided lists) against a call with these
+    heads alone (divided), forward in one and in two phases, and the training pair.  Both forms
+    round the probabilities against the same reference, so O differs only by the order of float32 sums:
+    at most S = 4 * keep products are added into an element, each sum off by at most 2^-24 of the largest
+    partial one, which the typical case passes by far less (sqrt(S) 2^-24 = 8e-7 of |O|).  Against the spacing of
+    bfloat16 values (2^-8 |O| or more) that moves fewer than one in a hundred elements, by one
+    spacing (2^-7 |O| at most).  With a reference per slice about one in three moves."""
+    torch, lf = gpu
+    heads, few = 600 // (2 * -(-frame_len // 64)) + 1, 3
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=6, heads=heads, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    x["dO"] = synth.make_upstream_grad(w)
+    Q, K, V, dO = (_dev(torch, x[k]) for k in ("Q", "K", "V", "dO"))
+    n_q, n_k, cur = (v * w.blocks_per_frame for v in (w.frames_per_chunk, w.frames, w.frames_per_chunk))
+    rng = np.random.default_rng(keep)
+    pick = min(keep, n_k - cur)
+    lists = np.stack([np.stack([np.concatenate([np.sort(rng.choice(n_k - cur, pick, replace=False)),
+                                                np.arange(n_k - cur, n_k)]) for _ in range(n_q)])
+                      for _ in range(heads)]).astype(np.int32)
+    lists[0, 0, :3] = [-3, -2, -1]               # the first valid id is not the first entry
+    print(f"divided or not: heads={heads} d={head_dim} n={frame_len} L={lists.shape[-1]}", flush=True)
+    idx = torch.from_numpy(lists).cuda()
+    b = lf.lf_chunk_budget(w.chunk_idx, w.schedule)
+    b.n_sink = b.n_win = 0
+    b.k_frames, b.k_blocks, b.list_len = w.hist_frames, pick, lists.shape[-1]
+
+    def calls(hs):
+        q, k, v, g, i = (t[:hs].contiguous() for t in (Q, K, V, dO, idx))
+        out, lse2 = lf.lf_sparse_attn_fwd(q, k, v, i, w.frame_len, w.block)
+        two = lf.lf_sparse_attn_split(q, k, v, i, w.frame_len, w.block, b)
+        grads = lf.lf_sparse_attn_bwd(q, k, v, out, g, lse2, i, w.frame_len, w.block)
+        torch.cuda.synchronize()
+        return (out, two) + grads, lse2
+    (many, lse_many), (alone, lse_alone) = calls(heads), calls(few)
+    for name, a, c in zip(("O", "O in two phases", "dQ", "dK", "dV"), many, alone):
+        a, c = a[:few].double(), c.double()
+        share = float((a != c).double().mean())
+        print(f"  {name}: {share:.2e} of the elements differ", flush=True)
+        if name.startswith("O"):
+            assert share <= 1e-2 and bool(((a - c).abs() <= 2.0 ** -7 * c.abs() + 1e-6).all()), (name, share)
+        else:
+            # O's rare steps reach the gradients through delta = dO . O: less than a spacing on average
+            assert float((a - c).norm() / c.norm()) <= 5e-4, name
+    # log2 of a float32 sum of keep * 64 probabilities, in another order
+    assert float((lse_many[:few] - lse_alone).abs().max()) <= 1.5 * keep * 64 * 2.0 ** -24 + 2.0 ** -20
