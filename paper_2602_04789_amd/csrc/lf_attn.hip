@@ -767,7 +767,7 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.state_ml = reinterpret_cast<float2*>(const_cast<float*>(state_ml));
   a.total_wg = dm->H * dm->n_q;
   hipStream_t st = (hipStream_t)stream;
-  if (lf_split_lists(a.total_wg, list_len)) {
+  if (lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k)) {
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
     const hipError_t rc = dm->d == 128

@@ -942,7 +942,7 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_q; a.streams = dm->n_k;
   a.total_wg = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
-  const bool split = lf_split_lists(a.total_wg, list_len);
+  const bool split = lf_split_lists_dq(dm->d, a.total_wg, list_len);
   a.order = order;
   a.order_cnt = tcnt;
   a.order_n_k = dm->n_k;

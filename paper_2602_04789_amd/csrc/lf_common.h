@@ -28,19 +28,31 @@ struct lf_dims {
 // Validates shape (and budget when non-NULL); returns LF_OK or an lf_status.
 int lf_derive(const lf_shape* s, const lf_budget* b, lf_dims* out);
 
-// Whether the query-major attention kernels divide each list among the four pairs of wavefronts of
-// a workgroup instead of giving every (head, query block) one pair.  A divided block takes a
-// compute unit (256 of them) to itself at d = 128.  Measured, d = 128, forward call / backward call
-// (dQ divided, the rest as it was), us before -> after:
-//   <= 256 blocks: 192 blocks, lists of 8: 18.0 -> 14.3 / 53.5 -> 48.9; of 40: 51.1 -> 27.9 / 130 -> 97;
-//     lists of 4 are one step a slice: 13.5 -> 13.3 / 41.1 -> 41.6, not divided;
-//   two rounds: 320 blocks, lists of 16: 27.8 -> 31.2 / 90.3 -> 89.1; of 40: 54.8 -> 52.1 / 158 -> 149;
-//     480 blocks, lists of 40: 63.1 -> 56.2 / 199 -> 188;
-//   three: 560 blocks, lists of 40: 74.4 -> 80.4 / 217 -> 242.
-// At d = 64 two divided blocks share a compute unit and the gain is larger (480 blocks, lists of 40:
-// 47.3 -> 37.8 / 165 -> 153; of 8: 16.0 -> 18.3 / 57.4 -> 58.5); the same line serves.
-inline bool lf_split_lists(int blocks, int list_len) {
-  return (blocks <= 256 && list_len >= 6) || (blocks <= 512 && list_len >= 32);
+// Whether a query-major attention kernel divides each list among the four pairs of wavefronts of a
+// workgroup instead of giving every (head, query block) one pair.  `blocks` is the number of
+// these pairs, list_len the entries walked, n_k the KV blocks of a head.  A divided block has a compute unit (of 256)
+// to itself, so with more than 256 of them the second round starts when the first ends, and the
+// undivided form keeps more loads of one list's tiles in flight per compute unit.
+// Forward, d = 128, us undivided -> divided (random lists):
+//   <= 256 blocks: 192 blocks, lists of 6: 13.6 -> 12.4; of 195: 222 -> 109; lists of 4 are one step a slice;
+//   <= 512, lists that hold at least half of the KV blocks: 286 blocks, 151 of 234: 164 -> 149; 490, 110 of 126:
+//     122 -> 119; 432, 92 of 120: 106 -> 102; 360, 108 of 192: 124 -> 117; but 348, 34 of 60: 44 -> 49;
+//   <= 512, sparser lists: 432 blocks, 91 of 672: 114 -> 139; 300, 57 of 300: 70 -> 84; 288, 187 of 1224:
+//     207 -> 229; 312, 135 of 468 (150 -> 137) is the other way;
+//   > 512: 624 blocks, 72 of 80: 116 -> 122; 560, 236 of 280: 331 -> 334.
+// Forward, d = 64: 208 blocks, lists of 52: 48 -> 23; 336 blocks, lists of 29: 30.3 -> 32.3; 280, of 35: 34.1 -> 32.6;
+//   512, of 63: 58 -> 54; 450, of 196: 167 -> 132; 768, of 37: 48 -> 57.
+inline bool lf_split_lists(int d, int blocks, int list_len, int n_k) {
+  if (blocks <= 256) return list_len >= 6;
+  if (blocks > 512) return false;
+  return d == 64 ? list_len >= 32 : list_len >= 96 && 2 * (int64_t)list_len >= n_k;
+}
+// dQ (backward call, the rest the same), d = 128: 132 blocks, lists of 6: 33.5 -> 34.6, of 8: 38.7 -> 34.4 (80 blocks);
+// 384 blocks, of 4: 119 -> 128; 350, of 14: 114 -> 120; 512, of 41: 254 -> 257; 324, of 53: 191 -> 171; 400, of 69: 277 -> 256;
+// 576, of 18: 106 -> 123.  d = 64: 125 blocks, lists of 6: 29.7 -> 30.6; 78, of 7: 25.9 -> 24.9; 120, of 138: 213 -> 160; 390,
+// of 26: 87 -> 94; 304, of 57: 151 -> 157; 494, of 144: 460 -> 449.
+inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
+  return (blocks <= 256 && list_len >= 7) || (d == 128 && blocks <= 512 && list_len >= 48);
 }
 
 // Kernel launchers (defined in the .hip files); return LF_OK or LF_ERR_HIP.

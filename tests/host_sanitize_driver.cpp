@@ -156,6 +156,16 @@ int main() {
     p.head_dim = 96; EXPECT(lf_qk_norm_rope(P, (const float*)P, (const float*)P, (const float*)P, &p, P, nullptr) == LF_ERR_SHAPE);
     p.head_dim = 128; p.eps = NAN; EXPECT(lf_qk_norm_rope(P, (const float*)P, (const float*)P, (const float*)P, &p, P, nullptr) == LF_ERR_SHAPE); }
   EXPECT(g_launches == accepted);   // none of the rejected calls reached a launcher
+  // division of lists: not where it measured slower (two rounds of divided blocks on short or sparse
+  // lists at d = 128; dQ at d = 64)
+  EXPECT(lf_split_lists(128, 256, 6, 1000) && !lf_split_lists(128, 256, 5, 1000) && !lf_split_lists(64, 256, 5, 8));
+  EXPECT(!lf_split_lists(128, 261, 32, 153) && !lf_split_lists(128, 432, 91, 672) && !lf_split_lists(128, 300, 57, 300));
+  EXPECT(!lf_split_lists(128, 288, 187, 1224) && !lf_split_lists(128, 348, 34, 60) && !lf_split_lists(128, 257, 95, 96));
+  EXPECT(lf_split_lists(128, 512, 96, 192) && !lf_split_lists(128, 512, 96, 193) && !lf_split_lists(128, 513, 96, 96));
+  EXPECT(lf_split_lists(64, 512, 32, 1000) && !lf_split_lists(64, 512, 31, 31) && !lf_split_lists(64, 513, 200, 200));
+  EXPECT(lf_split_lists_dq(128, 256, 7) && lf_split_lists_dq(64, 256, 7) && !lf_split_lists_dq(128, 256, 6));
+  EXPECT(lf_split_lists_dq(128, 512, 48) && !lf_split_lists_dq(128, 512, 47) && !lf_split_lists_dq(128, 513, 200));
+  EXPECT(!lf_split_lists_dq(64, 257, 200));
   for (int st = -9; st <= 1; ++st) EXPECT(lf_strerror(st) != nullptr && strlen(lf_strerror(st)) > 0);
   EXPECT(lf_version() >= 100);
 

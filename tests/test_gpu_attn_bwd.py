@@ -323,10 +323,12 @@ def test_training_step_replays_from_a_captured_graph(gpu):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("heads,list_len", [(2, 5), (2, 6), (2, 9), (16, 31), (16, 32), (17, 32), (1, 47)])
+@pytest.mark.parametrize("heads,list_len", [(2, 5), (2, 6), (2, 7), (2, 9), (16, 31), (16, 32), (17, 32),
+                                            (16, 47), (16, 48), (17, 48), (1, 47)])
 def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len, head_dim):
     """dQ with and without each list divided among four pairs of wavefronts (both sides of the edges
-    of that rule, 512 and 544 query blocks among them), one head of each against the oracle."""
+    of that rule: list lengths 6/7, at d = 128 and more than 256 query blocks 47/48; 512 and 544 query
+    blocks), one head of each against the oracle."""
     torch, lf = gpu
     w = synth.small_ragged(frame_len=1000, chunk_idx=2, heads=heads, head_dim=head_dim)
     x = synth.make_inputs(w)

@@ -525,11 +525,11 @@ def test_rollout_calls_40_heads(gpu, chunk, step):
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("heads,list_len", [(2, 5), (2, 6), (2, 7), (8, 31), (16, 31), (16, 32), (16, 33), (17, 32),
-                                            (2, 129), (2, 517)])
+                                            (16, 95), (16, 96), (17, 96), (2, 129), (2, 517)])
 def test_lists_divided_among_the_wavefronts_of_a_workgroup(gpu, heads, list_len, head_dim):
     """The attention kernels divide lists among four pairs of wavefronts when a call has few query
-    blocks: both sides of each edge of that rule (list lengths 5/6 and 31/32, 512 and 544 query
-    blocks), slices of unequal length, slices without any valid id, several decode passes, ragged
+    blocks: both sides of each edge of that rule (list lengths 5/6, for more than 256 query blocks 31/32 at
+    d = 64 and 95/96 at d = 128; 512 and 544 query blocks), slices of unequal length, slices without any valid id, several decode passes, ragged
     query blocks, a continued state (the two-phase call) and the log-sum-exp, on lists with
     out-of-range and repeated ids."""
     torch, lf = gpu
