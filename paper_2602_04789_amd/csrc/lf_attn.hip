@@ -116,7 +116,7 @@ __device__ __forceinline__ void lds_barrier() {
 // order of float32 sums differs.  A call with few query blocks leaves compute units idle while
 // every wavefront goes through its list step by step (one wavefront per SIMD: 0.55 - 0.8 us a step,
 // mostly latency); dividing the list shortens that chain.
-template <int D, int WAVES, bool DENSE, int SPLIT = 1>
+template <int D, int WAVES, bool DENSE, int SPLIT = 1, bool EARLY_V = false>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs a) {
   constexpr int QPW = DENSE ? 1 : WAVES / 2;    // tile stages per workgroup
   constexpr int QB = QPW / SPLIT;               // query blocks per workgroup
@@ -514,27 +514,34 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
         }
       };
       softmax();
-      // The V^T fragments of the first k-step are requested ahead of the second half of the score
-      // product (against requesting them after it: whole blocks 103.2 -> 101.8 us, 16 heads x 64 at the
-      // last chunk 307 -> 300, 12 heads x 128 345.3 -> 344.3), with a divided list after it (17.0
-      // against 17.4).
+      // The V^T fragments of the first k-step are requested after the second half of the score product;
+      // EARLY_V: ahead of it (lf_launch_attn says where that is faster).  The late request is
+      // written in two ways because the compiler schedules them differently.  In place, the exponentials lie among
+      // the K reads and matrix instructions of that half; as a function, the K reads come first.  The former is
+      // the faster one at d = 128 (1 - 2 % over 512 blocks, 1 - 5 % below), the latter at d = 64 (336 blocks, lists of 15: 21.6 us in
+      // place, 19.5; 896 blocks, of 252: 339, 317) and with divided lists longer than 70.
       const uint16_t* Vs16 = reinterpret_cast<const uint16_t*>(cur + TILE);
+      auto vfrag = [&](int u, int mb) __attribute__((always_inline)) {
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, Vs16 + vaddr(u, 0, mb)));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, Vs16 + vaddr(u, 1, mb)));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      };
       bf16x8 vf0[MB];
       auto first_v = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, Vs16 + vaddr(0, 0, mb)));
-          const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, Vs16 + vaddr(0, 1, mb)));
-          vf0[mb] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        for (int mb = 0; mb < MB; ++mb) vf0[mb] = vfrag(0, mb);
       };
-      if constexpr (SPLIT == 1) {
+      if constexpr (EARLY_V) {
         first_v();
         __builtin_amdgcn_sched_barrier(0);
         snext = s_half(other, snext, KS / 2);
-      } else {
+      } else if constexpr (D == 64 || SPLIT > 1) {
         snext = s_half(other, snext, KS / 2);
         first_v();
+      } else {
+        snext = s_half(other, snext, KS / 2);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) vf0[mb] = vfrag(0, mb);
       }
       // Rare: the row sum says the reference is far too low (or was never set).  Then the
       // maxima are taken, the reference moves up to them and P^T is made again.
@@ -561,10 +568,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
         oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf0[mb], pf[0], oacc[mb], 0, 0, 0);
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, Vs16 + vaddr(1, 0, mb)));
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(bf16x4, Vs16 + vaddr(1, 1, mb)));
-        const bf16x8 vf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[1], oacc[mb], 0, 0, 0);
+        oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag(1, mb), pf[1], oacc[mb], 0, 0, 0);
       }
       // Probe builds only (liblf_hsa_probe_*.so, for `bench.py --sensitivity`): redundant work added
       // to every step to see how much the step lengthens when one unit gets more to do.  The extra
@@ -775,12 +779,18 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
         : lf_launch(lf_attn_kernel<64, 8, false, 4>, dim3(grid), dim3(512), 0, st, a);
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
+  // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
+  // whole blocks to the end.  Measured late -> early, us: whole frames, 624 query blocks, lists of 61: 104 -> 101; 864, of 89:
+  // 172 -> 170; 768, of 18: 40.3 -> 39.7; at most one workgroup a unit: 384, of 23: 31.0 -> 32.7; a last round that
+  // is partly filled: 1 368, of 166: 502 -> 518; ragged frames: 640, of 82: 144.1 -> 145.0, 624, of 29: 54.5 -> 55.2.
+  const bool early_v = dm->d == 128 && dm->n % 64 == 0 && a.total_wg > 512 && a.total_wg <= 1024;
   constexpr int kListWaves = 4;                  // two query blocks per workgroup
   const int n_wg = (a.total_wg + kListWaves / 2 - 1) / (kListWaves / 2);
   a.wg_per_xcd = (n_wg + 7) / 8;
   const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
   const hipError_t rc = dm->d == 128
-      ? lf_launch(lf_attn_kernel<128, kListWaves, false>, dim3(grid), dim3(64 * kListWaves), 0, st, a)
+      ? lf_launch(early_v ? lf_attn_kernel<128, kListWaves, false, 1, true> : lf_attn_kernel<128, kListWaves, false>,
+                  dim3(grid), dim3(64 * kListWaves), 0, st, a)
       : lf_launch(lf_attn_kernel<64, kListWaves, false>, dim3(grid), dim3(64 * kListWaves), 0, st, a);
   return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
 }

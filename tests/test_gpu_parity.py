@@ -649,3 +649,31 @@ def test_a_head_gives_the_same_whether_its_lists_are_divided_or_not(gpu, frame_l
             assert float((a - c).norm() / c.norm()) <= 5e-4, name
     # log2 of a float32 sum of keep * 64 probabilities, in another order
     assert float((lse_many[:few] - lse_alone).abs().max()) <= 1.5 * keep * 64 * 2.0 ** -24 + 2.0 ** -20
+
+
+def test_the_place_of_the_v_request_does_not_change_a_bit(gpu):
+    """Whole frames at d = 128: 512, 520 and 1 024 query blocks and 1 032, where the kernel asks for V
+    late, early, early and late.  The heads that all calls share give the same bits, and sampled
+    blocks of them match the oracle."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=256, chunk_idx=3, heads=129, head_dim=128)
+    x = synth.make_inputs(w)
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    n_q, n_k, L = w.frames_per_chunk * w.blocks_per_frame, w.frames * w.blocks_per_frame, 13
+    rng = np.random.default_rng(1)
+    lists = rng.integers(-1, n_k + 1, (w.heads, n_q, L)).astype(np.int32)
+    outs = []
+    for heads in (64, 65, 128, 129):
+        print(f"place of the V request: {heads * n_q} query blocks", flush=True)
+        idx = torch.from_numpy(lists[:heads]).cuda()
+        outs.append(lf.lf_sparse_attn(Q[:heads], K[:heads], V[:heads], idx, w.frame_len, w.block)[:64])
+    torch.cuda.synchronize()
+    for o in outs[1:]:
+        assert torch.equal(o.view(torch.int16), outs[0].view(torch.int16))
+    got = outs[0].float().cpu().numpy().astype(np.float64)
+    Qf, Kf, Vf = (_host_f32(x[k][:64]) for k in "QKV")
+    for h, r in ((0, 0), (63, n_q - 1), (31, 3)):
+        kept = [int(c) for c in lists[h, r] if 0 <= c < n_k]
+        lo, hi = O.block_token_range(r, w.frame_len, w.block)
+        err = np.abs(got[h, lo:hi] - O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, kept, w.frame_len, w.block))
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max())
