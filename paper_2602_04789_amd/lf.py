@@ -200,8 +200,12 @@ def _stream_ptr(stream) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
     torch = _torch or _get_torch()
-    # the current device's current stream, without building a Stream object around it (2 us)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the current device's current stream; where torch has the function, without building a Stream object
+    # around it (2 us).  It is not part of torch's public interface.
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return raw(torch.cuda.current_device())
 
 
 def lf_select_mask(Q, Kcache, frame_len: int, block: int, budget: lf_budget, indices=None,

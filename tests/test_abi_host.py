@@ -314,3 +314,16 @@ def test_host_side_under_address_and_undefined_behaviour_sanitizers(tmp_path):
                UBSAN_OPTIONS="print_stacktrace=1")
     res = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, env=env, timeout=120)
     assert res.returncode == 0 and "ALL OK" in res.stdout, res.stdout[-3000:]
+
+
+def test_stream_lookup_does_without_the_private_torch_function(monkeypatch):
+    """The binding takes the current stream from a function that is not part of torch's public interface
+    where there is one, and from the public interface otherwise."""
+    from types import SimpleNamespace as N
+    from paper_2602_04789_amd import lf
+    cuda = N(current_device=lambda: 3, current_stream=lambda: N(cuda_stream=11))
+    monkeypatch.setattr(lf, "_torch", N(_C=N(), cuda=cuda))
+    assert lf._stream_ptr(None) == 11
+    monkeypatch.setattr(lf, "_torch", N(_C=N(_cuda_getCurrentRawStream=lambda d: 100 + d), cuda=cuda))
+    assert lf._stream_ptr(None) == 103
+    assert lf._stream_ptr(N(cuda_stream=7)) == 7
