@@ -114,9 +114,24 @@ __device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins
     const int h = i / a.order_n_k;
     return h * a.order_n_k + (int)((uint64_t)(uint32_t)(i - h * a.order_n_k) * a.order_step % (uint32_t)a.order_n_k);
   };
+  // Every block of the share with its bin, U at a time: their loads (and LDS atomics) are in flight together.
+  // A long history has thousands of blocks a share, and one at a time the loop outlasts the dQ launch.
+  auto each_block = [&](auto put) __attribute__((always_inline)) {
+    constexpr int U = 8;
+    for (int i0 = w0 + tid; i0 < w1; i0 += U * threads) {
+      int w[U], b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u] = at(min(i0 + u * threads, w1 - 1));
+#pragma unroll
+      for (int u = 0; u < U; ++u) b[u] = min(a.order_cnt[w[u]], kOrderBins - 1);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + u * threads < w1) put(w[u], b[u]);
+    }
+  };
   for (int i = tid; i < kOrderBins; i += threads) bins[i] = 0;
   __syncthreads();
-  for (int i = w0 + tid; i < w1; i += threads) atomicAdd(&bins[min(a.order_cnt[at(i)], kOrderBins - 1)], 1);
+  each_block([&](int, int b) { atomicAdd(&bins[b], 1); });
   __syncthreads();
   // bins[b] <- number of places in bins above b (where bin b starts in the descending order); lane l
   // of the first wavefront takes the l-th sixteen bins from the top
@@ -142,10 +157,7 @@ __device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins
     }
   }
   __syncthreads();
-  for (int i = w0 + tid; i < w1; i += threads) {
-    const int w = at(i);
-    a.order[w0 + atomicAdd(&bins[min(a.order_cnt[w], kOrderBins - 1)], 1)] = w;
-  }
+  each_block([&](int w, int b) { a.order[w0 + atomicAdd(&bins[b], 1)] = w; });
 }
 
 // dQ: a workgroup of two wavefronts owns a query block (wavefront rh its rows [32 rh, +32)) and

@@ -366,3 +366,39 @@ def test_few_kv_blocks_take_two_groups_of_wavefronts(gpu, heads, list_len, head_
         ref = O.sparse_attention_backward(Qf, Kf, Vf, dOf, lists[h:h + 1], w.frame_len, w.block)
         for name, g, want in zip(("dQ", "dK", "dV"), got, ref):
             _close(name, g[h:h + 1], want)
+
+
+@pytest.mark.parametrize("heads,frames", [(5, 1700), (8, 1025), (1, 9), (3, 2730)])
+def test_every_kv_block_is_written_over_a_long_history(gpu, heads, frames):
+    """The launch order of dK and dV is made from the transposed lists' lengths, a share of the (head, KV block)
+    pairs per XCD, several blocks at a time by each thread: shares of 1 063, 1 025 (one more than a pass of 128
+    threads takes), 2 and 1 024 blocks.  Gradients that start as garbage are written everywhere: the
+    oracle's values where a list keeps the block, zeros elsewhere."""
+    torch, lf = gpu
+    n, d, L = 64, 64, 9
+    w = synth.small_ragged(frame_len=n, frames_per_chunk=1, chunk_idx=frames, heads=heads, head_dim=d, n_chunks=frames)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(heads)
+    Q, K, V, dO = (torch.randn((heads, t, d), generator=g, device="cuda").to(torch.bfloat16)
+                   for t in (n, frames * n, frames * n, n))
+    rng = np.random.default_rng(frames)
+    lists = np.stack([np.sort(rng.choice(frames, L, replace=False))[None] for _ in range(heads)]).astype(np.int32)
+    print(f"long history: heads={heads} frames={frames}", flush=True)
+    idx = torch.from_numpy(lists).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, n, 64)
+    grads = tuple(torch.full_like(t, 7.0) for t in (Q, K, V))
+    lf.lf_sparse_attn_bwd(Q, K, V, out, dO, lse2, idx, n, 64, grads=grads)
+    torch.cuda.synchronize()
+    dQ, dK, dV = (t.float().cpu().numpy().astype(np.float64) for t in grads)
+    Qf, dOf = (t.float().cpu().numpy() for t in (Q, dO))
+    for h in range(heads):
+        cols = np.concatenate([np.arange(c * n, (c + 1) * n) for c in lists[h, 0]])
+        rest = np.setdiff1d(np.arange(frames * n), cols)
+        assert (dK[h, rest] == 0).all() and (dV[h, rest] == 0).all()
+        # the kept columns alone, as a history of their own
+        rows = torch.from_numpy(cols).cuda()
+        Kf, Vf = (t[h, rows].float().cpu().numpy()[None] for t in (K, V))
+        rQ, rK, rV = O.sparse_attention_backward(Qf[h:h + 1], Kf, Vf, dOf[h:h + 1],
+                                                 np.arange(L, dtype=np.int32)[None, None], n, 64)
+        for name, got, ref in (("dQ", dQ[h:h + 1], rQ), ("dK", dK[h:h + 1, cols], rK), ("dV", dV[h:h + 1, cols], rV)):
+            _close(name, got, ref)
