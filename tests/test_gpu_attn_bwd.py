@@ -72,8 +72,8 @@ SMALL = {
     "short_frame": lambda: synth.small_ragged(frame_len=40, chunk_idx=5, heads=2, k_frames=1),
     "tail_31": lambda: synth.small_ragged(frame_len=95, chunk_idx=3, heads=2),
     "tail_33_d64": lambda: synth.small_ragged(frame_len=97, chunk_idx=3, heads=2, head_dim=64),
-    # 260 one-block frames per chunk: lists of 266 entries and transposed lists of 260, both past
-    # the 256 entries the kernels decode per pass
+    # 260 one-block frames per chunk: transposed lists of 260 entries, past the 256 that the dK / dV launch
+    # decodes per pass (the lists of 266 are divided here; test_dq_over_more_than_one_decode_pass has dQ's passes)
     "many_query_blocks": lambda: synth.small_ragged(frame_len=64, chunk_idx=2, frames_per_chunk=260, heads=1,
                                                     head_dim=64, k_frames=3, n_sink=1, n_win=2),
 }
@@ -402,3 +402,102 @@ def test_every_kv_block_is_written_over_a_long_history(gpu, heads, frames):
                                                  np.arange(L, dtype=np.int32)[None, None], n, 64)
         for name, got, ref in (("dQ", dQ[h:h + 1], rQ), ("dK", dK[h:h + 1, cols], rK), ("dV", dV[h:h + 1, cols], rV)):
             _close(name, got, ref)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,per_chunk,frames,list_len", [(20, 26, 300, 257), (20, 26, 300, 300), (1, 2, 1100, 1026)])
+def test_dq_over_more_than_one_decode_pass(gpu, heads, per_chunk, frames, list_len, head_dim):
+    """dQ decodes 256 list entries per pass: 520 query blocks with lists of 257 and 300 (undivided), and 2 with
+    lists of 1 026 (divided: quarters of 257).  Strided tensors, ids out of range at both ends of the
+    lists, a query block without a valid id, blocks that no list keeps, an explicit scale, two calls with the same bits.
+    The key-major launch has more than 256 KV blocks, so one group of wavefronts each."""
+    torch, lf = gpu
+    n, scale = 40, 0.1                      # one short block per frame
+    w = synth.small_ragged(frame_len=n, frames_per_chunk=per_chunk, chunk_idx=1, heads=heads, head_dim=head_dim)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(list_len)
+
+    def strided(tokens, pad_tok, pad_ch):
+        t = torch.full((heads, tokens + pad_tok, head_dim + pad_ch), float("nan"), dtype=torch.bfloat16, device="cuda")
+        view = t[:, 1:1 + tokens, :head_dim]
+        view.copy_(torch.randn(view.shape, generator=g, device="cuda"))
+        return view
+    Q, K, V = strided(per_chunk * n, 3, 8), strided(frames * n, 5, 16), strided(frames * n, 2, 24)
+    dO, Oview = strided(per_chunk * n, 4, 8), strided(per_chunk * n, 4, 8)
+    rng = np.random.default_rng(list_len)
+    lists = np.empty((heads, per_chunk, list_len), dtype=np.int32)
+    for h in range(heads):
+        for r in range(per_chunk):
+            keep = np.sort(rng.choice(frames - 2, list_len - 5, replace=False))
+            lists[h, r] = np.concatenate([[-9, -3], keep, [frames, frames + 1, frames + 9]])
+    lists[heads - 1, 1] = np.arange(list_len) - list_len       # no valid id
+    print(f"dQ passes: heads={heads} d={head_dim} blocks {heads * per_chunk} list length {list_len}", flush=True)
+    idx = torch.from_numpy(lists).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, n, 64, softmax_scale=scale, O=Oview)
+    grads = [lf.lf_sparse_attn_bwd(Q, K, V, out, dO, lse2, idx, n, 64, softmax_scale=scale) for _ in range(2)]
+    torch.cuda.synchronize()
+    for a, b in zip(*grads):
+        assert torch.equal(a.contiguous().view(torch.int16), b.contiguous().view(torch.int16))
+    dQ, dK, dV = (t.float().cpu().numpy().astype(np.float64) for t in grads[0])
+    h = heads - 1
+    Qf, Kf, Vf, dOf = (t[h:h + 1].float().cpu().numpy() for t in (Q, K, V, dO))
+    valid = np.empty((1, per_chunk), dtype=object)
+    for r in range(per_chunk):
+        valid[0, r] = [int(c) for c in lists[h, r] if 0 <= c < frames]
+    valid[0, 1] = [0]                        # stands for no block: without an upstream gradient it adds nothing
+    dOf[0, n:2 * n] = 0
+    ref = O.sparse_attention_backward(Qf, Kf, Vf, dOf, valid, n, 64, scale=scale)
+    for name, got, want in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
+        _close(name, got[h:h + 1], want)
+    assert (dQ[h, n:2 * n] == 0).all() and torch.isposinf(lse2[h, n:2 * n]).all()
+    assert (dK[:, (frames - 2) * n:] == 0).all() and (dV[:, (frames - 2) * n:] == 0).all()
+
+
+@pytest.mark.parametrize("frame_len,head_dim", [(200, 128), (256, 128), (200, 64)])
+def test_training_step_with_many_query_blocks_replays(gpu, frame_len, head_dim):
+    """test_training_step_replays_from_a_captured_graph on 528 query blocks, the undivided kernels: the step
+    replayed from a graph on new inputs, and run twice, gives the bits of the eager step."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=3, heads=66, head_dim=head_dim)
+    b = lf.lf_chunk_budget(w.chunk_idx, w.schedule)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(frame_len)
+    Q, K, V, dO = (torch.empty((w.heads, t, head_dim), dtype=torch.bfloat16, device="cuda")
+                   for t in (w.q_len, w.kv_len, w.kv_len, w.q_len))
+
+    def new_inputs():
+        for t in (Q, K, V, dO):
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+            t[t.abs() < 2.0 ** -30] = 0
+    sh = lf.make_shape(Q, K, V, Q, frame_len=w.frame_len, block=w.block)
+    ws = torch.empty(lf.lf_workspace_bytes(sh, b), dtype=torch.uint8, device="cuda")
+    bws = torch.empty(lf.lf_attn_bwd_workspace_bytes(sh), dtype=torch.uint8, device="cuda")
+    idx = torch.empty((w.heads, w.frames_per_chunk * w.blocks_per_frame, b.list_len), dtype=torch.int32, device="cuda")
+    out, lse2 = torch.empty_like(Q), torch.empty((w.heads, w.q_len), dtype=torch.float32, device="cuda")
+    grads = tuple(torch.empty_like(t) for t in (Q, K, V))
+
+    def step():
+        lf.lf_select_mask(Q, K, w.frame_len, w.block, b, indices=idx, workspace=ws)
+        lf.lf_sparse_attn_fwd(Q, K, V, idx, w.frame_len, w.block, O=out, lse2=lse2)
+        lf.lf_sparse_attn_bwd(Q, K, V, out, dO, lse2, idx, w.frame_len, w.block, workspace=bws, grads=grads)
+    new_inputs()
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for replay in range(3):
+        print(f"graph replay {replay}: n={frame_len} d={head_dim}", flush=True)
+        new_inputs()
+        bws.fill_(255)
+        for t in grads + (out,):
+            t.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in grads + (out,)]
+        for t in grads + (out,):
+            t.fill_(5.0)
+        step()
+        torch.cuda.synchronize()
+        for a, e in zip(got, grads + (out,)):
+            assert torch.equal(a.view(torch.int16), e.view(torch.int16))

@@ -208,8 +208,9 @@ def test_attention_list_edge_cases(gpu):
         "unordered": np.tile(np.array([n_k - 1, 0, 5, 2], np.int32), (w.heads, n_q, 1)),
         "invalid_ids_skipped": np.tile(np.array([-1, 3, n_k, 1 << 30, 4], np.int32), (w.heads, n_q, 1)),
         "duplicate": np.tile(np.array([2, 2, 7], np.int32), (w.heads, n_q, 1)),
-        # the kernel decodes 256 list entries per pass: just below, at and above one pass, then
-        # two passes plus one entry and five passes with a short last one
+        # long lists.  With these few query blocks they are divided among four pairs of wavefronts, which
+        # decode 128 entries of their quarter per pass; the edges of the passes of either form are in
+        # test_list_lengths_around_the_decode_passes
         "len_255": np.tile((np.arange(255, dtype=np.int32) * 5) % n_k, (w.heads, n_q, 1)),
         "len_256": np.tile((np.arange(256, dtype=np.int32) * 5) % n_k, (w.heads, n_q, 1)),
         "len_257": np.tile((np.arange(257, dtype=np.int32) * 5) % n_k, (w.heads, n_q, 1)),
@@ -246,8 +247,8 @@ def test_attention_list_edge_cases(gpu):
 @pytest.mark.parametrize("frame_len,head_dim", [(200, 128), (232, 128), (224, 64)])
 def test_lists_whose_half_tile_counts_differ(gpu, frame_len, head_dim):
     """A listed block of at most 32 tokens is one step of the kernel, a longer one two, an id out
-    of range none, and the two query blocks of a workgroup take the longer one's step count: lists
-    of equal length whose neighbours differ in all of that (only tail blocks, only full blocks, a
+    of range none, and the query blocks of a workgroup (in a call of so few: the four parts of a
+    divided list) take the longest one's step count: lists of equal length whose neighbours differ in all of that (only tail blocks, only full blocks, a
     mix with invalid ids, hardly any valid id), with tails of 8, 40 and 32 tokens, two query
     frames so that a short query block sits inside the chunk, and more than one decode pass."""
     torch, lf = gpu
@@ -677,3 +678,98 @@ def test_the_place_of_the_v_request_does_not_change_a_bit(gpu):
         lo, hi = O.block_token_range(r, w.frame_len, w.block)
         err = np.abs(got[h, lo:hi] - O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, kept, w.frame_len, w.block))
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max())
+
+
+def _mixed_lists(w, heads, L, rng):
+    """[heads, n_q, L]: neighbours differ in their number of half tiles (only short tail blocks, only full
+    ones, a mix with ids out of range, hardly any valid id, and per head one list without any)."""
+    nb, n_q, n_k = w.blocks_per_frame, w.frames_per_chunk * w.blocks_per_frame, w.frames * w.blocks_per_frame
+    ids = np.arange(n_k, dtype=np.int32)
+    lists = rng.integers(-2, n_k + 2, (heads, n_q, L)).astype(np.int32)
+    for h in range(heads):
+        for r in range(n_q):
+            kind = (r + h) % 4
+            if kind == 0:
+                lists[h, r] = rng.choice(ids[ids % nb == nb - 1], L)
+            elif kind == 1:
+                lists[h, r] = rng.choice(ids[ids % nb != nb - 1], L)
+            elif kind == 3:
+                lists[h, r] = -1
+                lists[h, r, rng.integers(0, L)] = rng.integers(0, n_k)
+        lists[h, h % n_q] = n_k
+    return lists
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,lengths", [(130, (255, 256, 257, 513)), (2, (511, 512, 513, 1024, 1025))])
+def test_list_lengths_around_the_decode_passes(gpu, heads, lengths, head_dim):
+    """Lists are decoded 256 entries per pass where every pair of wavefronts has a query block of its own (130
+    heads, 520 query blocks) and 128 entries of each quarter where they are divided (2 heads, 8 query blocks): lengths
+    around one and two passes of either form, on lists whose numbers of half tiles differ between
+    the query blocks of a workgroup, from tensors carved out of larger ones, also into guarded memory."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=72, chunk_idx=4, heads=heads, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
+
+    def strided(bits, value):
+        H, L, d = bits.shape
+        buf = torch.full((H, L + 5, d + 8), value, dtype=torch.bfloat16, device="cuda")
+        view = buf[:, 2:2 + L, :d]
+        view.copy_(_dev(torch, bits))
+        return buf, view
+    (_, Q), (_, K), (_, V), (Obuf, Oview) = (strided(x[k], float("nan")) for k in "QKVQ")
+    rng = np.random.default_rng(heads)
+    n_q, n_k = w.frames_per_chunk * w.blocks_per_frame, w.frames * w.blocks_per_frame
+    for L in lengths:
+        print(f"decode passes: heads={heads} d={head_dim} list length {L}", flush=True)
+        lists = _mixed_lists(w, heads, L, rng)
+        idx = torch.from_numpy(lists).cuda()
+        out = lf.lf_sparse_attn(Q, K, V, idx, w.frame_len, w.block, O=Oview)
+        torch.cuda.synchronize()
+        got = out.float().cpu().numpy().astype(np.float64)
+        assert np.isfinite(got).all()
+        again = lf.lf_sparse_attn(Q, K, V, idx, w.frame_len, w.block, O=torch.empty_like(Oview))
+        assert torch.equal(again.view(torch.int16), out.view(torch.int16))
+        for h in sorted({0, 1, heads // 2, heads - 1}):
+            for r in range(n_q):
+                kept = [int(c) for c in lists[h, r] if 0 <= c < n_k]
+                lo, hi = O.block_token_range(r, w.frame_len, w.block)
+                if not kept:
+                    assert np.all(got[h, lo:hi] == 0.0)
+                    continue
+                ref = O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, kept, w.frame_len, w.block)
+                err = np.abs(got[h, lo:hi] - ref)
+                assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (L, h, r, err.max())
+    # nothing outside the O view was touched
+    assert torch.isnan(Obuf[:, :2].float()).all() and torch.isnan(Obuf[:, 2 + w.q_len:].float()).all()
+    assert torch.isnan(Obuf[:, :, w.head_dim:].float()).all()
+
+
+@pytest.mark.parametrize("scale", [0.25, 1.0, 4.0])
+@pytest.mark.parametrize("frame_len,head_dim", [(200, 128), (256, 128), (200, 64)])
+def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, scale):
+    """test_attention_with_extreme_logits on 528 query blocks, where each list is walked by one pair of
+    wavefronts (V requested early for the whole frames of 256): the reference moves inside the list."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=4, heads=66, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    n = w.frame_len
+    Kf = _host_f32(x["K"]).copy()
+    Kf[:, 0:n] *= 0.05          # a first frame with tiny logits, then much larger ones
+    Kf[:, 2 * n:3 * n] *= 3.0
+    K = synth.f32_to_bf16_bits(Kf)
+    lists = O.full_lists(w.heads, n, w.block, w.frames_per_chunk, w.frames)
+    print(f"extreme logits, many query blocks: n={n} d={head_dim} scale {scale}", flush=True)
+    out = lf.lf_sparse_attn(_dev(torch, x["Q"]), _dev(torch, K), _dev(torch, x["V"]), torch.from_numpy(lists).cuda(),
+                            n, w.block, softmax_scale=scale)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    Qf, Kf, Vf = _host_f32(x["Q"]), _host_f32(K), _host_f32(x["V"])
+    for h in (0, 33, 65):
+        for r in range(lists.shape[1]):
+            lo, hi = O.block_token_range(r, n, w.block)
+            ref = O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, list(lists[h, r]), n, w.block, scale=scale)
+            err = np.abs(got[h, lo:hi] - ref)
+            assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
