@@ -5,7 +5,9 @@
 // [32 rh, 32 rh + 32) with its own online-softmax state (m, l, O): nothing crosses
 // wavefronts, and there is no merge at the end.  A workgroup holds two such query blocks and two
 // workgroups share a compute unit, so every SIMD holds two wavefronts, free to be in different
-// parts of their step (the matrix core of one beside the vector ALU of the other).  Each listed
+// parts of their step (the matrix core of one beside the vector ALU of the other).  In a call with
+// few query blocks a workgroup holds one, its list is divided among four such pairs, and their
+// states are merged through LDS.  Each listed
 // KV block is taken as half tiles of 32 KV rows (two, or one when the block has at most 32
 // tokens): the 32 x d K and V half tiles are brought into a double-buffered LDS
 // stage by asynchronous global->LDS loads, a wavefront's share of a half tile in one group
@@ -120,8 +122,9 @@ template <int D, int WAVES, bool DENSE, int SPLIT = 1, bool EARLY_V = false>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs a) {
   constexpr int QPW = DENSE ? 1 : WAVES / 2;    // tile stages per workgroup
   constexpr int QB = QPW / SPLIT;               // query blocks per workgroup
-  // half tiles decoded per pass (power of two); half of them where the lists are divided, so that two
-  // such workgroups of d = 64 fit the LDS of a compute unit
+  // Half tiles decoded per pass (power of two).  Where the lists are divided, half of them: a thread then
+  // decodes one list entry, which is as many as a quarter of a list nearly always has (512: 0.1 - 0.4 us longer,
+  // 72 blocks of d 64 with lists of 6 9.0 -> 9.2 us, 84 of d 128 with lists of 44 28.7 -> 28.9).
   constexpr int kMaxEnt = SPLIT > 1 ? 256 : 512;
   constexpr int WPQ = WAVES / QPW;              // wavefronts that share one tile stage
   constexpr int kThreads = 64 * WPQ;            // ... and their threads

@@ -374,8 +374,9 @@ extern "C" int lf_sparse_attn_fwd(const void* Q, const void* K, const void* V, c
                         stream);
 }
 
-// Scratch of lf_sparse_attn_bwd: -delta float32 [H][q_len] (room for two values per row), the transposed lists int32
-// [H][n_k][n_q], their lengths int32 [H][n_k] and the launch order int32 [H][n_k].
+// Scratch of lf_sparse_attn_bwd: -delta float32 [H][q_len], the transposed lists int32 [H][n_k][n_q], their
+// lengths int32 [H][n_k] and the launch order int32 [H][n_k].  A row of -delta has room for two values, of which one is
+// used: the size a caller may have laid out is kept as it was when the log-sum-exp was copied there too.
 static size_t attn_bwd_bytes(const lf_dims& dm, size_t* off_tlist, size_t* off_tcnt, size_t* off_order) {
   const size_t rows = (size_t)dm.H * dm.f * dm.n;
   const size_t o1 = align_up(rows * 2 * sizeof(float), 256);

@@ -42,9 +42,11 @@ __device__ __forceinline__ void unpack8(const uint4& u, float (&x)[8]) {
 // the mean of squares and the rotation.  NI = 0: any length; the second pass reads the token again.
 // What bounds it: one wavefront per token is one round of wavefronts on the chip at the sizes of a
 // chunk (4 680 tokens), so the time is one token's chain -- read, reduce over the lanes, scale,
-// rotate, write -- on top of the bytes.  The chain holds one trip to memory: the norm weight and the
-// angles (which depend on the lane only, not on the head) are requested together with the token.
-// 12 heads x 128, 4 680 tokens: 9.3 us a call with the token read twice and the weights and angles requested where used, 8.6 us now (28.8 MB: 3.3 TB/s).
+// rotate, write -- on top of the bytes.  The angles, which depend on the lane only and not on the head, are
+// requested together with the token; so are the norm weights of tokens up to 256 chunks (8 registers per
+// chunk), and longer tokens ask for theirs after the reduction, from the L2.
+// 12 heads x 128, 4 680 tokens: 9.3 us a call with the token read twice and the weights and angles requested where used,
+// 8.6 us now (28.8 MB: 3.3 TB/s).
 template <int D, int NI>
 __global__ __launch_bounds__(64 * kTokensPerWg) void lf_qk_norm_rope_kernel(ProducerArgs a) {
   constexpr int CH = D / 8;
