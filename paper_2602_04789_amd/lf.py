@@ -202,8 +202,9 @@ def _stream_ptr(stream) -> int:
     torch = _torch or _get_torch()
     # the current device's current stream; where torch has the function, without building a Stream object
     # around it (2 us).  It is not part of torch's public interface.
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None:
+    try:
+        raw = torch._C._cuda_getCurrentRawStream
+    except AttributeError:
         return int(torch.cuda.current_stream().cuda_stream)
     return raw(torch.cuda.current_device())
 
