@@ -52,7 +52,7 @@ struct BwdArgs {
   int32_t* order;        // owner handled by workgroup slot w of the key-major launch (made beside the dQ launch)
   const int32_t* order_cnt;                      // dQ launch: entries per transposed list, for the order
   int order_total, order_per_xcd, order_n_k;
-  uint32_t order_step;
+  uint32_t order_step, order_stride;             // step through a head; (threads of a workgroup x step) mod n_k
   int64_t x_tok, x_head, y_tok, y_head, a1_tok, a1_head, a2_tok, a2_head;
   int64_t o1_tok, o1_head, o2_tok, o2_head;
   int n, nb, owners, streams, list_len, list_stride, q_len;
@@ -109,19 +109,24 @@ constexpr int kOrderBins = 1024;
 __device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins /* [kOrderBins] in LDS */) {
   const int threads = blockDim.x, tid = threadIdx.x;
   const int w0 = xcd * a.order_per_xcd, w1 = min(a.order_total, w0 + a.order_per_xcd);
-  // block at place i of the sequence
-  auto at = [&](int i) -> int {
-    const int h = i / a.order_n_k;
-    return h * a.order_n_k + (int)((uint64_t)(uint32_t)(i - h * a.order_n_k) * a.order_step % (uint32_t)a.order_n_k);
-  };
+  // Block at place i of the sequence: head i / n_k, and in it the block i step mod n_k (whole heads before it
+  // drop out of the remainder), which moves on by a constant when i moves on by the number of threads.
+  const uint32_t nk = (uint32_t)a.order_n_k;
+  const uint32_t c0 = (uint32_t)((uint64_t)((uint32_t)(w0 + tid) % nk) * a.order_step % nk);
   // Every block of the share with its bin, U at a time: their loads (and LDS atomics) are in flight together.
   // A long history has thousands of blocks a share, and one at a time the loop outlasts the dQ launch.
   auto each_block = [&](auto put) __attribute__((always_inline)) {
     constexpr int U = 8;
+    uint32_t c = c0;
     for (int i0 = w0 + tid; i0 < w1; i0 += U * threads) {
       int w[U], b[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) w[u] = at(min(i0 + u * threads, w1 - 1));
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * threads;
+        w[u] = i < w1 ? (int)((uint32_t)i / nk * nk + c) : w[0];   // past the end: any block, loaded and dropped
+        c += a.order_stride;
+        c -= c >= nk ? nk : 0;
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) b[u] = min(a.order_cnt[w[u]], kOrderBins - 1);
 #pragma unroll
@@ -963,6 +968,7 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.order_step = spread_step((uint32_t)dm->n_k);
   // eight workgroups in front for the order of the next launch
   const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(split ? 4 * kThreads : kThreads));
+  a.order_stride = (uint32_t)((uint64_t)block1.x * a.order_step % (uint32_t)dm->n_k);
   hipError_t rc = dm->d == 128
       ? lf_launch(split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>, grid1, block1, 0, st, a)
       : lf_launch(split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>, grid1, block1, 0, st, a);
