@@ -22,73 +22,12 @@
 //              dQ^T += K^T dS'
 //     dK, dV:  owner = KV block (X = K, Y = V), stream = query blocks (A1 = Q, A2 = dO),
 //              dK^T += Q^T dS'  and  dV^T += dO^T P', by two kinds of wavefront that share P'
-#include <hip/hip_runtime.h>
-#include <math.h>
-#include <stdint.h>
-
-#include "lf_common.h"
+#include "lf_attn_bwd.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef int int32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kThreads = 128;    // two wavefronts of 32 owner rows each
 constexpr int kPass = 256;       // list entries decoded per pass
-
-struct BwdArgs {
-  const uint16_t* X;     // owner-side operand of the scores (Q for dQ, K for dK and dV)
-  const uint16_t* Y;     // owner-side operand of dP (dO for dQ, V for dK)
-  const uint16_t* A1;    // streamed operand of the scores (K for dQ, Q for dK and dV)
-  const uint16_t* A2;    // streamed operand of dP (V for dQ, dO for dK and dV)
-  uint16_t* out1;        // dQ or dK: scale * sum of A1^T dS'
-  uint16_t* out2;        // dV: sum of A2^T P'
-  const float* lse2;     // log-sum-exp per query row (exp2 domain), [H][q_len]
-  const float* ndelta;   // -delta per query row, [H][q_len]
-  const int32_t* idx;    // lists: [H][owners][list_stride]
-  const int32_t* cnt;    // key-major: entries per transposed list
-  int32_t* order;        // owner handled by workgroup slot w of the key-major launch (made beside the dQ launch)
-  const int32_t* order_cnt;                      // dQ launch: entries per transposed list, for the order
-  int order_total, order_per_xcd, order_n_k;
-  uint32_t order_step, order_stride;             // step through a head; (threads of a workgroup x step) mod n_k
-  int64_t x_tok, x_head, y_tok, y_head, a1_tok, a1_head, a2_tok, a2_head;
-  int64_t o1_tok, o1_head, o2_tok, o2_head;
-  int n, nb, owners, streams, list_len, list_stride, q_len;
-  int total_wg, wg_per_xcd;
-  float c, scale;
-};
-
-union Frag {
-  uint4 u;
-  bf16x8 v;
-};
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-
-// One swizzle for both tiles of a step, since each is read both ways.  Row reads: 16 bytes per
-// lane, 16 consecutive rows at one logical chunk per quarter wavefront, which must land in 16
-// different chunks.  Transposing reads: half a wavefront takes four consecutive chunks from each
-// of four consecutive rows (4 k .. 4 k + 3), which must land in four different quarters of the
-// banks.  For 256-byte rows: the row's two low bits go to the chunk's two high bits (the four
-// rows of a transposing read differ there), the next two row bits to the chunk's two low bits
-// (constant within a transposing read, and together a bijection of the 16 rows of a row read).
-template <int CH> __device__ __forceinline__ int swz(int row, int ch) {
-  return CH == 16 ? ch ^ (((row & 3) << 2) | ((row >> 2) & 3)) : ch ^ ((row & 1) << 2);
-}
-// The transposing read of rows 8..15 of a 16-row group sees row bit 3, i.e. chunk bit 1, flipped:
-// 16 elements aside.
-template <int CH> constexpr int kTrHiFlip = CH == 16 ? 16 : 0;
-
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
 
 // Launch order of the key-major pass: its workgroups differ in work by the length of their
 // transposed list (a sink or current-chunk block is kept by every query block, a block of the
@@ -490,6 +429,23 @@ constexpr int kKvThreads = 256;
 // 12: 64 blocks 49.9 -> 47.8, 256 blocks 52.9 -> 50.4; of 24: 256 blocks 76.6 -> 70.0; two rounds, of 12:
 // 384 blocks 59.5 -> 66.8.  d = 64, of 12: 256 blocks 49.1 -> 46.9, 384 blocks 55.8 -> 58.8.
 constexpr int kKvSplitBlocks = 256;
+// Whether a call at d = 128 goes to the kernel with one wavefront per SIMD (lf_attn_bwd_wide.hip).  That kernel has the shorter
+// loop, but nobody works on its SIMDs while a list starts and ends, and a compute unit that has only one workgroup left (the
+// last round, of 512) leaves two of its SIMDs idle.  So the lists have to be long enough -- a KV block's list holds
+// list_len n_q / n_k query blocks on the mean -- and the last round more than half full, or one of many.  Backward call in us, this
+// file's kernel and that one, lists of one length:
+//   900 blocks:    mean 10: 101 and 103,  16: 139 and 138,  24: 189 and 184,  45: 322 and 304
+//   1 800 blocks:  mean 10: 175 and 183,  16: 248 and 250,  24: 350 and 342,  45: 622 and 589
+//   6 300 blocks:  mean 10: 562 and 583,  16: 826 and 823,  24: 1 171 and 1 143,  45: 2 078 and 1 994
+//   1 152 blocks (last round 128):  mean 16: 170 and 176,  24: 240 and 244,  48: 455 and 453
+//   256 blocks (two pairs of wavefronts each):  mean 16: 63 and 65,  24: 82 and 82,  48: 133 and 129
+//   320 blocks:  mean 16: 83 and 87,  48: 190 and 192;  512 blocks:  mean 16: 91 and 93,  32: 148 and 148
+// Lists of very different lengths (a training chunk with history: some blocks kept by every query block) gain more: 6 300
+// blocks of mean 19: 1 241 and 1 192.
+static bool kv_wide(int blocks, int64_t entries, int n_k) {
+  if (blocks <= kKvSplitBlocks) return entries >= (int64_t)32 * n_k;
+  return (blocks > 1536 || (blocks > 512 && (blocks - 1) % 512 >= 256)) && entries >= (int64_t)18 * n_k;
+}
 // SPLIT = 2: a workgroup holds two such groups of four wavefronts, each with a stage of its own and half of
 // the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.
 template <int D, int SPLIT>
@@ -986,6 +942,8 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.wg_per_xcd = (a.total_wg + 7) / 8;
   const dim3 grid2((unsigned)(a.wg_per_xcd * 8));
   const bool halves = a.total_wg <= kKvSplitBlocks;
+  if (dm->d == 128 && kv_wide(a.total_wg, (int64_t)list_len * dm->n_q, dm->n_k))
+    return lf_launch_attn_bwd_kv_wide(a, st) == hipSuccess ? LF_OK : LF_ERR_HIP;
   const dim3 block2((unsigned)(halves ? 2 * kKvThreads : kKvThreads));
   rc = dm->d == 128
       ? lf_launch(halves ? lf_attn_bwd_kv_kernel<128, 2> : lf_attn_bwd_kv_kernel<128, 1>, grid2, block2, 0, st, a)

@@ -127,6 +127,48 @@ def test_full_lists_match_library_autodiff_of_dense_attention(gpu):
         _close(name, got, ref.cpu().numpy().astype(np.float64))
 
 
+# The d = 128 kernel for long lists (mean transposed list of 32 and more) at its edges: odd and even numbers of half tiles,
+# blocks of 1, 31, 32, 33 and 64 tokens, more query blocks per list than a pass decodes (256), blocks with two pairs of
+# wavefronts (256 KV blocks and fewer) and with one (769 to 1 024 here).
+LONG_LISTS = {
+    "odd_two_pairs": lambda: synth.small_ragged(frame_len=33, chunk_idx=2, frames_per_chunk=91, heads=1, head_dim=128,
+                                                k_frames=3, n_sink=1, n_win=2),
+    "short_blocks": lambda: synth.small_ragged(frame_len=31, chunk_idx=2, frames_per_chunk=90, heads=5, head_dim=128,
+                                               k_frames=3, n_sink=1, n_win=2),
+    "one_token_tail": lambda: synth.small_ragged(frame_len=65, chunk_idx=2, frames_per_chunk=51, heads=1, head_dim=128,
+                                                 k_frames=3, n_sink=1, n_win=2),
+    "half_tail_one_pair": lambda: synth.small_ragged(frame_len=96, chunk_idx=2, frames_per_chunk=45, heads=5, head_dim=128,
+                                                     k_frames=3, n_sink=1, n_win=2),
+    "two_passes": lambda: synth.small_ragged(frame_len=64, chunk_idx=2, frames_per_chunk=390, heads=1, head_dim=128,
+                                             k_frames=3, n_sink=1, n_win=2),
+}
+
+
+@pytest.mark.parametrize("name", list(LONG_LISTS))
+def test_long_lists_at_d128_match_oracle(gpu, name):
+    torch, lf = gpu
+    w = LONG_LISTS[name]()
+    x = synth.make_inputs(w)
+    x["dO"] = synth.make_upstream_grad(w)
+    lists = _oracle_lists(w, x)
+    n_k = w.frames * w.blocks_per_frame
+    print(f"case {name}: lists {lists.shape}, {n_k} KV blocks", flush=True)
+    assert lists.shape[1] * lists.shape[2] >= 32 * n_k
+    assert w.heads * n_k <= 256 or 768 < w.heads * n_k <= 1024
+    (dQ, dK, dV), _ = _run(torch, lf, w, x, lists)
+    rQ, rK, rV = O.sparse_attention_backward(_f32(x["Q"]), _f32(x["K"]), _f32(x["V"]), _f32(x["dO"]),
+                                             lists, w.frame_len, w.block)
+    _close("dQ", dQ, rQ)
+    _close("dK", dK, rK)
+    _close("dV", dV, rV)
+    # blocks whose scores are -inf for every query row: probability zero, finite gradients (also beside rows
+    # past a short block's count, which are loaded as zeros)
+    x["Q"][..., 0] = 0x3F80      # 1
+    x["K"][:, : w.frame_len, 0] = 0xFF80      # -inf
+    (dQ, dK, dV), _ = _run(torch, lf, w, x, lists)
+    assert np.isfinite(dV).all() and not dV[:, : w.frame_len].any() and not dK[:, : w.frame_len].any()
+
+
 def test_list_edge_cases_and_strided_tensors(gpu):
     """Out-of-range ids skipped; a query block whose list holds no valid id (zero dQ rows, +inf
     log-sum-exp, no contribution to dK and dV); KV blocks that no list keeps (zero dK and dV
