@@ -25,7 +25,7 @@ def probe_lib(tag: str) -> str:
     return os.path.join(PKG, f"liblf_hsa_probe_{tag}.so")
 OBJ = os.path.join(PKG, "_build")
 
-SOURCES = ["lf_host.cpp", "lf_select.hip", "lf_attn.hip", "lf_attn_bwd.hip", "lf_attn_bwd_wide.hip", "lf_producer.hip"]
+SOURCES = ["lf_host.cpp", "lf_select.hip", "lf_attn.hip", "lf_attn_wide.hip", "lf_attn_bwd.hip", "lf_attn_bwd_wide.hip", "lf_producer.hip"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
           "-Wall", "-Wno-unused-function"]
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -37,7 +37,8 @@ DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-pa
 # NaNs first: that drops one vector instruction per score.  The selection kernels keep the
 # default: their comparisons define the bit-exact index lists.  The scheduling strategy is the
 # one that measured fastest for this kernel (1-2 % over the default on three workloads).
-PER_FILE = {"lf_attn.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]}
+PER_FILE = {"lf_attn.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-sched-strategy=max-memory-clause"],
+            "lf_attn_wide.hip": ["-fno-honor-nans"]}
 
 
 def _hipcc() -> str:

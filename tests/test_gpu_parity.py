@@ -773,3 +773,48 @@ def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, scale):
             ref = O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, list(lists[h, r]), n, w.block, scale=scale)
             err = np.abs(got[h, lo:hi] - ref)
             assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
+
+
+# One wavefront per query block (d = 128, 513 to 1 024 query blocks, lists of 32 and more) at its edges: blocks of 1, 31, 32, 33
+# and 64 tokens, lists with 0, 1, 2, 3 valid ids and with odd and even numbers of half tiles, more entries than a pass
+# decodes (512), the log-sum-exp beside it.
+@pytest.mark.parametrize("frame_len,list_len", [(31, 33), (64, 32), (65, 47), (96, 48), (97, 40), (64, 515), (33, 1030)])
+def test_one_wavefront_per_query_block(gpu, frame_len, list_len):
+    torch, lf = gpu
+    nb = -(-frame_len // 64)
+    heads, f = 9, 64 // nb
+    F = max(f, -(-list_len // nb))
+    rng = np.random.default_rng(frame_len)
+    mk = lambda t: synth.f32_to_bf16_bits(rng.standard_normal((heads, t * frame_len, 128), dtype=np.float32))
+    x = {"Q": mk(f), "K": mk(F), "V": mk(F)}
+    n_q, n_k = f * nb, F * nb
+    assert 512 < heads * n_q <= 1024
+    lists = np.stack([[rng.permutation(n_k)[:list_len] for _ in range(n_q)] for _ in range(heads)])
+    lists = np.pad(lists, ((0, 0), (0, 0), (0, list_len - lists.shape[2])), constant_values=-1)
+    for r in range(4):                 # few valid ids, at the list's end and beginning
+        lists[0, r, : list_len - r] = -1
+        lists[1, r, r:] = n_k
+    lists[2, 0, ::2] = -1
+    x["Q"][8, 5] = 0x7FC0              # a NaN row stays in its row
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    idx = torch.from_numpy(lists.astype(np.int32)).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, frame_len, 64)
+    got = out.float().cpu().numpy()
+    assert torch.equal(out.view(torch.int16), lf.lf_sparse_attn(Q, K, V, idx, frame_len, 64).view(torch.int16))
+    assert np.isnan(got[8, 5]).all()
+    got[8, 5] = 0.0
+    assert np.isfinite(got).all()
+    Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
+    for h, r in [(0, 0), (0, 1), (0, 2), (0, 3), (1, 0), (1, 1), (1, 2), (1, 3), (2, 0), (8, 0), (8, n_q - 1), (5, n_q // 2)]:
+        kept = [c for c in lists[h, r] if 0 <= c < n_k]
+        lo, hi = O.block_token_range(r, frame_len, 64)
+        if not kept:
+            assert not got[h, lo:hi].any() and np.isinf(lse2[h, lo:hi].cpu().numpy()).all()
+            continue
+        ref = O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, kept, frame_len, 64)
+        if h == 8 and lo <= 5 < hi:
+            ref[5 - lo] = 0.0
+        err = np.abs(got[h, lo:hi] - ref)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
+    again = [lf.lf_sparse_attn(Q, K, V, idx, frame_len, 64).view(torch.int16) for _ in range(5)]
+    assert all(torch.equal(a, again[0]) for a in again)
