@@ -40,6 +40,8 @@ struct WideArgs {
   int total, wg_per_xcd;
   float c;              // softmax_scale * log2(e)
   float* lse2;
+  const float* state_o;   // O and (m, l) to go on from, or null
+  const float2* state_ml;
   int q_len;
 };
 
@@ -184,6 +186,26 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
   // for the largest call, 323 with these products (and 340 with the values taken apart and added in float32).
   f32x4 l_run[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
   const s16x4 one4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  if (a.state_o != nullptr) {
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int row = 32 * hh + ln;
+      if (row >= q_cnt) continue;
+      const int64_t at = (int64_t)h * a.q_len + qtok0 + row;
+      const float2 ml = a.state_ml[at];
+      m_run[hh] = ml.x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) l_run[hh][i] = kg == 0 ? ml.y : 0.0f;   // the two lanes of a row each carry part of the sum
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 v = *reinterpret_cast<const float4*>(a.state_o + at * D + 32 * mb + 8 * g + 4 * kg);
+          oacc[hh][mb][4 * g + 0] = v.x; oacc[hh][mb][4 * g + 1] = v.y;
+          oacc[hh][mb][4 * g + 2] = v.z; oacc[hh][mb][4 * g + 3] = v.w;
+        }
+    }
+  }
 
   auto row_max = [](const f32x16& sc) __attribute__((always_inline)) {
     float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
@@ -437,7 +459,7 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
 
 int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_shape* s, const lf_dims* dm,
                         const int32_t* indices, int32_t list_len, int32_t list_stride, float scale, void* O,
-                        float* lse2, void* stream) {
+                        const float* state_o, const float* state_ml, float* lse2, void* stream) {
   WideArgs a = {};
   a.Q = (const uint16_t*)Q;
   a.K = (const uint16_t*)K;
@@ -463,6 +485,8 @@ int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_sh
   a.wg_per_xcd = (a.total + 7) / 8;
   a.c = scale * 1.4426950408889634f;
   a.lse2 = lse2;
+  a.state_o = state_o;
+  a.state_ml = reinterpret_cast<const float2*>(state_ml);
   a.q_len = dm->f * dm->n;
   return lf_launch(lf_attn_wide_kernel, dim3((unsigned)(a.wg_per_xcd * 8)), dim3(64), 0, (hipStream_t)stream, a) == hipSuccess
              ? LF_OK : LF_ERR_HIP;

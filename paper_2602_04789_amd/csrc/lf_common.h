@@ -71,7 +71,7 @@ int lf_static_scratch(void** ptr);
 // The undivided call at d = 128 with one wavefront per query block.
 int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_shape* s, const lf_dims* dm,
                         const int32_t* indices, int32_t list_len, int32_t list_stride, float scale, void* O,
-                        float* lse2, void* stream);
+                        const float* state_o, const float* state_ml, float* lse2, void* stream);
 int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* s,
                    const lf_dims* dm, const int32_t* indices, int32_t list_len, int32_t list_stride,
                    float scale, void* O, const float* state_o, const float* state_ml, float* lse2,

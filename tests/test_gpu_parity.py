@@ -818,3 +818,25 @@ def test_one_wavefront_per_query_block(gpu, frame_len, list_len):
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
     again = [lf.lf_sparse_attn(Q, K, V, idx, frame_len, 64).view(torch.int16) for _ in range(5)]
     assert all(torch.equal(a, again[0]) for a in again)
+
+
+@pytest.mark.parametrize("frame_len", [200, 256, 161])
+def test_one_wavefront_per_query_block_continues_a_state(gpu, frame_len):
+    """The list-driven phase after the dense one over the current chunk, on 544 to 576 query blocks."""
+    torch, lf = gpu
+    nb = -(-frame_len // 64)
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=8, heads=-(-544 // (2 * nb)), keep_fixed=0.9, k_frames=10)
+    x = synth.make_inputs(w)
+    b = lf.lf_chunk_budget(w.chunk_idx, w.schedule)
+    n_q = w.frames_per_chunk * nb
+    assert b.current_mandatory == 1 and b.k_blocks >= 32 and 512 < w.heads * n_q <= 1024
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    idx = lf.lf_select_mask(Q, K, frame_len, w.block, b)
+    got = lf.lf_sparse_attn_split(Q, K, V, idx, frame_len, w.block, b).float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    lists = idx.cpu().numpy()
+    for h, r in ((0, 0), (0, n_q - 1), (w.heads // 2, nb - 1), (w.heads - 1, n_q - 1)):
+        lo, hi = O.block_token_range(r, frame_len, w.block)
+        ref = O.sparse_attention_block(*(_host_f32(x[k][h]) for k in "QKV"), r, [int(c) for c in lists[h, r]], frame_len, w.block)
+        err = np.abs(got[h, lo:hi] - ref)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
