@@ -18,7 +18,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblf_hsa.so")
 BENCH_LIB = os.path.join(PKG, "liblf_bench.so")
-PROBES = ("tr", "k", "mfma", "exp")
+PROBES = ("none", "tr", "k", "mfma", "exp")
 
 
 def probe_lib(tag: str) -> str:
@@ -74,10 +74,10 @@ def build(verbose: bool = False, extra_device_flags=()) -> str:
         objs.append(obj)
     _run([hipcc, "-shared", "-o", LIB] + objs + ["--offload-arch=gfx950"])
     # probe builds of the library for `bench.py --sensitivity`: the attention kernel with redundant
-    # work per step for one unit each (LF_PROBE_*), everything else the same objects
+    # work per step for one unit each (LF_PROBE_*; none: without), everything else the same objects
     for tag in PROBES:
         pobj = os.path.join(OBJ, f"lf_attn_probe_{tag}_hip.o")
-        _run([hipcc, "-c", os.path.join(CSRC, "lf_attn.hip"), "-o", pobj, f"-DLF_PROBE_{tag.upper()}"] +
+        _run([hipcc, "-c", os.path.join(CSRC, "lf_attn.hip"), "-o", pobj, "-DLF_PROBE", f"-DLF_PROBE_{tag.upper()}"] +
              COMMON + DEVICE + PER_FILE["lf_attn.hip"])
         _run([hipcc, "-shared", "-o", probe_lib(tag)] + [o for o in objs if os.path.basename(o) != "lf_attn_hip.o"] + [pobj] +
              ["--offload-arch=gfx950"])

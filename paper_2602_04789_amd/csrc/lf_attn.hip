@@ -788,9 +788,12 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   // 900, of 32: 68.2 -> 65.5, of 128: 234 -> 223; 1 024, of 16: 42.5 -> 42.9, of 64: 134.0 -> 131.6; 1 800, of 16: 77.5 -> 76.4, of
   // 32: 133 -> 129; 3 000, of 128: 740 -> 709; 6 000, of 128: 1 505 -> 1 447; but 320, of 32: 42 -> 51; 1 152, of 64:
   // 196 -> 214; 1 536, of 64: 206 -> 217; 2 560 (half a last round), of 64: 333 -> 343.
+  // Probe builds lengthen this file's kernel, so they stay with it.
+#ifndef LF_PROBE
   if (dm->d == 128 && list_len >= 32 && a.total_wg > 512 &&
       (a.total_wg <= 1024 || (a.total_wg - 1) % 1024 >= 700))
     return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, list_stride, scale, O, state_o, state_ml, lse2, stream);
+#endif
   // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
   // whole blocks to the end.  Measured late -> early, us: whole frames, 624 query blocks, lists of 61: 104 -> 101; 864, of 89:
   // 172 -> 170; 768, of 18: 40.3 -> 39.7; at most one workgroup a unit: 384, of 23: 31.0 -> 32.7; a last round that
