@@ -477,10 +477,12 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // requests past the end (empty: they write zeros)
   }
 
+  // Role 1 loads the tiles of both, and its requests past the end of the list write zeros: role 0 may put its sums where Q was
+  // only when they have landed.  (Role 1's last meeting in the loop leaves those of the last window in flight.)
+  __syncthreads();
   if constexpr (SPLIT > 1) {
     // the second pair leaves its sums where its tiles were, the first adds them to its own
     float4* const sums = reinterpret_cast<float4*>(role ? stages[1].o[0] : stages[1].q[0]);
-    __syncthreads();
     if (slice == 1) {
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh)
@@ -505,8 +507,8 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
         }
   }
   // Accumulator i of acc[hh][mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of owner row 32 hh + ln.  The rows go through LDS
-  // (16-byte chunks XORed with the row, where this role's tiles were and the other role has read them), so that four rows of
-  // 256 bytes leave with one store.
+  // (16-byte chunks XORed with the row, where this role's tiles were: the barrier above follows the other role's reads of them and
+  // all loads into them), so that four rows of 256 bytes leave with one store.
   char* const rows = reinterpret_cast<char*>(role ? st.o[0] : st.q[0]);
   const float factor = role ? a.scale : 1.0f;
 #pragma unroll

@@ -169,6 +169,59 @@ def test_long_lists_at_d128_match_oracle(gpu, name):
     assert np.isfinite(dV).all() and not dV[:, : w.frame_len].any() and not dK[:, : w.frame_len].any()
 
 
+# The kernel for long lists against the general one, which takes the same call with a head less (13 x 64 KV blocks are 320
+# past a full round of 512, 12 x 64 only 256): the sums are in the same order, so dK and dV are the same bits.  Every KV
+# block is kept by `kept` query blocks: 36 to 42 half tiles of full blocks, odd numbers of them in short frames, and (64, 0):
+# lists of 40 random ids, some out of range, two blocks that no list keeps and a query block without a valid id.
+@pytest.mark.parametrize("frame_len,kept", [(64, 18), (64, 19), (64, 20), (64, 21), (31, 18), (31, 19), (31, 20), (31, 21),
+                                            (33, 19), (64, 0), (50, 0)])
+def test_long_lists_have_the_bits_of_the_general_kernel(gpu, frame_len, kept):
+    torch, lf = gpu
+    heads, n_k, d = 13, 64, 128
+    L = kept or 40
+    rng = np.random.default_rng(100 * frame_len + kept)
+    x = {k: synth.f32_to_bf16_bits(rng.standard_normal((heads, n_k * frame_len, d), dtype=np.float32)) for k in ("Q", "K", "V", "dO")}
+    if kept:
+        lists = np.broadcast_to(np.sort((np.arange(n_k)[:, None] + np.arange(L)) % n_k, axis=1), (heads, n_k, L)).copy()
+    else:
+        ids = np.setdiff1d(np.arange(n_k), (5, n_k - 1))
+        lists = np.stack([[np.sort(rng.choice(ids, L, replace=False)) for _ in range(n_k)] for _ in range(heads)])
+        lists[:, ::3, 0], lists[:, ::2, -1] = -2, n_k + 3
+        lists[1, 2] = n_k
+    assert L * n_k >= 18 * n_k and (heads * n_k - 1) % 512 >= 256 > ((heads - 1) * n_k - 1) % 512
+    print(f"long lists: frames of {frame_len}, {kept} query blocks a KV block", flush=True)
+
+    def strided(bits, pad):
+        view = torch.zeros((heads, bits.shape[1] + 3, d + pad), dtype=torch.bfloat16, device="cuda")[:, 1:-2, :d]
+        view.copy_(_dev(torch, bits))
+        return view
+    Q, K, V, dO = (strided(x[k], 0 if kept else p) for k, p in (("Q", 8), ("K", 16), ("V", 24), ("dO", 40)))
+    idx = torch.from_numpy(lists.astype(np.int32)).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, frame_len, 64, O=torch.empty_strided(dO.shape, dO.stride(), dtype=dO.dtype, device="cuda"))
+
+    def run(H):
+        grads = tuple(torch.empty_strided(t[:H].shape, t.stride(), dtype=t.dtype, device="cuda").fill_(7.0) for t in (Q, K, V))
+        lf.lf_sparse_attn_bwd(Q[:H], K[:H], V[:H], out[:H], dO[:H], lse2[:H], idx[:H], frame_len, 64, grads=grads)
+        return grads
+    got, want = run(heads), run(heads - 1)
+    for name, g, e in zip(("dQ", "dK", "dV"), got, want):
+        if name != "dQ":
+            assert torch.equal(g[:-1].view(torch.int16), e.view(torch.int16)), name
+    for _ in range(10):
+        for g, e in zip(run(heads), got):
+            assert torch.equal(g.view(torch.int16), e.view(torch.int16))
+    if kept:
+        h = heads - 1
+        refs = O.sparse_attention_backward(*(_f32(x[k][h:]) for k in ("Q", "K", "V", "dO")), lists[h:], frame_len, 64)
+        for name, g, ref in zip(("dQ", "dK", "dV"), got, refs):
+            _close(name, g[h:].float().cpu().numpy().astype(np.float64), ref)
+            _close(name + " rows 32 to 63", *(t.reshape(n_k, frame_len, d)[:, 32:] for t in (g[h].float().cpu().numpy(), ref[0]))) \
+                if frame_len > 32 else None
+    else:
+        for g in got[1:]:
+            assert not g[:, 5 * frame_len: 6 * frame_len].any() and not g[:, (n_k - 1) * frame_len:].any()
+
+
 def test_list_edge_cases_and_strided_tensors(gpu):
     """Out-of-range ids skipped; a query block whose list holds no valid id (zero dQ rows, +inf
     log-sum-exp, no contribution to dK and dV); KV blocks that no list keeps (zero dK and dV
