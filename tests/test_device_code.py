@@ -1,0 +1,63 @@
+"""What the compiler makes of kernels whose loops count their own loads, from the assembly of this source (no GPU)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2602_04789_amd import build as B
+
+
+@pytest.fixture(scope="module")
+def kv_wide(tmp_path_factory):
+    """Kernel name -> lines of lf_attn_bwd_wide.hip as built."""
+    try:
+        hipcc = B._hipcc()
+    except RuntimeError:
+        pytest.skip("hipcc not found")
+    out = str(tmp_path_factory.mktemp("asm") / "kv_wide.s")
+    src = "lf_attn_bwd_wide.hip"
+    subprocess.run([hipcc, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out] + B.COMMON + B.DEVICE +
+                   B.PER_FILE.get(src, []), check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    kernels, name = {}, None
+    with open(out) as f:
+        for line in f:
+            if re.match(r"_Z\w+:", line):
+                name = line.split(":")[0]
+                kernels[name] = []
+            elif line.startswith(".Lfunc_end"):
+                name = None
+            elif name:
+                kernels[name].append(line.split(";")[0].strip())
+    assert len(kernels) == 2     # blocks with one and with two pairs of wavefronts
+    return kernels
+
+
+def test_loops_wait_for_counted_loads_only(kv_wide):
+    """The loops of the two roles (two windows of 32 matrix instructions): no register is reloaded in them and nothing but
+    the two counted waits of the loading role waits for memory, so the tile loads of two half tiles stay in flight."""
+    for name, code in kv_wide.items():
+        labels = {m[1]: i for i, l in enumerate(code) for m in [re.match(r"(\.LBB\w+):", l)] if m}
+        loops = []
+        for i, l in enumerate(code):
+            m = re.match(r"s_c?branch\w*\s+(\.LBB\w+)", l)
+            if m and labels[m[1]] < i and sum("v_mfma" in x for x in code[labels[m[1]]: i]) == 64:
+                loops.append(code[labels[m[1]]: i])
+        assert len(loops) == 2, name
+        for body in loops:
+            loads = sum("buffer_load" in x for x in body)
+            waits = [re.search(r"vmcnt\((\d+)\)", x)[1] for x in body if "vmcnt" in x]
+            print(name, "loads", loads, "waits", waits)
+            assert loads in (0, 36) and waits == (["18", "18"] if loads else [])
+            assert not any("scratch_" in x or "global_" in x for x in body)
+
+
+def test_output_rows_are_staged_behind_a_barrier(kv_wide):
+    """Output rows go through LDS where loaded tiles were (the only 8-byte LDS stores): behind the last products stand a wait
+    for all loads, then a barrier, then the first of them."""
+    for name, code in kv_wide.items():
+        store = next(i for i, l in enumerate(code) if l.startswith("ds_write_b64"))
+        product = max(i for i, l in enumerate(code[:store]) if "v_mfma" in l)
+        wait = next((i for i in range(product, store) if "vmcnt(0)" in code[i]), store)
+        print(name, "product", product, "wait", wait, "store", store)
+        assert any("s_barrier" in l for l in code[wait:store])
