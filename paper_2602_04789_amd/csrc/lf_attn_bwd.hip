@@ -434,17 +434,21 @@ constexpr int kKvSplitBlocks = 256;
 // last round, of 512) leaves two of its SIMDs idle.  So the lists have to be long enough -- a KV block's list holds
 // list_len n_q / n_k query blocks on the mean -- and the last round more than half full, or one of many.  Backward call in us, this
 // file's kernel and that one, lists of one length:
-//   900 blocks:    mean 10: 101 and 103,  16: 139 and 138,  24: 189 and 184,  45: 322 and 304
-//   1 800 blocks:  mean 10: 175 and 183,  16: 248 and 250,  24: 350 and 342,  45: 622 and 589
-//   6 300 blocks:  mean 10: 562 and 583,  16: 826 and 823,  24: 1 171 and 1 143,  45: 2 078 and 1 994
-//   1 152 blocks (last round 128):  mean 16: 170 and 176,  24: 240 and 244,  48: 455 and 453
-//   256 blocks (two pairs of wavefronts each):  mean 16: 63 and 65,  24: 82 and 82,  48: 133 and 129
-//   320 blocks:  mean 16: 83 and 87,  48: 190 and 192;  512 blocks:  mean 16: 91 and 93,  32: 148 and 148
-// Lists of very different lengths (a training chunk with history: some blocks kept by every query block) gain more: 6 300
-// blocks of mean 19: 1 241 and 1 192.
+//     900 blocks:  mean 10: 102 and 101,  16: 140 and 136,  28: 214 and 202,  45: 324 and 304
+//   1 800 blocks:  mean 10: 175 and 178,  16: 249 and 244,  28: 402 and 386,  45: 631 and 588
+//   6 300 blocks:  mean 10: 559 and 561,  16: 821 and 801,  28: 1 339 and 1 279,  45: 2 085 and 1 981
+//   1 088 blocks (last round 64):  mean 16: 170 and 173,  24: 241 and 240,  32: 316 and 316
+//   256 blocks (two pairs of wavefronts each):  mean 16: 54 and 56;  320 blocks:  mean 10: 50 and 53
+// Lists as the mask selection makes them differ in length, and with few rounds the longest of them decide: how much faster the call
+// is with that kernel, least and mean of 5 to 30 calls:
+//   769 to 1 024 blocks:    mean 18 to 20: 0.97, 1.01;  20 to 22: 0.96, 1.00;  25 to 28: 0.99, 1.03;  28 to 32: 1.00, 1.04;  45: 1.01, 1.05
+//   1 281 to 1 536 blocks:  mean 18 to 20: 0.99, 1.03;  20 to 22: 0.98, 1.04;  22 to 25: 1.01, 1.04;  28 to 32: 1.01, 1.04
+//   1 537 blocks and more:  mean 16 to 18: 1.00, 1.03;  18 to 20: 1.00, 1.03;  28 to 32: 1.01, 1.05
+//   257 to 512 blocks:      mean 28 to 32: 0.97, 1.00;  36 to 42: 0.98, 1.01;  up to 256:  mean 25 to 28: 0.98, 1.01;  32 to 36: 1.01, 1.04
 static bool kv_wide(int blocks, int64_t entries, int n_k) {
   if (blocks <= kKvSplitBlocks) return entries >= (int64_t)32 * n_k;
-  return (blocks > 1536 || (blocks > 512 && (blocks - 1) % 512 >= 256)) && entries >= (int64_t)18 * n_k;
+  if (blocks <= 1536) return blocks > 512 && (blocks - 1) % 512 >= 256 && entries >= (int64_t)(blocks <= 1024 ? 28 : 22) * n_k;
+  return entries >= (int64_t)18 * n_k;
 }
 // SPLIT = 2: a workgroup holds two such groups of four wavefronts, each with a stage of its own and half of
 // the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.

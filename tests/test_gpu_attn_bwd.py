@@ -171,10 +171,10 @@ def test_long_lists_at_d128_match_oracle(gpu, name):
 
 # The kernel for long lists against the general one, which takes the same call with a head less (13 x 64 KV blocks are 320
 # past a full round of 512, 12 x 64 only 256): the sums are in the same order, so dK and dV are the same bits.  Every KV
-# block is kept by `kept` query blocks: 36 to 42 half tiles of full blocks, odd numbers of them in short frames, and (64, 0):
+# block is kept by `kept` query blocks: 56 to 62 half tiles of full blocks, odd numbers of them in short frames, and (64, 0):
 # lists of 40 random ids, some out of range, two blocks that no list keeps and a query block without a valid id.
-@pytest.mark.parametrize("frame_len,kept", [(64, 18), (64, 19), (64, 20), (64, 21), (31, 18), (31, 19), (31, 20), (31, 21),
-                                            (33, 19), (64, 0), (50, 0)])
+@pytest.mark.parametrize("frame_len,kept", [(64, 28), (64, 29), (64, 30), (64, 31), (31, 28), (31, 29), (31, 30), (31, 31),
+                                            (33, 29), (64, 0), (50, 0)])
 def test_long_lists_have_the_bits_of_the_general_kernel(gpu, frame_len, kept):
     torch, lf = gpu
     heads, n_k, d = 13, 64, 128
@@ -188,7 +188,7 @@ def test_long_lists_have_the_bits_of_the_general_kernel(gpu, frame_len, kept):
         lists = np.stack([[np.sort(rng.choice(ids, L, replace=False)) for _ in range(n_k)] for _ in range(heads)])
         lists[:, ::3, 0], lists[:, ::2, -1] = -2, n_k + 3
         lists[1, 2] = n_k
-    assert L * n_k >= 18 * n_k and (heads * n_k - 1) % 512 >= 256 > ((heads - 1) * n_k - 1) % 512
+    assert L >= 28 and (heads * n_k - 1) % 512 >= 256 > ((heads - 1) * n_k - 1) % 512
     print(f"long lists: frames of {frame_len}, {kept} query blocks a KV block", flush=True)
 
     def strided(bits, pad):
