@@ -795,9 +795,11 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
     return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, list_stride, scale, O, state_o, state_ml, lse2, stream);
 #endif
   // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
-  // whole blocks to the end.  Measured late -> early, us: whole frames, 624 query blocks, lists of 61: 104 -> 101; 864, of 89:
-  // 172 -> 170; 768, of 18: 40.3 -> 39.7; at most one workgroup a unit: 384, of 23: 31.0 -> 32.7; a last round that
-  // is partly filled: 1 368, of 166: 502 -> 518; ragged frames: 640, of 82: 144.1 -> 145.0, 624, of 29: 54.5 -> 55.2.
+  // whole blocks to the end (lists of 32 and more have gone to the other kernel by here).  Measured late -> early, us, lists as
+  // selected: whole frames, 594 query blocks, lists of 31: 56.0 -> 54.5; 576, of 22: 42.0 -> 40.9; 816, of 13: 32.6 -> 32.3; 936,
+  // of 11: 30.5 both; 1 014, of 14: 38.0 -> 38.2 (2 458 calls: 1.015 times as fast on the mean, 0.994 at the least); but at most one
+  // workgroup a unit: 384, of 23: 31.0 -> 32.7; a last round that is partly filled: 1 368, of 166: 502 -> 518; ragged
+  // frames: 624, of 29: 54.5 -> 55.2.
   const bool early_v = dm->d == 128 && dm->n % 64 == 0 && a.total_wg > 512 && a.total_wg <= 1024;
   constexpr int kListWaves = 4;                  // two query blocks per workgroup
   const int n_wg = (a.total_wg + kListWaves / 2 - 1) / (kListWaves / 2);
