@@ -701,11 +701,12 @@ def _mixed_lists(w, heads, L, rng):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-@pytest.mark.parametrize("heads,lengths", [(130, (255, 256, 257, 513)), (2, (511, 512, 513, 1024, 1025))])
+@pytest.mark.parametrize("heads,lengths", [(130, (255, 256, 257, 513)), (260, (255, 256, 257, 513)), (2, (511, 512, 513, 1024, 1025))])
 def test_list_lengths_around_the_decode_passes(gpu, heads, lengths, head_dim):
-    """Lists are decoded 256 entries per pass where every pair of wavefronts has a query block of its own (130
-    heads, 520 query blocks) and 128 entries of each quarter where they are divided (2 heads, 8 query blocks): lengths
-    around one and two passes of either form, on lists whose numbers of half tiles differ between
+    """Lists are decoded 256 entries per pass where every pair of wavefronts has a query block of its own (260
+    heads, 1 040 query blocks; at d = 64 also 130 heads, 520), 512 where every wavefront has one (130 heads at
+    d = 128) and 128 entries of each quarter where they are divided (2 heads, 8 query blocks): lengths
+    around one and two passes, on lists whose numbers of half tiles differ between
     the query blocks of a workgroup, from tensors carved out of larger ones, also into guarded memory."""
     torch, lf = gpu
     w = synth.small_ragged(frame_len=72, chunk_idx=4, heads=heads, head_dim=head_dim)
@@ -747,12 +748,14 @@ def test_list_lengths_around_the_decode_passes(gpu, heads, lengths, head_dim):
 
 
 @pytest.mark.parametrize("scale", [0.25, 1.0, 4.0])
-@pytest.mark.parametrize("frame_len,head_dim", [(200, 128), (256, 128), (200, 64)])
-def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, scale):
-    """test_attention_with_extreme_logits on 528 query blocks, where each list is walked by one pair of
-    wavefronts (V requested early for the whole frames of 256): the reference moves inside the list."""
+@pytest.mark.parametrize("frame_len,head_dim,heads,chunk", [(200, 128, 66, 4), (256, 128, 66, 4), (200, 64, 66, 4),
+                                                            (200, 128, 132, 4), (256, 128, 66, 3)])
+def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, heads, chunk, scale):
+    """test_attention_with_extreme_logits on many query blocks, where each list is walked by one pair of wavefronts
+    (d = 64; 1 056 query blocks; 528 with lists of 24) or by one wavefront (528 with lists of 32): the reference
+    moves inside the list."""
     torch, lf = gpu
-    w = synth.small_ragged(frame_len=frame_len, chunk_idx=4, heads=66, head_dim=head_dim)
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=chunk, heads=heads, head_dim=head_dim)
     x = synth.make_inputs(w)
     n = w.frame_len
     Kf = _host_f32(x["K"]).copy()
@@ -767,7 +770,7 @@ def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, scale):
     got = out.float().cpu().numpy().astype(np.float64)
     assert np.isfinite(got).all()
     Qf, Kf, Vf = _host_f32(x["Q"]), _host_f32(K), _host_f32(x["V"])
-    for h in (0, 33, 65):
+    for h in (0, heads // 2, heads - 1):
         for r in range(lists.shape[1]):
             lo, hi = O.block_token_range(r, n, w.block)
             ref = O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, list(lists[h, r]), n, w.block, scale=scale)
@@ -775,20 +778,21 @@ def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, scale):
             assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
 
 
-# One wavefront per query block (d = 128, 513 to 1 024 query blocks, lists of 32 and more) at its edges: blocks of 1, 31, 32, 33
-# and 64 tokens, lists with 0, 1, 2, 3 valid ids and with odd and even numbers of half tiles, more entries than a pass
-# decodes (512), the log-sum-exp beside it.
-@pytest.mark.parametrize("frame_len,list_len", [(31, 33), (64, 32), (65, 47), (96, 48), (97, 40), (64, 515), (33, 1030)])
-def test_one_wavefront_per_query_block(gpu, frame_len, list_len):
+# One wavefront per query block (d = 128, lists of 32 and more, 513 to 1 024 query blocks or 1 792: a second round of 768) at its
+# edges: blocks of 1, 31, 32, 33 and 64 tokens, lists with 0, 1, 2, 3 valid ids and with odd and even numbers of half
+# tiles, more entries than a pass decodes (512), the log-sum-exp beside it.
+@pytest.mark.parametrize("frame_len,list_len,heads", [(31, 33, 9), (64, 32, 9), (65, 47, 9), (96, 48, 9), (97, 40, 9), (64, 515, 9),
+                                                      (33, 1030, 9), (31, 33, 28), (65, 47, 28)])
+def test_one_wavefront_per_query_block(gpu, frame_len, list_len, heads):
     torch, lf = gpu
     nb = -(-frame_len // 64)
-    heads, f = 9, 64 // nb
+    f = 64 // nb
     F = max(f, -(-list_len // nb))
     rng = np.random.default_rng(frame_len)
     mk = lambda t: synth.f32_to_bf16_bits(rng.standard_normal((heads, t * frame_len, 128), dtype=np.float32))
     x = {"Q": mk(f), "K": mk(F), "V": mk(F)}
     n_q, n_k = f * nb, F * nb
-    assert 512 < heads * n_q <= 1024
+    assert heads * n_q in (576, 1792)
     lists = np.stack([[rng.permutation(n_k)[:list_len] for _ in range(n_q)] for _ in range(heads)])
     lists = np.pad(lists, ((0, 0), (0, 0), (0, list_len - lists.shape[2])), constant_values=-1)
     for r in range(4):                 # few valid ids, at the list's end and beginning
@@ -805,7 +809,7 @@ def test_one_wavefront_per_query_block(gpu, frame_len, list_len):
     got[8, 5] = 0.0
     assert np.isfinite(got).all()
     Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
-    for h, r in [(0, 0), (0, 1), (0, 2), (0, 3), (1, 0), (1, 1), (1, 2), (1, 3), (2, 0), (8, 0), (8, n_q - 1), (5, n_q // 2)]:
+    for h, r in [(0, 0), (0, 1), (0, 2), (0, 3), (1, 0), (1, 1), (1, 2), (1, 3), (2, 0), (8, 0), (8, n_q - 1), (5, n_q // 2), (heads - 1, 1)]:
         kept = [c for c in lists[h, r] if 0 <= c < n_k]
         lo, hi = O.block_token_range(r, frame_len, 64)
         if not kept:
