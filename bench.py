@@ -223,8 +223,8 @@ def run_select_phases(torch, lf, synth, workload):
 
 
 def run_fill_scan(torch, lf, synth, workload):
-    """The attention kernel on the same shapes with 3 .. 28 heads, i.e. from fewer workgroups than
-    compute units to four per unit: how its time grows with the fill of the chip."""
+    """The attention call on the same shapes with 3 .. 28 heads, i.e. from fewer query blocks than
+    compute units to eight per unit: how its time grows with the fill of the chip."""
     from dataclasses import replace
     base = _workloads()[workload]()
     rows = []
@@ -247,13 +247,12 @@ def run_fill_scan(torch, lf, synth, workload):
             e1.record()
             torch.cuda.synchronize()
             ts.append(e0.elapsed_time(e1) / 20)
-        n_wg = (heads * w.frames_per_chunk * w.blocks_per_frame + 1) // 2
-        rows.append({"heads": heads, "workgroups": n_wg, "ms": min(ts), "us_per_head": min(ts) * 1e3 / heads,
+        rows.append({"heads": heads, "query_blocks": heads * w.frames_per_chunk * w.blocks_per_frame, "ms": min(ts), "us_per_head": min(ts) * 1e3 / heads,
                      "tflops": flops / (min(ts) * 1e-3) / 1e12})
         del Q, K, V, out, idx
     print(json.dumps({"fill_scan": rows, "workload": base.name,
-                      "what": "lf_sparse_attn alone, 20 launches back to back, minimum of 3 rounds; two query "
-                              "blocks per workgroup, two workgroups per compute unit at a time"}))
+                      "what": "lf_sparse_attn alone, 20 launches back to back, minimum of 3 rounds; a compute unit holds "
+                              "four query blocks at a time, one where lists are divided"}))
 
 
 def run_sensitivity(torch, lf, synth, workload):
@@ -268,7 +267,7 @@ def run_sensitivity(torch, lf, synth, workload):
     idx = lf.lf_select_mask(Q, K, w.frame_len, w.block, b)
     flops = kept_flops(idx.cpu().numpy(), w)
     # per step a wavefront does 16 transposing V reads, 8 K fragment reads, 16 MFMAs, 16 exp2
-    cases = [("product", "none", "nothing extra"),
+    cases = [("plain", "none", "nothing extra"),
              ("v_reads_x2", "tr", "+16 ds_read_b64_tr_b16 per step (+100 %)"),
              ("k_reads_x2", "k", "+8 ds_read_b128 per step (+100 %)"),
              ("mfma_x1.5", "mfma", "+8 v_mfma_f32_32x32x16_bf16 per step (+50 %)"),
@@ -297,7 +296,7 @@ def run_sensitivity(torch, lf, synth, workload):
             e1.record()
             torch.cuda.synchronize()
             res[i]["ms"].append(e0.elapsed_time(e1) / 20)
-            res[i]["output_equals_product"] = bool(torch.equal(out.view(torch.int16), ref.view(torch.int16)))
+            res[i]["output_equals_plain"] = bool(torch.equal(out.view(torch.int16), ref.view(torch.int16)))
     lf._lib = product
     base = min(res[0]["ms"])
     for r in res:
@@ -628,8 +627,8 @@ def main():
         "select_ms_median_min": [float(np.median(sel_all)), float(sel_all.min())],
         "attn_ms_median_min": [float(np.median(attn_all)), float(attn_all.min())],
         "kept_gflop": flops / 1e9, "tile_gflop": tile_flops / 1e9,
-        "roofline": {"kernel": "lf_attn_kernel (list-driven)" if not use_split else
-                               "lf_sparse_attn_split: dense + list-driven lf_attn_kernel launches together",
+        "roofline": {"kernel": "list-driven attention (lf_attn_wide_kernel where the call fills the chip, else lf_attn_kernel)"
+                               if not use_split else "lf_sparse_attn_split: dense and list-driven launch together",
                      "bound": "mfma", "achieved": attn_tflops,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": attn_tflops / PEAK_BF16_TFLOPS,
                      "traffic": traffic.get("attn") if args.workload == "last_chunk" and not use_split else None},
