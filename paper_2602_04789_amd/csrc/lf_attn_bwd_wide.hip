@@ -18,8 +18,9 @@ namespace {
 // other half, where vector instructions reach them (left to itself it copies the accumulators around the loop or spills).
 // The compiler does not see the latency of those instructions: `settle` waits for the last ones before their results are
 // read, and vector results used by them are at least two instructions old (slot order; s_nop before the last products).
-// Largest backward call of a 12 x 128 model (4 680 queries, 32 760 keys): this kernel 800 us before, 715 us now
-// (1.52 to 1.43 million cycles; per window of 32 slots about 1 600 cycles); calls of 0.32 and 1.23 ms take 0.31 and 1.18 ms.
+// Largest dK/dV launch of a 12 x 128 model (4 680 queries, 32 760 keys): 1.52 million cycles with that kernel, 1.40 with this one, and
+// the whole backward call 1 215 us before, 1 150 now; with 4 680 keys 316 and 296.  Matrix cores busy for 0.48 of the cycles, a
+// fifth of the wave cycles in waits, about 36 registers a wavefront spilled around the loop (none is touched in it).
 constexpr int kWideEnt = 512;      // half tiles decoded per pass
 // Up to this many (head, KV block) pairs a block takes two pairs of wavefronts, each with half of the list: a compute unit holds
 // two workgroups of one pair, so fewer blocks leave SIMDs idle.  Backward call in us, one pair and two: 256 blocks with

@@ -9,7 +9,7 @@
 // in the other half, where vector instructions reach them (left to itself the compiler copies O around the loop).
 // The compiler does not see those instructions' latency: `settle` waits before O is read or changed.
 // A load goes to the place that the reads before it leave, so each is preceded by a wait that counts the LDS reads issued since.
-// 12 x 128, 4 680 queries, lists of 131 blocks: 333 us before, 323 now; 40 heads: 1 209 and 1 177.
+// 12 x 128, 4 680 queries, lists of 188 blocks: 333 us before, 323 now; 40 heads: 1 209 and 1 177.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
