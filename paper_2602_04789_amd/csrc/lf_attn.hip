@@ -7,7 +7,7 @@
 // workgroups share a compute unit, so every SIMD holds two wavefronts, free to be in different
 // parts of their step (the matrix core of one beside the vector ALU of the other).  In a call with
 // few query blocks a workgroup holds one, its list is divided among four such pairs, and their
-// states are merged through LDS.  Each listed
+// states are merged through LDS; with fewer still, each row half of a query block has a workgroup of its own.  Each listed
 // KV block is taken as half tiles of 32 KV rows (two, or one when the block has at most 32
 // tokens): the 32 x d K and V half tiles are brought into a double-buffered LDS
 // stage by asynchronous global->LDS loads, a wavefront's share of a half tile in one group
@@ -118,9 +118,14 @@ __device__ __forceinline__ void lds_barrier() {
 // order of float32 sums differs.  A call with few query blocks leaves compute units idle while
 // every wavefront goes through its list step by step (one wavefront per SIMD: 0.55 - 0.8 us a step,
 // mostly latency); dividing the list shortens that chain.
-template <int D, int WAVES, bool DENSE, int SPLIT = 1, bool EARLY_V = false>
+// HALF (with SPLIT = WAVES): the workgroup has one row half of a query block (32 rows), and each wavefront a slice of
+// the list and a tile stage of its own, so no barrier stands in the loop.  A call that leaves compute units idle gets through with
+// twice as many of them: what bounds a workgroup there is the issue and the LDS reads of its own eight wavefronts (lists whose tiles
+// all lie in the L2 take as long).  24 blocks, d = 128: a step of four half tiles 0.78 -> 0.50 us, lists of 16 14.3 -> 10.4 us
+// in all, of 64 33.9 -> 23.4; d = 64 (eight slices instead of four) lists of 16 10.1 -> 8.1, of 64 23.8 -> 14.3.
+template <int D, int WAVES, bool DENSE, int SPLIT = 1, bool EARLY_V = false, bool HALF = false>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs a) {
-  constexpr int QPW = DENSE ? 1 : WAVES / 2;    // tile stages per workgroup
+  constexpr int QPW = DENSE ? 1 : HALF ? WAVES : WAVES / 2;   // tile stages per workgroup
   constexpr int QB = QPW / SPLIT;               // query blocks per workgroup
   // Half tiles decoded per pass (power of two).  Where the lists are divided, half of them: a thread then
   // decodes one list entry, which is as many as a quarter of a list nearly always has (512: 0.1 - 0.4 us longer,
@@ -136,6 +141,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   constexpr int TILE = 32 * CH;             // uint4 per half tile (32 KV rows)
   static_assert(LPW >= 1 && LPW * RPI * WPQ == 32, "a half tile must split evenly over the wavefronts");
   static_assert(SPLIT == 1 || (!DENSE && SPLIT == QPW && MB * 4 % SPLIT == 0), "a split block has the workgroup to itself");
+  static_assert(!HALF || SPLIT == WAVES, "a wavefront for each slice of a row half");
 
   __shared__ uint4 buf0_all[QPW][2 * TILE];          // K | V of even tiles
   __shared__ uint4 buf1_all[QPW][2 * TILE];          // K | V of odd tiles
@@ -153,7 +159,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   const bool w_valid = w < a.total_wg;
   w = min(w, a.total_wg - 1);
   const int per_head = DENSE ? a.wg_per_head : a.n_q;
-  const int h = w / per_head, r = w % per_head;
+  const int h = (HALF ? w >> 1 : w) / per_head, r = (HALF ? w >> 1 : w) % per_head;
   uint4* const buf0 = buf0_all[qb];
   uint4* const buf1 = buf1_all[qb];
   int2* const ent = ent_all[qb];
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
 
   const int tid = threadIdx.x % kThreads, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront inside its query block, in a scalar register
-  const int rh = wave;
+  const int rh = HALF ? w & 1 : wave;
   const int ln = lane & 31, kg = lane >> 5;
 
   // first query token and number of query rows of this workgroup: a query block of <= 64
@@ -169,6 +175,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   const int qtok0 = DENSE ? r * a.rows_per_wg : (r / a.nb) * a.n + (r % a.nb) * 64;
   const int q_cnt = DENSE ? min(a.rows_per_wg, a.q_len - qtok0) : min(64, a.n - (r % a.nb) * 64);
   const int qrow = 32 * rh + ln;
+  if (HALF && 32 * rh >= q_cnt) return;   // the other half of a short query block
 
   // The list entries of the first pass are requested first, so that they travel together with
   // the Q fragments instead of after them.
@@ -218,8 +225,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     // load i carries the immediate offset 1024 i, which moves its LDS target to the i-th stripe
     // and is taken off the memory offset here (row >= RPI i and a row is at least 1024 / RPI
     // bytes, so the difference is not negative)
-    koff[i] = (uint32_t)row * (uint32_t)k_row_bytes + (uint32_t)k_swz<CH>(row, ld_p) * 16u - 1024u * i;
-    voff[i] = (uint32_t)row * (uint32_t)v_row_bytes + (uint32_t)v_swz<CH>(row, ld_p) * 16u - 1024u * i;
+    koff[i] = (uint32_t)row * (uint32_t)k_row_bytes + (uint32_t)k_swz<CH>(row, ld_p) * 16u - 1024u * (i & 3);
+    voff[i] = (uint32_t)row * (uint32_t)v_row_bytes + (uint32_t)v_swz<CH>(row, ld_p) * 16u - 1024u * (i & 3);
   }
   // (first token, token count) of half tile i of the pass, wavefront-uniform; past the pass's
   // last half tile an empty one (count 0: its loads touch no memory and its scores are masked).
@@ -247,13 +254,17 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   auto fetch_all = [&](int32x4 rs, uint4* dst, const uint32_t (&off)[LPW]) __attribute__((always_inline)) {
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)LDS_PTR(void, dst + RPI * LPW * wave * CH));
-    if constexpr (LPW == 4)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                   "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
-                   "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
-                   "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
-                   "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
-                   :: "s"(lds0), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(rs) : "memory", "m0");
+    if constexpr (LPW >= 4) {
+#pragma unroll
+      for (int i = 0; i < LPW; i += 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+                     "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
+                     :: "s"(lds0 + 1024u * i), "v"(off[i]), "v"(off[i + 1]), "v"(off[i + 2]), "v"(off[i + 3]), "s"(rs)
+                     : "memory", "m0");
+    }
     else if constexpr (LPW == 2)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                    "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
@@ -342,6 +353,16 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   // block's end (such a row has no state, and when one row moves all of the wavefront do).
   bool need_ref = SPLIT > 1 && (a.state_o == nullptr || q_cnt % 32 != 0);
 
+  // Between the wavefronts that share a tile stage; one that has it alone waits for its own LDS reads only.
+  auto tile_barrier = []() __attribute__((always_inline)) {
+    if constexpr (HALF) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    } else {
+      lds_barrier();
+    }
+  };
   // Row maxima (both lanes of a row) of a half tile's scores.
   auto row_max = [](const f32x16& sc) __attribute__((always_inline)) {
     float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
@@ -419,6 +440,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       }
       __syncthreads();
       if (nsteps == 0) continue;   // no valid id in this pass, for any query block of the workgroup
+      if constexpr (HALF) nsteps = nh_q;
     }
     // Software pipeline, one step deep (a step, "tile" below, is one half tile of 32 KV rows):
     // iteration t computes S^T of tile t+1 (matrix core)
@@ -453,7 +475,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     };
 
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    lds_barrier();
+    tile_barrier();
     f32x16 zero16;
 #pragma unroll
     for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
@@ -490,7 +512,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     auto tile = [&](int t, uint4* cur, uint4* other) __attribute__((always_inline)) {
       const int cnt = e0.y;
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // this wavefront's share of K_{t+1}, V_t has landed
-      lds_barrier();                             // ... everyone's has; K_t and V_{t-1} are no longer read
+      tile_barrier();                            // ... everyone's has; K_t and V_{t-1} are no longer read
       // half tile t+3 is looked up now and made wavefront-uniform at the end of the step
       const int2 e_raw = DENSE ? make_int2(0, 0) : ent[(t + 3) & (kMaxEnt - 1)];
       const int32x4 krs = k_rsrc(e2), vrs = v_rsrc(e1);
@@ -630,6 +652,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     if (active) {
       for (int t = 0; t < nsteps; t += 2) {
         tile(t, buf0, buf1);
+        if (HALF && t + 1 == nsteps) break;
         tile(t + 1, buf1, buf0);
       }
     } else {
@@ -670,7 +693,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     constexpr int NGRP = MB * 4, PER = NGRP / SPLIT;   // float4 groups of a row, and per wavefront
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));          // the last requests (empty tiles) write zeros
     __syncthreads();
-    float4* const mine = reinterpret_cast<float4*>(rh == 0 ? buf0 : buf1);
+    const int part = HALF ? 0 : rh;                    // row half within the workgroup
+    float4* const mine = reinterpret_cast<float4*>(part == 0 ? buf0 : buf1);
     static_assert(NGRP * 64 == 2 * TILE, "a row half of O fills one tile buffer");
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -678,13 +702,13 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       for (int g = 0; g < 4; ++g)
         mine[(mb * 4 + g) * 64 + lane] =
             make_float4(oacc[mb][4 * g + 0], oacc[mb][4 * g + 1], oacc[mb][4 * g + 2], oacc[mb][4 * g + 3]);
-    if (kg == 0) ent[32 * rh + ln] = make_int2(__float_as_int(m_run), __float_as_int(l_run));
+    if (kg == 0) ent[32 * part + ln] = make_int2(__float_as_int(m_run), __float_as_int(l_run));
     __syncthreads();
     float m = -1.0e30f, l = 0.0f, f[SPLIT];
     int2 ml[SPLIT];
 #pragma unroll
     for (int q2 = 0; q2 < SPLIT; ++q2) {
-      ml[q2] = ent_all[q2][32 * rh + ln];
+      ml[q2] = ent_all[q2][32 * part + ln];
       m = fmaxf(m, __int_as_float(ml[q2].x));
     }
 #pragma unroll
@@ -703,7 +727,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int q2 = 0; q2 < SPLIT; ++q2) {
-        const float4 v = reinterpret_cast<const float4*>(rh == 0 ? buf0_all[q2] : buf1_all[q2])[grp * 64 + lane];
+        const float4 v = reinterpret_cast<const float4*>(part == 0 ? buf0_all[q2] : buf1_all[q2])[grp * 64 + lane];
         o[0] = fmaf(v.x, f[q2], o[0]); o[1] = fmaf(v.y, f[q2], o[1]);
         o[2] = fmaf(v.z, f[q2], o[2]); o[3] = fmaf(v.w, f[q2], o[3]);
       }
@@ -774,6 +798,15 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.state_ml = reinterpret_cast<float2*>(const_cast<float*>(state_ml));
   a.total_wg = dm->H * dm->n_q;
   hipStream_t st = (hipStream_t)stream;
+  if (lf_halve_blocks(dm->d, a.total_wg, list_len)) {
+    a.total_wg *= 2;
+    a.wg_per_xcd = (a.total_wg + 7) / 8;
+    const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
+    const hipError_t rc = dm->d == 128
+        ? lf_launch(lf_attn_kernel<128, 4, false, 4, false, true>, dim3(grid), dim3(256), 0, st, a)
+        : lf_launch(lf_attn_kernel<64, 8, false, 8, false, true>, dim3(grid), dim3(512), 0, st, a);
+    return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
+  }
   if (lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k)) {
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);

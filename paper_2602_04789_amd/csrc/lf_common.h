@@ -34,7 +34,7 @@ int lf_derive(const lf_shape* s, const lf_budget* b, lf_dims* out);
 // to itself, so with more than 256 of them the second round starts when the first ends, and the
 // undivided form keeps more loads of one list's tiles in flight per compute unit.
 // Forward, d = 128, us undivided -> divided (random lists):
-//   <= 256 blocks: 192 blocks, lists of 6: 13.6 -> 12.4; of 195: 222 -> 109; lists of 4 are one step a slice;
+//   <= 256 blocks (up to 128 lf_halve_blocks comes first): 192 blocks, lists of 6: 13.6 -> 12.4; of 195: 222 -> 109; lists of 4 are one step a slice;
 //   <= 512, lists that hold at least half of the KV blocks: 286 blocks, 151 of 234: 164 -> 149; 490, 110 of 126:
 //     122 -> 119; 432, 92 of 120: 106 -> 102; 360, 108 of 192: 124 -> 117; but 348, 34 of 60: 44 -> 49;
 //   <= 512, sparser lists: 432 blocks, 91 of 672: 114 -> 139; 300, 57 of 300: 70 -> 84; 288, 187 of 1224:
@@ -47,6 +47,11 @@ inline bool lf_split_lists(int d, int blocks, int list_len, int n_k) {
   if (blocks > 512) return false;
   return d == 64 ? list_len >= 32 : list_len >= 96 && 2 * (int64_t)list_len >= n_k;
 }
+// Whether the two row halves of each (head, query block) get a workgroup each, and with it a compute unit: as
+// long as there are no more of them than compute units.  us, one workgroup a block -> two, in a row of calls: 128 blocks, d = 128,
+// lists of 2: 8.6 -> 7.6, of 6: 12.3 -> 9.3, of 32: 20.8 -> 16.8; d = 64, of 2: 6.6 -> 6.8, of 3: 7.4 -> 6.9, of 32: 15.0 -> 11.8; but
+// 135 blocks (two rounds), d = 128, of 16: 16.1 -> 21.9; d = 64: 10.3 -> 15.8.
+inline bool lf_halve_blocks(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 2 : 3); }
 // dQ (backward call, the rest the same), d = 128: 132 blocks, lists of 6: 33.5 -> 34.6, of 8: 38.7 -> 34.4 (80 blocks);
 // 384 blocks, of 4: 119 -> 128; 350, of 14: 114 -> 120; 512, of 41: 254 -> 257; 324, of 53: 191 -> 171; 400, of 69: 277 -> 256;
 // 576, of 18: 106 -> 123.  d = 64: 125 blocks, lists of 6: 29.7 -> 30.6; 78, of 7: 25.9 -> 24.9; 120, of 138: 213 -> 160; 390,

@@ -1,0 +1,85 @@
+"""Calls with few query or KV blocks, whose row halves get workgroups of their own, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import hsa_oracle as O
+from paper_2602_04789_amd import synth
+from test_gpu_parity import MAX_ABS, MEAN_ABS, _dev, _host_f32, gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(rng, heads, n_q, n_k, length):
+    """Ascending lists with ids out of range at both ends, some with few valid ids or none."""
+    lists = np.full((heads, n_q, length), n_k + 1, dtype=np.int64)
+    for h in range(heads):
+        for r in range(n_q):
+            ids = np.sort(rng.permutation(n_k)[:length])
+            lists[h, r, :len(ids)] = ids
+    lists[0, 0, 1:] = n_k                     # one valid id: all slices but one are empty
+    lists[0, n_q - 1, :-1] = -1               # the last entry only
+    lists[0, n_q - 1, -1] = n_k - 1
+    lists[heads - 1, 0] = -1                  # none: zero rows
+    return lists.astype(np.int32)
+
+
+# 128 query blocks and, just past the rule, 132; last blocks of 1, 32, 33 and 64 rows; lists around each rule's edges, of
+# fewer entries than slices, and (1 030) of more half tiles a slice than a pass of the decode holds
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,frame_len,frames,length", [(2, 64, 4, 1), (2, 96, 4, 2), (2, 97, 4, 3), (32, 65, 5, 9), (33, 96, 5, 9),
+                                                           (3, 31, 9, 8), (2, 97, 60, 65), (1, 64, 1030, 1030)])
+def test_forward_of_few_query_blocks(gpu, heads, frame_len, frames, length, head_dim):  # noqa: F811
+    torch, lf = gpu
+    nb, f = -(-frame_len // 64), 2
+    rng = np.random.default_rng(frame_len + length)
+    mk = lambda t: synth.f32_to_bf16_bits(rng.standard_normal((heads, t * frame_len, head_dim), dtype=np.float32))
+    x = {"Q": mk(f), "K": mk(frames), "V": mk(frames)}
+    n_q, n_k = f * nb, frames * nb
+    lists = _lists(rng, heads, n_q, n_k, length)
+    print(f"few query blocks: {heads * n_q} d={head_dim} n={frame_len} list length {length}", flush=True)
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    idx = torch.from_numpy(lists).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, frame_len, 64)
+    again = lf.lf_sparse_attn(Q, K, V, idx, frame_len, 64)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16))
+    got, lse2 = out.float().cpu().numpy().astype(np.float64), lse2.cpu().numpy()
+    Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
+    for h, r in {(0, 0), (0, n_q - 1), (heads - 1, 0), (heads - 1, n_q - 1), (heads // 2, nb - 1)}:
+        kept = [int(c) for c in lists[h, r] if 0 <= c < n_k]
+        lo, hi = O.block_token_range(r, frame_len, 64)
+        if not kept:
+            assert not got[h, lo:hi].any() and np.isposinf(lse2[h, lo:hi]).all()
+            continue
+        err = np.abs(got[h, lo:hi] - O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, kept, frame_len, 64))
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
+        cols = np.concatenate([np.arange(*O.block_token_range(c, frame_len, 64)) for c in kept])
+        s = Qf[h, lo:hi].astype(np.float64) @ Kf[h, cols].astype(np.float64).T / np.sqrt(head_dim) / np.log(2.0)
+        top = s.max(axis=1)
+        ref2 = top + np.log2(np.exp2(s - top[:, None]).sum(axis=1))
+        # the row sum is of probabilities rounded to bfloat16: at most 2^-8 of it, 2^-8 / ln 2 in log2
+        assert np.abs(lse2[h, lo:hi] - ref2).max() <= 2.0 ** -8 / np.log(2.0) + 1e-4
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("frame_len,keep", [(96, 2), (97, 7), (200, 19)])
+def test_a_state_is_continued_over_few_query_blocks(gpu, frame_len, keep, head_dim):  # noqa: F811
+    """The list-driven phase after the dense one over the current chunk, a slice of which carries the state."""
+    torch, lf = gpu
+    w = synth.small_ragged(frame_len=frame_len, chunk_idx=6, heads=2, head_dim=head_dim)
+    x = synth.make_inputs(w)
+    n_q, n_k = (t * w.blocks_per_frame for t in (w.frames_per_chunk, w.frames))
+    b = lf.lf_chunk_budget(w.chunk_idx, w.schedule)
+    b.n_sink = b.n_win = 0
+    b.k_frames, b.k_blocks, b.list_len = w.hist_frames, keep, keep + n_q
+    rng = np.random.default_rng(keep)
+    lists = np.stack([np.stack([np.concatenate([np.sort(rng.permutation(n_k - n_q)[:keep]), np.arange(n_k - n_q, n_k)])
+                                for _ in range(n_q)]) for _ in range(w.heads)]).astype(np.int32)
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    got = lf.lf_sparse_attn_split(Q, K, V, torch.from_numpy(lists).cuda(), frame_len, 64, b).float().cpu().numpy().astype(np.float64)
+    Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
+    for h in range(w.heads):
+        for r in range(n_q):
+            lo, hi = O.block_token_range(r, frame_len, 64)
+            err = np.abs(got[h, lo:hi] - O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, [int(c) for c in lists[h, r]], frame_len, 64))
+            assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
