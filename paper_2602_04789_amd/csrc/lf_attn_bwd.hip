@@ -108,14 +108,18 @@ __device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins
 // walks the block's list of KV blocks in half tiles of 32 KV rows.  SPLIT > 1: the workgroup has
 // SPLIT such pairs with a tile stage each, every pair walks a SPLIT-th of the list (the barriers are
 // common, the slices equally long but for empty entries at the end), and their sums are added
-// through LDS in a fixed order: for calls with too few query blocks to fill the chip.
-template <int D, int SPLIT>
-__global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
+// through LDS in a fixed order: for calls with too few query blocks to fill the chip.  HALF: for fewer still, the
+// workgroup has one row half of a query block, and a slice is one wavefront with a stage of its own, without barriers in
+// the loop (four slices at d = 128, where LDS holds no more stages, eight at d = 64).
+template <int D, int SPLIT, bool HALF = false>
+__global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 && SPLIT == 1 ? 3 : 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
+  constexpr int WPS = HALF ? 1 : 2;         // wavefronts that share a tile stage
+  constexpr int kThreads = 64 * WPS;        // ... and their threads
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;
   constexpr int MB = D / 32;
   constexpr int RPI = 64 / CH;
-  constexpr int LPW = 32 / (RPI * 2);
+  constexpr int LPW = 32 / (RPI * WPS);
   constexpr int TILE = 32 * CH;             // uint4 per 32-row tile
   constexpr int NBUF = 2;
 
@@ -129,7 +133,7 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
   }
   const int w = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3) - 1;
   if (w >= a.total_wg) return;
-  const int h = w / a.owners, r = w % a.owners;
+  const int h = (HALF ? w >> 1 : w) / a.owners, r = (HALF ? w >> 1 : w) % a.owners;
   const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
   uint4 (*const buf)[2 * TILE] = buf_all[slice];
   int2* const ent = ent_all[slice];
@@ -140,8 +144,10 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
   // owner block: tokens [otok0, otok0 + o_cnt); this lane's owner row (a column of S')
   const int otok0 = (r / a.nb) * a.n + (r % a.nb) * 64;
   const int o_cnt = min(64, a.n - (r % a.nb) * 64);
-  const int orow = 32 * wave + ln;
+  const int rh = HALF ? w & 1 : wave;       // row half
+  const int orow = 32 * rh + ln;
   const bool o_ok = orow < o_cnt;
+  if (HALF && 32 * rh >= o_cnt) return;     // the other half of a short query block
 
   // this pair's slice: entries [slice n_ent, +n_ent) of the list, of which my_ent exist
   const int n_ent = (a.list_len + SPLIT - 1) / SPLIT;
@@ -179,8 +185,8 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     const int row = RPI * (LPW * wave + i) + ld_r;
-    off1[i] = (uint32_t)row * a1_row_bytes + (uint32_t)swz<CH>(row, ld_p) * 16u - 1024u * i;
-    off2[i] = (uint32_t)row * a2_row_bytes + (uint32_t)swz<CH>(row, ld_p) * 16u - 1024u * i;
+    off1[i] = (uint32_t)row * a1_row_bytes + (uint32_t)swz<CH>(row, ld_p) * 16u - 1024u * (i & 3);
+    off2[i] = (uint32_t)row * a2_row_bytes + (uint32_t)swz<CH>(row, ld_p) * 16u - 1024u * (i & 3);
   }
   auto rsrc = [](const char* base, uint32_t row_bytes, int2 e) {
     int32x4 rs;
@@ -194,14 +200,17 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
   auto fetch = [&](int32x4 rs, uint4* dst, const uint32_t (&off)[LPW]) __attribute__((always_inline)) {
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)LDS_PTR(void, dst + RPI * LPW * wave * CH));
-    if constexpr (LPW == 4)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                   "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
-                   "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
-                   "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
-                   "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
-                   :: "s"(lds0), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(rs) : "memory", "m0");
-    else
+    if constexpr (LPW >= 4) {
+#pragma unroll
+      for (int i = 0; i < LPW; i += 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+                     "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
+                     :: "s"(lds0 + 1024u * i), "v"(off[i]), "v"(off[i + 1]), "v"(off[i + 2]), "v"(off[i + 3]), "s"(rs)
+                     : "memory", "m0");
+    } else
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                    "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
                    "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
@@ -343,7 +352,13 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
       const int cnt = e_cur.y;
       const int2 e_raw = ent[min((t + 2) >> 1, n_local - 1)];
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-      lds_barrier();                       // (waits for e_raw too)
+      if constexpr (HALF) {                // the stage is this wavefront's own: only its own reads have to be done
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+      } else {
+        lds_barrier();                     // (waits for e_raw too)
+      }
       if (t + 1 < steps) request(e_nxt, other);
       e_cur = e_nxt;
       e_nxt = half(e_raw, t);              // (t + 2 is as even as t)
@@ -373,7 +388,7 @@ __global__ __launch_bounds__(kThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) vo
     constexpr int NGRP = MB * 4, PER = NGRP / SPLIT;
     static_assert(NGRP * 64 == 2 * TILE && NGRP % SPLIT == 0, "a row half fills one tile buffer");
     __syncthreads();                          // no request is in flight: the last step makes none
-    float4* const mine = reinterpret_cast<float4*>(buf[wave]);
+    float4* const mine = reinterpret_cast<float4*>(buf[wave]);   // (wave: the row half within the workgroup)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -919,7 +934,12 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_q; a.streams = dm->n_k;
   a.total_wg = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
-  const bool split = lf_split_lists_dq(dm->d, a.total_wg, list_len);
+  const bool halve = lf_halve_blocks_dq(dm->d, a.total_wg, list_len);
+  const bool split = !halve && lf_split_lists_dq(dm->d, a.total_wg, list_len);
+  if (halve) {
+    a.total_wg *= 2;
+    a.wg_per_xcd = (a.total_wg + 7) / 8;
+  }
   a.order = order;
   a.order_cnt = tcnt;
   a.order_n_k = dm->n_k;
@@ -927,11 +947,13 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.order_per_xcd = (a.order_total + 7) / 8;
   a.order_step = spread_step((uint32_t)dm->n_k);
   // eight workgroups in front for the order of the next launch
-  const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(split ? 4 * kThreads : kThreads));
+  const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(halve ? (dm->d == 128 ? 256 : 512) : split ? 4 * kThreads : kThreads));
   a.order_stride = (uint32_t)((uint64_t)block1.x * a.order_step % (uint32_t)dm->n_k);
   hipError_t rc = dm->d == 128
-      ? lf_launch(split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>, grid1, block1, 0, st, a)
-      : lf_launch(split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>, grid1, block1, 0, st, a);
+      ? lf_launch(halve ? lf_attn_bwd_q_kernel<128, 4, true> : split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>,
+                  grid1, block1, 0, st, a)
+      : lf_launch(halve ? lf_attn_bwd_q_kernel<64, 8, true> : split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>,
+                  grid1, block1, 0, st, a);
   if (rc != hipSuccess) return LF_ERR_HIP;
   // dK and dV
   a.X = (const uint16_t*)K;   a.x_tok = s->k_stride_tok;  a.x_head = s->k_stride_head;

@@ -59,6 +59,10 @@ inline bool lf_halve_blocks(int d, int blocks, int list_len) { return blocks <= 
 inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
   return (blocks <= 256 && list_len >= 7) || (d == 128 && blocks <= 512 && list_len >= 48);
 }
+// As lf_halve_blocks.  Backward call, one workgroup a block -> two: d = 128, 24 blocks, lists of 2: 21.5 -> 21.0, of 4: 24.1 -> 21.2, of
+// 16: 32.5 -> 26.7, of 64: 60.9 -> 43.9; 128 blocks, of 2: 25.2 -> 26.2, of 4: 29.0 -> 27.4, of 32: 57.5 -> 52.7; d = 64, 128 blocks, of 4:
+// 21.3 -> 23.1, of 6: 23.7 -> 23.3, of 32: 52.3 -> 43.1; 56 blocks, of 28: 45.9 -> 36.4.
+inline bool lf_halve_blocks_dq(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 4 : 6); }
 
 // Kernel launchers (defined in the .hip files); return LF_OK or LF_ERR_HIP.
 int lf_launch_select(const void* Q, const void* K, const lf_shape* s, const lf_budget* b,

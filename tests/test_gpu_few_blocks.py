@@ -4,6 +4,7 @@ import pytest
 
 from oracle import hsa_oracle as O
 from paper_2602_04789_amd import synth
+from test_gpu_attn_bwd import _close
 from test_gpu_parity import MAX_ABS, MEAN_ABS, _dev, _host_f32, gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -83,3 +84,47 @@ def test_a_state_is_continued_over_few_query_blocks(gpu, frame_len, keep, head_d
             lo, hi = O.block_token_range(r, frame_len, 64)
             err = np.abs(got[h, lo:hi] - O.sparse_attention_block(Qf[h], Kf[h], Vf[h], r, [int(c) for c in lists[h, r]], frame_len, 64))
             assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
+
+
+def _gradients(torch, lf, rng, heads, frame_len, per_chunk, frames, head_dim, lists):
+    mk = lambda t: synth.f32_to_bf16_bits(rng.standard_normal((heads, t * frame_len, head_dim), dtype=np.float32))
+    x = {"Q": mk(per_chunk), "K": mk(frames), "V": mk(frames), "dO": mk(per_chunk)}
+    Q, K, V, dO = (_dev(torch, x[k]) for k in ("Q", "K", "V", "dO"))
+    idx = torch.from_numpy(lists).cuda()
+    out, lse2 = lf.lf_sparse_attn_fwd(Q, K, V, idx, frame_len, 64)
+    grads = tuple(torch.full_like(t, float("nan")) for t in (Q, K, V))
+    runs = []
+    for _ in range(2):
+        lf.lf_sparse_attn_bwd(Q, K, V, out, dO, lse2, idx, frame_len, 64, grads=grads)
+        torch.cuda.synchronize()
+        runs.append([g.clone() for g in grads])
+    assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(*runs))
+    return x, [g.float().cpu().numpy().astype(np.float64) for g in runs[0]]
+
+
+def _check_head(x, grads, lists, h, n_k, frame_len):
+    """One head against the oracle; a query block without a valid id takes part with a zero upstream gradient."""
+    Qf, Kf, Vf, dOf = (_host_f32(x[k])[h:h + 1].copy() for k in ("Q", "K", "V", "dO"))
+    kept = np.empty((1, lists.shape[1]), dtype=object)
+    for r in range(lists.shape[1]):
+        kept[0, r] = [int(c) for c in lists[h, r] if 0 <= c < n_k]
+        if not kept[0, r]:
+            lo, hi = O.block_token_range(r, frame_len, 64)
+            assert not grads[0][h, lo:hi].any()
+            kept[0, r], dOf[0, lo:hi] = [0], 0
+    for name, got, want in zip(("dQ", "dK", "dV"), grads, O.sparse_attention_backward(Qf, Kf, Vf, dOf, kept, frame_len, 64)):
+        _close(name, got[h:h + 1], want)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("heads,frame_len,frames,length", [(2, 64, 4, 3), (2, 96, 4, 4), (2, 97, 4, 5), (2, 65, 4, 6), (32, 65, 5, 9), (33, 96, 5, 9),
+                                                           (3, 31, 9, 8), (1, 64, 1030, 1030)])
+def test_dq_of_few_query_blocks(gpu, heads, frame_len, frames, length, head_dim):  # noqa: F811
+    torch, lf = gpu
+    nb = -(-frame_len // 64)
+    rng = np.random.default_rng(frame_len + length)
+    lists = _lists(rng, heads, 2 * nb, frames * nb, length)
+    print(f"few query blocks, backward: {heads * 2 * nb} d={head_dim} n={frame_len} list length {length}", flush=True)
+    x, grads = _gradients(torch, lf, rng, heads, frame_len, 2, frames, head_dim, lists)
+    for h in {0, heads - 1}:
+        _check_head(x, grads, lists, h, frames * nb, frame_len)
