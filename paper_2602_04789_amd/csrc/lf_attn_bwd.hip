@@ -114,7 +114,7 @@ __device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins
 template <int D, int SPLIT, bool HALF = false>
 __global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 && SPLIT == 1 ? 3 : 2) void lf_attn_bwd_q_kernel(BwdArgs a) {
   constexpr int WPS = HALF ? 1 : 2;         // wavefronts that share a tile stage
-  constexpr int kThreads = 64 * WPS;        // ... and their threads
+  constexpr int kStageThreads = 64 * WPS;        // ... and their threads
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;
   constexpr int MB = D / 32;
@@ -134,10 +134,10 @@ __global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 
   const int w = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3) - 1;
   if (w >= a.total_wg) return;
   const int h = (HALF ? w >> 1 : w) / a.owners, r = (HALF ? w >> 1 : w) % a.owners;
-  const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
+  const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kStageThreads) : 0;
   uint4 (*const buf)[2 * TILE] = buf_all[slice];
   int2* const ent = ent_all[slice];
-  const int tid = threadIdx.x % kThreads, lane = tid & 63;
+  const int tid = threadIdx.x % kStageThreads, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, kg = lane >> 5;
 
@@ -334,7 +334,7 @@ __global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 
     const int n_local = l1 - l0, steps = 2 * n_local;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
-    for (int i = tid; i < n_local; i += kThreads) {
+    for (int i = tid; i < n_local; i += kStageThreads) {
       const int cidx = l0 + i < my_ent ? list[l0 + i] : -1;
       const bool ok = (unsigned)cidx < (unsigned)a.streams;
       const int tau = ok ? cidx / a.nb : 0, j = ok ? cidx % a.nb : 0;
@@ -439,11 +439,16 @@ __global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 
 // keeps one owner operand and one accumulator set, which fits two wavefronts per SIMD (two
 // workgroups per CU, not in step with each other).
 constexpr int kKvThreads = 256;
-// Calls with at most kKvSplitBlocks (head, KV block) pairs give a block two groups of wavefronts: such a
-// workgroup has a compute unit (of 256) to itself at d = 128.  Backward call in us, d = 128, mean transposed list of
-// 12: 64 blocks 49.9 -> 47.8, 256 blocks 52.9 -> 50.4; of 24: 256 blocks 76.6 -> 70.0; two rounds, of 12:
-// 384 blocks 59.5 -> 66.8.  d = 64, of 12: 256 blocks 49.1 -> 46.9, 384 blocks 55.8 -> 58.8.
+// Calls at d = 128 with at most kKvSplitBlocks (head, KV block) pairs give a block two groups of wavefronts: such a
+// workgroup has a compute unit (of 256) to itself.  Backward call in us, mean transposed list of
+// 12: 256 blocks 52.9 -> 50.4; of 24: 76.6 -> 70.0; two rounds, of 12: 384 blocks 59.5 -> 66.8.
 constexpr int kKvSplitBlocks = 256;
+// With at most this many pairs the two row halves of a KV block get a workgroup each, of two groups of two wavefronts, as long as
+// that brings compute units to work: at d = 128 one such workgroup fills a unit's LDS, at d = 64 two fit.  Backward call in us, a
+// workgroup a block -> two: d = 128, 128 blocks, mean list 1: 22.5 -> 19.5, 8: 33.8 -> 29.7, 64: 93.8 -> 90.3; but 168 blocks, 14: 47.6 ->
+// 58.0.  d = 64, 168 blocks, 9: 36.4 -> 33.0; 256 blocks, 4: 28.1 -> 23.7, 16: 45.5 -> 45.3; 352 blocks, 2: 22.7 -> 22.3, 16: 62.4 -> 59.1;
+// 384 blocks, 2: 22.2 -> 22.6, 11: 47.3 -> 47.9; 480 blocks, 32: 132 -> 137.
+constexpr int kKvHalfBlocks128 = 128, kKvHalfBlocks64 = 352;
 // Whether a call at d = 128 goes to the kernel with one wavefront per SIMD (lf_attn_bwd_wide.hip).  That kernel has the shorter
 // loop, but nobody works on its SIMDs while a list starts and ends, and a compute unit that has only one workgroup left (the
 // last round, of 512) leaves two of its SIMDs idle.  So the lists have to be long enough -- a KV block's list holds
@@ -453,7 +458,7 @@ constexpr int kKvSplitBlocks = 256;
 //   1 800 blocks:  mean 10: 175 and 178,  16: 249 and 244,  28: 402 and 386,  45: 631 and 588
 //   6 300 blocks:  mean 10: 559 and 561,  16: 821 and 801,  28: 1 339 and 1 279,  45: 2 085 and 1 981
 //   1 088 blocks (last round 64):  mean 16: 170 and 173,  24: 241 and 240,  32: 316 and 316
-//   256 blocks (two pairs of wavefronts each):  mean 16: 54 and 56;  320 blocks:  mean 10: 50 and 53
+//   256 blocks (two groups or pairs of wavefronts each):  mean 16: 54 and 56;  320 blocks:  mean 10: 50 and 53
 // Lists as the mask selection makes them differ in length, and with few rounds the longest of them decide: how much faster the call
 // is with that kernel, least and mean of 5 to 30 calls:
 //   769 to 1 024 blocks:    mean 18 to 20: 0.97, 1.01;  20 to 22: 0.96, 1.00;  25 to 28: 0.99, 1.03;  28 to 32: 1.00, 1.04;  45: 1.01, 1.05
@@ -466,42 +471,46 @@ static bool kv_wide(int blocks, int64_t entries, int n_k) {
   return entries >= (int64_t)18 * n_k;
 }
 // SPLIT = 2: a workgroup holds two such groups of four wavefronts, each with a stage of its own and half of
-// the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.
-template <int D, int SPLIT>
-__global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) void lf_attn_bwd_kv_kernel(BwdArgs a) {
+// the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.  HALF: the workgroup
+// owns one row half of the block, and a group is its two wavefronts.
+template <int D, int SPLIT, bool HALF = false>
+__global__ __launch_bounds__((HALF ? 128 : kKvThreads) * SPLIT, HALF ? 1 : D == 64 && SPLIT == 1 ? 3 : 2) void lf_attn_bwd_kv_kernel(BwdArgs a) {
+  constexpr int WPG = HALF ? 2 : 4;         // wavefronts of a group
+  constexpr int kGroupThreads = 64 * WPG;      // ... and their threads
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;
   constexpr int MB = D / 32;
   constexpr int RPI = 64 / CH;              // tile rows one wavefront load instruction covers
-  constexpr int LPW = 32 / (RPI * 4);       // load instructions per wavefront, per tensor, per half tile
+  constexpr int LPW = 32 / (RPI * WPG);     // load instructions per wavefront, per tensor, per half tile
   constexpr int T32 = 32 * CH;              // uint4 per half tile (32 rows)
-  static_assert(LPW == 1 || LPW == 2, "a half tile splits over four wavefronts");
+  static_assert(LPW == 1 || LPW == 2 || LPW == 4, "a half tile splits over the wavefronts of a group");
 
   __shared__ uint4 buf_all[SPLIT][3][2 * T32];   // [half tile mod 3][Q | dO]
-  __shared__ float4 st_all[SPLIT][3][4][16];     // lse2 (role 0) or -delta (role 1) of the 32 streamed rows, one copy per
+  __shared__ float4 st_all[SPLIT][3][WPG][16];     // lse2 (role 0) or -delta (role 1) of the 32 streamed rows, one copy per
                                             // wavefront; its upper half takes the zeros of the lanes past the 32 rows
-  __shared__ uint4 ph_all[SPLIT][2][2][2][64];   // P' handoff: [step parity][rh][k-step][lane]
+  __shared__ uint4 ph_all[SPLIT][2][WPG / 2][2][64];   // P' handoff: [step parity][row half][k-step][lane]
   __shared__ int2 ent_all[SPLIT][kPass];
 
   const int slot = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
-  if (slot >= a.total_wg) return;
-  const int w = a.order[slot];
+  if ((HALF ? slot >> 1 : slot) >= a.total_wg) return;
+  const int w = a.order[HALF ? slot >> 1 : slot];
   const int h = w / a.owners, r = w % a.owners;
-  const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kKvThreads) : 0;
+  const int slice = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kGroupThreads) : 0;
   uint4 (*const buf)[2 * T32] = buf_all[slice];
-  float4 (*const st)[4][16] = st_all[slice];
-  uint4 (*const ph)[2][2][64] = ph_all[slice];
+  float4 (*const st)[WPG][16] = st_all[slice];
+  uint4 (*const ph)[WPG / 2][2][64] = ph_all[slice];
   int2* const ent = ent_all[slice];
-  const int tid = threadIdx.x % kKvThreads, lane = tid & 63;
+  const int tid = threadIdx.x % kGroupThreads, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rh = wave & 1, pair = rh;
-  const bool is_ds = wave >= 2;             // role 1: dP', dS', dK
+  const int rh = HALF ? slot & 1 : wave & 1, pair = HALF ? 0 : rh;
+  const bool is_ds = wave >= WPG / 2;       // role 1: dP', dS', dK
   const int ln = lane & 31, kg = lane >> 5;
 
   const int otok0 = (r / a.nb) * a.n + (r % a.nb) * 64;
   const int o_cnt = min(64, a.n - (r % a.nb) * 64);
   const int orow = 32 * rh + ln;
   const bool o_ok = orow < o_cnt;
+  if (HALF && 32 * rh >= o_cnt) return;     // the other half of a short KV block
   // this group's slice of the list: entries [slice n_ent, +n_ent), of which my_ent exist
   const int n_all = a.cnt[(int64_t)h * a.owners + r];
   const int n_ent = (n_all + SPLIT - 1) / SPLIT;
@@ -523,7 +532,7 @@ __global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) 
   const char* STh = reinterpret_cast<const char*>((is_ds ? a.ndelta : a.lse2) + (int64_t)h * a.q_len);
   const uint32_t a1_row_bytes = (uint32_t)(a.a1_tok * 2), a2_row_bytes = (uint32_t)(a.a2_tok * 2);
 
-  // tile loads: wavefront `wave` fills rows [8 wave, +8) of a half tile with LPW instructions
+  // tile loads: wavefront `wave` fills its share of a half tile's rows with LPW instructions
   const int ld_r = lane / CH, ld_p = lane % CH;
   uint32_t off1[LPW], off2[LPW];
 #pragma unroll
@@ -545,7 +554,14 @@ __global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) 
   auto fetch = [&](int32x4 rs, uint4* dst, const uint32_t (&off)[LPW]) __attribute__((always_inline)) {
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)LDS_PTR(void, dst + RPI * LPW * wave * CH));
-    if constexpr (LPW == 2)
+    if constexpr (LPW == 4)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                   "buffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+                   "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 lds\n\t"
+                   "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 lds\n\t"
+                   "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 lds"
+                   :: "s"(lds0), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(rs) : "memory", "m0");
+    else if constexpr (LPW == 2)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                    "buffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
                    "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds"
@@ -648,7 +664,7 @@ __global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) 
     const int n_local = min(n_ent - l0, kPass);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
-    for (int i = tid; i < n_local; i += kKvThreads) {
+    for (int i = tid; i < n_local; i += kGroupThreads) {
       const int cidx = l0 + i < my_ent ? list[l0 + i] : -1;
       const bool ok = (unsigned)cidx < (unsigned)a.streams;
       const int tau = ok ? cidx / a.nb : 0, j = ok ? cidx % a.nb : 0;
@@ -766,7 +782,7 @@ __global__ __launch_bounds__(kKvThreads * SPLIT, D == 64 && SPLIT == 1 ? 3 : 2) 
   if constexpr (SPLIT > 1) {
     // the second group leaves its sums where both groups' tiles were, the first adds them to its own
     constexpr int NGRP = MB * 4;
-    static_assert(SPLIT == 2 && 4 * NGRP * 64 <= 2 * 3 * 2 * T32, "the sums of four wavefronts fit the stages");
+    static_assert(SPLIT == 2 && WPG * NGRP * 64 <= 2 * 3 * 2 * T32, "the sums of a group fit the stages");
     float4* const sums = reinterpret_cast<float4*>(buf_all) + wave * NGRP * 64;
     __syncthreads();
     if (slice == 1) {
@@ -966,13 +982,20 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_k; a.streams = dm->n_q;
   a.total_wg = dm->H * dm->n_k;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
+  if (a.total_wg <= (dm->d == 128 ? kKvHalfBlocks128 : kKvHalfBlocks64)) {
+    a.wg_per_xcd *= 2;     // both halves of a block on the XCD its place in the order belongs to
+    const dim3 grid((unsigned)(a.wg_per_xcd * 8));
+    rc = dm->d == 128 ? lf_launch(lf_attn_bwd_kv_kernel<128, 2, true>, grid, dim3(2 * 128), 0, st, a)
+                      : lf_launch(lf_attn_bwd_kv_kernel<64, 2, true>, grid, dim3(2 * 128), 0, st, a);
+    return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
+  }
   const dim3 grid2((unsigned)(a.wg_per_xcd * 8));
-  const bool halves = a.total_wg <= kKvSplitBlocks;
+  const bool groups = dm->d == 128 && a.total_wg <= kKvSplitBlocks;
   if (dm->d == 128 && kv_wide(a.total_wg, (int64_t)list_len * dm->n_q, dm->n_k))
     return lf_launch_attn_bwd_kv_wide(a, st) == hipSuccess ? LF_OK : LF_ERR_HIP;
-  const dim3 block2((unsigned)(halves ? 2 * kKvThreads : kKvThreads));
-  rc = dm->d == 128
-      ? lf_launch(halves ? lf_attn_bwd_kv_kernel<128, 2> : lf_attn_bwd_kv_kernel<128, 1>, grid2, block2, 0, st, a)
-      : lf_launch(halves ? lf_attn_bwd_kv_kernel<64, 2> : lf_attn_bwd_kv_kernel<64, 1>, grid2, block2, 0, st, a);
+  const dim3 block2((unsigned)(groups ? 2 * kKvThreads : kKvThreads));
+  rc = dm->d == 64 ? lf_launch(lf_attn_bwd_kv_kernel<64, 1>, grid2, block2, 0, st, a)
+       : groups    ? lf_launch(lf_attn_bwd_kv_kernel<128, 2>, grid2, block2, 0, st, a)
+                   : lf_launch(lf_attn_bwd_kv_kernel<128, 1>, grid2, block2, 0, st, a);
   return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
 }

@@ -128,3 +128,21 @@ def test_dq_of_few_query_blocks(gpu, heads, frame_len, frames, length, head_dim)
     x, grads = _gradients(torch, lf, rng, heads, frame_len, 2, frames, head_dim, lists)
     for h in {0, heads - 1}:
         _check_head(x, grads, lists, h, frames * nb, frame_len)
+
+
+# 128 and 132 KV blocks (the edge at d = 128), 352 and 360 (at d = 64); last blocks of 1, 32, 33 and 64 rows; transposed lists of 0, 1, odd
+# and even lengths and of every query block
+@pytest.mark.parametrize("head_dim,heads,frame_len,per_chunk,frames,length", [
+    (128, 32, 65, 2, 2, 3), (128, 33, 96, 2, 2, 3), (64, 44, 97, 2, 4, 5), (64, 45, 97, 2, 4, 5), (128, 2, 96, 3, 9, 1), (64, 2, 31, 3, 9, 2),
+    (128, 1, 64, 5, 20, 11), (64, 1, 65, 5, 20, 11), (128, 1, 64, 128, 128, 128), (64, 1, 64, 352, 352, 40)])
+def test_gradients_of_few_kv_blocks(gpu, head_dim, heads, frame_len, per_chunk, frames, length):  # noqa: F811
+    torch, lf = gpu
+    nb = -(-frame_len // 64)
+    rng = np.random.default_rng(frame_len + length)
+    lists = _lists(rng, heads, per_chunk * nb, frames * nb, length)
+    first = lists[:, 1:, 0]
+    first[(first >= 0) & (first < frames * nb)] = 0                       # KV block 0 is in (nearly) every list
+    print(f"few KV blocks: {heads * frames * nb} d={head_dim} n={frame_len} list length {length}", flush=True)
+    x, grads = _gradients(torch, lf, rng, heads, frame_len, per_chunk, frames, head_dim, lists)
+    for h in {0, heads - 1}:
+        _check_head(x, grads, lists, h, frames * nb, frame_len)
