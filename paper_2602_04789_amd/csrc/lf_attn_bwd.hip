@@ -29,81 +29,6 @@ namespace {
 constexpr int kThreads = 128;    // two wavefronts of 32 owner rows each
 constexpr int kPass = 256;       // list entries decoded per pass
 
-// Launch order of the key-major pass: its workgroups differ in work by the length of their
-// transposed list (a sink or current-chunk block is kept by every query block, a block of the
-// middle history by few).  Workgroup indices go round-robin to the eight XCDs, so every XCD works
-// through a fixed set of blocks: `per_xcd` places of the sequence "head after head, and inside a
-// head the KV blocks in steps of `step` blocks".  All heads carry the same number of tiles; where
-// an XCD's share ends inside a head, the step (about 0.618 n_k, prime to n_k) spreads the share
-// evenly over the head's blocks, heavy and light.  With the blocks in plain order the XCD that
-// got the head's second half, current chunk included, had 27 % more tiles than the one with the
-// first half, and a quarter of the launch's time was spent waiting for it (12 heads, 525 KV
-// blocks: the forward and backward calls together 1780 us, now 1672 us).
-// Inside an XCD workgroups are started in index order, so the long ones go first: one workgroup per
-// XCD sorts its share by descending count with a counting sort.  These eight ride at the front of
-// the dQ launch, which does not need the order (a launch of their own took 5 us).  The place of equal counts
-// among each other is left to the order the atomics happen to take: any permutation is valid,
-// and the gradients do not depend on which workgroup computes a block.
-constexpr int kOrderBins = 1024;
-__device__ __forceinline__ void order_share(const BwdArgs& a, int xcd, int* bins /* [kOrderBins] in LDS */) {
-  const int threads = blockDim.x, tid = threadIdx.x;
-  const int w0 = xcd * a.order_per_xcd, w1 = min(a.order_total, w0 + a.order_per_xcd);
-  // Block at place i of the sequence: head i / n_k, and in it the block i step mod n_k (whole heads before it
-  // drop out of the remainder), which moves on by a constant when i moves on by the number of threads.
-  const uint32_t nk = (uint32_t)a.order_n_k;
-  const uint32_t c0 = (uint32_t)((uint64_t)((uint32_t)(w0 + tid) % nk) * a.order_step % nk);
-  // Every block of the share with its bin, U at a time: their loads (and LDS atomics) are in flight together.
-  // A long history has thousands of blocks a share, and one at a time the loop outlasts the dQ launch.
-  auto each_block = [&](auto put) __attribute__((always_inline)) {
-    constexpr int U = 8;
-    uint32_t c = c0;
-    for (int i0 = w0 + tid; i0 < w1; i0 += U * threads) {
-      int w[U], b[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + u * threads;
-        w[u] = i < w1 ? (int)((uint32_t)i / nk * nk + c) : w[0];   // past the end: any block, loaded and dropped
-        c += a.order_stride;
-        c -= c >= nk ? nk : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) b[u] = min(a.order_cnt[w[u]], kOrderBins - 1);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (i0 + u * threads < w1) put(w[u], b[u]);
-    }
-  };
-  for (int i = tid; i < kOrderBins; i += threads) bins[i] = 0;
-  __syncthreads();
-  each_block([&](int, int b) { atomicAdd(&bins[b], 1); });
-  __syncthreads();
-  // bins[b] <- number of places in bins above b (where bin b starts in the descending order); lane l
-  // of the first wavefront takes the l-th sixteen bins from the top
-  if (tid < 64) {
-    constexpr int PER = kOrderBins / 64;
-    int cnt[PER], sum = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      cnt[j] = bins[kOrderBins - 1 - (PER * tid + j)];
-      sum += cnt[j];
-    }
-    int run = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int up = __shfl_up(run, d);
-      if (tid >= d) run += up;
-    }
-    run -= sum;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      bins[kOrderBins - 1 - (PER * tid + j)] = run;
-      run += cnt[j];
-    }
-  }
-  __syncthreads();
-  each_block([&](int w, int b) { a.order[w0 + atomicAdd(&bins[b], 1)] = w; });
-}
-
 // dQ: a workgroup of two wavefronts owns a query block (wavefront rh its rows [32 rh, +32)) and
 // walks the block's list of KV blocks in half tiles of 32 KV rows.  SPLIT > 1: the workgroup has
 // SPLIT such pairs with a tile stage each, every pair walks a SPLIT-th of the list (the barriers are
@@ -469,6 +394,15 @@ static bool kv_wide(int blocks, int64_t entries, int n_k) {
   if (blocks <= kKvSplitBlocks) return entries >= (int64_t)32 * n_k;
   if (blocks <= 1536) return blocks > 512 && (blocks - 1) % 512 >= 256 && entries >= (int64_t)(blocks <= 1024 ? 28 : 22) * n_k;
   return entries >= (int64_t)18 * n_k;
+}
+// Whether the dQ launch takes the kernel with one wavefront per query block (lf_attn_bwd_q_wide.hip): a SIMD holds one of its
+// wavefronts, so the last round of 1 024 query blocks has to be filled well enough.  dQ with the launch before it, this file's
+// kernel against that one, lists of 8 and 150: 520 blocks 1.02, 1.07; 768: 1.05, 1.06; 1 024: 1.05, 1.04; 1 040: 0.95, 0.91; 1 200: 0.96,
+// 1.02; 1 300: 1.03, 1.05; 1 500: 1.08, 1.09; 2 040: 1.18, 1.26; 2 060, of 8 and 64: 1.00, 0.99; 2 100: 1.03, 1.01; 3 016, of 8 and 150: 1.11, 1.13;
+// 3 090, of 8 and 64: 1.01, 1.01.  At most 512 blocks: 0.95 .. 1.01.  Lists of 2 and 4: 520 blocks 0.99, 1.00; 1 300: 0.96, 0.98; 3 090: 1.03, 0.92.
+static bool q_wide(int d, int blocks, int list_len) {
+  if (d != 128 || list_len < 8 || blocks <= 512) return false;
+  return blocks <= 1024 || (blocks - 1) % 1024 >= (blocks <= 2048 ? 256 : 48);
 }
 // SPLIT = 2: a workgroup holds two such groups of four wavefronts, each with a stage of its own and half of
 // the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.  HALF: the workgroup
@@ -963,13 +897,19 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.order_per_xcd = (a.order_total + 7) / 8;
   a.order_step = spread_step((uint32_t)dm->n_k);
   // eight workgroups in front for the order of the next launch
-  const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(halve ? (dm->d == 128 ? 256 : 512) : split ? 4 * kThreads : kThreads));
-  a.order_stride = (uint32_t)((uint64_t)block1.x * a.order_step % (uint32_t)dm->n_k);
-  hipError_t rc = dm->d == 128
-      ? lf_launch(halve ? lf_attn_bwd_q_kernel<128, 4, true> : split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>,
-                  grid1, block1, 0, st, a)
-      : lf_launch(halve ? lf_attn_bwd_q_kernel<64, 8, true> : split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>,
-                  grid1, block1, 0, st, a);
+  hipError_t rc;
+  if (!halve && !split && q_wide(dm->d, a.total_wg, list_len)) {
+    a.order_stride = (uint32_t)((uint64_t)64 * a.order_step % (uint32_t)dm->n_k);
+    rc = lf_launch_attn_bwd_q_wide(a, st);
+  } else {
+    const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(halve ? (dm->d == 128 ? 256 : 512) : split ? 4 * kThreads : kThreads));
+    a.order_stride = (uint32_t)((uint64_t)block1.x * a.order_step % (uint32_t)dm->n_k);
+    rc = dm->d == 128
+        ? lf_launch(halve ? lf_attn_bwd_q_kernel<128, 4, true> : split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>,
+                    grid1, block1, 0, st, a)
+        : lf_launch(halve ? lf_attn_bwd_q_kernel<64, 8, true> : split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>,
+                    grid1, block1, 0, st, a);
+  }
   if (rc != hipSuccess) return LF_ERR_HIP;
   // dK and dV
   a.X = (const uint16_t*)K;   a.x_tok = s->k_stride_tok;  a.x_head = s->k_stride_head;

@@ -61,3 +61,32 @@ def test_output_rows_are_staged_behind_a_barrier(kv_wide):
         wait = next((i for i in range(product, store) if "vmcnt(0)" in code[i]), store)
         print(name, "product", product, "wait", wait, "store", store)
         assert any("s_barrier" in l for l in code[wait:store])
+
+
+def test_the_dq_loop_counts_its_loads(tmp_path):
+    """The loop of dQ with one wavefront per query block (a window of 48 matrix instructions): 16 tile loads, one wait for the
+    sixteen before, no other wait for memory; no register is reloaded, no scalar load counts with the LDS reads, and M0 is
+    written only with the first load of each group of four."""
+    try:
+        hipcc = B._hipcc()
+    except RuntimeError:
+        pytest.skip("hipcc not found")
+    src, out = "lf_attn_bwd_q_wide.hip", str(tmp_path / "q_wide.s")
+    subprocess.run([hipcc, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out] + B.COMMON + B.DEVICE +
+                   B.PER_FILE.get(src, []), check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    with open(out) as f:
+        code = [x for x in (line.split(";")[0].strip() for line in f) if x]
+    labels = {m[1]: i for i, l in enumerate(code) for m in [re.match(r"(\.LBB\w+):", l)] if m}
+    loops = []
+    for i, l in enumerate(code):
+        m = re.match(r"s_c?branch\w*\s+(\.LBB\w+)", l)
+        if m and labels[m[1]] < i and sum("v_mfma" in x for x in code[labels[m[1]]: i]) == 48:
+            loops.append(code[labels[m[1]]: i])
+    body = max(loops, key=len)         # (the masking of short half tiles branches back into it)
+    waits = [x for x in body if "vmcnt" in x]
+    print(waits)
+    assert waits == ["s_waitcnt vmcnt(16)"] and sum("buffer_load" in x for x in body) == 16
+    assert not any(re.match(r"(scratch|global|flat|s_load|s_buffer)_", x) for x in body)
+    m0 = [i for i, x in enumerate(body) if re.match(r"s_\w+ m0,", x)]
+    assert len(m0) == 4 and all(sum("buffer_load" in x for x in body[i: i + 3]) == 1 and "v_mfma" in body[i + 1] for i in m0)
+    assert not any("m0" in x for i, x in enumerate(body) if i not in m0)
