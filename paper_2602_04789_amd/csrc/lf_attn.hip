@@ -6,7 +6,7 @@
 // wavefronts, and there is no merge at the end.  A workgroup holds two such query blocks and two
 // workgroups share a compute unit, so every SIMD holds two wavefronts, free to be in different
 // parts of their step (the matrix core of one beside the vector ALU of the other).  In a call with
-// few query blocks a workgroup holds one, its list is divided among four such pairs, and their
+// few query blocks a workgroup holds one, its list is divided among two or four such pairs, and their
 // states are merged through LDS; with fewer still, each row half of a query block has a workgroup of its own.  Each listed
 // KV block is taken as half tiles of 32 KV rows (two, or one when the block has at most 32
 // tokens): the 32 x d K and V half tiles are brought into a double-buffered LDS
@@ -807,12 +807,13 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
         : lf_launch(lf_attn_kernel<64, 8, false, 8, false, true>, dim3(grid), dim3(512), 0, st, a);
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
-  if (lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k)) {
+  const int parts = lf_two_parts(dm->d, a.total_wg, list_len) ? 2 : lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k) ? 4 : 1;
+  if (parts > 1) {
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
     const hipError_t rc = dm->d == 128
-        ? lf_launch(lf_attn_kernel<128, 8, false, 4>, dim3(grid), dim3(512), 0, st, a)
-        : lf_launch(lf_attn_kernel<64, 8, false, 4>, dim3(grid), dim3(512), 0, st, a);
+        ? lf_launch(parts == 4 ? lf_attn_kernel<128, 8, false, 4> : lf_attn_kernel<128, 4, false, 2>, dim3(grid), dim3(128 * parts), 0, st, a)
+        : lf_launch(parts == 4 ? lf_attn_kernel<64, 8, false, 4> : lf_attn_kernel<64, 4, false, 2>, dim3(grid), dim3(128 * parts), 0, st, a);
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
   // One wavefront per query block (lf_attn_wide.hip; d = 128): a SIMD holds one of its wavefronts, so it is

@@ -30,7 +30,7 @@ constexpr int kThreads = 128;    // two wavefronts of 32 owner rows each
 constexpr int kPass = 256;       // list entries decoded per pass
 
 // dQ: a workgroup of two wavefronts owns a query block (wavefront rh its rows [32 rh, +32)) and
-// walks the block's list of KV blocks in half tiles of 32 KV rows.  SPLIT > 1: the workgroup has
+// walks the block's list of KV blocks in half tiles of 32 KV rows.  SPLIT > 1 (two or four): the workgroup has
 // SPLIT such pairs with a tile stage each, every pair walks a SPLIT-th of the list (the barriers are
 // common, the slices equally long but for empty entries at the end), and their sums are added
 // through LDS in a fixed order: for calls with too few query blocks to fill the chip.  HALF: for fewer still, the
@@ -885,7 +885,7 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.total_wg = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
   const bool halve = lf_halve_blocks_dq(dm->d, a.total_wg, list_len);
-  const bool split = !halve && lf_split_lists_dq(dm->d, a.total_wg, list_len);
+  const int parts = halve ? 1 : lf_two_parts_dq(dm->d, a.total_wg, list_len) ? 2 : lf_split_lists_dq(dm->d, a.total_wg, list_len) ? 4 : 1;
   if (halve) {
     a.total_wg *= 2;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
@@ -898,17 +898,17 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.order_step = spread_step((uint32_t)dm->n_k);
   // eight workgroups in front for the order of the next launch
   hipError_t rc;
-  if (!halve && !split && q_wide(dm->d, a.total_wg, list_len)) {
+  if (!halve && parts == 1 && q_wide(dm->d, a.total_wg, list_len)) {
     a.order_stride = (uint32_t)((uint64_t)64 * a.order_step % (uint32_t)dm->n_k);
     rc = lf_launch_attn_bwd_q_wide(a, st);
   } else {
-    const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(halve ? (dm->d == 128 ? 256 : 512) : split ? 4 * kThreads : kThreads));
+    const dim3 grid1((unsigned)(a.wg_per_xcd * 8 + 8)), block1((unsigned)(halve ? (dm->d == 128 ? 256 : 512) : parts * kThreads));
     a.order_stride = (uint32_t)((uint64_t)block1.x * a.order_step % (uint32_t)dm->n_k);
     rc = dm->d == 128
-        ? lf_launch(halve ? lf_attn_bwd_q_kernel<128, 4, true> : split ? lf_attn_bwd_q_kernel<128, 4> : lf_attn_bwd_q_kernel<128, 1>,
-                    grid1, block1, 0, st, a)
-        : lf_launch(halve ? lf_attn_bwd_q_kernel<64, 8, true> : split ? lf_attn_bwd_q_kernel<64, 4> : lf_attn_bwd_q_kernel<64, 1>,
-                    grid1, block1, 0, st, a);
+        ? lf_launch(halve ? lf_attn_bwd_q_kernel<128, 4, true> : parts == 4 ? lf_attn_bwd_q_kernel<128, 4>
+                    : parts == 2 ? lf_attn_bwd_q_kernel<128, 2> : lf_attn_bwd_q_kernel<128, 1>, grid1, block1, 0, st, a)
+        : lf_launch(halve ? lf_attn_bwd_q_kernel<64, 8, true> : parts == 4 ? lf_attn_bwd_q_kernel<64, 4>
+                    : parts == 2 ? lf_attn_bwd_q_kernel<64, 2> : lf_attn_bwd_q_kernel<64, 1>, grid1, block1, 0, st, a);
   }
   if (rc != hipSuccess) return LF_ERR_HIP;
   // dK and dV

@@ -28,11 +28,36 @@ struct lf_dims {
 // Validates shape (and budget when non-NULL); returns LF_OK or an lf_status.
 int lf_derive(const lf_shape* s, const lf_budget* b, lf_dims* out);
 
+// Whether a query-major attention kernel divides each list in two parts, one for each pair of wavefronts of a workgroup.
+// Two such blocks share a compute unit at d = 128 (three at d = 64), so that a call in which the undivided form, two blocks to a
+// workgroup, leaves one wavefront on a SIMD has two there; with at most 256 blocks there is less to merge than with four parts.
+// Forward, us, undivided or in four parts (where lf_split_lists says so) -> in two (random lists):
+//   129 to 256 blocks: 200 blocks, d = 128, lists of 3: 10.6 -> 9.7, of 4: 11.5 -> 9.4, of 8: 12.4 -> 11.4, of 14: 16.2 -> 14.6, of 20: 17.8 ->
+//     18.1, of 120: 63.7 -> 74.7; lists of 1: 0.96 - 1.00.  d = 64, of 4: 9.1 -> 7.4, of 8: 9.0 both, of 10: 10.7 -> 9.7, of 12: 10.3 -> 10.5, of 120: 44.7 -> 55.2;
+//   257 to 512: d = 128, 260 blocks, of 7: 15.2 -> 16.0, of 8: 16.6 -> 15.9, of 32: 42.3 -> 33.5, of 64: 76.9 -> 56.2; 510 blocks, of
+//     8: 20.3 -> 19.4, of 32: 49.1 -> 43.4, of 120: 143 -> 132.  d = 64, 260 blocks, of 5: 9.9 -> 10.2, of 8: 12.3 -> 11.0, of 32: 30.2 -> 23.8;
+//     (Lists of 8 to 15 in 449 to 512 blocks would gain 3 - 10 %, but stay undivided, with the bits of the calls of 513 to 1 024 blocks.)
+//   more: d = 128, 520 blocks, of 16: 36.5 -> 38.4.  d = 64, 580 blocks, of 1: 0.89, of 2: 1.06, of 32: 41.6 -> 33.0; 760 blocks,
+//     of 8: 1.02, of 120: 137 -> 112; 780 (a second round), of 32: 0.93.
+inline bool lf_two_parts(int d, int blocks, int list_len) {
+  if (blocks <= 256) return list_len >= 2 && list_len <= (d == 128 ? 14 : 10);
+  if (d == 128) return blocks <= 512 && list_len >= (blocks <= 448 ? 8 : 16);
+  return blocks <= 768 && list_len >= (blocks <= 512 ? 6 : 2);
+}
+// dQ and the launch before it, us, likewise: 200 blocks, d = 128, lists of 3: 12.9 -> 13.4, of 4: 14.4 -> 13.5, of 8: 17.9 -> 16.6, of 14: 23.1 -> 21.3, of
+// 20: 25.1 -> 25.8; 256 blocks, of 14: 26.7 -> 22.8, of 20: 29.6 -> 28.6; d = 64, 200 blocks, of 4: 11.6 -> 10.8, of 14: 19.9 -> 18.1, of 20: 21.7 -> 22.5.
+// d = 128, 260 blocks, of 8: 26.1 -> 22.6, of 32: 67.6 -> 45.8; 510 blocks, of 7: 29.6 -> 30.3, of 8: 31.1 -> 30.4, of 32: 75.3 -> 62.3, of 120: 190 -> 187;
+// 520, of 32: 75.1 -> 84.1.  d = 64, 510 blocks, of 8: 21.1 -> 21.2, of 12: 26.0 -> 25.7, of 32: 53.0 -> 49.4; 260, of 64: 92.0 -> 84.1; 520, of 32: 65.9 -> 74.3.
+inline bool lf_two_parts_dq(int d, int blocks, int list_len) {
+  if (blocks <= 256) return list_len >= 4 && list_len <= 14;
+  return blocks <= 512 && list_len >= (d == 128 ? 8 : 10);
+}
 // Whether a query-major attention kernel divides each list among the four pairs of wavefronts of a
 // workgroup instead of giving every (head, query block) one pair.  `blocks` is the number of
 // these pairs, list_len the entries walked, n_k the KV blocks of a head.  A divided block has a compute unit (of 256)
 // to itself, so with more than 256 of them the second round starts when the first ends, and the
-// undivided form keeps more loads of one list's tiles in flight per compute unit.
+// undivided form keeps more loads of one list's tiles in flight per compute unit.  (The launchers ask lf_halve_blocks and lf_two_parts
+// first: what is left to decide here are lists of more than 14 or 10 in calls of 129 to 256 blocks.)
 // Forward, d = 128, us undivided -> divided (random lists):
 //   <= 256 blocks (up to 128 lf_halve_blocks comes first): 192 blocks, lists of 6: 13.6 -> 12.4; of 195: 222 -> 109; lists of 4 are one step a slice;
 //   <= 512, lists that hold at least half of the KV blocks: 286 blocks, 151 of 234: 164 -> 149; 490, 110 of 126:

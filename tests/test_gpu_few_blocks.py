@@ -146,3 +146,29 @@ def test_gradients_of_few_kv_blocks(gpu, head_dim, heads, frame_len, per_chunk, 
     x, grads = _gradients(torch, lf, rng, heads, frame_len, per_chunk, frames, head_dim, lists)
     for h in {0, heads - 1}:
         _check_head(x, grads, lists, h, frames * nb, frame_len)
+
+
+# Lists in two parts: 132, 256, 258, 512, 516 (and at d = 64 768, 772) query blocks, list lengths at both ends of the rules
+@pytest.mark.parametrize("head_dim,heads,frame_len,length", [
+    (128, 33, 97, 2), (128, 33, 96, 14), (128, 64, 65, 15), (128, 129, 64, 8), (128, 128, 97, 9), (128, 129, 97, 9), (128, 128, 96, 129),
+    (64, 33, 97, 3), (64, 64, 96, 10), (64, 64, 65, 11), (64, 129, 64, 6), (64, 129, 97, 7), (64, 192, 96, 9), (64, 193, 65, 9), (64, 129, 64, 140)])
+def test_lists_in_two_parts(gpu, head_dim, heads, frame_len, length):  # noqa: F811
+    torch, lf = gpu
+    nb = -(-frame_len // 64)
+    frames = max(2, -(-length // nb) + 1)
+    rng = np.random.default_rng(frame_len + length)
+    n_q, n_k = 2 * nb, frames * nb
+    lists = _lists(rng, heads, n_q, n_k, length)
+    print(f"two parts: {heads * n_q} blocks d={head_dim} n={frame_len} list length {length}", flush=True)
+    x, grads = _gradients(torch, lf, rng, heads, frame_len, 2, frames, head_dim, lists)
+    Q, K, V = (_dev(torch, x[k]) for k in "QKV")
+    got = lf.lf_sparse_attn(Q, K, V, torch.from_numpy(lists).cuda(), frame_len, 64).float().cpu().numpy().astype(np.float64)
+    for h in {0, heads - 1}:
+        _check_head(x, grads, lists, h, n_k, frame_len)
+        Qf, Kf, Vf = (_host_f32(x[k][h]) for k in "QKV")
+        for r in range(n_q):
+            kept = [int(c) for c in lists[h, r] if 0 <= c < n_k]
+            lo, hi = O.block_token_range(r, frame_len, 64)
+            ref = O.sparse_attention_block(Qf, Kf, Vf, r, kept, frame_len, 64) if kept else 0.0
+            err = np.abs(got[h, lo:hi] - ref)
+            assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (h, r, err.max(), err.mean())
