@@ -24,12 +24,13 @@
 //
 // The same per-wavefront step serves two kernels.  The list-driven one above, and a dense one
 // for KV blocks that every query block of a head keeps (the always-selected current-chunk
-// frames of Eq. 9): there a workgroup of 4 wavefronts owns 128 consecutive query rows and
+// frames of Eq. 9, where there are many of them: lf_two_phases): there a workgroup of 4 wavefronts owns 128 consecutive query rows and
 // walks one contiguous KV token range, so a K/V half tile brought into LDS serves 4 x 32 query
 // rows instead of 2 x 32 (8 wavefronts per workgroup measured slower: then the two wavefronts
 // of a SIMD wait at the same barrier and run their phases in step).  The dense kernel leaves its online-softmax state (reference m, row
-// sum l, unnormalised O) per query row in float32, and the list-driven kernel can start from
-// such a state instead of from zero: together they compute one softmax over the union.
+// sum l, unnormalised O) per query row in float32, and the undivided list-driven kernel can start from
+// such a state instead of from zero: together they compute one softmax over the union.  Elsewhere those blocks
+// are the unread last entries of every list (own_len, tail0).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -54,6 +55,8 @@ struct AttnArgs {
   int64_t v_stride_tok, v_stride_head, o_stride_tok, o_stride_head;
   int n, nb, n_q, n_k;
   int list_len;     // entries walked per list
+  int own_len;      // ... of which this many are read; entry i beyond is block tail0 + i
+  int tail0;
   int list_stride;  // entries between two lists in memory
   int total_wg, wg_per_xcd;
   float c;  // softmax_scale * log2(e)
@@ -114,7 +117,7 @@ __device__ __forceinline__ void lds_barrier() {
 // workgroup measured 2 % faster than one; the lists are equally long).  SPLIT > 1 (= WAVES / 2): the
 // pairs share one query block, each walks a SPLIT-th of its list, and their online-softmax states
 // are merged through LDS at the end.  All pairs start from the reference that one pair walking the whole
-// list would take (the row maxima of the list's first half tile, or that of the state carried on), so that the probabilities are rounded to the same bfloat16 values in either form and only the
+// list would take (the row maxima of the list's first half tile), so that the probabilities are rounded to the same bfloat16 values in either form and only the
 // order of float32 sums differs.  A call with few query blocks leaves compute units idle while
 // every wavefront goes through its list step by step (one wavefront per SIMD: 0.55 - 0.8 us a step,
 // mostly latency); dividing the list shortens that chain.
@@ -182,14 +185,16 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   // A slice is entries [qb slice_len, (qb + 1) slice_len) of the list, the last ones shorter or empty.
   const int slice_len = SPLIT > 1 ? (a.list_len + SPLIT - 1) / SPLIT : a.list_len;
   const int my_len = SPLIT > 1 ? min(max(a.list_len - qb * slice_len, 0), slice_len) : a.list_len;
-  const int32_t* list = DENSE ? nullptr : a.idx + ((int64_t)h * a.n_q + r) * a.list_stride + (SPLIT > 1 ? qb * slice_len : 0);
+  const int first = SPLIT > 1 ? qb * slice_len : 0;
+  const int32_t* list = DENSE ? nullptr : a.idx + ((int64_t)h * a.n_q + r) * a.list_stride + first;
+  const int my_own = min(my_len, a.own_len - first);   // entries of the slice that are read
   constexpr int EPT = DENSE ? 1 : kMaxEnt / 2 / kThreads;   // list entries per thread and pass (up to two half tiles each)
   int pre[EPT];
   if constexpr (!DENSE) {
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
       const int i = EPT * tid + j;
-      pre[j] = i < my_len ? list[i] : -1;
+      pre[j] = i < my_own ? list[i] : -1;
     }
   }
   // A wavefront whose 32 query rows all lie past the end of a short query block loads its share
@@ -329,29 +334,24 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   // Accumulator i of oacc[mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of query row qrow; the
   // stored state uses the same order within a row, so a lane moves float4s.
   float* state_row = nullptr;
-  if (a.state_o != nullptr && qrow < q_cnt) {
+  if (SPLIT == 1 && a.state_o != nullptr && qrow < q_cnt) {
     const int64_t row = (int64_t)h * a.q_len + qtok0 + qrow;
     state_row = a.state_o + row * D;
     if constexpr (!DENSE) {
       const float2 ml = a.state_ml[row];
       m_run = ml.x;
-      if (SPLIT == 1 || qb == 0) {         // one slice carries the state on, all start from its reference
-        l_run = kg == 0 ? ml.y : 0.0f;     // the two lanes of a row each carry part of the sum
+      l_run = kg == 0 ? ml.y : 0.0f;       // the two lanes of a row each carry part of the sum
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const float4 v = *reinterpret_cast<const float4*>(state_row + 32 * mb + 8 * g + 4 * kg);
-            oacc[mb][4 * g + 0] = v.x; oacc[mb][4 * g + 1] = v.y;
-            oacc[mb][4 * g + 2] = v.z; oacc[mb][4 * g + 3] = v.w;
-          }
-      }
+        for (int g = 0; g < 4; ++g) {
+          const float4 v = *reinterpret_cast<const float4*>(state_row + 32 * mb + 8 * g + 4 * kg);
+          oacc[mb][4 * g + 0] = v.x; oacc[mb][4 * g + 1] = v.y;
+          oacc[mb][4 * g + 2] = v.z; oacc[mb][4 * g + 3] = v.w;
+        }
     }
   }
-  // Divided list: the reference is taken from the list's first half tile, by the wavefronts that would
-  // move theirs there if they walked it alone: those without a state, and those with rows past a short
-  // block's end (such a row has no state, and when one row moves all of the wavefront do).
-  bool need_ref = SPLIT > 1 && (a.state_o == nullptr || q_cnt % 32 != 0);
+  bool need_ref = SPLIT > 1;   // divided list: the reference is taken from the list's first half tile, once
 
   // Between the wavefronts that share a tile stage; one that has it alone waits for its own LDS reads only.
   auto tile_barrier = []() __attribute__((always_inline)) {
@@ -396,7 +396,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
         const int i = l0 + EPT * tid + e;
-        const int c = i < min(l1, my_len) ? (l0 == 0 ? pre[e] : list[i]) : -1;
+        int c = i < min(l1, my_own) ? (l0 == 0 ? pre[e] : list[i]) : -1;
+        if (i >= my_own && i < min(l1, my_len)) c = a.tail0 + first + i;
         const bool ok = (unsigned)c < (unsigned)a.n_k;
         const int tau = ok ? c / a.nb : 0, j = ok ? c % a.nb : 0;
         htok[e] = tau * a.n + j * 64;
@@ -490,18 +491,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
         const int cnt = __builtin_amdgcn_readfirstlane(e_ref.y);
         f32x16 sref = s_half(buf1 + TILE, s_half(buf1 + TILE, zero16, 0), KS / 2);
         if (cnt < 32) mask_past(sref, cnt);
-        if (a.state_o == nullptr || 32 * rh + 32 > q_cnt) {
-          const float m_new = fmaxf(m_run, row_max(sref) * a.c);
-          if (a.state_o != nullptr) {      // without one there is nothing to rescale yet
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-            l_run *= alpha;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
-          }
-          m_run = m_new;
-        }
+        m_run = fmaxf(m_run, row_max(sref) * a.c);
         need_ref = false;
       }
     }
@@ -520,6 +510,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       if (cnt < 32) mask_past(sacc, cnt);
       f32x16 snext = s_half(other, zero16, 0);
       fetch_k(krs, cur);
+      // Here the compiler would put the exponentials ahead of the request (144 blocks, lists of 99: 34.9 us instead of 34.5, 36.4 instead of 35.1 with
+      // tiles that are in no cache yet); elsewhere the fixed place is 1 - 3 % slower.
+      if constexpr (D == 64 && SPLIT == 4) __builtin_amdgcn_sched_barrier(0);
       // P^T = exp2(s c - m_run), packed to bfloat16 in the
       // B-operand layout of the second product; row sums from the packed values.
       bf16x8 pf[2];
@@ -782,8 +775,9 @@ static AttnArgs attn_args(const void* Q, const void* K, const void* V, const lf_
   return a;
 }
 
-// List-driven kernel: walks the first list_len entries of every list (lists are list_stride
-// entries apart); with a state (state_o, state_ml) it continues that online softmax.
+// List-driven kernel: walks the list_len entries of every list.  With a state (state_o, state_ml: lists of list_stride entries whose
+// last ones are the current chunk's blocks) it continues that online softmax over the first list_len of them, or, where
+// lf_launch_attn_dense has left none, walks them all, the last list_stride - list_len without reading them.
 int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* s,
                    const lf_dims* dm, const int32_t* indices, int32_t list_len, int32_t list_stride,
                    float scale, void* O, const float* state_o, const float* state_ml, float* lse2,
@@ -792,13 +786,19 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.O = (uint16_t*)O;
   a.lse2 = lse2;
   a.idx = indices;
+  a.own_len = list_len;
+  a.tail0 = dm->n_k - list_stride;
+  a.total_wg = dm->H * dm->n_q;
+  if (state_o != nullptr && !lf_two_phases(dm->d, a.total_wg, dm->n_q)) {
+    state_o = state_ml = nullptr;
+    list_len = list_stride;
+  }
   a.list_len = list_len;
   a.list_stride = list_stride;
   a.state_o = const_cast<float*>(state_o);
   a.state_ml = reinterpret_cast<float2*>(const_cast<float*>(state_ml));
-  a.total_wg = dm->H * dm->n_q;
   hipStream_t st = (hipStream_t)stream;
-  if (lf_halve_blocks(dm->d, a.total_wg, list_len)) {
+  if (state_o == nullptr && lf_halve_blocks(dm->d, a.total_wg, list_len)) {
     a.total_wg *= 2;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
@@ -807,7 +807,7 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
         : lf_launch(lf_attn_kernel<64, 8, false, 8, false, true>, dim3(grid), dim3(512), 0, st, a);
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
-  const int parts = lf_two_parts(dm->d, a.total_wg, list_len) ? 2 : lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k) ? 4 : 1;
+  const int parts = state_o != nullptr ? 1 : lf_two_parts(dm->d, a.total_wg, list_len) ? 2 : lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k) ? 4 : 1;
   if (parts > 1) {
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
@@ -824,9 +824,9 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   // 196 -> 214; 1 536, of 64: 206 -> 217; 2 560 (half a last round), of 64: 333 -> 343.
   // Probe builds lengthen this file's kernel, so they stay with it.
 #ifndef LF_PROBE
-  if (dm->d == 128 && list_len >= 32 && a.total_wg > 512 &&
+  if (dm->d == 128 && state_o == nullptr && list_len >= 32 && a.total_wg > 512 &&
       (a.total_wg <= 1024 || (a.total_wg - 1) % 1024 >= 700))
-    return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, list_stride, scale, O, state_o, state_ml, lse2, stream);
+    return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, scale, O, lse2, stream);
 #endif
   // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
   // whole blocks to the end (lists of 32 and more have gone to the other kernel by here).  Measured late -> early, us, lists as
@@ -847,10 +847,12 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
 }
 
 // Dense kernel over KV tokens [kv0, kv1) for every query row of every head; writes the state.
-// The rows of a head are dealt evenly to ceil(q_len / (32 WAVES)) workgroups.
+// The rows of a head are dealt evenly to ceil(q_len / (32 WAVES)) workgroups.  Launches nothing where
+// lf_launch_attn takes the blocks of that range with the others (lf_two_phases).
 int lf_launch_attn_dense(const void* Q, const void* K, const void* V, const lf_shape* s,
                          const lf_dims* dm, int kv0, int kv1, float scale, float* state_o,
                          float* state_ml, void* stream) {
+  if (!lf_two_phases(dm->d, dm->H * dm->n_q, dm->n_q)) return LF_OK;
   AttnArgs a = attn_args(Q, K, V, s, dm, scale);
   a.state_o = state_o;
   a.state_ml = reinterpret_cast<float2*>(state_ml);

@@ -36,12 +36,10 @@ struct WideArgs {
   uint32_t k_row_bytes, v_row_bytes;
   int n, nb, n_q, n_k;
   uint32_t nb_inv;      // floor((2^32 - 1) / nb)
-  int list_len, list_stride;
+  int list_len, own_len, tail0;   // entries of a list; those of them that are read; entry i beyond is block tail0 + i
   int total, wg_per_xcd;
   float c;              // softmax_scale * log2(e)
   float* lse2;
-  const float* state_o;   // O and (m, l) to go on from, or null
-  const float2* state_ml;
   int q_len;
 };
 
@@ -89,7 +87,7 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
   const int h = w / a.n_q, r = w % a.n_q;
   const int lane = threadIdx.x & 63, ln = lane & 31, kg = lane >> 5;
   const int jb = r % a.nb, qtok0 = (r / a.nb) * a.n + jb * 64, q_cnt = min(64, a.n - jb * 64);
-  const int32_t* list = a.idx + ((int64_t)h * a.n_q + r) * a.list_stride;
+  const int32_t* list = a.idx + ((int64_t)h * a.n_q + r) * a.list_len;
 
   bf16x8 qf[2][KS];
 #pragma unroll
@@ -186,27 +184,6 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
   // for the largest call, 323 with these products (and 340 with the values taken apart and added in float32).
   f32x4 l_run[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
   const s16x4 one4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
-  if (a.state_o != nullptr) {
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int row = 32 * hh + ln;
-      if (row >= q_cnt) continue;
-      const int64_t at = (int64_t)h * a.q_len + qtok0 + row;
-      const float2 ml = a.state_ml[at];
-      m_run[hh] = ml.x;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) l_run[hh][i] = kg == 0 ? ml.y : 0.0f;   // the two lanes of a row each carry part of the sum
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 v = *reinterpret_cast<const float4*>(a.state_o + at * D + 32 * mb + 8 * g + 4 * kg);
-          oacc[hh][mb][4 * g + 0] = v.x; oacc[hh][mb][4 * g + 1] = v.y;
-          oacc[hh][mb][4 * g + 2] = v.z; oacc[hh][mb][4 * g + 3] = v.w;
-        }
-    }
-  }
-
   auto row_max = [](const f32x16& sc) __attribute__((always_inline)) {
     float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
 #pragma unroll
@@ -224,11 +201,12 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = i0 + 64 * j + lane;
-        ids[j] = i < l1 ? list[i] : -1;
+        ids[j] = i < min(l1, a.own_len) ? list[i] : -1;
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const uint32_t c = (uint32_t)ids[j];
+        const int i = i0 + 64 * j + lane;
+        const uint32_t c = (uint32_t)(i >= a.own_len && i < l1 ? a.tail0 + i : ids[j]);
         uint32_t tau = __umulhi(c, a.nb_inv);
         uint32_t rem = c - tau * a.nb;
         if (rem >= (uint32_t)a.nb) { rem -= a.nb; ++tau; }
@@ -458,8 +436,8 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
 }  // namespace
 
 int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_shape* s, const lf_dims* dm,
-                        const int32_t* indices, int32_t list_len, int32_t list_stride, float scale, void* O,
-                        const float* state_o, const float* state_ml, float* lse2, void* stream) {
+                        const int32_t* indices, int32_t list_len, int32_t own_len, float scale, void* O, float* lse2,
+                        void* stream) {
   WideArgs a = {};
   a.Q = (const uint16_t*)Q;
   a.K = (const uint16_t*)K;
@@ -480,13 +458,12 @@ int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_sh
   a.n_k = dm->n_k;
   a.nb_inv = 0xffffffffu / (uint32_t)dm->nb;
   a.list_len = list_len;
-  a.list_stride = list_stride;
+  a.own_len = own_len;
+  a.tail0 = dm->n_k - list_len;
   a.total = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total + 7) / 8;
   a.c = scale * 1.4426950408889634f;
   a.lse2 = lse2;
-  a.state_o = state_o;
-  a.state_ml = reinterpret_cast<const float2*>(state_ml);
   a.q_len = dm->f * dm->n;
   return lf_launch(lf_attn_wide_kernel, dim3((unsigned)(a.wg_per_xcd * 8)), dim3(64), 0, (hipStream_t)stream, a) == hipSuccess
              ? LF_OK : LF_ERR_HIP;

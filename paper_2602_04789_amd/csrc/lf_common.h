@@ -89,6 +89,19 @@ inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
 // 21.3 -> 23.1, of 6: 23.7 -> 23.3, of 32: 52.3 -> 43.1; 56 blocks, of 28: 45.9 -> 36.4.
 inline bool lf_halve_blocks_dq(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 4 : 6); }
 
+// Whether lf_sparse_attn_split computes the current chunk's blocks, n_q of them in every list, in a dense phase of their own, whose
+// state the list-driven kernel goes on from.  A tile then serves 128 query rows, but the state of every row goes to memory and
+// back, and both phases have a last round to fill.  One pass, in how much of the time of two phases (lists of 7 and 60 beside the chunk's blocks):
+//   chunks of 75 blocks: 16 query blocks 0.51, 300 0.75, 450 0.82, 900 0.94, 3 000 0.95 (d = 64: 0.99), 6 000 0.94;
+//   of 150: 450 0.87, 900 0.95, 2 400 0.98 - 1.02, 3 600 1.05, 6 000 0.97 - 0.99;
+//   of 200: 800 0.95 (d = 64: 1.00), 1 200 1.00 - 1.02, 2 400 1.01 - 1.04, 4 800 0.98;  of 225: 900 0.97, 1 350 1.01, 1 800 0.96, 2 700 1.03, 5 400 1.05;
+//   of 300: 600 0.95, 900 0.97 (d = 64: 1.01), 1 200 1.02, 1 800 0.97 (d = 64: 1.02), 3 600 1.09, 7 200 1.09;
+// d = 128 with a well filled last round has the kernel of lf_attn_wide.hip for the one pass (1 800, 4 800 above).
+inline bool lf_two_phases(int d, int blocks, int n_q) {
+  if (n_q < 200) return false;
+  return d == 64 ? blocks > 768 : blocks > 1024 && (blocks - 1) % 1024 < 700;
+}
+
 // Kernel launchers (defined in the .hip files); return LF_OK or LF_ERR_HIP.
 int lf_launch_select(const void* Q, const void* K, const lf_shape* s, const lf_budget* b,
                      const lf_dims* dm, int32_t* indices, void* workspace, void* stream);
@@ -102,10 +115,10 @@ int lf_launch_qk_norm_rope(const void* X, const float* g, const float* cosv, con
 // Device address of the library's static scratch on the current device (looked up on the first
 // call per device); LF_OK or LF_ERR_HIP.
 int lf_static_scratch(void** ptr);
-// The undivided call at d = 128 with one wavefront per query block.
+// The undivided call at d = 128 with one wavefront per query block; entries from own_len on are the cache's last blocks, unread.
 int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_shape* s, const lf_dims* dm,
-                        const int32_t* indices, int32_t list_len, int32_t list_stride, float scale, void* O,
-                        const float* state_o, const float* state_ml, float* lse2, void* stream);
+                        const int32_t* indices, int32_t list_len, int32_t own_len, float scale, void* O, float* lse2,
+                        void* stream);
 int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* s,
                    const lf_dims* dm, const int32_t* indices, int32_t list_len, int32_t list_stride,
                    float scale, void* O, const float* state_o, const float* state_ml, float* lse2,

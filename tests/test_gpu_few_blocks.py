@@ -64,8 +64,9 @@ def test_forward_of_few_query_blocks(gpu, heads, frame_len, frames, length, head
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("frame_len,keep", [(96, 2), (97, 7), (200, 19)])
-def test_a_state_is_continued_over_few_query_blocks(gpu, frame_len, keep, head_dim):  # noqa: F811
-    """The list-driven phase after the dense one over the current chunk, a slice of which carries the state."""
+def test_current_blocks_behind_the_read_entries(gpu, frame_len, keep, head_dim):  # noqa: F811
+    """lf_sparse_attn_split on few query blocks, one pass: the list's first entries are read, the current chunk's blocks are
+    taken without reading their entries."""
     torch, lf = gpu
     w = synth.small_ragged(frame_len=frame_len, chunk_idx=6, heads=2, head_dim=head_dim)
     x = synth.make_inputs(w)
@@ -77,7 +78,9 @@ def test_a_state_is_continued_over_few_query_blocks(gpu, frame_len, keep, head_d
     lists = np.stack([np.stack([np.concatenate([np.sort(rng.permutation(n_k - n_q)[:keep]), np.arange(n_k - n_q, n_k)])
                                 for _ in range(n_q)]) for _ in range(w.heads)]).astype(np.int32)
     Q, K, V = (_dev(torch, x[k]) for k in "QKV")
-    got = lf.lf_sparse_attn_split(Q, K, V, torch.from_numpy(lists).cuda(), frame_len, 64, b).float().cpu().numpy().astype(np.float64)
+    unread = lists.copy()
+    unread[:, :, keep:] = -7
+    got = lf.lf_sparse_attn_split(Q, K, V, torch.from_numpy(unread).cuda(), frame_len, 64, b).float().cpu().numpy().astype(np.float64)
     Qf, Kf, Vf = (_host_f32(x[k]) for k in "QKV")
     for h in range(w.heads):
         for r in range(n_q):
