@@ -164,6 +164,13 @@ def make_shape(Q, K, V=None, O=None, frame_len: int = 0, block: int = 64) -> lf_
                     i(os_(1)), i(os_(0)))
 
 
+def _shape_of(Q, K, qs, ks, vs, os_, frame_len, block) -> lf_shape:
+    """make_shape of tensors whose strides _strides has returned (plain numbers: 0.5 us instead of 1.6)."""
+    heads, q_len, d = Q.shape
+    return lf_shape(heads, d, int(frame_len), int(block), q_len, K.shape[1], LF_BF16, 0,
+                    qs[1], qs[0], ks[1], ks[0], vs[1], vs[0], os_[1], os_[0])
+
+
 def lf_workspace_bytes(shape: lf_shape, budget: lf_budget) -> int:
     return int(load().lf_workspace_bytes(C.byref(shape), C.byref(budget)))
 
@@ -196,6 +203,16 @@ def _check_tensor(t, name: str):
         raise ValueError(f"{name} must be [H, L, d] with d contiguous")
 
 
+def _strides(t, name: str):
+    """Strides of a tensor that _check_tensor accepts, all in one call."""
+    if t.is_cuda and t.dtype is (_torch or _get_torch()).bfloat16:
+        st = t.stride()
+        if len(st) == 3 and st[2] == 1:
+            return st
+    _check_tensor(t, name)
+    return t.stride()
+
+
 def _stream_ptr(stream) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
@@ -213,18 +230,16 @@ def lf_select_mask(Q, Kcache, frame_len: int, block: int, budget: lf_budget, ind
                    workspace=None, stream=None):
     """Enqueue mask selection; returns the int32 [H, n_q, list_len] index tensor (device)."""
     torch = _torch or _get_torch()
-    _check_tensor(Q, "Q")
-    _check_tensor(Kcache, "Kcache")
-    sh = make_shape(Q, Kcache, frame_len=frame_len, block=block)
-    lib = load()
+    qs, ks = _strides(Q, "Q"), _strides(Kcache, "Kcache")
+    sh = _shape_of(Q, Kcache, qs, ks, ks, qs, frame_len, block)
     nb = -(-frame_len // block)
-    n_q = (sh.q_len // frame_len) * nb if frame_len > 0 else 0
     if indices is None:
+        n_q = (sh.q_len // frame_len) * nb if frame_len > 0 else 0
         indices = torch.empty((sh.heads, n_q, max(int(budget.list_len), 0)), dtype=torch.int32,
                               device=Q.device)
     if workspace is None:
         workspace = torch.empty(max(lf_workspace_bytes(sh, budget), 256), dtype=torch.uint8, device=Q.device)
-    rc = lib.lf_select_mask(Q.data_ptr(), Kcache.data_ptr(), C.byref(sh), C.byref(budget),
+    rc = (_lib or load()).lf_select_mask(Q.data_ptr(), Kcache.data_ptr(), C.byref(sh), C.byref(budget),
                             indices.data_ptr(), workspace.data_ptr(),
                             workspace.numel() * workspace.element_size(), _stream_ptr(stream))
     if rc != LF_OK:
@@ -279,20 +294,19 @@ def lf_select_mask_cached(Q, kcache, max_frames: int, kv_len: int, frame_len: in
     """Mask selection with the pooled keys taken from ``kcache``; returns the index tensor.
     With ``Kcache`` the current chunk's block means are refreshed from it in the same call."""
     torch = _torch or _get_torch()
-    _check_tensor(Q, "Q")
-    if Kcache is not None:
-        _check_tensor(Kcache, "Kcache")
-    sh = make_shape(Q, Q if Kcache is None else Kcache, frame_len=frame_len, block=block)
+    qs = _strides(Q, "Q")
+    ks = qs if Kcache is None else _strides(Kcache, "Kcache")
+    sh = _shape_of(Q, Q if Kcache is None else Kcache, qs, ks, ks, qs, frame_len, block)
     sh.kv_len = int(kv_len)
     nb = -(-frame_len // block)
-    n_q = (sh.q_len // frame_len) * nb if frame_len > 0 else 0
     if indices is None:
+        n_q = (sh.q_len // frame_len) * nb if frame_len > 0 else 0
         indices = torch.empty((sh.heads, n_q, max(int(budget.list_len), 0)), dtype=torch.int32,
                               device=Q.device)
     if workspace is None:
         workspace = torch.empty(max(lf_workspace_bytes(sh, budget), 256), dtype=torch.uint8,
                                 device=Q.device)
-    rc = load().lf_select_mask_cached(Q.data_ptr(), None if Kcache is None else Kcache.data_ptr(),
+    rc = (_lib or load()).lf_select_mask_cached(Q.data_ptr(), None if Kcache is None else Kcache.data_ptr(),
                                       kcache.data_ptr(),
                                       kcache.numel() * kcache.element_size(), int(max_frames),
                                       C.byref(sh), C.byref(budget), indices.data_ptr(),
@@ -308,21 +322,19 @@ def lf_sparse_attn(Q, Kcache, Vcache, indices, frame_len: int, block: int,
                    softmax_scale: float = 0.0, O=None, stream=None):
     """Enqueue blockwise sparse attention; returns O (bfloat16 [H, q_len, d], device)."""
     torch = _torch or _get_torch()
-    _check_tensor(Q, "Q")
-    _check_tensor(Kcache, "Kcache")
-    _check_tensor(Vcache, "Vcache")
+    qs, ks, vs = _strides(Q, "Q"), _strides(Kcache, "Kcache"), _strides(Vcache, "Vcache")
     if not indices.is_cuda or indices.dtype != torch.int32 or not indices.is_contiguous():
         raise ValueError("indices must be a contiguous int32 GPU tensor [H, n_q, list_len]")
     if O is None:
         O = torch.empty_like(Q, memory_format=torch.contiguous_format)
-    _check_tensor(O, "O")
-    sh = make_shape(Q, Kcache, Vcache, O, frame_len=frame_len, block=block)
+    sh = _shape_of(Q, Kcache, qs, ks, vs, _strides(O, "O"), frame_len, block)
     n_q = (sh.q_len // frame_len) * (-(-frame_len // block)) if frame_len > 0 else -1
-    if indices.dim() != 3 or indices.shape[0] != sh.heads or indices.shape[1] != n_q:
+    ishape = indices.shape
+    if len(ishape) != 3 or ishape[0] != sh.heads or ishape[1] != n_q:
         raise ValueError("indices must be [H, n_q, list_len]")
-    rc = load().lf_sparse_attn(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), C.byref(sh),
-                               indices.data_ptr(), int(indices.shape[-1]), float(softmax_scale),
-                               O.data_ptr(), _stream_ptr(stream))
+    rc = (_lib or load()).lf_sparse_attn(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), C.byref(sh),
+                                         indices.data_ptr(), ishape[2], float(softmax_scale),
+                                         O.data_ptr(), _stream_ptr(stream))
     if rc != LF_OK:
         raise LfError(rc, "lf_sparse_attn")
     return O
@@ -337,21 +349,18 @@ def lf_sparse_attn_split(Q, Kcache, Vcache, indices, frame_len: int, block: int,
     """Blockwise sparse attention in two phases (dense over the current chunk, list-driven over
     the retrieved blocks); returns O.  ``indices`` as written by lf_select_mask for ``budget``."""
     torch = _torch or _get_torch()
-    _check_tensor(Q, "Q")
-    _check_tensor(Kcache, "Kcache")
-    _check_tensor(Vcache, "Vcache")
+    qs, ks, vs = _strides(Q, "Q"), _strides(Kcache, "Kcache"), _strides(Vcache, "Vcache")
     if not indices.is_cuda or indices.dtype != torch.int32 or not indices.is_contiguous():
         raise ValueError("indices must be a contiguous int32 GPU tensor [H, n_q, list_len]")
     if O is None:
         O = torch.empty_like(Q, memory_format=torch.contiguous_format)
-    _check_tensor(O, "O")
-    sh = make_shape(Q, Kcache, Vcache, O, frame_len=frame_len, block=block)
+    sh = _shape_of(Q, Kcache, qs, ks, vs, _strides(O, "O"), frame_len, block)
     n_q = (sh.q_len // frame_len) * (-(-frame_len // block)) if frame_len > 0 else -1
     if indices.dim() != 3 or tuple(indices.shape) != (sh.heads, n_q, int(budget.list_len)):
         raise ValueError("indices must be [H, n_q, budget.list_len]")
     if workspace is None:
         workspace = torch.empty(max(lf_attn_workspace_bytes(sh), 256), dtype=torch.uint8, device=Q.device)
-    rc = load().lf_sparse_attn_split(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), C.byref(sh),
+    rc = (_lib or load()).lf_sparse_attn_split(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), C.byref(sh),
                                      C.byref(budget), indices.data_ptr(), float(softmax_scale),
                                      O.data_ptr(), workspace.data_ptr(),
                                      workspace.numel() * workspace.element_size(), _stream_ptr(stream))
@@ -365,7 +374,8 @@ def _check_lists(indices, sh, frame_len):
     if not indices.is_cuda or indices.dtype != torch.int32 or not indices.is_contiguous():
         raise ValueError("indices must be a contiguous int32 GPU tensor [H, n_q, list_len]")
     n_q = (sh.q_len // frame_len) * (-(-frame_len // sh.block)) if frame_len > 0 else -1
-    if indices.dim() != 3 or indices.shape[0] != sh.heads or indices.shape[1] != n_q:
+    ishape = indices.shape
+    if len(ishape) != 3 or ishape[0] != sh.heads or ishape[1] != n_q:
         raise ValueError("indices must be [H, n_q, list_len]")
 
 
@@ -374,20 +384,17 @@ def lf_sparse_attn_fwd(Q, Kcache, Vcache, indices, frame_len: int, block: int,
     """Blockwise sparse attention that also leaves the rows' log-sum-exp (exp2 domain) for
     lf_sparse_attn_bwd; returns (O, lse2)."""
     torch = _torch or _get_torch()
-    _check_tensor(Q, "Q")
-    _check_tensor(Kcache, "Kcache")
-    _check_tensor(Vcache, "Vcache")
+    qs, ks, vs = _strides(Q, "Q"), _strides(Kcache, "Kcache"), _strides(Vcache, "Vcache")
     if O is None:
         O = torch.empty_like(Q, memory_format=torch.contiguous_format)
-    _check_tensor(O, "O")
-    sh = make_shape(Q, Kcache, Vcache, O, frame_len=frame_len, block=block)
+    sh = _shape_of(Q, Kcache, qs, ks, vs, _strides(O, "O"), frame_len, block)
     _check_lists(indices, sh, frame_len)
     if lse2 is None:
         lse2 = torch.empty((sh.heads, sh.q_len), dtype=torch.float32, device=Q.device)
     if lse2.dtype != torch.float32 or not lse2.is_cuda or not lse2.is_contiguous() \
             or tuple(lse2.shape) != (sh.heads, sh.q_len):
         raise ValueError("lse2 must be a contiguous float32 GPU tensor [H, q_len]")
-    rc = load().lf_sparse_attn_fwd(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), C.byref(sh),
+    rc = (_lib or load()).lf_sparse_attn_fwd(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), C.byref(sh),
                                    indices.data_ptr(), int(indices.shape[-1]), float(softmax_scale),
                                    O.data_ptr(), lse2.data_ptr(), _stream_ptr(stream))
     if rc != LF_OK:
@@ -405,11 +412,11 @@ def lf_sparse_attn_bwd(Q, Kcache, Vcache, O, dO, lse2, indices, frame_len: int, 
     strides of Q, Kcache and Vcache (``grads``: three such tensors to write into instead of new
     ones).  ``indices`` ascending and duplicate-free per list."""
     torch = _torch or _get_torch()
-    for t, name in ((Q, "Q"), (Kcache, "Kcache"), (Vcache, "Vcache"), (O, "O"), (dO, "dO")):
-        _check_tensor(t, name)
-    if tuple(dO.shape) != tuple(O.shape) or dO.stride() != O.stride():
+    qs, ks, vs = _strides(Q, "Q"), _strides(Kcache, "Kcache"), _strides(Vcache, "Vcache")
+    os_, gs = _strides(O, "O"), _strides(dO, "dO")
+    if dO.shape != O.shape or gs != os_:
         raise ValueError("dO must have the shape and strides of O")
-    sh = make_shape(Q, Kcache, Vcache, O, frame_len=frame_len, block=block)
+    sh = _shape_of(Q, Kcache, qs, ks, vs, os_, frame_len, block)
     _check_lists(indices, sh, frame_len)
     if lse2.dtype != torch.float32 or not lse2.is_cuda or not lse2.is_contiguous() \
             or tuple(lse2.shape) != (sh.heads, sh.q_len):
@@ -420,14 +427,13 @@ def lf_sparse_attn_bwd(Q, Kcache, Vcache, O, dO, lse2, indices, frame_len: int, 
         dV = torch.empty_strided(Vcache.shape, Vcache.stride(), dtype=Q.dtype, device=Q.device)
     else:
         dQ, dK, dV = grads
-        for g, t, name in ((dQ, Q, "dQ"), (dK, Kcache, "dK"), (dV, Vcache, "dV")):
-            _check_tensor(g, name)
-            if tuple(g.shape) != tuple(t.shape) or g.stride() != t.stride():
+        for g, t, st, name in ((dQ, Q, qs, "dQ"), (dK, Kcache, ks, "dK"), (dV, Vcache, vs, "dV")):
+            if _strides(g, name) != st or g.shape != t.shape:
                 raise ValueError(f"{name} must have the shape and strides of its input")
     if workspace is None:
         workspace = torch.empty(max(lf_attn_bwd_workspace_bytes(sh), 256), dtype=torch.uint8,
                                 device=Q.device)
-    rc = load().lf_sparse_attn_bwd(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), O.data_ptr(),
+    rc = (_lib or load()).lf_sparse_attn_bwd(Q.data_ptr(), Kcache.data_ptr(), Vcache.data_ptr(), O.data_ptr(),
                                    dO.data_ptr(), lse2.data_ptr(), C.byref(sh), indices.data_ptr(),
                                    int(indices.shape[-1]), float(softmax_scale), dQ.data_ptr(),
                                    dK.data_ptr(), dV.data_ptr(), workspace.data_ptr(),
@@ -442,20 +448,22 @@ def lf_qk_norm_rope(X, g, cos_table, sin_table, heads: int, Y, eps: float = 1e-6
     """RMSNorm + rotary embedding of the token-major activation X [L, >= H*d] (bfloat16) into the
     head-major tensor Y [H, L, d] (bfloat16; may be a view into Q or into the K cache)."""
     torch = _torch or _get_torch()
-    if X.dtype != torch.bfloat16 or Y.dtype != torch.bfloat16 or X.dim() != 2 or Y.dim() != 3:
+    xs, ys, Xsh, Ysh = X.stride(), Y.stride(), X.shape, Y.shape
+    if X.dtype != torch.bfloat16 or Y.dtype != torch.bfloat16 or len(xs) != 2 or len(ys) != 3:
         raise ValueError("X must be bfloat16 [L, H*d] and Y bfloat16 [H, L, d]")
-    if X.stride(1) != 1 or Y.stride(2) != 1 or not (X.is_cuda and Y.is_cuda):
+    if xs[1] != 1 or ys[2] != 1 or not (X.is_cuda and Y.is_cuda):
         raise ValueError("X and Y must be GPU tensors with contiguous channels")
     for t in (g, cos_table, sin_table):
         if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous():
             raise ValueError("g, cos_table, sin_table must be contiguous float32 GPU tensors")
-    heads, tokens, d, Ysh = int(heads), int(X.shape[0]), int(Y.shape[2]), Y.shape
+    heads, tokens, d = int(heads), Xsh[0], Ysh[2]
     p = lf_producer_shape(heads, d, tokens, int(bool(across_heads)), int(pairing), float(eps),
-                          int(X.stride(0)), int(Y.stride(1)), int(Y.stride(0)))
+                          xs[0], ys[1], ys[0])
+    csh = cos_table.shape
     if Ysh[0] != heads or Ysh[1] != tokens or g.numel() != heads * d \
-            or tuple(cos_table.shape) != (tokens, d // 2) or cos_table.shape != sin_table.shape:
+            or csh != (tokens, d // 2) or csh != sin_table.shape:
         raise ValueError("shapes of Y, g or the angle tables do not fit X")
-    rc = load().lf_qk_norm_rope(X.data_ptr(), g.data_ptr(), cos_table.data_ptr(), sin_table.data_ptr(),
+    rc = (_lib or load()).lf_qk_norm_rope(X.data_ptr(), g.data_ptr(), cos_table.data_ptr(), sin_table.data_ptr(),
                                 C.byref(p), Y.data_ptr(), _stream_ptr(stream))
     if rc != LF_OK:
         raise LfError(rc, "lf_qk_norm_rope")
