@@ -1,8 +1,6 @@
 // dQ of the blockwise sparse attention at head dimension 128, one wavefront per query block.
 #include "lf_attn_bwd.h"
-
-#include <type_traits>
-#include <utility>
+#include "lf_slots.h"
 
 namespace {
 
@@ -22,11 +20,6 @@ constexpr int kQWideEnt = 256;     // half tiles decoded per pass: four register
 constexpr int lgkmcnt_imm(int n) { return 15 | (3 << 14) | (7 << 4) | (n << 8); }
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <typename F, int... I>
-__device__ __forceinline__ void each_slot(const F& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
 
 __global__ __launch_bounds__(64, 1) void lf_attn_bwd_q_wide_kernel(BwdArgs a) {
   constexpr int D = 128, CH = D / 8, KS = D / 16, MB = D / 32;
@@ -138,16 +131,6 @@ __global__ __launch_bounds__(64, 1) void lf_attn_bwd_q_wide_kernel(BwdArgs a) {
   auto mfma = [](f32x16& c, const bf16x8& x, const bf16x8& y) __attribute__((always_inline)) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(x), "a"(y));
   };
-
-  // A product with load j of a quarter behind it.  The first one of a quarter sets M0 (the LDS base; the product stands between
-  // that and the load), which nothing else in the loop writes.
-#define LF_LOAD(op, cons, c, x, ycons, y, rs, lds0, o, j)                                                                               \
-  if constexpr ((j) == 0)                                                                                                             \
-    asm volatile("s_mov_b32 m0, %3\n\t" op "\n\tbuffer_load_dwordx4 %4, %5, 0 offen lds"                                             \
-                 : cons(c) : "v"(x), ycons(y), "s"(lds0), "v"(o), "s"(rs) : "memory", "m0");                                            \
-  else                                                                                                                                \
-    asm volatile(op "\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:%5 lds"                                                           \
-                 : cons(c) : "v"(x), ycons(y), "v"(o), "s"(rs), "n"((j) * 1024) : "memory");
 
   f32x16 acc[2][MB];
 #pragma unroll
@@ -340,9 +323,9 @@ __global__ __launch_bounds__(64, 1) void lf_attn_bwd_q_wide_kernel(BwdArgs a) {
           if constexpr (j == 0) rs = l < 8 ? rsrc(Kh, k_pitch, e3, l >> 2) : rsrc(Vh, v_pitch, e3, (l >> 2) - 2);
           const uint32_t lds0 = (l < 8 ? kp : vp) + (l & 4 ? kTile / 2 : 0);
           const uint32_t o = l < 8 ? koff[j] : voff[j];
-          if constexpr (i % 3 == 0) { LF_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+v", sc[0], rk[k], "a", xf[0][k], rs, lds0, o, j) }
-          else if constexpr (i % 3 == 1) { LF_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+v", dp[0], rv[k], "a", yf[0][k], rs, lds0, o, j) }
-          else { LF_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+a", acc[0][k % MB], join(tlo[k], thi[k]), "v",
+          if constexpr (i % 3 == 0) { LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+v", sc[0], rk[k], "a", xf[0][k], rs, lds0, o, j) }
+          else if constexpr (i % 3 == 1) { LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+v", dp[0], rv[k], "a", yf[0][k], rs, lds0, o, j) }
+          else { LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+a", acc[0][k % MB], join(tlo[k], thi[k]), "v",
                          __builtin_bit_cast(bf16x8, pk[0][k / MB]), rs, lds0, o, j) }
         } else {
           if constexpr (i == 0) mfma_zero(sc[0], rk[k], xf[0][k]);
@@ -400,8 +383,6 @@ __global__ __launch_bounds__(64, 1) void lf_attn_bwd_q_wide_kernel(BwdArgs a) {
 }
 
 }  // namespace
-
-#undef LF_LOAD
 
 hipError_t lf_launch_attn_bwd_q_wide(const BwdArgs& a, hipStream_t st) {
   return lf_launch(lf_attn_bwd_q_wide_kernel, dim3((unsigned)(a.wg_per_xcd * 8 + 8)), dim3(64), 0, st, a);

@@ -5,16 +5,21 @@
 // once per 32 query rows, this one once per 64, and it has no barrier: K and V are private to the wavefront, two half tiles of each.
 // A step works on half tile t in 32 slots of one matrix instruction (32 cycles) each, kept as written by sched_barrier: 16 of
 // S of t + 1 and then 16 of O += V^T P of t - 1, with the exponentials of t, the LDS reads for what comes next and the loads of K
-// of t + 3 and V of t + 1 beside them.  O is named by inline assembly in the accumulation half of the register file; scores stay
+// of t + 3 and V of t + 1 beside them.  Products and exponentials are inline assembly: as builtins the compiler moves them
+// together, which leaves slots too full beside empty ones.  A slot holds about one exponential (16 cycles of issue), one scaling,
+// half a conversion and one or two LDS reads or loads; the loads go one to a slot, with M0 written once per four.  O is named by inline assembly in the accumulation half of the register file; scores stay
 // in the other half, where vector instructions reach them (left to itself the compiler copies O around the loop).
 // The compiler does not see those instructions' latency: `settle` waits before O is read or changed.
 // A load goes to the place that the reads before it leave, so each is preceded by a wait that counts the LDS reads issued since.
-// 12 x 128, 4 680 queries, lists of 188 blocks: 333 us before, 323 now; 40 heads: 1 209 and 1 177.
+// 12 x 128, 4 680 queries, lists of 188 blocks: 333 us with two wavefronts per query block, 323 with one, of these slots 319;
+// 12 x 2 880, lists of 40: 70.5 us with the products as builtins and the loads four at a time, 68.9 now; 30 x 6 400, lists of 64:
+// 385 and 381.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
 #include "lf_common.h"
+#include "lf_slots.h"
 
 namespace {
 
@@ -23,7 +28,8 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int int32x4 __attribute__((ext_vector_type(4)));
 
 struct WideArgs {
@@ -183,7 +189,8 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
   // lane sees another row's.  The dot product that adds two values at a time does not overlap with the matrix cores: 332 us with it
   // for the largest call, 323 with these products (and 340 with the values taken apart and added in float32).
   f32x4 l_run[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
-  const s16x4 one4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  u32x2 one4 = {0x3f803f80u, 0x3f803f80u};
+  asm volatile("" : "+a"(one4));   // stays there: made anew in front of a product it would be read too early
   auto row_max = [](const f32x16& sc) __attribute__((always_inline)) {
     float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
 #pragma unroll
@@ -236,7 +243,7 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
 
     bf16x8 kf[KS], vf[2 * MB];
     f32x16 s0[2], s1[2];
-    bf16x8 p0[2][2], p1[2][2];
+    u32x4 p0[2][2], p1[2][2];
     auto read_k = [&](const uint4* tile) __attribute__((always_inline)) {
 #pragma unroll
       for (int s = 0; s < KS; ++s) kf[s] = __builtin_bit_cast(bf16x8, tile[kaddr[s]]);
@@ -268,97 +275,119 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
         for (int i = 0; i < 16; ++i)
           if (8 * (i >> 2) + 4 * kg + (i & 3) >= cnt) sc[hh][i] = -INFINITY;
     };
+    asm volatile("s_nop 15" : "+v"(s0[0]), "+v"(s0[1]));
     if ((e0 & 63u) < 32u) mask(s0, (int)(e0 & 63u));
-    auto step = [&](int t, bool first, bool last, uint4* k_free, uint4* k_next, uint4* vt, f32x16 (&sc)[2], f32x16 (&sn)[2],
-                    bf16x8 (&pc)[2][2], const bf16x8 (&pv)[2][2]) __attribute__((always_inline)) {
+    auto step = [&](int t, auto first_, auto last_, uint4* k_free, uint4* k_next, uint4* vt, f32x16 (&sc)[2], f32x16 (&sn)[2],
+                    u32x4 (&pc)[2][2], const u32x4 (&pv)[2][2]) __attribute__((always_inline)) {
+      constexpr bool first = decltype(first_)::value, last = decltype(last_)::value;
       uint32_t e_raw;
       // V of t - 1 has landed (K of t + 2 and V of t are in flight)
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
       float x[4], ee[4];
-      f32x4 l_new[2] = {l_run[0], l_run[1]};
-      auto xval = [&](int i) __attribute__((always_inline)) { return fmaf(sc[i >> 4][i & 15], a.c, -m_run[i >> 4]); };
-      int32x4 krs, vrs;
+      const u32x2 ones4 = one4;
+      const float l_old[2] = {l_run[0][0], l_run[1][0]};
+      int32x4 rs;
       bf16x4 vlo[2 * MB], vhi[2 * MB];
+      // Value v of the softmax is scaled in slot at(v) = 0 .. 28, exp2 in the next one, packed (odd v) and, four at a time,
+      // added to the row's sum in the one after.
       auto soft = [&](int i) __attribute__((always_inline)) {
-        const int hh = i >> 4, e = i & 15;
-        if (i + 2 < 32) x[(i + 2) & 3] = xval(i + 2);
-        if (i + 1 < 32) ee[(i + 1) & 3] = __builtin_amdgcn_exp2f(x[(i + 1) & 3]);
-        if (e & 1) {
-          const bf16x2 pr = {(__bf16)ee[(i - 1) & 3], (__bf16)ee[i & 3]};
-          pc[hh][e >> 3][(e & 7) - 1] = pr[0];
-          pc[hh][e >> 3][e & 7] = pr[1];
-          if ((e & 3) == 3) {
-            const bf16x4 p4 = {pc[hh][e >> 3][(e & 7) - 3], pc[hh][e >> 3][(e & 7) - 2], pr[0], pr[1]};
-            l_new[hh] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(one4, __builtin_bit_cast(s16x4, p4), l_new[hh], 0, 0, 0);
-          }
-        }
-      };
-      // value v of the softmax belongs to slot v - 4, the first eight to slots 0 to 3
-      auto soft_slot = [&](int i) __attribute__((always_inline)) {
-        if (i == 0) {
-          x[0] = xval(0);
-          x[1] = xval(1);
-          ee[0] = __builtin_amdgcn_exp2f(x[0]);
-        }
-        if (i < 4) { soft(2 * i); soft(2 * i + 1); }
-        else if (i < 28) soft(i + 4);
-      };
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int s = i >> 1, hh = i & 1;
-        if (s == 0) mfma_first(sn[hh], kf[s], qf[hh][s]);
-        else mfma_next(sn[hh], kf[s], qf[hh][s]);
-        if (!first) {
-          if (i & 1) vhi[i >> 1] = vread(vt, i >> 3, 1, (i >> 1) & 3);
+        for (int v = 0; v < 32; ++v) {
+          const int at = v * 28 / 31, hh = v >> 4, e = v & 15;
+          if (i == at + 2 && (e & 1)) {
+            asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(pc[hh][e >> 3][(e & 7) >> 1]) : "v"(ee[(v - 1) & 3]), "v"(ee[v & 3]));
+          }
+          if (i == at + 1) asm volatile("v_exp_f32 %0, %1" : "=v"(ee[v & 3]) : "v"(x[v & 3]));
+          if (i == at) asm volatile("v_fma_f32 %0, %1, %2, -%3" : "=v"(x[v & 3]) : "v"(sc[hh][e]), "s"(a.c), "v"(m_run[hh]));
+        }
+      };
+      // The sums come behind a slot's other instructions, a slot after their last value is packed: a product may read what a
+      // vector instruction wrote two instructions before at the earliest.
+      auto sums = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 3; v < 32; v += 4)
+          if (i == v * 28 / 31 + 3) {
+            const int hh = v >> 4, e = v & 15;
+            const u32x2 p4 = {pc[hh][e >> 3][((e & 7) >> 1) - 1], pc[hh][e >> 3][(e & 7) >> 1]};
+            if (v == 31) asm volatile("s_nop 1\n\tv_mfma_f32_4x4x4_16b_bf16 %0, %1, %2, %0" : "+v"(l_run[hh]) : "a"(ones4), "v"(p4));
+            else asm volatile("v_mfma_f32_4x4x4_16b_bf16 %0, %1, %2, %0" : "+v"(l_run[hh]) : "a"(ones4), "v"(p4));
+          }
+      };
+      auto place = [&](const uint4* dst) __attribute__((always_inline)) {
+        return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)LDS_PTR(void, &st)) +
+               (uint32_t)(reinterpret_cast<const char*>(dst) - reinterpret_cast<const char*>(&st));
+      };
+      auto score_slot = [&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value, s = i >> 1, hh = i & 1;
+        if constexpr (i == 4) rs = rsrc(Kh, a.k_row_bytes, e3);
+        if constexpr (i >= 5 && i < 13) {
+          constexpr int l = i - 5;
+          if constexpr (last) {
+            if constexpr ((l & 3) == 0) fetch4(rs, k_free + (l >> 2) * (TILE / 2), koff + (l & 4));
+          } else {
+            LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+v", sn[hh], kf[s], "a", qf[hh][s], rs,
+                                place(k_free + (l >> 2) * (TILE / 2)), koff[l], l & 3)
+          }
+        } else if constexpr (last) {   // no tile follows
+        } else if constexpr (s == 0) {
+          asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(sn[hh]) : "v"(kf[s]), "a"(qf[hh][s]));
+        } else {
+          asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(sn[hh]) : "v"(kf[s]), "a"(qf[hh][s]));
+        }
+        if constexpr (!first) {
+          if constexpr (hh) vhi[i >> 1] = vread(vt, i >> 3, 1, (i >> 1) & 3);
           else vlo[i >> 1] = vread(vt, i >> 3, 0, (i >> 1) & 3);
         }
-        if (i == 2) krs = rsrc(Kh, a.k_row_bytes, e3);
-        if (i == 4) {   // K of t + 1 is in registers
-          if (first) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(0));
-          else __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(5));
-        }
-        if (i == 5) fetch4(krs, k_free, koff);
-        if (i == 9) fetch4(krs, k_free + TILE / 2, koff + 4);
-        soft_slot(i);
+        if constexpr (i == 4) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(first ? 0 : 5));   // K of t + 1 is in registers
+        soft(i);
+        sums(i);
         __builtin_amdgcn_sched_barrier(0);
-      }
+      };
+      each_slot(score_slot, std::make_integer_sequence<int, 16>{});
 #pragma unroll
       for (int i = 0; i < 2 * MB; ++i) vf[i] = __builtin_shufflevector(vlo[i], vhi[i], 0, 1, 2, 3, 4, 5, 6, 7);
-      if (first) __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));   // K of t + 2
-      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(first ? 8 : 16));   // K of t + 2
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
-      unsigned long long far = 0;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int u = i >> 3, mb = (i >> 1) & 3, hh = i & 1;
-        if (!first) accumulate(oacc[hh][mb], vf[u * MB + mb], pv[hh][u]);
-        if (i < 12 && i % 3 != 2) kf[i - i / 3] = __builtin_bit_cast(bf16x8, k_next[kaddr[i - i / 3]]);
-        if (i == 0) vrs = rsrc(Vh, a.v_row_bytes, e1);
-        if (i == 2) e_raw = st.ent[(t + 4) & (kEnt - 1)];
-        if (i == 4) {   // V of t - 1 is in registers (no reads of K follow in the last step: they are unused there)
-          if (last) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(0));
-          else __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(5));
+      auto value_slot = [&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value, u = i >> 3, mb = (i >> 1) & 3, hh = i & 1;
+        if constexpr (i == 4) rs = rsrc(Vh, a.v_row_bytes, e1);
+        if constexpr (i >= 5 && i < 13) {
+          constexpr int l = i - 5;
+          const uint32_t to = place(vt + (l >> 2) * (TILE / 2));
+          if constexpr (first) {
+            if constexpr ((l & 3) == 0) fetch4(rs, vt + (l >> 2) * (TILE / 2), voff + (l & 4));
+          } else {
+            LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+a", oacc[hh][mb], vf[u * MB + mb], "v",
+                                __builtin_bit_cast(bf16x8, pv[hh][u]), rs, to, voff[l], l & 3)
+          }
+        } else if constexpr (!first) {
+          accumulate(oacc[hh][mb], vf[u * MB + mb], __builtin_bit_cast(bf16x8, pv[hh][u]));
         }
-        if (i == 5) fetch4(vrs, vt, voff);
-        if (i == 9) fetch4(vrs, vt + TILE / 2, voff + 4);
-        soft_slot(16 + i);
-        if (i == 15) far = __ballot(fmaxf(l_new[0][0], l_new[1][0]) > kSumMax);
+        if constexpr (i < 12 && i % 3 != 2) kf[i - i / 3] = __builtin_bit_cast(bf16x8, k_next[kaddr[i - i / 3]]);
+        if constexpr (i == 2) e_raw = st.ent[(t + 4) & (kEnt - 1)];
+        // V of t - 1 is in registers (no reads of K follow in the last step: they are unused there)
+        if constexpr (i == 4) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(last ? 0 : 5));
+        soft(16 + i);
+        sums(16 + i);
         __builtin_amdgcn_sched_barrier(0);
-      }
+      };
+      each_slot(value_slot, std::make_integer_sequence<int, 16>{});
+      asm volatile("s_nop 4" : "+v"(l_run[0]), "+v"(l_run[1]));
+      const unsigned long long far = __ballot(fmaxf(l_run[0][0], l_run[1][0]) > kSumMax);
       const int next_cnt = (int)(e1 & 63u);
       if (far != 0ull || next_cnt < 32) {
         if (far != 0ull) {
           settle();
 #pragma unroll
           for (int hh = 0; hh < 2; ++hh) {
-            if (__ballot(l_new[hh][0] > kSumMax) == 0ull) continue;
+            if (__ballot(l_run[hh][0] > kSumMax) == 0ull) continue;
             const float m_new = fmaxf(m_run[hh], row_max(sc[hh]) * a.c);
             const float alpha = __builtin_amdgcn_exp2f(m_run[hh] - m_new);
             m_run[hh] = m_new;
-            float l = l_run[hh][0] * alpha;
+            float l = l_old[hh] * alpha;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -367,30 +396,29 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
             for (int e = 0; e < 16; e += 2) {
               const float pa = __builtin_amdgcn_exp2f(fmaf(sc[hh][e], a.c, -m_new)), pb = __builtin_amdgcn_exp2f(fmaf(sc[hh][e + 1], a.c, -m_new));
               const bf16x2 pr = {(__bf16)pa, (__bf16)pb};
-              pc[hh][e >> 3][e & 7] = pr[0];
-              pc[hh][e >> 3][(e & 7) + 1] = pr[1];
+              pc[hh][e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, pr);
               l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l, false);
             }
-            l_new[hh][0] = l_new[hh][1] = l_new[hh][2] = l_new[hh][3] = l;
+            l_run[hh][0] = l_run[hh][1] = l_run[hh][2] = l_run[hh][3] = l;
           }
           settle();
         }
         if (next_cnt < 32) mask(sn, next_cnt);
       }
-      l_run[0] = l_new[0];
-      l_run[1] = l_new[1];
       e0 = e1; e1 = e2; e2 = e3;
       e3 = __builtin_amdgcn_readfirstlane(t + 4 < nt ? e_raw : 0u);
       __builtin_amdgcn_sched_barrier(0);
     };
-    step(0, true, false, st.k[1], st.k[0], st.v[1], s0, s1, p0, p1);
+    const std::true_type yes{};
+    const std::false_type no{};
+    step(0, yes, no, st.k[1], st.k[0], st.v[1], s0, s1, p0, p1);
     int t = 1;
     for (; t + 1 < nt; t += 2) {
-      step(t, false, false, st.k[0], st.k[1], st.v[0], s1, s0, p1, p0);
-      step(t + 1, false, false, st.k[1], st.k[0], st.v[1], s0, s1, p0, p1);
+      step(t, no, no, st.k[0], st.k[1], st.v[0], s1, s0, p1, p0);
+      step(t + 1, no, no, st.k[1], st.k[0], st.v[1], s0, s1, p0, p1);
     }
     if (t < nt) {
-      step(t, false, true, st.k[0], st.k[1], st.v[0], s1, s0, p1, p0);
+      step(t, no, yes, st.k[0], st.k[1], st.v[0], s1, s0, p1, p0);
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) { p0[hh][0] = p1[hh][0]; p0[hh][1] = p1[hh][1]; }
     }
@@ -404,7 +432,7 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int u = i >> 3, mb = (i >> 1) & 3, hh = i & 1;
-        accumulate(oacc[hh][mb], vf[u * MB + mb], p0[hh][u]);
+        accumulate(oacc[hh][mb], vf[u * MB + mb], __builtin_bit_cast(bf16x8, p0[hh][u]));
       }
       settle();
     }

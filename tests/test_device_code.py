@@ -90,3 +90,94 @@ def test_the_dq_loop_counts_its_loads(tmp_path):
     m0 = [i for i, x in enumerate(body) if re.match(r"s_\w+ m0,", x)]
     assert len(m0) == 4 and all(sum("buffer_load" in x for x in body[i: i + 3]) == 1 and "v_mfma" in body[i + 1] for i in m0)
     assert not any("m0" in x for i, x in enumerate(body) if i not in m0)
+
+
+def _registers(text):
+    out = set()
+    for m in re.finditer(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)", text):
+        first, last = (m[2], m[3]) if m[2] else (m[4], m[4])
+        out |= {(m[1], i) for i in range(int(first), int(last) + 1)}
+    return out
+
+
+def _hazards(code):
+    """Pairs of a matrix and a vector instruction that stand closer than the hardware allows, in the order of the listing.
+    History entries: text, kind, registers written, wait states from its issue to that of the next instruction."""
+    bad, seen = [], []
+    for line in code:
+        m = re.match(r"([sv]_\w+|ds_\w+|buffer_\w+|global_\w+)\s*(.*)", line)
+        if not m:
+            continue
+        op, args = m[1], re.split(r",\s*(?![^\[]*\])", m[2])
+        product = "mfma" in op
+        vector = op.startswith("v_") and not product
+        written = _registers(args[0]) if product or vector else set()
+        if "swap" in op:
+            written |= _registers(args[1])
+        read = _registers(" ".join(args[1:] if product or vector else args))
+        cost = int(args[0], 0) + 1 if op == "s_nop" else 1
+        since = 0
+        for text, kind, regs, c in reversed(seen):
+            if since >= 11:
+                break
+            if product and kind == "vector" and since < 2 and regs & read:
+                bad.append((since, text, line))
+            need = written | read if vector else read if not product and not op.startswith("s_") else set()
+            if regs & need and since < {"mfma": 11, "small": 5}.get(kind, 0):
+                bad.append((since, text, line))
+            since += c
+        if product:            # issues when the product before it has left the unit: 8 passes of four cycles
+            since = 0
+            for _, kind, _, c in reversed(seen):
+                since += c
+                if kind in ("mfma", "small"):
+                    cost = max(1, (8 if kind == "mfma" else 2) - since)
+                    break
+        kind = ("small" if "4x4x4" in op else "mfma") if product else "vector" if vector else "other"
+        seen = seen[-40:] + [(line, kind, written, cost)]
+    return bad
+
+
+def _assembly(src, tmp_path):
+    try:
+        hipcc = B._hipcc()
+    except RuntimeError:
+        pytest.skip("hipcc not found")
+    out = str(tmp_path / "a.s")
+    subprocess.run([hipcc, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out] + B.COMMON + B.DEVICE +
+                   B.PER_FILE.get(src, []), check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    with open(out) as f:
+        return [x for x in (line.split(";")[0].strip() for line in f) if x]
+
+
+@pytest.mark.parametrize("src", ["lf_attn_wide.hip", "lf_attn_bwd_q_wide.hip", "lf_attn_bwd_wide.hip"])
+def test_products_written_as_assembly_keep_their_distance(src, tmp_path):
+    """What the compiler cannot see: a product needs two wait states behind a vector instruction that writes its source, a
+    vector, LDS or memory instruction eleven behind the product whose result it uses (five behind a 4 x 4 x 4 one)."""
+    assert _hazards(["v_mov_b32 v1, 0", "s_nop 0", "v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], v[8:23]"])
+    assert _hazards(["v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], 0", "s_nop 8", "v_exp_f32 v9, v1"])
+    assert not _hazards(["v_mov_b32 v1, 0", "s_nop 1", "v_mfma_f32_4x4x4_16b_bf16 v[8:11], v[0:1], v[4:5], 0", "s_nop 4",
+                         "v_exp_f32 v9, v1"])
+    assert _hazards(_assembly(src, tmp_path)) == []
+
+
+def test_the_forward_loop_counts_its_loads(tmp_path):
+    """The loop of the forward kernel with one wavefront per query block (two steps of 32 products of 32 x 32 x 16 and 8 sums): 16
+    tile loads a step, two waits for the sixteen before, no register reloaded and no scalar load; M0 is written only with the
+    first load of each group of four."""
+    code = _assembly("lf_attn_wide.hip", tmp_path)
+    labels = {m[1]: i for i, l in enumerate(code) for m in [re.match(r"(\.LBB\w+):", l)] if m}
+    loops = []
+    for i, l in enumerate(code):
+        m = re.match(r"s_c?branch\w*\s+(\.LBB\w+)", l)
+        if m and labels[m[1]] < i and sum("v_mfma_f32_32x32x16" in x for x in code[labels[m[1]]: i]) == 64:
+            loops.append(code[labels[m[1]]: i])
+    body = max(loops, key=len)
+    waits = [x for x in body if "vmcnt" in x]
+    print(waits)
+    assert waits == ["s_waitcnt vmcnt(16)"] * 4 and sum("buffer_load" in x for x in body) == 32
+    assert sum("v_mfma_f32_4x4x4" in x for x in body) == 16
+    assert not any(re.match(r"(scratch|global|flat|s_load|s_buffer)_", x) for x in body)
+    m0 = [i for i, x in enumerate(body) if re.match(r"s_\w+ m0,", x)]
+    assert len(m0) == 8 and all(sum("buffer_load" in x for x in body[i: i + 3]) == 1 and "v_mfma" in body[i + 1] for i in m0)
+    assert not any("m0" in x for i, x in enumerate(body) if i not in m0)
