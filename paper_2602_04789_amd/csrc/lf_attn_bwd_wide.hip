@@ -1,5 +1,6 @@
 // dK and dV of the blockwise sparse attention at head dimension 128, one wavefront per SIMD.
 #include "lf_attn_bwd.h"
+#include "lf_slots.h"
 
 namespace {
 
@@ -13,14 +14,18 @@ namespace {
 // of owner rows.  Role 0 and role 1 need about the same time, so the two SIMDs of a pair wait for each other only a little.
 // The loop is a list of slots, each one matrix instruction (32 cycles) with the vector, LDS and load
 // instructions of another part of the window that fit beside it; the accumulating and the score-like products take turns, since two
-// products into the same accumulators would follow each other at once.  sched_barrier keeps the slots as written.
-// The accumulators are named by inline assembly in the accumulation half of the register file; the compiler keeps the scores in the
-// other half, where vector instructions reach them (left to itself it copies the accumulators around the loop or spills).
+// products into the same accumulators would follow each other at once.  sched_barrier and inline assembly keep the slots as
+// written; a slot has room for seven instructions beside its product.  Loads go one to a slot behind a product, and what they need
+// (resource, addresses of the next places) is made in slots that have room: with loads four at a time, their resources at the
+// window's top and packing where the compiler put it, role 1 had slots of 19 to 23 instructions beside empty ones, and role 0
+// waited for it (training step of 12 x 128, 4 680 queries: 32 760 keys 1 465 -> 1 441 us, 4 680 keys 387.5 -> 379.6).
+// The accumulators are named by inline assembly in the accumulation half of the register file; the scores stay in the other half,
+// where vector instructions reach them (left to itself the compiler copies the accumulators around the loop or spills).
 // The compiler does not see the latency of those instructions: `settle` waits for the last ones before their results are
 // read, and vector results used by them are at least two instructions old (slot order; s_nop before the last products).
-// Largest dK/dV launch of a 12 x 128 model (4 680 queries, 32 760 keys): 1.52 million cycles with that kernel, 1.40 with this one, and
-// the whole backward call 1 215 us before, 1 150 now; with 4 680 keys 316 and 296.  Matrix cores busy for 0.48 of the cycles, a
-// fifth of the wave cycles in waits, about 36 registers a wavefront spilled around the loop (none is touched in it).
+// Largest dK/dV launch of a 12 x 128 model (4 680 queries, 32 760 keys): 1.52 million cycles with that kernel, 1.40 with this one's first form, and
+// the whole backward call 1 215 us and 1 150; with 4 680 keys 316 and 296.  Up to 52 registers a wavefront are spilled around the
+// loop (none is touched in it).
 constexpr int kWideEnt = 512;      // half tiles decoded per pass
 // Up to this many (head, KV block) pairs a block takes two pairs of wavefronts, each with half of the list: a compute unit holds
 // two workgroups of one pair, so fewer blocks leave SIMDs idle.  Backward call in us, one pair and two: 256 blocks with
@@ -39,7 +44,7 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
     uint4 q[4][T32], o[4][T32];             // Q and dO, half tile mod 4
     uint4 p[2][2][2][64];                   // P' handed over: [half tile mod 2][owner half][k-step][lane]
     float4 lse[4][16], nd[4][16];           // row statistics, the upper halves take the zeros of the lanes past the 32 rows
-    uint32_t ent[kWideEnt];                 // first token << 6 | token count per half tile of a pass
+    uint32_t ent[kWideEnt + 8];             // first token << 6 | token count per half tile of a pass; read up to 5 past it
   };
   __shared__ Stage stages[SPLIT];
 
@@ -80,18 +85,18 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
     }
   }
 
-  // Tile loads, global -> LDS: load i of a half tile fills rows [4 i, +4); the buffer resource is the half tile itself,
-  // so rows past its count read as zeros.
+  // Tile loads, global -> LDS, 16 rows at a time: load i fills rows [4 i, +4) of them; the buffer resource is those rows, so rows
+  // past the half tile's count read as zeros, and both parts of a half tile use the same four offsets.
   const char* Qh = reinterpret_cast<const char*>(a.A1 + (int64_t)h * a.a1_head);
   const char* Oh = reinterpret_cast<const char*>(a.A2 + (int64_t)h * a.a2_head);
   const char* Lh = reinterpret_cast<const char*>(a.lse2 + (int64_t)h * a.q_len);
   const char* Dh = reinterpret_cast<const char*>(a.ndelta + (int64_t)h * a.q_len);
   const uint32_t q_pitch = (uint32_t)(a.a1_tok * 2), o_pitch = (uint32_t)(a.a2_tok * 2);
-  uint32_t qoff[8], ooff[8];
+  uint32_t qoff[4], ooff[4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 4; ++i) {
     const int row = 4 * i + (lane >> 4);
-    const uint32_t at = (uint32_t)swz<CH>(row, lane & 15) * 16u - 1024u * (i & 3);
+    const uint32_t at = (uint32_t)swz<CH>(row, lane & 15) * 16u - 1024u * i;
     qoff[i] = (uint32_t)row * q_pitch + at;
     ooff[i] = (uint32_t)row * o_pitch + at;
   }
@@ -105,6 +110,14 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
     rs[2] = __builtin_amdgcn_readfirstlane((int)((e & 63u) * pitch));
     rs[3] = 0x00020000;
     return rs;
+  };
+  auto lower_rows = [](int32x4& rs, uint32_t pitch) __attribute__((always_inline)) {   // from the first 16 rows to the others
+    const uint64_t b = ((uint64_t)(uint32_t)rs[1] << 32 | (uint32_t)rs[0]) + (uint64_t)16 * pitch;
+    rs[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    rs[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    uint32_t end;
+    asm("s_max_u32 %0, %1, %2" : "=s"(end) : "s"(rs[2]), "s"(16u * pitch) : "scc");
+    rs[2] = (int)(end - 16u * pitch);
   };
   auto fetch4 = [&](int32x4 rs, uint32_t lds0, const uint32_t* o) __attribute__((always_inline)) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
@@ -121,15 +134,17 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
   };
   // half tile e (entry) -> a place: nine loads
   auto request_q = [&](uint32_t e, int j) __attribute__((always_inline)) {
-    const int32x4 rs = rsrc(Qh, q_pitch, e);
+    int32x4 rs = rsrc(Qh, q_pitch, e);
     fetch4(rs, lds_at(st.q[j]), qoff);
-    fetch4(rs, lds_at(st.q[j]) + kTile / 2, qoff + 4);
+    lower_rows(rs, q_pitch);
+    fetch4(rs, lds_at(st.q[j]) + kTile / 2, qoff);
     fetch_stat(rsrc(Lh, 4u, e), lds_at(st.lse[j]));
   };
   auto request_o = [&](uint32_t e, int j) __attribute__((always_inline)) {
-    const int32x4 rs = rsrc(Oh, o_pitch, e);
+    int32x4 rs = rsrc(Oh, o_pitch, e);
     fetch4(rs, lds_at(st.o[j]), ooff);
-    fetch4(rs, lds_at(st.o[j]) + kTile / 2, ooff + 4);
+    lower_rows(rs, o_pitch);
+    fetch4(rs, lds_at(st.o[j]) + kTile / 2, ooff);
     fetch_stat(rsrc(Dh, 4u, e), lds_at(st.nd[j]));
   };
 
@@ -144,18 +159,27 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
   };
   auto join = [](const bf16x4& lo, const bf16x4& hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7); };
   // c += x y, held in the accumulation registers
-  auto accumulate = [](f32x16& c, const bf16x8& x, const bf16x8& y) __attribute__((always_inline)) {
+  auto accumulate = [](f32x16& c, const bf16x8& x, const u32x4& y) __attribute__((always_inline)) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
   };
-  auto mfma = [](const bf16x8& x, const bf16x8& y, const f32x16& c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0); };
+  // scores: c = x y from zero, from c0, and c += x y, in registers that vector instructions reach
+  auto mfma_zero = [](f32x16& c, const bf16x8& x, const bf16x8& y) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(x), "v"(y));
+  };
+  auto mfma_from = [](f32x16& c, const bf16x8& x, const bf16x8& y, const f32x16& c0) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(c) : "v"(x), "v"(y), "v"(c0));
+  };
+  auto mfma = [](f32x16& c, const bf16x8& x, const bf16x8& y) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(x), "v"(y));
+  };
 
-  f32x16 acc[2][MB], zero16;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
+  f32x16 acc[2][MB];
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[hh][mb] = zero16;
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[hh][mb][i] = 0.0f;
 
   // the last products into acc[1] have been written
   auto settle = [&]() __attribute__((always_inline)) {
@@ -198,14 +222,19 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
     if (longest == 0) continue;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     auto ent_at = [&](int i) -> uint32_t {
-      const uint32_t e = st.ent[i & (kWideEnt - 1)];
+      const uint32_t e = st.ent[i];
       return __builtin_amdgcn_readfirstlane(i < nt ? e : 0u);
+    };
+    auto entry = [&](int i, uint32_t raw) __attribute__((always_inline)) {      // what was read at i, without a branch
+      uint32_t e;
+      asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, %3, 0" : "=s"(e) : "s"(i), "s"(nt), "s"(__builtin_amdgcn_readfirstlane(raw)) : "scc");
+      return e;
     };
     uint32_t e0 = ent_at(0), e1 = ent_at(1), e2 = ent_at(2);   // half tiles t, t + 1, t + 2
     bf16x8 rf[KS];                     // row fragments
     bf16x4 tlo[2 * MB], thi[2 * MB];   // transposed fragments
     f32x16 sc[2];                      // S' or dP' - delta: [owner half]
-    bf16x8 pk[2][2];                   // P' or dS', packed: [owner half][k-step]
+    u32x4 pk[2][2];                    // P' or dS', packed: [owner half][k-step]
     // LDS addresses of this lane's fragments in place 0: rows of what this role loads, transposed reads of the other's.  Those of the
     // transposed reads are made here in every pass (at_lane hides that they do not change): kept over the whole kernel they are
     // spilled, and the wait for their reload stood in the loop, a vmcnt(0) in every second window that drained the tile loads
@@ -236,24 +265,21 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
       const f32x4 q = *(const __attribute__((address_space(3))) f32x4*)(saddr + 256u * j + 32u * g);
       v[4 * g] = q[0]; v[4 * g + 1] = q[1]; v[4 * g + 2] = q[2]; v[4 * g + 3] = q[3];
     };
-    auto hop_rows = [&]() __attribute__((always_inline)) {
-#pragma unroll
-      for (int s = 0; s < KS; ++s) raddr[s] += (uint32_t)hop;
+    // in slots 8 to 15 of phase 1, one address each: rows behind the first window of a pair, transposed reads behind the second
+    auto hop_one = [&](int b, int i) __attribute__((always_inline)) {
+      uint32_t& at = b == 0 ? raddr[i] : tbase[i];
+      asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(hop));
+      if (b == 1 && i == 7) {
+        far ^= 2 * kTile;
+        hop = -hop;
+      }
     };
-    auto hop_back = [&]() __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < 2 * MB; ++i) tbase[i] += (uint32_t)hop;
-      far ^= 2 * kTile;
-      hop = -hop;
-    };
+    static_assert(KS == 8 && 2 * MB == 8, "one address a slot");
 #pragma unroll
     for (int f = 0; f < 2 * MB; ++f)
 #pragma unroll
       for (int e = 0; e < 4; ++e) tlo[f][e] = thi[f][e] = (__bf16)0.0f;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pk[1][u][e] = (__bf16)0.0f;
+    pk[1][0] = pk[1][1] = u32x4{0u, 0u, 0u, 0u};
     if (role == 0) {
       f32x16 lse;
       float x[2] = {-INFINITY, -INFINITY}, ee[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -262,15 +288,18 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
         sc[1][i] = -INFINITY;
         lse[i] = 0.0f;
       }
-      auto fma_of = [&](int hh, int v) __attribute__((always_inline)) { x[v & 1] = fmaf(sc[hh][v], a.c, -lse[v]); };
-      auto exp_of = [&](int v) __attribute__((always_inline)) { ee[v & 3] = __builtin_amdgcn_exp2f(x[v & 1]); };
-      auto pack_of = [&](int hh, int v) __attribute__((always_inline)) {   // v odd
-        pk[hh][v >> 3][(v & 7) - 1] = (__bf16)ee[(v - 1) & 3];
-        pk[hh][v >> 3][v & 7] = (__bf16)ee[v & 3];
+      auto fma_of = [&](int hh, int v) __attribute__((always_inline)) {
+        asm volatile("v_fma_f32 %0, %1, %2, -%3" : "=v"(x[v & 1]) : "v"(sc[hh][v]), "s"(a.c), "v"(lse[v]));
       };
-      // rows past a short half tile's count were loaded as zeros: their scores become -inf (P' = 0)
+      auto exp_of = [&](int v) __attribute__((always_inline)) { asm volatile("v_exp_f32 %0, %1" : "=v"(ee[v & 3]) : "v"(x[v & 1])); };
+      auto pack_of = [&](int hh, int v) __attribute__((always_inline)) {   // v odd
+        asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(pk[hh][v >> 3][(v & 7) >> 1]) : "v"(ee[(v - 1) & 3]), "v"(ee[v & 3]));
+      };
+      // rows past a short half tile's count were loaded as zeros: their scores become -inf (P' = 0); the last of their products
+      // stands right before
       auto mask = [&](int hh, int cnt) __attribute__((always_inline)) {
         if (cnt < 32) {
+          asm volatile("s_nop 15" : "+v"(sc[hh]));
 #pragma unroll
           for (int i = 0; i < 16; ++i)
             if (8 * (i >> 2) + 4 * kg + (i & 3) >= cnt) sc[hh][i] = -INFINITY;
@@ -289,7 +318,8 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
         for (int i = 0; i < 16; ++i) {
           const int k = i >> 1;
           soft(i, 0);
-          if (i & 1) sc[1] = mfma(rf[k], of[1][k], k == 0 ? zero16 : sc[1]);
+          if (i == 1) mfma_zero(sc[1], rf[k], of[1][k]);
+          else if (i & 1) mfma(sc[1], rf[k], of[1][k]);
           else accumulate(acc[1][k % MB], join(tlo[k], thi[k]), pk[1][k / MB]);
           if (i == 3) stat4(lse, b, 3);
           if (i == 4 && b == 1) saddr += (uint32_t)(hop >> 5);
@@ -302,7 +332,7 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
           }
           if (i >= 9 && (i & 1)) rf[(i - 9) >> 1] = row_frag(b ^ 1, (i - 9) >> 1);
           if (i == 12) st.p[b][0][0][lane] = __builtin_bit_cast(uint4, pk[0][0]);
-          if (i == 14) e_raw = st.ent[(t + 2) & (kWideEnt - 1)];
+          if (i == 14) e_raw = st.ent[t + 2];
           __builtin_amdgcn_sched_barrier(0);
         }
         mask(1, (int)(e0 & 63u));
@@ -311,7 +341,8 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
         for (int i = 0; i < 16; ++i) {
           const int k = i >> 1;
           soft(i, 1);
-          if (i & 1) sc[0] = mfma(rf[k], of[0][k], k == 0 ? zero16 : sc[0]);
+          if (i == 1) mfma_zero(sc[0], rf[k], of[0][k]);
+          else if (i & 1) mfma(sc[0], rf[k], of[0][k]);
           else accumulate(acc[0][k % MB], join(tlo[k], thi[k]), pk[0][k / MB]);
           if (i < 6) {
             const int f = 5 + (i >> 1);
@@ -324,13 +355,12 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
           if (i == 11) stat4(lse, b ^ 1, 1);
           if (i == 13) stat4(lse, b ^ 1, 2);
           if (i == 12) st.p[b][1][0][lane] = __builtin_bit_cast(uint4, pk[1][0]);
-          if (i == 13 && b == 0) hop_rows();
-          if (i == 13 && b == 1) hop_back();
+          if (i >= 8) hop_one(b, i - 8);
           __builtin_amdgcn_sched_barrier(0);
         }
         mask(0, (int)(e1 & 63u));
         e0 = e1;
-        e1 = __builtin_amdgcn_readfirstlane(t + 2 < nt ? e_raw : 0u);
+        e1 = entry(t + 2, e_raw);
         __builtin_amdgcn_sched_barrier(0);
       };
       // the first four half tiles of Q; the others come from the other role
@@ -345,7 +375,11 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
 #pragma unroll
       for (int g = 0; g < 4; ++g) stat4(lse, 0, g);
 #pragma unroll
-      for (int s = 0; s < KS; ++s) sc[0] = mfma(rf[s], of[0][s], s == 0 ? zero16 : sc[0]);
+      for (int s = 0; s < KS; ++s) {
+        if (s == 0) mfma_zero(sc[0], rf[s], of[0][s]);
+        else mfma(sc[0], rf[s], of[0][s]);
+      }
+      asm volatile("s_nop 15" : "+v"(sc[0]));
       mask(0, (int)(e0 & 63u));
       __builtin_amdgcn_sched_barrier(0);
       for (int t = 0; t < longest; t += 2) {
@@ -376,79 +410,94 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
 #pragma unroll
       for (int i = 0; i < 16; ++i) sc[1][i] = 0.0f;
       auto mul_of = [&](int hh, int v) __attribute__((always_inline)) {
-        const bf16x8 p = __builtin_bit_cast(bf16x8, pu[hh][v >> 3]);
-        m[v & 1] = (float)p[v & 7] * sc[hh][v];
-        if (v & 1) {
-          pk[hh][v >> 3][(v & 7) - 1] = (__bf16)m[0];
-          pk[hh][v >> 3][v & 7] = (__bf16)m[1];
-        }
+        const uint32_t p = reinterpret_cast<const uint32_t*>(&pu[hh][v >> 3])[(v & 7) >> 1];
+        if (v & 1)
+          asm volatile("v_and_b32 %1, 0xffff0000, %2\n\tv_mul_f32 %1, %1, %3\n\tv_cvt_pk_bf16_f32 %0, %4, %1"
+                       : "=v"(pk[hh][v >> 3][(v & 7) >> 1]), "=&v"(m[1]) : "v"(p), "v"(sc[hh][v]), "v"(m[0]));
+        else
+          asm volatile("v_lshlrev_b32 %0, 16, %1\n\tv_mul_f32 %0, %0, %2" : "=&v"(m[0]) : "v"(p), "v"(sc[hh][v]));
       };
-      // The pair meets in slot 10 of phase 1, after which P' of half tile t + 1 is there; value v of a half in slot v + 2.
+      // The pair meets in slot 10 of phase 1, behind the window's last load, after which P' of half tile t + 1 is there; value v of a half in slot v + 2.
       // This role loads for both: it has less vector work.
       auto meet = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(18));    // all but the last request of dO and of Q has landed
         lds_barrier();
       };
-      auto window = [&](int t, int b) __attribute__((always_inline)) {
-        uint32_t e_raw = 0;
-        const int32x4 rs = rsrc(Oh, o_pitch, e2), rss = rsrc(Dh, 4u, e2);
-        int32x4 rq, rqs;
+      // The product of slot i with a tile load behind it in slots 2 to 9.
+      int32x4 rs, rl = rsrc(Lh, 4u, 0), rd = rsrc(Dh, 4u, 0);
+      uint32_t e_raw = 0;
+      auto tile_rsrc = [&](const char* base, uint32_t pitch, uint32_t e) __attribute__((always_inline)) {
+        asm volatile("" : "+s"(e));
+        const uint64_t at = (uint64_t)base + (uint64_t)(e >> 6) * pitch;
+        rs[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+        rs[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+        rs[3] = 0x00020000;
+      };
+      // row statistics: the resource ends behind the half tile's rows
+      auto load_stat = [&](int32x4& r, uint32_t e, uint32_t lds0) __attribute__((always_inline)) {
+        asm volatile("" : "+s"(e));      // made here, not at the loop's top
+        const uint32_t first = (e >> 6) * 4u;
+        r[2] = __builtin_amdgcn_readfirstlane((int)(first + (e & 63u) * 4u));
+        uint32_t off;
+        asm volatile("s_mov_b32 m0, %3\n\tv_add_u32 %0, %1, %2\n\tbuffer_load_dword %0, %4, 0 offen lds"
+                     : "=&v"(off) : "s"(first), "v"(st_off), "s"(lds0), "s"(r) : "memory", "m0");
+      };
+      auto window = [&](int t, auto bc) __attribute__((always_inline)) {
+        constexpr int b = decltype(bc)::value;
         const uint32_t here = far ^ (2 * kTile);
         const uint32_t to = b ? here : far + kTile;     // place of half tile t + 3 of dO; that of t + 4 of Q is this one's
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int k = i >> 1;
-          mul_of(i < 2 ? 1 : 0, (i + 14) & 15);
-          if (i & 1) sc[1] = mfma(rf[k], of[1][k], k == 0 ? nd : sc[1]);
-          else accumulate(acc[1][k % MB], join(tlo[k], thi[k]), pk[1][k / MB]);
-          if (i == 3) pu[1][1] = st.p[b][1][1][lane];
-          if (i == 4 && b == 1) saddr += (uint32_t)(hop >> 5);
-          if (i == 2) fetch4(rs, lds_at(st.o[0]) + to, ooff);
-          if (i == 6) fetch4(rs, lds_at(st.o[0]) + to + kTile / 2, ooff + 4);
-          if (i == 8) fetch_stat(rss, lds_at(st.nd[0]) + (to >> 5));
-          if (i >= 4 && i < 14) {
-            const int f = (i - 4) >> 1;
-            if (i & 1) thi[f] = tread(b, f, 1);
-            else tlo[f] = tread(b, f, 0);
+        auto slot = [&](auto ic) __attribute__((always_inline)) {
+          constexpr int ph = decltype(ic)::value >> 4, hh = 1 - ph, i = decltype(ic)::value & 15, k = i >> 1, j = (i - 2) & 3;
+          mul_of(i < 2 ? hh : 1 - hh, (i + 14) & 15);
+          if constexpr (ph == 1 && i == 2) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(10));   // rows 0 to 15 of Q have been read
+          if constexpr (ph == 1 && i == 6) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(3));    // rows 16 to 31
+          if constexpr (i == 6) lower_rows(rs, ph ? q_pitch : o_pitch);
+          const uint32_t lds0 = (ph ? lds_at(st.q[b]) + here : lds_at(st.o[0]) + to) + (i >= 6 ? kTile / 2 : 0);
+          const uint32_t o = i < 2 || i > 9 ? 0u : ph ? qoff[j] : ooff[j];
+          if constexpr (i >= 2 && i < 10) {
+            if constexpr (i & 1) { LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+v", sc[hh], rf[k], "v", of[hh][k], rs, lds0, o, j) }
+            else { LF_PRODUCT_AND_LOAD("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0", "+a", acc[hh][k % MB], join(tlo[k], thi[k]), "v", pk[hh][k / MB], rs, lds0, o, j) }
+          } else if constexpr (i == 1) {
+            mfma_from(sc[hh], rf[k], of[hh][k], nd);
+          } else if constexpr (i & 1) {
+            mfma(sc[hh], rf[k], of[hh][k]);
+          } else {
+            accumulate(acc[hh][k % MB], join(tlo[k], thi[k]), pk[hh][k / MB]);
           }
-          if (i >= 8 && !(i & 1)) stat4(nd, b ^ 1, (i - 8) >> 1);
-          if (i >= 9 && (i & 1)) rf[(i - 9) >> 1] = row_frag(b ^ 1, (i - 9) >> 1);
-          if (i == 15) e_raw = st.ent[(t + 5) & (kWideEnt - 1)];
+          if constexpr (ph == 0) {
+            if constexpr (i == 12) tile_rsrc(Qh, q_pitch, e3);      // of the next phase's loads
+            if constexpr (i == 13) rs[2] = __builtin_amdgcn_readfirstlane((int)((e3 & 63u) * q_pitch));
+            if constexpr (i == 3) pu[1][1] = st.p[b][1][1][lane];
+            if constexpr (i == 4 && b == 1) saddr += (uint32_t)(hop >> 5);
+            if constexpr (i == 10) load_stat(rd, e2, lds_at(st.nd[0]) + (to >> 5));
+            // a fragment of Q gives its place to the next one behind its last product
+            if constexpr (i & 1) {
+              tlo[k] = tread(b, k, 0);
+              thi[k] = tread(b, k, 1);
+            }
+            if constexpr (i >= 8 && !(i & 1)) stat4(nd, b ^ 1, (i - 8) >> 1);
+            if constexpr (i >= 9 && (i & 1)) rf[(i - 9) >> 1] = row_frag(b ^ 1, (i - 9) >> 1);
+            if constexpr (i == 15) e_raw = st.ent[t + 5];
+          } else {
+            if constexpr (i < 8 && (i & 1)) rf[4 + (i >> 1)] = row_frag(b ^ 1, 4 + (i >> 1));
+            if constexpr (i == 13) tile_rsrc(Oh, o_pitch, e3);
+            if constexpr (i == 14) rs[2] = __builtin_amdgcn_readfirstlane((int)((e3 & 63u) * o_pitch));
+            if constexpr (i == 10) {
+              load_stat(rl, e3, lds_at(st.lse[b]) + (here >> 5));
+              meet();
+              pu[0][0] = st.p[b ^ 1][0][0][lane];
+            }
+            if constexpr (i == 11) pu[0][1] = st.p[b ^ 1][0][1][lane];
+            if constexpr (i == 12) pu[1][0] = st.p[b ^ 1][1][0][lane];
+            if constexpr (i >= 8) hop_one(b, i - 8);
+            if constexpr (i == 15) {
+              e2 = e3;
+              e3 = entry(t + 5, e_raw);
+            }
+          }
           __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int k = i >> 1;
-          mul_of(i < 2 ? 0 : 1, (i + 14) & 15);
-          if (i & 1) sc[0] = mfma(rf[k], of[0][k], k == 0 ? nd : sc[0]);
-          else accumulate(acc[0][k % MB], join(tlo[k], thi[k]), pk[0][k / MB]);
-          if (i < 6) {
-            const int f = 5 + (i >> 1);
-            if (i & 1) thi[f] = tread(b, f, 1);
-            else tlo[f] = tread(b, f, 0);
-          }
-          if (i < 8 && (i & 1)) rf[4 + (i >> 1)] = row_frag(b ^ 1, 4 + (i >> 1));
-          if (i == 6) {
-            rq = rsrc(Qh, q_pitch, e3);
-            rqs = rsrc(Lh, 4u, e3);
-          }
-          if (i == 7) {
-            __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(1));      // the transposed fragments of Q are in registers
-            fetch4(rq, lds_at(st.q[b]) + here, qoff);
-          }
-          if (i == 8) fetch4(rq, lds_at(st.q[b]) + here + kTile / 2, qoff + 4);
-          if (i == 9) fetch_stat(rqs, lds_at(st.lse[b]) + (here >> 5));
-          if (i == 11 && b == 0) hop_rows();
-          if (i == 11 && b == 1) hop_back();
-          if (i == 10) meet();
-          if (i == 10) pu[0][0] = st.p[b ^ 1][0][0][lane];
-          if (i == 11) pu[0][1] = st.p[b ^ 1][0][1][lane];
-          if (i == 12) pu[1][0] = st.p[b ^ 1][1][0][lane];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        e2 = e3;
-        e3 = __builtin_amdgcn_readfirstlane(t + 5 < nt ? e_raw : 0u);
+        };
+        each_slot(slot, std::make_integer_sequence<int, 32>{});
       };
       request_o(e0, 0);
       request_o(e1, 1);
@@ -460,7 +509,11 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
 #pragma unroll
       for (int g = 0; g < 4; ++g) stat4(nd, 0, g);
 #pragma unroll
-      for (int s = 0; s < KS; ++s) sc[0] = mfma(rf[s], of[0][s], s == 0 ? nd : sc[0]);
+      for (int s = 0; s < KS; ++s) {
+        if (s == 0) mfma_from(sc[0], rf[s], of[0][s], nd);
+        else mfma(sc[0], rf[s], of[0][s]);
+      }
+      asm volatile("s_nop 15" : "+v"(sc[0]));
       e2 = ent_at(3);
       e3 = ent_at(4);
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(9));     // half tile 1 of dO has landed
@@ -468,10 +521,11 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
       pu[0][0] = st.p[0][0][0][lane];
       pu[0][1] = st.p[0][0][1][lane];
       pu[1][0] = st.p[0][1][0][lane];
+      rs = rsrc(Oh, o_pitch, e2);
       __builtin_amdgcn_sched_barrier(0);
       for (int t = 0; t < longest; t += 2) {
-        window(t, 0);
-        window(t + 1, 1);
+        window(t, std::integral_constant<int, 0>{});
+        window(t + 1, std::integral_constant<int, 1>{});
       }
 #pragma unroll
       for (int v = 14; v < 16; ++v) mul_of(1, v);

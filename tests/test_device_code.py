@@ -52,6 +52,24 @@ def test_loops_wait_for_counted_loads_only(kv_wide):
             assert not any("scratch_" in x or "global_" in x for x in body)
 
 
+def test_tile_loads_stand_behind_products_with_their_m0(kv_wide):
+    """In the loading role's loop M0 is written only with the first load of each group of four (a product between them) and with
+    each load of row statistics, and no scalar load counts with the LDS reads that the loop's waits count."""
+    for name, code in kv_wide.items():
+        code = [x for x in code if x]
+        labels = {m[1]: i for i, l in enumerate(code) for m in [re.match(r"(\.LBB\w+):", l)] if m}
+        ends = [(labels[m[1]], i) for i, l in enumerate(code) for m in [re.match(r"s_c?branch\w*\s+(\.LBB\w+)", l)] if m and labels[m[1]] < i]
+        bodies = [code[a:b] for a, b in ends if sum("v_mfma" in x for x in code[a:b]) == 64]
+        body = next(b for b in bodies if any("buffer_load" in x for x in b))
+        m0 = [i for i, x in enumerate(body) if re.match(r"s_\w+ m0,", x)]
+        print(name, "M0 written", len(m0))
+        assert len(m0) == 12 and all("buffer_load" in body[i + 2] and re.match("v_", body[i + 1]) for i in m0)
+        assert not any("m0" in x for i, x in enumerate(body) if i not in m0)
+        loads = [i for i, x in enumerate(body) if "buffer_load_dwordx4" in x]
+        assert len(loads) == 32 and all("v_mfma" in body[i - 1] for i in loads)
+        assert not any(re.match(r"s_(buffer_)?load", x) for b in bodies for x in b)
+
+
 def test_output_rows_are_staged_behind_a_barrier(kv_wide):
     """Output rows go through LDS where loaded tiles were (the only 8-byte LDS stores): behind the last products stand a wait
     for all loads, then a barrier, then the first of them."""
