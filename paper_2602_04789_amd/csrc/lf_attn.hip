@@ -817,21 +817,21 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
   // One wavefront per query block (lf_attn_wide.hip; d = 128): a SIMD holds one of its wavefronts, so it is
-  // the faster one where the last round of 1 024 query blocks is nearly full, and its start and end count where lists
-  // are short.  Measured, this file's kernel -> that one, us: 576 query blocks, lists of 32: 56.7 -> 52.2; 768, of 64: 110.9 -> 107.8;
-  // 900, of 32: 68.2 -> 65.5, of 128: 234 -> 223; 1 024, of 16: 42.5 -> 42.9, of 64: 134.0 -> 131.6; 1 800, of 16: 77.5 -> 76.4, of
-  // 32: 133 -> 129; 3 000, of 128: 740 -> 709; 6 000, of 128: 1 505 -> 1 447; but 320, of 32: 42 -> 51; 1 152, of 64:
-  // 196 -> 214; 1 536, of 64: 206 -> 217; 2 560 (half a last round), of 64: 333 -> 343.
+  // the faster one where the last round of 1 024 query blocks is more than half full (this file's kernel has room for 2 048
+  // wavefronts of half a block: its last round takes as long for one block as for 1 024), and its start and end count where lists
+  // are short.  How much faster, least and mean of 6 calls each, lists as selected: 513 to 768 blocks, lists of 16 to 23 and 24 to 31:
+  // 1.07, 1.09 and 1.08, 1.10; 769 to 1 024: 1.01, 1.04 and 1.02, 1.03; 1 537 to 1 792, of 16 to 23 and 32 to 63: 1.02, 1.03 and 1.02, 1.04;
+  // 1 793 to 2 048, of 16 to 23: 1.00, 1.02; 2 561 to 2 816: 1.00, 1.01; 2 817 to 3 072: 1.01, 1.03; 3 000, of 128: 740 -> 709 us; but 320, of
+  // 32: 42 -> 51 us; 1 281 to 1 536, of 16 to 63: 0.94, 0.96; 2 305 to 2 560: 0.94, 0.95; 769 to 1 024, of 1 to 9: 0.95, 0.98.
   // Probe builds lengthen this file's kernel, so they stay with it.
 #ifndef LF_PROBE
-  if (dm->d == 128 && state_o == nullptr && list_len >= 32 && a.total_wg > 512 &&
-      (a.total_wg <= 1024 || (a.total_wg - 1) % 1024 >= 700))
+  if (dm->d == 128 && state_o == nullptr && list_len >= 16 && (a.total_wg - 1) % 1024 >= 512)
     return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, scale, O, lse2, stream);
 #endif
   // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
-  // whole blocks to the end (lists of 32 and more have gone to the other kernel by here).  Measured late -> early, us, lists as
-  // selected: whole frames, 594 query blocks, lists of 31: 56.0 -> 54.5; 576, of 22: 42.0 -> 40.9; 816, of 13: 32.6 -> 32.3; 936,
-  // of 11: 30.5 both; 1 014, of 14: 38.0 -> 38.2 (2 458 calls: 1.015 times as fast on the mean, 0.994 at the least); but at most one
+  // whole blocks to the end (lists of 16 and more have gone to the other kernel by here).  Measured late -> early, us, lists as
+  // selected: whole frames, 816 query blocks, lists of 13: 32.6 -> 32.3; 936, of 11: 30.5 both; 1 014, of 14: 38.0 -> 38.2 (2 458 calls with
+  // lists up to 31: 1.015 times as fast on the mean, 0.994 at the least); but at most one
   // workgroup a unit: 384, of 23: 31.0 -> 32.7; a last round that is partly filled: 1 368, of 166: 502 -> 518; ragged
   // frames: 624, of 29: 54.5 -> 55.2.
   const bool early_v = dm->d == 128 && dm->n % 64 == 0 && a.total_wg > 512 && a.total_wg <= 1024;

@@ -375,25 +375,18 @@ constexpr int kKvSplitBlocks = 256;
 // 384 blocks, 2: 22.2 -> 22.6, 11: 47.3 -> 47.9; 480 blocks, 32: 132 -> 137.
 constexpr int kKvHalfBlocks128 = 128, kKvHalfBlocks64 = 352;
 // Whether a call at d = 128 goes to the kernel with one wavefront per SIMD (lf_attn_bwd_wide.hip).  That kernel has the shorter
-// loop, but nobody works on its SIMDs while a list starts and ends, and a compute unit that has only one workgroup left (the
-// last round, of 512) leaves two of its SIMDs idle.  So the lists have to be long enough -- a KV block's list holds
-// list_len n_q / n_k query blocks on the mean -- and the last round more than half full, or one of many.  Backward call in us, this
-// file's kernel and that one, lists of one length:
-//     900 blocks:  mean 10: 102 and 101,  16: 140 and 136,  28: 214 and 202,  45: 324 and 304
-//   1 800 blocks:  mean 10: 175 and 178,  16: 249 and 244,  28: 402 and 386,  45: 631 and 588
-//   6 300 blocks:  mean 10: 559 and 561,  16: 821 and 801,  28: 1 339 and 1 279,  45: 2 085 and 1 981
-//   1 088 blocks (last round 64):  mean 16: 170 and 173,  24: 241 and 240,  32: 316 and 316
-//   256 blocks (two groups or pairs of wavefronts each):  mean 16: 54 and 56;  320 blocks:  mean 10: 50 and 53
-// Lists as the mask selection makes them differ in length, and with few rounds the longest of them decide: how much faster the call
-// is with that kernel, least and mean of 5 to 30 calls:
-//   769 to 1 024 blocks:    mean 18 to 20: 0.97, 1.01;  20 to 22: 0.96, 1.00;  25 to 28: 0.99, 1.03;  28 to 32: 1.00, 1.04;  45: 1.01, 1.05
-//   1 281 to 1 536 blocks:  mean 18 to 20: 0.99, 1.03;  20 to 22: 0.98, 1.04;  22 to 25: 1.01, 1.04;  28 to 32: 1.01, 1.04
-//   1 537 blocks and more:  mean 16 to 18: 1.00, 1.03;  18 to 20: 1.00, 1.03;  28 to 32: 1.01, 1.05
-//   257 to 512 blocks:      mean 28 to 32: 0.97, 1.00;  36 to 42: 0.98, 1.01;  up to 256:  mean 25 to 28: 0.98, 1.01;  32 to 36: 1.01, 1.04
+// loop, but nobody works on its SIMDs while a list starts and ends.  So the lists have to be long enough -- a KV block's list holds
+// list_len n_q / n_k query blocks on the mean -- and longer where few blocks share the chip and the longest list decides.  How much
+// faster the backward call is with that kernel, lists as the mask selection makes them, least and mean of 2 to 13 calls:
+//   129 to 256 blocks:      mean 9 to 11: 0.95, 1.02;  12 to 14: 0.97, 1.04;  18 to 20: 1.01, 1.06;  24 to 26: 1.10, 1.12;  36 to 38: 1.07, 1.11
+//   257 to 512 blocks:      mean 9 to 11: 0.97, 1.01;  12 to 14: 0.99, 1.01;  15 to 17: 0.99, 1.01;  18 to 20: 1.01, 1.06;  24 to 26: 1.04, 1.05
+//   513 to 768 blocks:      mean 9 to 11: 1.01, 1.03;  12 to 14: 0.98, 1.02;  15 to 17: 1.04, 1.07;  18 to 20: 1.02, 1.04;  33 to 35: 1.05, 1.09
+//   769 to 1 024 blocks:    mean 9 to 11: 0.97, 1.00;  12 to 14: 1.00, 1.02;  15 to 17: 1.01, 1.04;  18 to 20: 1.00, 1.05;  27 to 29: 1.07, 1.09
+//   1 025 to 1 280 blocks:  mean 9 to 11: 0.98, 1.02;  12 to 14: 1.04, 1.05;  15 to 17: 1.04, 1.05;  24 to 26: 1.04, 1.08;  33 to 35: 1.05, 1.08
+//   1 281 to 1 536 blocks:  mean 9 to 11: 0.98, 1.00;  12 to 14: 1.02, 1.02;  18 to 20: 1.03, 1.04;  27 to 29: 1.06, 1.08
+//   1 537 blocks and more:  mean 9 to 11: 0.98, 1.03;  12 to 14: 1.05, 1.06;  18 to 20: 1.02, 1.05;  30 to 32: 1.06, 1.07
 static bool kv_wide(int blocks, int64_t entries, int n_k) {
-  if (blocks <= kKvSplitBlocks) return entries >= (int64_t)32 * n_k;
-  if (blocks <= 1536) return blocks > 512 && (blocks - 1) % 512 >= 256 && entries >= (int64_t)(blocks <= 1024 ? 28 : 22) * n_k;
-  return entries >= (int64_t)18 * n_k;
+  return entries >= (int64_t)(blocks <= 512 ? 18 : 15) * n_k;
 }
 // Whether the dQ launch takes the kernel with one wavefront per query block (lf_attn_bwd_q_wide.hip): a SIMD holds one of its
 // wavefronts, so the last round of 1 024 query blocks has to be filled well enough.  dQ with the launch before it, this file's

@@ -752,7 +752,7 @@ def test_list_lengths_around_the_decode_passes(gpu, heads, lengths, head_dim):
                                                             (200, 128, 132, 4), (256, 128, 66, 3)])
 def test_extreme_logits_with_many_query_blocks(gpu, frame_len, head_dim, heads, chunk, scale):
     """test_attention_with_extreme_logits on many query blocks, where each list is walked by one pair of wavefronts
-    (d = 64; 1 056 query blocks; 528 with lists of 24) or by one wavefront (528 with lists of 32): the reference
+    (d = 64; 1 056 query blocks) or by one wavefront (528): the reference
     moves inside the list."""
     torch, lf = gpu
     w = synth.small_ragged(frame_len=frame_len, chunk_idx=chunk, heads=heads, head_dim=head_dim)
