@@ -59,6 +59,7 @@ struct AttnArgs {
   int tail0;
   int list_stride;  // entries between two lists in memory
   int total_wg, wg_per_xcd;
+  int first;  // divided lists: the first (head, query block) pair of the launch
   float c;  // softmax_scale * log2(e)
   // Online-softmax state per query row, float32: O unnormalised [H][q_len][d] and (m, l)
   // [H][q_len].  The dense kernel writes it; the list-driven kernel starts from it when
@@ -162,7 +163,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
   const bool w_valid = w < a.total_wg;
   w = min(w, a.total_wg - 1);
   const int per_head = DENSE ? a.wg_per_head : a.n_q;
-  const int h = (HALF ? w >> 1 : w) / per_head, r = (HALF ? w >> 1 : w) % per_head;
+  const int pair = (HALF ? w >> 1 : w) + (SPLIT > 1 ? a.first : 0);
+  const int h = pair / per_head, r = pair % per_head;
   uint4* const buf0 = buf0_all[qb];
   uint4* const buf1 = buf1_all[qb];
   int2* const ent = ent_all[qb];
@@ -775,6 +777,23 @@ static AttnArgs attn_args(const void* Q, const void* K, const void* V, const lf_
   return a;
 }
 
+// Whether the full rounds of 1 024 query blocks of a call go to the kernel with one wavefront per block and the blocks past
+// them, few enough to divide their lists, to a launch of their own.  Otherwise the call takes as long as one with a full last round.
+// How much faster, least and mean (random lists, one and two full rounds before the others):
+//   1 to 256 blocks past them:    lists of 16 to 23: 1.02, 1.13;  24 to 31: 1.06, 1.16;  32 to 63: 1.06, 1.20;  64 to 160: 1.09, 1.22
+//   257 to 448 blocks past them:  lists of 9 to 13: 0.90, 0.93;  19 to 31: 1.00, 1.03;  41 to 130: 1.08, 1.11
+// (1 050 blocks, lists of 188: 544 us as one launch.)  Lists of 8 to 15 would gain up to 17 % with few blocks past the rounds, but
+// stay one launch, with the bits of the calls of 512 to 1 024 blocks.
+static bool full_rounds_apart(int d, int blocks, int list_len, int n_k) {
+#ifdef LF_PROBE
+  return false;        // probe builds lengthen this file's kernel only
+#endif
+  const int past = blocks % 1024;
+  if (d != 128 || blocks <= 1024 || past == 0) return false;
+  if (list_len < 16 || past > 448 || (past > 256 && list_len < 32)) return false;
+  return lf_halve_blocks(d, past, list_len) || lf_two_parts(d, past, list_len) || lf_split_lists(d, past, list_len, n_k);
+}
+
 // List-driven kernel: walks the list_len entries of every list.  With a state (state_o, state_ml: lists of list_stride entries whose
 // last ones are the current chunk's blocks) it continues that online softmax over the first list_len of them, or, where
 // lf_launch_attn_dense has left none, walks them all, the last list_stride - list_len without reading them.
@@ -798,6 +817,12 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.state_o = const_cast<float*>(state_o);
   a.state_ml = reinterpret_cast<float2*>(const_cast<float*>(state_ml));
   hipStream_t st = (hipStream_t)stream;
+  if (state_o == nullptr && full_rounds_apart(dm->d, a.total_wg, list_len, dm->n_k)) {
+    a.first = a.total_wg / 1024 * 1024;
+    const int rc = lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, a.first, scale, O, lse2, stream);
+    if (rc != LF_OK) return rc;
+    a.total_wg -= a.first;
+  }
   if (state_o == nullptr && lf_halve_blocks(dm->d, a.total_wg, list_len)) {
     a.total_wg *= 2;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
@@ -826,7 +851,7 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   // Probe builds lengthen this file's kernel, so they stay with it.
 #ifndef LF_PROBE
   if (dm->d == 128 && state_o == nullptr && list_len >= 16 && (a.total_wg - 1) % 1024 >= 512)
-    return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, scale, O, lse2, stream);
+    return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, a.total_wg, scale, O, lse2, stream);
 #endif
   // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
   // whole blocks to the end (lists of 16 and more have gone to the other kernel by here).  Measured late -> early, us, lists as

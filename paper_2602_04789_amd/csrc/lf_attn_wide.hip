@@ -464,7 +464,7 @@ __global__ __launch_bounds__(64, 1) void lf_attn_wide_kernel(WideArgs a) {
 }  // namespace
 
 int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_shape* s, const lf_dims* dm,
-                        const int32_t* indices, int32_t list_len, int32_t own_len, float scale, void* O, float* lse2,
+                        const int32_t* indices, int32_t list_len, int32_t own_len, int blocks, float scale, void* O, float* lse2,
                         void* stream) {
   WideArgs a = {};
   a.Q = (const uint16_t*)Q;
@@ -488,7 +488,7 @@ int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_sh
   a.list_len = list_len;
   a.own_len = own_len;
   a.tail0 = dm->n_k - list_len;
-  a.total = dm->H * dm->n_q;
+  a.total = blocks;
   a.wg_per_xcd = (a.total + 7) / 8;
   a.c = scale * 1.4426950408889634f;
   a.lse2 = lse2;

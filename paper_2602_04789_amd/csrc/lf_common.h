@@ -115,9 +115,9 @@ int lf_launch_qk_norm_rope(const void* X, const float* g, const float* cosv, con
 // Device address of the library's static scratch on the current device (looked up on the first
 // call per device); LF_OK or LF_ERR_HIP.
 int lf_static_scratch(void** ptr);
-// The undivided call at d = 128 with one wavefront per query block; entries from own_len on are the cache's last blocks, unread.
+// The first `blocks` query blocks of a call at d = 128 with one wavefront each; entries from own_len on are the cache's last blocks, unread.
 int lf_launch_attn_wide(const void* Q, const void* K, const void* V, const lf_shape* s, const lf_dims* dm,
-                        const int32_t* indices, int32_t list_len, int32_t own_len, float scale, void* O, float* lse2,
+                        const int32_t* indices, int32_t list_len, int32_t own_len, int blocks, float scale, void* O, float* lse2,
                         void* stream);
 int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* s,
                    const lf_dims* dm, const int32_t* indices, int32_t list_len, int32_t list_stride,
