@@ -36,6 +36,7 @@
 #include <stdint.h>
 
 #include "lf_common.h"
+#include "lf_slots.h"
 
 namespace {
 
@@ -455,14 +456,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     } else {
       e0 = hent(0); e1 = hent(1); e2 = hent(2);
     }
-    fetch_k(k_rsrc(e0), buf0);
-    fetch_v(v_rsrc(e0), buf0);
-    fetch_k(k_rsrc(e1), buf1);
+    fetch_k(aged(k_rsrc(e0)), buf0);
+    fetch_v(aged(v_rsrc(e0)), buf0);
+    fetch_k(aged(k_rsrc(e1)), buf1);
     int2 e_ref = make_int2(0, 0);
     if constexpr (SPLIT > 1) {
       if (need_ref) {                      // K of the list's first half tile, where V of half tile 1 comes later
         e_ref = ent_all[__builtin_amdgcn_readfirstlane(ref_slice)][0];
-        fetch_k(k_rsrc(e_ref), buf1 + TILE);
+        fetch_k(aged(k_rsrc(e_ref)), buf1 + TILE);
       }
     }
 
@@ -508,7 +509,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       // half tile t+3 is looked up now and made wavefront-uniform at the end of the step
       const int2 e_raw = DENSE ? make_int2(0, 0) : ent[(t + 3) & (kMaxEnt - 1)];
       const int32x4 krs = k_rsrc(e2), vrs = v_rsrc(e1);
-      fetch_v(vrs, other);
+      fetch_v(DENSE ? aged(vrs) : vrs, other);   // (the dense kernel makes its counts right here)
       if (cnt < 32) mask_past(sacc, cnt);
       f32x16 snext = s_half(other, zero16, 0);
       fetch_k(krs, cur);
@@ -638,7 +639,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
       lds_barrier();
       const int2 e_raw = ent[(t + 3) & (kMaxEnt - 1)];
       const int32x4 krs = k_rsrc(e2), vrs = v_rsrc(e1);
-      fetch_v(vrs, other);
+      fetch_v(DENSE ? aged(vrs) : vrs, other);   // (the dense kernel makes its counts right here)
       fetch_k(krs, cur);
       e0 = e1;
       e1 = e2;

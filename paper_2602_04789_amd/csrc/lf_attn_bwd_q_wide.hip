@@ -79,14 +79,19 @@ __global__ __launch_bounds__(64, 1) void lf_attn_bwd_q_wide_kernel(BwdArgs a) {
   const char* Vh = reinterpret_cast<const char*>(a.A2 + (int64_t)h * a.a2_head);
   const uint32_t k_pitch = (uint32_t)(a.a1_tok * 2), v_pitch = (uint32_t)(a.a2_tok * 2);
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)LDS_PTR(void, &st));
-  // quarter q of half tile e (entry); one head's K or V spans less than 2 GiB
+  // quarter q of half tile e (entry); one head's K or V spans less than 2 GiB.  Made by scalar instructions alone: a load behind a
+  // vector instruction that writes its resource would have to wait for it (five wait states, which nobody counts into assembly).
   auto rsrc = [](const char* base, uint32_t pitch, uint32_t e, int q) {
     int32x4 rs;
     const uint64_t b = (uint64_t)base + (uint64_t)(((e >> 6) + 16u * q) * pitch);
-    const int cnt = q ? max((int)(e & 63u) - 16, 0) : (int)(e & 63u);
+    uint32_t cnt = e & 63u;
+    if (q) {
+      asm("s_max_u32 %0, %1, 16" : "=s"(cnt) : "s"(cnt) : "scc");
+      cnt -= 16u;
+    }
     rs[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
     rs[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-    rs[2] = __builtin_amdgcn_readfirstlane((int)((uint32_t)cnt * pitch));
+    rs[2] = __builtin_amdgcn_readfirstlane((int)(cnt * pitch));
     rs[3] = 0x00020000;
     return rs;
   };
