@@ -464,6 +464,8 @@ __global__ __launch_bounds__(128 * SPLIT, 1) void lf_attn_bwd_kv_wide_kernel(Bwd
           } else {
             accumulate(acc[hh][k % MB], join(tlo[k], thi[k]), pk[hh][k / MB]);
           }
+          // The product of slot 1 reads nd for seven wait states: kept up to here, so that no vector instruction gets its place before.
+          if constexpr (i == 2) asm volatile("" :: "v"(nd));
           if constexpr (ph == 0) {
             if constexpr (i == 12) tile_rsrc(Qh, q_pitch, e3);      // of the next phase's loads
             if constexpr (i == 13) rs[2] = __builtin_amdgcn_readfirstlane((int)((e3 & 63u) * q_pitch));

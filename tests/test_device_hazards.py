@@ -114,6 +114,9 @@ def hazards(lines):
                 need = max(need, 1)
             if p.vector and x.product and made & x.read:
                 need = max(need, 2)
+            if p.product:
+                if x.vector and p.sources[2] - p.written & x.written:      # what the product starts from is read while it runs
+                    need = max(need, 7 if p.passes == 8 else 1)
             if since < need:
                 found.add((need, since, p.text, x.text))
             cost = stall(p) if p.product else p.states
@@ -129,6 +132,7 @@ LOAD = "buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
     (["v_readfirstlane_b32 s6, v0", "s_nop 2", "s_mov_b32 m0, s9", "s_nop 0", LOAD], 0),
     (["s_mul_i32 s6, s8, s9", "s_mov_b32 m0, s9", LOAD], 1),
     ([".LBB0_1:", "s_mov_b32 m0, s9", "s_nop 0", LOAD, "v_readfirstlane_b32 s7, v0", "s_cbranch_scc1 .LBB0_1", "s_endpgm"], 1),
+    (["v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], v[24:39]", "s_nop 5", "v_mov_b32 v30, 0"], 1),
     (["v_exp_f32 v9, v1", "v_mul_f32 v2, v9, v9"], 1),
     (["v_exp_f32 v9, v1", "s_nop 0", "v_mul_f32 v2, v9, v9"], 0),
     (["v_mov_b32 v1, 0", "s_nop 0", "v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], v[8:23]"], 1)])
@@ -150,7 +154,8 @@ def assembly(src):
 @pytest.mark.parametrize("src", SOURCES)
 def test_instructions_keep_their_distance_on_every_path(src):
     """In wait states: a load behind the vector instruction that wrote its resource 5, behind M0 1; a vector instruction behind one
-    that wrote a scalar register it reads 2, behind an exponential 1; a product behind a vector instruction 2."""
+    that wrote a scalar register it reads 2, behind an exponential 1; a product behind a vector instruction 2; what overwrites the
+    registers that a product starts from 7."""
     found = hazards(assembly(src))
     for f in found[:10]:
         print(*f)
