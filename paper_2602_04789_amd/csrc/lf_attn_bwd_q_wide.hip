@@ -355,12 +355,11 @@ __global__ __launch_bounds__(64, 1) void lf_attn_bwd_q_wide_kernel(BwdArgs a) {
     asm volatile("s_nop 7" : "+v"(pk[1][1]) :: "memory");
 #pragma unroll
     for (int k = 0; k < 2 * MB; ++k) accumulate(acc[1][k % MB], join(tlo[k], thi[k]), __builtin_bit_cast(bf16x8, pk[1][k / MB]));
+    // the last products have been written (here: behind the loop the compiler first copies the sums, and sees no reason to wait)
+    asm volatile("s_nop 15" : "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]));
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // requests past the end (empty: they write zeros)
     asm volatile("" ::: "memory");
   }
-  // the last products have been written
-  asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]));
-  asm volatile("s_nop 1" : "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]));
 
   // Accumulator i of acc[hh][mb] is channel 32 mb + 8 (i/4) + 4 kg + i%4 of owner row 32 hh + ln.  The rows go through LDS
   // (16-byte chunks XORed with the row), so that four rows of 256 bytes leave with one store.

@@ -115,6 +115,11 @@ def hazards(lines):
             if p.vector and x.product and made & x.read:
                 need = max(need, 2)
             if p.product:
+                far = 11 if p.passes == 8 else 5
+                if (x.vector and made & (x.read | x.written)) or (made & x.read and not x.product and not x.op.startswith("s_")):
+                    need = far
+                if x.product and made & (x.sources[0] | x.sources[1]):
+                    need = far
                 if x.vector and p.sources[2] - p.written & x.written:      # what the product starts from is read while it runs
                     need = max(need, 7 if p.passes == 8 else 1)
             if since < need:
@@ -132,6 +137,8 @@ LOAD = "buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
     (["v_readfirstlane_b32 s6, v0", "s_nop 2", "s_mov_b32 m0, s9", "s_nop 0", LOAD], 0),
     (["s_mul_i32 s6, s8, s9", "s_mov_b32 m0, s9", LOAD], 1),
     ([".LBB0_1:", "s_mov_b32 m0, s9", "s_nop 0", LOAD, "v_readfirstlane_b32 s7, v0", "s_cbranch_scc1 .LBB0_1", "s_endpgm"], 1),
+    (["v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], 0", "s_cbranch_scc1 .LBB0_2", "s_nop 15", ".LBB0_2:", "v_exp_f32 v9, v1"], 1),
+    (["v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], 0", "s_cbranch_scc1 .LBB0_2", "s_nop 15", ".LBB0_2:", "s_nop 9", "v_exp_f32 v9, v1"], 0),
     (["v_mfma_f32_32x32x16_bf16 v[8:23], v[0:3], v[4:7], v[24:39]", "s_nop 5", "v_mov_b32 v30, 0"], 1),
     (["v_exp_f32 v9, v1", "v_mul_f32 v2, v9, v9"], 1),
     (["v_exp_f32 v9, v1", "s_nop 0", "v_mul_f32 v2, v9, v9"], 0),
@@ -154,8 +161,8 @@ def assembly(src):
 @pytest.mark.parametrize("src", SOURCES)
 def test_instructions_keep_their_distance_on_every_path(src):
     """In wait states: a load behind the vector instruction that wrote its resource 5, behind M0 1; a vector instruction behind one
-    that wrote a scalar register it reads 2, behind an exponential 1; a product behind a vector instruction 2; what overwrites the
-    registers that a product starts from 7."""
+    that wrote a scalar register it reads 2, behind an exponential 1; a product behind a vector instruction 2; what uses a product's
+    result 11 (4 x 4 x 4: 5), what overwrites the registers that a product starts from 7."""
     found = hazards(assembly(src))
     for f in found[:10]:
         print(*f)
