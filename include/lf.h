@@ -217,8 +217,8 @@ int lf_sparse_attn(const void* Q, const void* Kcache, const void* Vcache,
  * Blockwise sparse attention (Eq. 13) for lists written by lf_select_mask with
  * budget->current_mandatory = 1.  The always-selected current-chunk frames of Eq. 9 put the same
  * f*nb KV blocks, one contiguous token range, into every list of a head; that part of every row's
- * softmax is a plain dense attention problem.  Where a chunk has many blocks (f*nb >= 200) and the call
- * many query blocks it is computed by a dense kernel (128 query rows
+ * softmax is a plain dense attention problem.  In calls with many query blocks whose frames leave much of
+ * their 64-row blocks empty it is computed by a dense kernel (128 query rows
  * per workgroup share each K/V tile), which leaves an online-softmax state per query row
  * (reference m, row sum l, unnormalised O, float32) in `workspace`; the list-driven kernel then
  * continues that state over the first budget->k_blocks entries of each list and writes O.

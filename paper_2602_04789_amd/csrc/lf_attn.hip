@@ -24,7 +24,7 @@
 //
 // The same per-wavefront step serves two kernels.  The list-driven one above, and a dense one
 // for KV blocks that every query block of a head keeps (the always-selected current-chunk
-// frames of Eq. 9, where there are many of them: lf_two_phases): there a workgroup of 4 wavefronts owns 128 consecutive query rows and
+// frames of Eq. 9, where that is faster: lf_two_phases): there a workgroup of 4 wavefronts owns 128 consecutive query rows and
 // walks one contiguous KV token range, so a K/V half tile brought into LDS serves 4 x 32 query
 // rows instead of 2 x 32 (8 wavefronts per workgroup measured slower: then the two wavefronts
 // of a SIMD wait at the same barrier and run their phases in step).  The dense kernel leaves its online-softmax state (reference m, row
@@ -809,7 +809,7 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.own_len = list_len;
   a.tail0 = dm->n_k - list_stride;
   a.total_wg = dm->H * dm->n_q;
-  if (state_o != nullptr && !lf_two_phases(dm->d, a.total_wg, dm->n_q)) {
+  if (state_o != nullptr && !lf_two_phases(*dm)) {
     state_o = state_ml = nullptr;
     list_len = list_stride;
   }
@@ -878,7 +878,7 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
 int lf_launch_attn_dense(const void* Q, const void* K, const void* V, const lf_shape* s,
                          const lf_dims* dm, int kv0, int kv1, float scale, float* state_o,
                          float* state_ml, void* stream) {
-  if (!lf_two_phases(dm->d, dm->H * dm->n_q, dm->n_q)) return LF_OK;
+  if (!lf_two_phases(*dm)) return LF_OK;
   AttnArgs a = attn_args(Q, K, V, s, dm, scale);
   a.state_o = state_o;
   a.state_ml = reinterpret_cast<float2*>(state_ml);

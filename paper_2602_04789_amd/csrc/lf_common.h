@@ -22,6 +22,7 @@ struct lf_dims {
   int H, d, n, f, F, F_h, nb, n_q, n_k, m;
   int n_tf;     // selected history frames: n_sink + n_win + k_frames
   int n_cand;   // |B_r|
+  int k_blocks; // retrieved blocks per list (0 without a budget)
   size_t off_qt, off_kt, off_kh, ws_bytes;
 };
 
@@ -90,16 +91,25 @@ inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
 inline bool lf_halve_blocks_dq(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 4 : 6); }
 
 // Whether lf_sparse_attn_split computes the current chunk's blocks, n_q of them in every list, in a dense phase of their own, whose
-// state the list-driven kernel goes on from.  A tile then serves 128 query rows, but the state of every row goes to memory and
-// back, and both phases have a last round to fill.  One pass, in how much of the time of two phases (lists of 7 and 60 beside the chunk's blocks):
-//   chunks of 75 blocks: 16 query blocks 0.51, 300 0.75, 450 0.82, 900 0.94, 3 000 0.95 (d = 64: 0.99), 6 000 0.94;
-//   of 150: 450 0.87, 900 0.95, 2 400 0.98 - 1.02, 3 600 1.05, 6 000 0.97 - 0.99;
-//   of 200: 800 0.95 (d = 64: 1.00), 1 200 1.00 - 1.02, 2 400 1.01 - 1.04, 4 800 0.98;  of 225: 900 0.97, 1 350 1.01, 1 800 0.96, 2 700 1.03, 5 400 1.05;
-//   of 300: 600 0.95, 900 0.97 (d = 64: 1.01), 1 200 1.02, 1 800 0.97 (d = 64: 1.02), 3 600 1.09, 7 200 1.09;
-// d = 128 with a well filled last round has the kernel of lf_attn_wide.hip for the one pass (1 800, 4 800 above).
-inline bool lf_two_phases(int d, int blocks, int n_q) {
-  if (n_q < 200) return false;
-  return d == 64 ? blocks > 768 : blocks > 1024 && (blocks - 1) % 1024 < 700;
+// state the list-driven kernel goes on from.  The dense phase takes the chunk's tokens as one row of tiles.  One pass takes every
+// query block as 64 rows and every KV block as whole half tiles of 32, so short frames that do not fill their blocks cost it
+// `padded / n^2` of the work there (frames of 97 tokens 1.7 times, of 200 1.4, of 1 560 1.03).  Against that, two
+// phases carry the state of every row through memory (as long as some 8 blocks of a list take), have two last rounds to fill, cannot divide
+// lists among wavefronts, and at d = 128 have the slower kernel for them, a share of the whole list that falls with the number of query blocks.
+// The line: 17 500 random calls, both ways each (mean, and worst, of what the slower choice would cost where this one is wrong):
+//   d = 128: 257 to 512 query blocks 0.0002, 0.05;  513 to 1 280: 0.003, 0.15;  more: 0.003, 0.10;  up to 256 one pass is always faster;
+//   d = 64:  257 to 768: 0.0003, 0.10;  more: 0.002, 0.17.
+// Time of one pass to that of two phases: frames of 97 tokens, chunk of 300 blocks, lists of 30 beside it, 1 500 query blocks: 1.27 (d = 64: 1.29);
+//   frames of 200, calls of more than 2 048: up to 1.2 (1.3), of 513 to 640: 0.7 to 1.1;  of 33: up to 2.0 (2.3);
+//   whole frames, d = 128: 75 blocks 0.75 to 0.95 (3 000 query blocks), 225: 1 125 query blocks 0.76, 1 800 0.93, 4 725 0.95, 300: 1 200
+//   0.81, 2 100 0.85, 6 000 0.97, but 1 500 1.01;  d = 64: 225: 675 0.75, 900 0.97, 2 700 0.99, 4 725 1.00.
+inline bool lf_two_phases(const lf_dims& m) {
+  const int blocks = m.H * m.n_q;
+  if (blocks <= 256) return false;
+  const double padded = 64.0 * m.nb * 32.0 * ((m.n + 31) / 32);
+  const double saved = m.n_q * (1.0 - (double)m.n * m.n / padded);      // blocks of the list
+  const double slower = m.d == 128 ? (blocks <= 512 ? 0.4 : blocks <= 1280 ? 0.15 : 0.07) : blocks <= 768 ? 0.4 : 0.0;
+  return saved > 8.0 + slower * (m.n_q + m.k_blocks);
 }
 
 // Kernel launchers (defined in the .hip files); return LF_OK or LF_ERR_HIP.

@@ -176,6 +176,7 @@ int lf_derive(const lf_shape* s, const lf_budget* b, lf_dims* o) {
   const int64_t n_cand = (int64_t)o->n_tf * o->nb + (b->current_mandatory ? 0 : (int64_t)o->f * o->nb);
   if (n_cand > LF_MAX_CAND_BLOCKS) return LF_ERR_BUDGET;
   o->n_cand = (int)n_cand;
+  o->k_blocks = b->k_blocks;
   if (b->k_blocks > o->n_cand) return LF_ERR_BUDGET;
   const int want_len = b->k_blocks + (b->current_mandatory ? o->f * o->nb : 0);
   if (b->list_len != want_len || want_len < 1) return LF_ERR_BUDGET;
