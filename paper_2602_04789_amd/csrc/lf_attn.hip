@@ -456,14 +456,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void lf_attn_kernel(AttnArgs
     } else {
       e0 = hent(0); e1 = hent(1); e2 = hent(2);
     }
-    fetch_k(aged(k_rsrc(e0)), buf0);
-    fetch_v(aged(v_rsrc(e0)), buf0);
-    fetch_k(aged(k_rsrc(e1)), buf1);
+    fetch_k(k_rsrc(e0), buf0);
+    fetch_v(v_rsrc(e0), buf0);
+    fetch_k(k_rsrc(e1), buf1);
     int2 e_ref = make_int2(0, 0);
     if constexpr (SPLIT > 1) {
       if (need_ref) {                      // K of the list's first half tile, where V of half tile 1 comes later
         e_ref = ent_all[__builtin_amdgcn_readfirstlane(ref_slice)][0];
-        fetch_k(aged(k_rsrc(e_ref)), buf1 + TILE);
+        fetch_k(aged(k_rsrc(e_ref)), buf1 + TILE);   // (the entry has been read right here)
       }
     }
 

@@ -148,22 +148,22 @@ def test_the_check_follows_the_control_flow(lines, count):
 
 
 @functools.lru_cache(maxsize=None)
-def assembly(src):
+def assembly(src, *defines):
     try:
         hipcc = B._hipcc()
     except RuntimeError:
         pytest.skip("hipcc not found")
     out = subprocess.run([hipcc, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", "-"] + B.COMMON + B.DEVICE +
-                         B.PER_FILE.get(src, []), check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True)
+                         B.PER_FILE.get(src, []) + list(defines), check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True)
     return out.stdout.splitlines()
 
 
-@pytest.mark.parametrize("src", SOURCES)
+@pytest.mark.parametrize("src", SOURCES + [f"lf_attn.hip -DLF_PROBE -DLF_PROBE_{tag.upper()}" for tag in B.PROBES])
 def test_instructions_keep_their_distance_on_every_path(src):
     """In wait states: a load behind the vector instruction that wrote its resource 5, behind M0 1; a vector instruction behind one
     that wrote a scalar register it reads 2, behind an exponential 1; a product behind a vector instruction 2; what uses a product's
     result 11 (4 x 4 x 4: 5), what overwrites the registers that a product starts from 7."""
-    found = hazards(assembly(src))
+    found = hazards(assembly(*src.split()))
     for f in found[:10]:
         print(*f)
     assert not found
