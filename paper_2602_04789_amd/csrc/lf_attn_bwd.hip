@@ -364,30 +364,6 @@ __global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 
 // keeps one owner operand and one accumulator set, which fits two wavefronts per SIMD (two
 // workgroups per CU, not in step with each other).
 constexpr int kKvThreads = 256;
-// Calls at d = 128 with at most kKvSplitBlocks (head, KV block) pairs give a block two groups of wavefronts: such a
-// workgroup has a compute unit (of 256) to itself.  Backward call in us, mean transposed list of
-// 12: 256 blocks 52.9 -> 50.4; of 24: 76.6 -> 70.0; two rounds, of 12: 384 blocks 59.5 -> 66.8.
-constexpr int kKvSplitBlocks = 256;
-// With at most this many pairs the two row halves of a KV block get a workgroup each, of two groups of two wavefronts, as long as
-// that brings compute units to work: at d = 128 one such workgroup fills a unit's LDS, at d = 64 two fit.  Backward call in us, a
-// workgroup a block -> two: d = 128, 128 blocks, mean list 1: 22.5 -> 19.5, 8: 33.8 -> 29.7, 64: 93.8 -> 90.3; but 168 blocks, 14: 47.6 ->
-// 58.0.  d = 64, 168 blocks, 9: 36.4 -> 33.0; 256 blocks, 4: 28.1 -> 23.7, 16: 45.5 -> 45.3; 352 blocks, 2: 22.7 -> 22.3, 16: 62.4 -> 59.1;
-// 384 blocks, 2: 22.2 -> 22.6, 11: 47.3 -> 47.9; 480 blocks, 32: 132 -> 137.
-constexpr int kKvHalfBlocks128 = 128, kKvHalfBlocks64 = 352;
-// Whether a call at d = 128 goes to the kernel with one wavefront per SIMD (lf_attn_bwd_wide.hip).  That kernel has the shorter
-// loop, but nobody works on its SIMDs while a list starts and ends.  So the lists have to be long enough -- a KV block's list holds
-// list_len n_q / n_k query blocks on the mean -- and longer where few blocks share the chip and the longest list decides.  How much
-// faster the backward call is with that kernel, lists as the mask selection makes them, least and mean of 2 to 13 calls:
-//   129 to 256 blocks:      mean 9 to 11: 0.95, 1.02;  12 to 14: 0.97, 1.04;  18 to 20: 1.01, 1.06;  24 to 26: 1.10, 1.12;  36 to 38: 1.07, 1.11
-//   257 to 512 blocks:      mean 9 to 11: 0.97, 1.01;  12 to 14: 0.99, 1.01;  15 to 17: 0.99, 1.01;  18 to 20: 1.01, 1.06;  24 to 26: 1.04, 1.05
-//   513 to 768 blocks:      mean 9 to 11: 1.01, 1.03;  12 to 14: 0.98, 1.02;  15 to 17: 1.04, 1.07;  18 to 20: 1.02, 1.04;  33 to 35: 1.05, 1.09
-//   769 to 1 024 blocks:    mean 9 to 11: 0.97, 1.00;  12 to 14: 1.00, 1.02;  15 to 17: 1.01, 1.04;  18 to 20: 1.00, 1.05;  27 to 29: 1.07, 1.09
-//   1 025 to 1 280 blocks:  mean 9 to 11: 0.98, 1.02;  12 to 14: 1.04, 1.05;  15 to 17: 1.04, 1.05;  24 to 26: 1.04, 1.08;  33 to 35: 1.05, 1.08
-//   1 281 to 1 536 blocks:  mean 9 to 11: 0.98, 1.00;  12 to 14: 1.02, 1.02;  18 to 20: 1.03, 1.04;  27 to 29: 1.06, 1.08
-//   1 537 blocks and more:  mean 9 to 11: 0.98, 1.03;  12 to 14: 1.05, 1.06;  18 to 20: 1.02, 1.05;  30 to 32: 1.06, 1.07
-static bool kv_wide(int blocks, int64_t entries, int n_k) {
-  return entries >= (int64_t)(blocks <= 512 ? 18 : 15) * n_k;
-}
 // Whether the dQ launch takes the kernel with one wavefront per query block (lf_attn_bwd_q_wide.hip): a SIMD holds one of its
 // wavefronts, so the last round of 1 024 query blocks has to be filled well enough.  dQ with the launch before it, this file's
 // kernel against that one, lists of 8 and 150: 520 blocks 1.02, 1.07; 768: 1.05, 1.06; 1 024: 1.05, 1.04; 1 040: 0.95, 0.91; 1 200: 0.96,
@@ -915,7 +891,8 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_k; a.streams = dm->n_q;
   a.total_wg = dm->H * dm->n_k;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
-  if (a.total_wg <= (dm->d == 128 ? kKvHalfBlocks128 : kKvHalfBlocks64)) {
+  const lf_kv_form form = lf_kv_form_of(dm->d, a.total_wg, list_len, dm->n_q, dm->n_k);
+  if (form == LF_KV_HALVES) {
     a.wg_per_xcd *= 2;     // both halves of a block on the XCD its place in the order belongs to
     const dim3 grid((unsigned)(a.wg_per_xcd * 8));
     rc = dm->d == 128 ? lf_launch(lf_attn_bwd_kv_kernel<128, 2, true>, grid, dim3(2 * 128), 0, st, a)
@@ -923,9 +900,8 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
   const dim3 grid2((unsigned)(a.wg_per_xcd * 8));
-  const bool groups = dm->d == 128 && a.total_wg <= kKvSplitBlocks;
-  if (dm->d == 128 && kv_wide(a.total_wg, (int64_t)list_len * dm->n_q, dm->n_k))
-    return lf_launch_attn_bwd_kv_wide(a, st) == hipSuccess ? LF_OK : LF_ERR_HIP;
+  const bool groups = form == LF_KV_GROUPS;
+  if (form == LF_KV_WIDE) return lf_launch_attn_bwd_kv_wide(a, st) == hipSuccess ? LF_OK : LF_ERR_HIP;
   const dim3 block2((unsigned)(groups ? 2 * kKvThreads : kKvThreads));
   rc = dm->d == 64 ? lf_launch(lf_attn_bwd_kv_kernel<64, 1>, grid2, block2, 0, st, a)
        : groups    ? lf_launch(lf_attn_bwd_kv_kernel<128, 2>, grid2, block2, 0, st, a)

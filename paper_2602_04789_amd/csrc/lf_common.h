@@ -90,6 +90,45 @@ inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
 // 21.3 -> 23.1, of 6: 23.7 -> 23.3, of 32: 52.3 -> 43.1; 56 blocks, of 28: 45.9 -> 36.4.
 inline bool lf_halve_blocks_dq(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 4 : 6); }
 
+// Which kernel computes dK and dV.  `blocks` is the number of (head, KV block) pairs; a KV block's list holds list_len n_q / n_k query
+// blocks on the mean.
+//   LF_KV_HALVES  the two row halves of a KV block get a workgroup each, of two groups of two wavefronts
+//   LF_KV_GROUPS  a workgroup of two groups of four wavefronts, half of the block's list each
+//   LF_KV_BLOCK   a workgroup of four wavefronts
+//   LF_KV_WIDE    one wavefront per SIMD (lf_attn_bwd_wide.hip)
+// Halves, as long as they bring compute units to work: at d = 128 one such workgroup fills a unit's LDS, at d = 64 two fit.  Backward call in us,
+// halves and the faster one of BLOCK and GROUPS, on lists of equal length / random / skewed (every query block draws from the same popular blocks):
+//   d = 64:  150 blocks, mean 16: 42.6, 42.0 / 46.3, 53.2 / 121.5, 165.4;  225 blocks, mean 8: 28.7, 28.9 / 31.1, 35.1 / 65.0, 85.8, mean 64: 118.8,
+//     118.0 / 120.4, 125.9 / 128.0, 130.1;  256 blocks, mean 200: 345, 344 / 347, 355 / 384, 397;  350 blocks, mean 8: 40.3, 40.5 / 41.9, 44.3 / 71.8,
+//     92.4, mean 64: 193, 207 / 193, 208 / 199, 213;  384 blocks, mean 11: 47.9, 47.3.
+//     Past 256 blocks some units have more than two, and where lists hold a few query blocks each and at least half of all there are (so that
+//     they hardly differ), halves take 1.05 to 1.11 of the time of BLOCK (mean up to 4; 0.96 to 1.02 from 4 to 8): those go by block.
+//   d = 128, halves in how much of the time of WIDE:  64 blocks, mean 16: 0.88 / 0.93 / 1.02;  128 blocks, mean 16: 0.88 / 0.92 / 1.05, mean 32: 0.95 / 0.98 /
+//     1.07, mean 48: 0.99 / 1.00 / 1.06, mean 64: 1.02 / 1.02 / 1.06, mean 128: 1.06 / 1.05 / 1.05;  168 blocks, mean 14, of GROUPS: 58.0, 47.6.
+// GROUPS, d = 128: such a workgroup has a compute unit (of 256) to itself.  Mean 12: 256 blocks 52.9 -> 50.4; of 24: 76.6 -> 70.0; two rounds, of 12: 384
+//   blocks 59.5 -> 66.8.
+// WIDE, d = 128: it has the shorter loop, but nobody works on its SIMDs while a list starts and ends.  So the lists have to be long enough, and longer
+// where few blocks share the chip and the longest list decides.  How much faster the backward call is with it, lists as the mask
+// selection makes them, least and mean of 2 to 13 calls:
+//   129 to 256 blocks:      mean 9 to 11: 0.95, 1.02;  12 to 14: 0.97, 1.04;  18 to 20: 1.01, 1.06;  24 to 26: 1.10, 1.12;  36 to 38: 1.07, 1.11
+//   257 to 512 blocks:      mean 9 to 11: 0.97, 1.01;  12 to 14: 0.99, 1.01;  15 to 17: 0.99, 1.01;  18 to 20: 1.01, 1.06;  24 to 26: 1.04, 1.05
+//   513 to 768 blocks:      mean 9 to 11: 1.01, 1.03;  12 to 14: 0.98, 1.02;  15 to 17: 1.04, 1.07;  18 to 20: 1.02, 1.04;  33 to 35: 1.05, 1.09
+//   769 to 1 024 blocks:    mean 9 to 11: 0.97, 1.00;  12 to 14: 1.00, 1.02;  15 to 17: 1.01, 1.04;  18 to 20: 1.00, 1.05;  27 to 29: 1.07, 1.09
+//   1 025 to 1 280 blocks:  mean 9 to 11: 0.98, 1.02;  12 to 14: 1.04, 1.05;  15 to 17: 1.04, 1.05;  24 to 26: 1.04, 1.08;  33 to 35: 1.05, 1.08
+//   1 281 to 1 536 blocks:  mean 9 to 11: 0.98, 1.00;  12 to 14: 1.02, 1.02;  18 to 20: 1.03, 1.04;  27 to 29: 1.06, 1.08
+//   1 537 blocks and more:  mean 9 to 11: 0.98, 1.03;  12 to 14: 1.05, 1.06;  18 to 20: 1.02, 1.05;  30 to 32: 1.06, 1.07
+enum lf_kv_form { LF_KV_HALVES, LF_KV_GROUPS, LF_KV_BLOCK, LF_KV_WIDE };
+inline lf_kv_form lf_kv_form_of(int d, int blocks, int list_len, int n_q, int n_k) {
+  const int64_t entries = (int64_t)list_len * n_q;      // mean list times n_k
+  if (d == 64) {
+    const bool few_and_all = entries <= (int64_t)4 * n_k && (int64_t)2 * list_len >= n_k;
+    return blocks <= 256 || (blocks <= 352 && !few_and_all) ? LF_KV_HALVES : LF_KV_BLOCK;
+  }
+  if (blocks <= 128) return entries >= (int64_t)48 * n_k ? LF_KV_WIDE : LF_KV_HALVES;
+  if (entries >= (int64_t)(blocks <= 512 ? 18 : 15) * n_k) return LF_KV_WIDE;
+  return blocks <= 256 ? LF_KV_GROUPS : LF_KV_BLOCK;
+}
+
 // Whether lf_sparse_attn_split computes the current chunk's blocks, n_q of them in every list, in a dense phase of their own, whose
 // state the list-driven kernel goes on from.  The dense phase takes the chunk's tokens as one row of tiles.  One pass takes every
 // query block as 64 rows and every KV block as whole half tiles of 32, so short frames that do not fill their blocks cost it
