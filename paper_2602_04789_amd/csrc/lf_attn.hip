@@ -778,21 +778,19 @@ static AttnArgs attn_args(const void* Q, const void* K, const void* V, const lf_
   return a;
 }
 
-// Whether the full rounds of 1 024 query blocks of a call go to the kernel with one wavefront per block and the blocks past
-// them, few enough to divide their lists, to a launch of their own.  Otherwise the call takes as long as one with a full last round.
-// How much faster, least and mean (random lists, one and two full rounds before the others):
-//   1 to 256 blocks past them:    lists of 16 to 23: 1.02, 1.13;  24 to 31: 1.06, 1.16;  32 to 63: 1.06, 1.20;  64 to 160: 1.09, 1.22
-//   257 to 448 blocks past them:  lists of 9 to 13: 0.90, 0.93;  19 to 31: 1.00, 1.03;  41 to 130: 1.08, 1.11
-// (1 050 blocks, lists of 188: 544 us as one launch.)  Lists of 8 to 15 would gain up to 17 % with few blocks past the rounds, but
-// stay one launch, with the bits of the calls of 512 to 1 024 blocks.
-static bool full_rounds_apart(int d, int blocks, int list_len, int n_k) {
+// Probe builds lengthen this file's kernel only, so all of their calls stay with it.
+static bool full_rounds_apart(int d, int blocks, int list_len) {
 #ifdef LF_PROBE
-  return false;        // probe builds lengthen this file's kernel only
+  return false;
 #endif
-  const int past = blocks % 1024;
-  if (d != 128 || blocks <= 1024 || past == 0) return false;
-  if (list_len < 16 || past > 448 || (past > 256 && list_len < 32)) return false;
-  return lf_halve_blocks(d, past, list_len) || lf_two_parts(d, past, list_len) || lf_split_lists(d, past, list_len, n_k);
+  return lf_full_rounds_apart(d, blocks, list_len);
+}
+static lf_form attn_form(int d, int blocks, int list_len, int n_k) {
+  const lf_form form = lf_attn_form(d, blocks, list_len, n_k);
+#ifdef LF_PROBE
+  if (form == LF_FORM_WIDE) return LF_FORM_BLOCK;
+#endif
+  return form;
 }
 
 // List-driven kernel: walks the list_len entries of every list.  With a state (state_o, state_ml: lists of list_stride entries whose
@@ -818,13 +816,14 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
   a.state_o = const_cast<float*>(state_o);
   a.state_ml = reinterpret_cast<float2*>(const_cast<float*>(state_ml));
   hipStream_t st = (hipStream_t)stream;
-  if (state_o == nullptr && full_rounds_apart(dm->d, a.total_wg, list_len, dm->n_k)) {
+  if (state_o == nullptr && full_rounds_apart(dm->d, a.total_wg, list_len)) {
     a.first = a.total_wg / 1024 * 1024;
     const int rc = lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, a.first, scale, O, lse2, stream);
     if (rc != LF_OK) return rc;
     a.total_wg -= a.first;
   }
-  if (state_o == nullptr && lf_halve_blocks(dm->d, a.total_wg, list_len)) {
+  const lf_form form = state_o != nullptr ? LF_FORM_BLOCK : attn_form(dm->d, a.total_wg, list_len, dm->n_k);
+  if (form == LF_FORM_HALVES) {
     a.total_wg *= 2;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
@@ -833,8 +832,8 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
         : lf_launch(lf_attn_kernel<64, 8, false, 8, false, true>, dim3(grid), dim3(512), 0, st, a);
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
-  const int parts = state_o != nullptr ? 1 : lf_two_parts(dm->d, a.total_wg, list_len) ? 2 : lf_split_lists(dm->d, a.total_wg, list_len, dm->n_k) ? 4 : 1;
-  if (parts > 1) {
+  if (form == LF_FORM_TWO || form == LF_FORM_FOUR) {
+    const int parts = form == LF_FORM_TWO ? 2 : 4;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
     const unsigned grid = (unsigned)(a.wg_per_xcd * 8);
     const hipError_t rc = dm->d == 128
@@ -842,18 +841,8 @@ int lf_launch_attn(const void* Q, const void* K, const void* V, const lf_shape* 
         : lf_launch(parts == 4 ? lf_attn_kernel<64, 8, false, 4> : lf_attn_kernel<64, 4, false, 2>, dim3(grid), dim3(128 * parts), 0, st, a);
     return rc == hipSuccess ? LF_OK : LF_ERR_HIP;
   }
-  // One wavefront per query block (lf_attn_wide.hip; d = 128): a SIMD holds one of its wavefronts, so it is
-  // the faster one where the last round of 1 024 query blocks is more than half full (this file's kernel has room for 2 048
-  // wavefronts of half a block: its last round takes as long for one block as for 1 024), and its start and end count where lists
-  // are short.  How much faster, least and mean of 6 calls each, lists as selected: 513 to 768 blocks, lists of 16 to 23 and 24 to 31:
-  // 1.07, 1.09 and 1.08, 1.10; 769 to 1 024: 1.01, 1.04 and 1.02, 1.03; 1 537 to 1 792, of 16 to 23 and 32 to 63: 1.02, 1.03 and 1.02, 1.04;
-  // 1 793 to 2 048, of 16 to 23: 1.00, 1.02; 2 561 to 2 816: 1.00, 1.01; 2 817 to 3 072: 1.01, 1.03; 3 000, of 128: 740 -> 709 us; but 320, of
-  // 32: 42 -> 51 us; 1 281 to 1 536, of 16 to 63: 0.94, 0.96; 2 305 to 2 560: 0.94, 0.95; 769 to 1 024, of 1 to 9: 0.95, 0.98.
-  // Probe builds lengthen this file's kernel, so they stay with it.
-#ifndef LF_PROBE
-  if (dm->d == 128 && state_o == nullptr && list_len >= 16 && (a.total_wg - 1) % 1024 >= 512)
+  if (form == LF_FORM_WIDE)
     return lf_launch_attn_wide(Q, K, V, s, dm, indices, list_len, a.own_len, a.total_wg, scale, O, lse2, stream);
-#endif
   // V requested early (d = 128): faster where every compute unit runs two workgroups side by side through
   // whole blocks to the end (lists of 16 and more have gone to the other kernel by here).  Measured late -> early, us, lists as
   // selected: whole frames, 816 query blocks, lists of 13: 32.6 -> 32.3; 936, of 11: 30.5 both; 1 014, of 14: 38.0 -> 38.2 (2 458 calls with

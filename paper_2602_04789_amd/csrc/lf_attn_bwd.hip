@@ -364,15 +364,6 @@ __global__ __launch_bounds__((HALF ? 64 : kThreads) * SPLIT, HALF ? 1 : D == 64 
 // keeps one owner operand and one accumulator set, which fits two wavefronts per SIMD (two
 // workgroups per CU, not in step with each other).
 constexpr int kKvThreads = 256;
-// Whether the dQ launch takes the kernel with one wavefront per query block (lf_attn_bwd_q_wide.hip): a SIMD holds one of its
-// wavefronts, so the last round of 1 024 query blocks has to be filled well enough.  dQ with the launch before it, this file's
-// kernel against that one, lists of 8 and 150: 520 blocks 1.02, 1.07; 768: 1.05, 1.06; 1 024: 1.05, 1.04; 1 040: 0.95, 0.91; 1 200: 0.96,
-// 1.02; 1 300: 1.03, 1.05; 1 500: 1.08, 1.09; 2 040: 1.18, 1.26; 2 060, of 8 and 64: 1.00, 0.99; 2 100: 1.03, 1.01; 3 016, of 8 and 150: 1.11, 1.13;
-// 3 090, of 8 and 64: 1.01, 1.01.  At most 512 blocks: 0.95 .. 1.01.  Lists of 2 and 4: 520 blocks 0.99, 1.00; 1 300: 0.96, 0.98; 3 090: 1.03, 0.92.
-static bool q_wide(int d, int blocks, int list_len) {
-  if (d != 128 || list_len < 8 || blocks <= 512) return false;
-  return blocks <= 1024 || (blocks - 1) % 1024 >= (blocks <= 2048 ? 256 : 48);
-}
 // SPLIT = 2: a workgroup holds two such groups of four wavefronts, each with a stage of its own and half of
 // the block's query blocks, and the sums are added through LDS: for calls with few KV blocks.  HALF: the workgroup
 // owns one row half of the block, and a group is its two wavefronts.
@@ -853,8 +844,9 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.owners = dm->n_q; a.streams = dm->n_k;
   a.total_wg = dm->H * dm->n_q;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
-  const bool halve = lf_halve_blocks_dq(dm->d, a.total_wg, list_len);
-  const int parts = halve ? 1 : lf_two_parts_dq(dm->d, a.total_wg, list_len) ? 2 : lf_split_lists_dq(dm->d, a.total_wg, list_len) ? 4 : 1;
+  const lf_form dq_form = lf_dq_form(dm->d, a.total_wg, list_len);
+  const bool halve = dq_form == LF_FORM_HALVES;
+  const int parts = dq_form == LF_FORM_TWO ? 2 : dq_form == LF_FORM_FOUR ? 4 : 1;
   if (halve) {
     a.total_wg *= 2;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
@@ -867,7 +859,7 @@ int lf_launch_attn_bwd(const void* Q, const void* K, const void* V, const void* 
   a.order_step = spread_step((uint32_t)dm->n_k);
   // eight workgroups in front for the order of the next launch
   hipError_t rc;
-  if (!halve && parts == 1 && q_wide(dm->d, a.total_wg, list_len)) {
+  if (dq_form == LF_FORM_WIDE) {
     a.order_stride = (uint32_t)((uint64_t)64 * a.order_step % (uint32_t)dm->n_k);
     rc = lf_launch_attn_bwd_q_wide(a, st);
   } else {

@@ -57,17 +57,12 @@ inline bool lf_two_parts_dq(int d, int blocks, int list_len) {
 // workgroup instead of giving every (head, query block) one pair.  `blocks` is the number of
 // these pairs, list_len the entries walked, n_k the KV blocks of a head.  A divided block has a compute unit (of 256)
 // to itself, so with more than 256 of them the second round starts when the first ends, and the
-// undivided form keeps more loads of one list's tiles in flight per compute unit.  (The launchers ask lf_halve_blocks and lf_two_parts
-// first: what is left to decide here are lists of more than 14 or 10 in calls of 129 to 256 blocks.)
+// undivided form keeps more loads of one list's tiles in flight per compute unit.  lf_attn_form and lf_dq_form ask for row halves and two
+// parts first, which leave to these two rules lists of more than 14 (at d = 64 the forward's of more than 10) in calls of 129 to 256 blocks; beyond
+// 256 they are as they were before lists were divided in two, and decide nothing.
 // Forward, d = 128, us undivided -> divided (random lists):
 //   <= 256 blocks (up to 128 lf_halve_blocks comes first): 192 blocks, lists of 6: 13.6 -> 12.4; of 195: 222 -> 109; lists of 4 are one step a slice;
-//   <= 512, lists that hold at least half of the KV blocks: 286 blocks, 151 of 234: 164 -> 149; 490, 110 of 126:
-//     122 -> 119; 432, 92 of 120: 106 -> 102; 360, 108 of 192: 124 -> 117; but 348, 34 of 60: 44 -> 49;
-//   <= 512, sparser lists: 432 blocks, 91 of 672: 114 -> 139; 300, 57 of 300: 70 -> 84; 288, 187 of 1224:
-//     207 -> 229; 312, 135 of 468 (150 -> 137) is the other way;
-//   > 512: 624 blocks, 72 of 80: 116 -> 122; 560, 236 of 280: 331 -> 334.
-// Forward, d = 64: 208 blocks, lists of 52: 48 -> 23; 336 blocks, lists of 29: 30.3 -> 32.3; 280, of 35: 34.1 -> 32.6;
-//   512, of 63: 58 -> 54; 450, of 196: 167 -> 132; 768, of 37: 48 -> 57.
+// Forward, d = 64: 208 blocks, lists of 52: 48 -> 23.
 inline bool lf_split_lists(int d, int blocks, int list_len, int n_k) {
   if (blocks <= 256) return list_len >= 6;
   if (blocks > 512) return false;
@@ -79,9 +74,7 @@ inline bool lf_split_lists(int d, int blocks, int list_len, int n_k) {
 // 135 blocks (two rounds), d = 128, of 16: 16.1 -> 21.9; d = 64: 10.3 -> 15.8.
 inline bool lf_halve_blocks(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 2 : 3); }
 // dQ (backward call, the rest the same), d = 128: 132 blocks, lists of 6: 33.5 -> 34.6, of 8: 38.7 -> 34.4 (80 blocks);
-// 384 blocks, of 4: 119 -> 128; 350, of 14: 114 -> 120; 512, of 41: 254 -> 257; 324, of 53: 191 -> 171; 400, of 69: 277 -> 256;
-// 576, of 18: 106 -> 123.  d = 64: 125 blocks, lists of 6: 29.7 -> 30.6; 78, of 7: 25.9 -> 24.9; 120, of 138: 213 -> 160; 390,
-// of 26: 87 -> 94; 304, of 57: 151 -> 157; 494, of 144: 460 -> 449.
+// d = 64: 125 blocks, lists of 6: 29.7 -> 30.6; 78, of 7: 25.9 -> 24.9; 120, of 138: 213 -> 160.
 inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
   return (blocks <= 256 && list_len >= 7) || (d == 128 && blocks <= 512 && list_len >= 48);
 }
@@ -89,6 +82,52 @@ inline bool lf_split_lists_dq(int d, int blocks, int list_len) {
 // 16: 32.5 -> 26.7, of 64: 60.9 -> 43.9; 128 blocks, of 2: 25.2 -> 26.2, of 4: 29.0 -> 27.4, of 32: 57.5 -> 52.7; d = 64, 128 blocks, of 4:
 // 21.3 -> 23.1, of 6: 23.7 -> 23.3, of 32: 52.3 -> 43.1; 56 blocks, of 28: 45.9 -> 36.4.
 inline bool lf_halve_blocks_dq(int d, int blocks, int list_len) { return blocks <= 128 && list_len >= (d == 128 ? 4 : 6); }
+
+// How a query-major kernel takes the (head, query block) pairs of a launch, asked in this order.
+//   LF_FORM_HALVES  the two row halves of a block get a workgroup each
+//   LF_FORM_TWO, LF_FORM_FOUR  a workgroup a block, its list divided among two or four pairs of wavefronts
+//   LF_FORM_WIDE    one wavefront a block (d = 128)
+//   LF_FORM_BLOCK   a pair of wavefronts a block, lists undivided
+enum lf_form { LF_FORM_HALVES, LF_FORM_TWO, LF_FORM_FOUR, LF_FORM_WIDE, LF_FORM_BLOCK };
+// One wavefront per query block (lf_attn_wide.hip; d = 128): a SIMD holds one of its wavefronts, so it is
+// the faster one where the last round of 1 024 query blocks is more than half full (the kernel of lf_attn.hip has room for 2 048
+// wavefronts of half a block: its last round takes as long for one block as for 1 024), and its start and end count where lists
+// are short.  How much faster, least and mean of 6 calls each, lists as selected: 513 to 768 blocks, lists of 16 to 23 and 24 to 31:
+// 1.07, 1.09 and 1.08, 1.10; 769 to 1 024: 1.01, 1.04 and 1.02, 1.03; 1 537 to 1 792, of 16 to 23 and 32 to 63: 1.02, 1.03 and 1.02, 1.04;
+// 1 793 to 2 048, of 16 to 23: 1.00, 1.02; 2 561 to 2 816: 1.00, 1.01; 2 817 to 3 072: 1.01, 1.03; 3 000, of 128: 740 -> 709 us; but 320, of
+// 32: 42 -> 51 us; 1 281 to 1 536, of 16 to 63: 0.94, 0.96; 2 305 to 2 560: 0.94, 0.95; 769 to 1 024, of 1 to 9: 0.95, 0.98.
+inline lf_form lf_attn_form(int d, int blocks, int list_len, int n_k) {
+  if (lf_halve_blocks(d, blocks, list_len)) return LF_FORM_HALVES;
+  if (lf_two_parts(d, blocks, list_len)) return LF_FORM_TWO;
+  if (lf_split_lists(d, blocks, list_len, n_k)) return LF_FORM_FOUR;
+  return d == 128 && list_len >= 16 && (blocks - 1) % 1024 >= 512 ? LF_FORM_WIDE : LF_FORM_BLOCK;
+}
+// Whether the full rounds of 1 024 query blocks of a call go to the kernel with one wavefront per block and the blocks past
+// them, few enough to divide their lists, to a launch of their own.  Otherwise the call takes as long as one with a full last round.
+// How much faster, least and mean (random lists, one and two full rounds before the others):
+//   1 to 256 blocks past them:    lists of 16 to 23: 1.02, 1.13;  24 to 31: 1.06, 1.16;  32 to 63: 1.06, 1.20;  64 to 160: 1.09, 1.22
+//   257 to 448 blocks past them:  lists of 9 to 13: 0.90, 0.93;  19 to 31: 1.00, 1.03;  41 to 130: 1.08, 1.11
+// (1 050 blocks, lists of 188: 544 us as one launch.)  Lists of 8 to 15 would gain up to 17 % with few blocks past the rounds, but
+// stay one launch, with the bits of the calls of 512 to 1 024 blocks.
+inline bool lf_full_rounds_apart(int d, int blocks, int list_len) {
+  const int past = blocks % 1024;
+  return d == 128 && blocks > 1024 && past > 0 && past <= 448 && list_len >= (past <= 256 ? 16 : 32);
+}
+// Whether the dQ launch takes the kernel with one wavefront per query block (lf_attn_bwd_q_wide.hip): a SIMD holds one of its
+// wavefronts, so the last round of 1 024 query blocks has to be filled well enough.  dQ with the launch before it, the
+// kernel of lf_attn_bwd.hip against that one, lists of 8 and 150: 520 blocks 1.02, 1.07; 768: 1.05, 1.06; 1 024: 1.05, 1.04; 1 040: 0.95, 0.91; 1 200: 0.96,
+// 1.02; 1 300: 1.03, 1.05; 1 500: 1.08, 1.09; 2 040: 1.18, 1.26; 2 060, of 8 and 64: 1.00, 0.99; 2 100: 1.03, 1.01; 3 016, of 8 and 150: 1.11, 1.13;
+// 3 090, of 8 and 64: 1.01, 1.01.  At most 512 blocks: 0.95 .. 1.01.  Lists of 2 and 4: 520 blocks 0.99, 1.00; 1 300: 0.96, 0.98; 3 090: 1.03, 0.92.
+inline bool lf_q_wide(int d, int blocks, int list_len) {
+  if (d != 128 || list_len < 8 || blocks <= 512) return false;
+  return blocks <= 1024 || (blocks - 1) % 1024 >= (blocks <= 2048 ? 256 : 48);
+}
+inline lf_form lf_dq_form(int d, int blocks, int list_len) {
+  if (lf_halve_blocks_dq(d, blocks, list_len)) return LF_FORM_HALVES;
+  if (lf_two_parts_dq(d, blocks, list_len)) return LF_FORM_TWO;
+  if (lf_split_lists_dq(d, blocks, list_len)) return LF_FORM_FOUR;
+  return lf_q_wide(d, blocks, list_len) ? LF_FORM_WIDE : LF_FORM_BLOCK;
+}
 
 // Which kernel computes dK and dV.  `blocks` is the number of (head, KV block) pairs; a KV block's list holds list_len n_q / n_k query
 // blocks on the mean.
