@@ -486,7 +486,8 @@ def main():
                     help="skip timing the step as one captured HIP graph")
     ap.add_argument("--attn", choices=("one_pass", "split"), default="one_pass",
                     help="attention call of the timed step: lf_sparse_attn (one list-driven kernel) or "
-                         "lf_sparse_attn_split (dense kernel over the current chunk + list-driven kernel)")
+                         "lf_sparse_attn_split (entries of the current chunk unread; one pass, or a dense phase first "
+                         "where frames leave much of their blocks empty)")
     ap.add_argument("--headline-only", action="store_true",
                     help="only the timed step: no cached selection, graph replay, pooling-only and split "
                          "timings, per_config list, micro-benchmarks or CPU baseline (for profiler runs)")
@@ -629,7 +630,7 @@ def main():
         "attn_ms_median_min": [float(np.median(attn_all)), float(attn_all.min())],
         "kept_gflop": flops / 1e9, "tile_gflop": tile_flops / 1e9,
         "roofline": {"kernel": "list-driven attention (lf_attn_wide_kernel where the call fills the chip, else lf_attn_kernel)"
-                               if not use_split else "lf_sparse_attn_split: dense and list-driven launch together",
+                               if not use_split else "lf_sparse_attn_split (one pass, or the dense and the list-driven launch together)",
                      "bound": "mfma", "achieved": attn_tflops,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": attn_tflops / PEAK_BF16_TFLOPS,
                      "traffic": traffic.get("attn") if args.workload == "last_chunk" and not use_split else None},
@@ -672,8 +673,8 @@ def main():
             e[1].record()
         torch.cuda.synchronize()
         s_ms = float(np.median([e[0].elapsed_time(e[1]) for e in se]))
-        res["attn_split"] = {"what": "lf_sparse_attn_split: dense kernel over the current chunk + list-driven kernel "
-                                     "over the retrieved blocks", "ms": s_ms,
+        res["attn_split"] = {"what": "lf_sparse_attn_split: the retrieved blocks of every list and the current chunk's "
+                                     "(one pass, or a dense phase over the latter first)", "ms": s_ms,
                              "achieved": flops / (s_ms * 1e-3) / 1e12, "unit": "TFLOP/s"}
         lf.lf_sparse_attn(Q, K, V, idx, w.frame_len, w.block, O=out)   # `out` again holds the one-pass result
     if not args.no_training:

@@ -346,8 +346,9 @@ def lf_attn_workspace_bytes(shape: lf_shape) -> int:
 
 def lf_sparse_attn_split(Q, Kcache, Vcache, indices, frame_len: int, block: int, budget: lf_budget,
                          softmax_scale: float = 0.0, O=None, workspace=None, stream=None):
-    """Blockwise sparse attention in two phases (dense over the current chunk, list-driven over
-    the retrieved blocks); returns O.  ``indices`` as written by lf_select_mask for ``budget``."""
+    """Blockwise sparse attention over the retrieved blocks of each list and the current chunk's
+    blocks, whose entries are not read (one pass, or a dense phase over the current chunk first:
+    the library chooses); returns O.  ``indices`` as written by lf_select_mask for ``budget``."""
     torch = _torch or _get_torch()
     qs, ks, vs = _strides(Q, "Q"), _strides(Kcache, "Kcache"), _strides(Vcache, "Vcache")
     if not indices.is_cuda or indices.dtype != torch.int32 or not indices.is_contiguous():
