@@ -107,7 +107,7 @@ inline lf_form lf_attn_form(int d, int blocks, int list_len, int n_k) {
 // How much faster, least and mean (random lists, one and two full rounds before the others):
 //   1 to 256 blocks past them:    lists of 16 to 23: 1.02, 1.13;  24 to 31: 1.06, 1.16;  32 to 63: 1.06, 1.20;  64 to 160: 1.09, 1.22
 //   257 to 448 blocks past them:  lists of 9 to 13: 0.90, 0.93;  19 to 31: 1.00, 1.03;  41 to 130: 1.08, 1.11
-// (1 050 blocks, lists of 188: 544 us as one launch.)  Lists of 8 to 15 would gain up to 17 % with few blocks past the rounds, but
+// (1 050 blocks, lists of 188: 544 us as one launch, 431 as two.)  Lists of 8 to 15 would gain up to 17 % with few blocks past the rounds, but
 // stay one launch, with the bits of the calls of 512 to 1 024 blocks.
 inline bool lf_full_rounds_apart(int d, int blocks, int list_len) {
   const int past = blocks % 1024;
