@@ -38,7 +38,7 @@ int lf_derive(const lf_shape* s, const lf_budget* b, lf_dims* out);
 //   257 to 512: d = 128, 260 blocks, of 7: 15.2 -> 16.0, of 8: 16.6 -> 15.9, of 32: 42.3 -> 33.5, of 64: 76.9 -> 56.2; 510 blocks, of
 //     8: 20.3 -> 19.4, of 32: 49.1 -> 43.4, of 120: 143 -> 132.  d = 64, 260 blocks, of 5: 9.9 -> 10.2, of 8: 12.3 -> 11.0, of 32: 30.2 -> 23.8;
 //     (Lists of 8 to 15 in 449 to 512 blocks would gain 3 - 10 %, but stay undivided, with the bits of the calls of 513 to 1 024 blocks.)
-//   more: d = 128, 520 blocks, of 16: 36.5 -> 38.4.  d = 64, 580 blocks, of 1: 0.89, of 2: 1.06, of 32: 41.6 -> 33.0; 760 blocks,
+//   more: d = 128, 520 blocks, of 16: 36.5 -> 38.4.  d = 64, 580 blocks, of 1: 0.89, of 2: 1.06, of 3: 0.98, of 4: 1.10, of 32: 41.6 -> 33.0; 760 blocks,
 //     of 8: 1.02, of 120: 137 -> 112; 780 (a second round), of 32: 0.93.
 inline bool lf_two_parts(int d, int blocks, int list_len) {
   if (blocks <= 256) return list_len >= 2 && list_len <= (d == 128 ? 14 : 10);
@@ -140,8 +140,9 @@ inline lf_form lf_dq_form(int d, int blocks, int list_len) {
 //   d = 64:  150 blocks, mean 16: 42.6, 42.0 / 46.3, 53.2 / 121.5, 165.4;  225 blocks, mean 8: 28.7, 28.9 / 31.1, 35.1 / 65.0, 85.8, mean 64: 118.8,
 //     118.0 / 120.4, 125.9 / 128.0, 130.1;  256 blocks, mean 200: 345, 344 / 347, 355 / 384, 397;  350 blocks, mean 8: 40.3, 40.5 / 41.9, 44.3 / 71.8,
 //     92.4, mean 64: 193, 207 / 193, 208 / 199, 213;  384 blocks, mean 11: 47.9, 47.3.
-//     Past 256 blocks some units have more than two, and where lists hold a few query blocks each and at least half of all there are (so that
-//     they hardly differ), halves take 1.05 to 1.11 of the time of BLOCK (mean up to 4; 0.96 to 1.02 from 4 to 8): those go by block.
+//     Past 256 blocks some units have more than two, and where lists hold a few query blocks each and most of all there are (so that
+//     they hardly differ), halves take longer than BLOCK: mean up to 4, at least half of all: 1.07 to 1.11 times;  5 to 8, three quarters and more: 1.02
+//     to 1.08, half to three quarters: 0.92 to 1.00;  9: 1.01, 0.90 to 0.97.
 //   d = 128, halves in how much of the time of WIDE:  64 blocks, mean 16: 0.88 / 0.93 / 1.02;  128 blocks, mean 16: 0.88 / 0.92 / 1.05, mean 32: 0.95 / 0.98 /
 //     1.07, mean 48: 0.99 / 1.00 / 1.06, mean 64: 1.02 / 1.02 / 1.06, mean 128: 1.06 / 1.05 / 1.05;  168 blocks, mean 14, of GROUPS: 58.0, 47.6.
 // GROUPS, d = 128: such a workgroup has a compute unit (of 256) to itself.  Mean 12: 256 blocks 52.9 -> 50.4; of 24: 76.6 -> 70.0; two rounds, of 12: 384
@@ -160,7 +161,8 @@ enum lf_kv_form { LF_KV_HALVES, LF_KV_GROUPS, LF_KV_BLOCK, LF_KV_WIDE };
 inline lf_kv_form lf_kv_form_of(int d, int blocks, int list_len, int n_q, int n_k) {
   const int64_t entries = (int64_t)list_len * n_q;      // mean list times n_k
   if (d == 64) {
-    const bool few_and_all = entries <= (int64_t)4 * n_k && (int64_t)2 * list_len >= n_k;
+    const bool few_and_all = (entries <= (int64_t)4 * n_k && (int64_t)2 * list_len >= n_k) ||
+                             (entries <= (int64_t)8 * n_k && (int64_t)4 * list_len >= (int64_t)3 * n_k);
     return blocks <= 256 || (blocks <= 352 && !few_and_all) ? LF_KV_HALVES : LF_KV_BLOCK;
   }
   if (blocks <= 128) return entries >= (int64_t)48 * n_k ? LF_KV_WIDE : LF_KV_HALVES;

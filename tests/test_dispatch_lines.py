@@ -59,6 +59,7 @@ HALVES, GROUPS, BLOCK, WIDE = range(4)
     # past 256 blocks: lists of a few query blocks each that hold at least half of all
     ((64, 333, 3, 3, 3), BLOCK), ((64, 256, 3, 3, 3), HALVES), ((64, 318, 3, 3, 6), BLOCK), ((64, 300, 4, 10, 10), HALVES), ((64, 300, 5, 8, 10), BLOCK),
     ((64, 300, 5, 9, 10), HALVES),
+    ((64, 351, 7, 9, 9), BLOCK), ((64, 351, 9, 9, 9), HALVES), ((64, 320, 7, 10, 10), HALVES), ((64, 320, 8, 10, 10), BLOCK),
     # d = 128: long lists of few blocks go to the kernel with one wavefront per SIMD
     ((128, 128, 48, 128, 128), WIDE), ((128, 128, 47, 128, 128), HALVES), ((128, 64, 64, 64, 64), WIDE), ((128, 129, 17, 43, 43), GROUPS),
     ((128, 129, 18, 43, 43), WIDE), ((128, 256, 17, 64, 64), GROUPS), ((128, 257, 17, 257, 257), BLOCK), ((128, 512, 18, 64, 64), WIDE),
